@@ -20,6 +20,7 @@ FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-ffp-contract=off",                       # FMAs are written out where the method needs them
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    "-mllvm", "-amdgpu-mfma-vgpr-form",        # accumulators in plain VGPRs: the store phase reads them without copies
     "-Wall", "-Wno-unused-function",
 ]
 

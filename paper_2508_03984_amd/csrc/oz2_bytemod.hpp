@@ -1,0 +1,58 @@
+// mod(x, p) of an int32 sum as the low byte of a register: the reduction of Algorithm 1 line 7 in
+// the store phase of the INT8 GEMM.  The constants per modulus and the arithmetic, in one place for
+// the device and for a host build (no HIP needed), so that the CPU can check every value.
+//
+// The accumulators start at -2^31 instead of 0, so that what they hold is u = x + 2^31 as an
+// unsigned number.  Then, with h = (p - 1) / 2:
+//   f = t + sum_j byte_j(u) (256^j mod p), one v_dot4_u32_u8.  t in [0, p) is chosen so that
+//       f = x - h (mod p); f <= 255 (1 + 3 * 255) + 255 < 2^18.  The added constant also holds
+//       0x4b000000, so that the result is the bits of the binary32 number 2^23 + f: no conversion;
+//   q = round(f / p) by one FMA that adds 1.5 * 2^23 + j.  f / p is at least 1/(2p) >= 2^-9 away from a
+//       half-integer, and the rounded 1/p misplaces it by less than 2^18 / 173 * 2^-24 < 2^-13;
+//   f - p q = mod(x, p) - h.  j is chosen so that -p j = h (mod 256), and what else the two bit
+//       patterns hold is a multiple of 256: the low byte of bits(f) - p * bits(q) is mod(x, p).
+// p = 256: the coefficients are (1, 0, 0, 0) and t = 0; the low byte of f is the result whatever q is.
+#pragma once
+#include <cmath>
+#include <cstdint>
+#include <cstring>
+
+namespace oz2 {
+
+struct ByteMod {
+    uint32_t coef;                      // 256^j mod p in byte j (p = 256: byte 0 only)
+    uint32_t base;                      // 0x4b000000 + t
+    float pinv, magic;                  // 1/p; 1.5 * 2^23 + j
+    int32_t neg_p;
+};
+
+inline ByteMod make_byte_mod(int p) {
+    ByteMod b{};
+    uint32_t power = 1 % p;
+    for (int j = 0; j < 4; ++j) { b.coef |= power << (8 * j); power = power * 256u % (uint32_t)p; }
+    const int h = (p - 1) / 2;
+    // x = u - 2^31, so t = -2^31 - h (mod p)
+    const int t = p == 256 ? 0 : (int)((((int64_t)p << 32) - ((int64_t)1 << 31) - h) % p);
+    b.base = 0x4b000000u + (uint32_t)t;
+    int j = 0;
+    if (p % 2) while ((unsigned)(-p * j - h) & 0xffu) ++j;
+    b.pinv = 1.0f / (float)p;
+    b.magic = 12582912.0f + (float)j;
+    b.neg_p = -p;
+    return b;
+}
+
+// What the device computes from the biased sum u: a word whose low byte is mod(u - 2^31, p).
+inline uint32_t byte_mod_word(uint32_t u, const ByteMod &b) {
+    uint32_t f = b.base;
+    for (int j = 0; j < 4; ++j) f += ((u >> (8 * j)) & 0xffu) * ((b.coef >> (8 * j)) & 0xffu);
+    float y, q;
+    std::memcpy(&y, &f, 4);
+    q = std::fmaf(y - 8388608.0f, b.pinv, b.magic);
+    uint32_t qb;
+    std::memcpy(&qb, &q, 4);
+    const int32_t q24 = (int32_t)(qb << 8) >> 8;            // the 24-bit operand of v_mad_i32_i24
+    return (uint32_t)q24 * (uint32_t)b.neg_p + f;
+}
+
+}  // namespace oz2

@@ -27,6 +27,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "oz2_bytemod.hpp"
 #include "oz2_kernels.hpp"
 
 namespace oz2 {
@@ -113,10 +114,30 @@ __device__ __forceinline__ uint32_t add_mod_bytes(uint32_t a, uint32_t b, int p)
     return even | (odd << 8);
 }
 
-struct GemmMods {                       // moduli of the slices and their mulhi multipliers
+struct GemmMods {                       // moduli of the slices and what their reductions need
     int32_t p[kMaxModuli];
-    int32_t pinv_prime[kMaxModuli];
+    int32_t pinv_prime[kMaxModuli];     // mulhi reduction (int32 forms)
+    ByteMod byte_mod[kMaxModuli];       // reduction to bytes (uint8 forms)
 };
+
+// The uint8 forms start their accumulators at -2^31 (see oz2_bytemod.hpp), the others at 0.
+constexpr int first_acc(int out) { return out == kOutU8 || out == kOutU8Fold ? (int)0x80000000 : 0; }
+
+// byte_mod_word on the device: with its share of the packing 15 cycles per wavefront and entry where
+// the mulhi form of mod_small takes 26.  Measured for whole calls, mulhi form -> this one: 8192 x 8192 x
+// 512, N = 15, 1299 -> 1245 us; 4096 x 3072 x 2048 prepared 454 -> 435 us; 4096^3, N = 14, 1142 -> 1121 us; no
+// difference at 16384^3, where the store phase is 2 % of a tile.
+__device__ __forceinline__ uint32_t byte_mod_word_dev(int acc, const ByteMod &b) {
+    const uint32_t f = __builtin_amdgcn_udot4((uint32_t)acc, b.coef, b.base, false);
+    const float q = __builtin_fmaf(__builtin_bit_cast(float, f) - 8388608.0f, b.pinv, b.magic);
+    return (uint32_t)__mul24(__builtin_bit_cast(int, q), b.neg_p) + f;
+}
+
+// The low bytes of four words in one.
+__device__ __forceinline__ uint32_t pack_low_bytes(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3) {
+    const uint32_t lo = __builtin_amdgcn_perm(w1, w0, 0x0c0c0400u), hi = __builtin_amdgcn_perm(w3, w2, 0x0c0c0400u);
+    return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+}
 
 // The LDS of a workgroup: STAGES stages of (A rows | B rows) x 64 bytes.  Declared here, not
 // passed around, so that every access is an offset from a base the compiler knows.
@@ -324,14 +345,15 @@ struct GemmCore {
     // The store phase (Algorithm 1 lines 6-7 in the forms listed at kOut...).  The B fragment is
     // the MFMA's first operand, so the 32x32 accumulator is the transposed block: lane l holds
     // row (l % 32) of the C block and, in registers 4g .. 4g+3, the four consecutive columns
-    // 8g + 4*(l / 32) + {0,1,2,3}.  The reduction is the mulhi form of Section 4.3 (an FP64
-    // floor/fma version measured 1.1 ms slower per launch at 16 x 16384^3).
+    // 8g + 4*(l / 32) + {0,1,2,3}.  The reduction to bytes is that of oz2_bytemod.hpp; the int32
+    // forms use the mulhi reduction of Section 4.3.
     template <int OUT>
     __device__ __forceinline__ void store(const v16i (&acc)[TM][TN], void *C, int s, int64_t bm, int64_t bn,
                                           int64_t c_ld, int64_t c_plane, const GemmMods &mods) const {
         const int p = mods.p[s], pv = mods.pinv_prime[s];
         const int64_t c_off = (int64_t)s * c_plane + bm * c_ld + bn;   // C: [slice][row][column]
         if (OUT == kOutU8 || OUT == kOutU8Fold) {
+            const ByteMod b = mods.byte_mod[s];
             // Four residues per register quad pack into one dword; the two half-wavefronts hold
             // alternating dwords of a row (columns 8g + 4*(l/32) ...), so they swap two dwords
             // each (lanes 0-31 end up with columns 0-15 of the block row, lanes 32-63 with 16-31)
@@ -345,12 +367,10 @@ struct GemmCore {
                 for (int j = 0; j < TN; ++j) {
                     uint32_t d[4];
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        d[g] = 0;
-#pragma unroll
-                        for (int c = 0; c < 4; ++c)
-                            d[g] |= (uint32_t)mod_small(acc[i][j][4 * g + c], p, pv) << (8 * c);
-                    }
+                    for (int g = 0; g < 4; ++g)
+                        d[g] = pack_low_bytes(byte_mod_word_dev(acc[i][j][4 * g], b), byte_mod_word_dev(acc[i][j][4 * g + 1], b),
+                                              byte_mod_word_dev(acc[i][j][4 * g + 2], b),
+                                              byte_mod_word_dev(acc[i][j][4 * g + 3], b));
                     // v_permlane32_swap(a, b): the upper half of a and the lower half of b change
                     // places, so lanes 0-31 get (d0 | d0 of lane + 32) and lanes 32-63 (d2 of lane
                     // - 32 | d2) in (a, b): the row's dwords in column order, no selects needed.
@@ -391,13 +411,13 @@ struct GemmCore {
                 }
     }
 
-    static __device__ __forceinline__ void clear(v16i (&acc)[TM][TN]) {
+    static __device__ __forceinline__ void fill(v16i (&acc)[TM][TN], int v) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = v;
     }
 };
 
@@ -418,7 +438,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_int8_gemm(const int8_t *__rest
     const int8_t *src = core.tile_source(A, B, s, tile_r, tile_c, Mp, Np, KB, kb0);
     core.issue_head(src, KT);
     v16i acc[TM][TN];
-    Core::clear(acc);
+    Core::fill(acc, first_acc(OUT));
     core.contract(src, KT, acc);
     const int64_t bm = (int64_t)tile_r * Core::BM, bn = (int64_t)tile_c * Core::BN;
     if (OUT == kOutMax) {
@@ -455,7 +475,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_int8_gemm_persistent(const int
     core.issue_head(src, KT);
     for (;;) {
         v16i acc[TM][TN];
-        Core::clear(acc);
+        Core::fill(acc, first_acc(OUT));
         core.contract(src, KT, acc);
         // Every wavefront has passed the last barrier, so nothing reads the LDS stages any more:
         // the head of this workgroup's next tile is requested now and travels while the results
@@ -599,7 +619,10 @@ hipError_t launch_int8_gemm(const int8_t *A, const int8_t *B, void *C, int batch
         return hipErrorInvalidValue;                       // whole tiles, 16-byte stores
     GemmMods mods{};
     if (ma)
-        for (int i = 0; i < ma->n; ++i) { mods.p[i] = ma->p[i]; mods.pinv_prime[i] = (int32_t)ma->pinv_prime[i]; }
+        for (int i = 0; i < ma->n; ++i) {
+            mods.p[i] = ma->p[i]; mods.pinv_prime[i] = (int32_t)ma->pinv_prime[i];
+            mods.byte_mod[i] = make_byte_mod(ma->p[i]);
+        }
     else if (as_u8 || fold)
         return hipErrorInvalidValue;                       // the reduced forms need the moduli
     if (as_u8)
