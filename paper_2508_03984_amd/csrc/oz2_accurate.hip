@@ -39,16 +39,16 @@ __global__ __launch_bounds__(256) void k_row_maxbits(const T *__restrict__ X, in
 }
 
 // pre[v] = 5 - floor(log2 max) (0 for an all-zero vector: its magnitudes are all 0 anyway), for
-// the rows of A and the columns of B in one go (their arrays adjoin); also clears the maxima of
-// Cbar for every K range (a kernel, not a memset: the call may be captured into a HIP graph).
+// the vectors of one factor; also clears their maxima of Cbar for every K range, `stride` apart (a
+// kernel, not a memset: the call may be captured into a HIP graph).
 __global__ __launch_bounds__(256) void k_preshift(const unsigned long long *__restrict__ maxbits,
-                                                  int64_t count, int ranges, int32_t *__restrict__ pre,
-                                                  int32_t *__restrict__ cmax) {
+                                                  int64_t vecs, int64_t stride, int ranges,
+                                                  int32_t *__restrict__ pre, int32_t *__restrict__ cmax) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= count) return;
+    if (i >= vecs) return;
     const uint64_t b = maxbits[i];
     pre[i] = b ? 5 - floor_log2_of_bits(b) : 0;
-    for (int r = 0; r < ranges; ++r) cmax[r * count + i] = 0;
+    for (int r = 0; r < ranges; ++r) cmax[r * stride + i] = 0;
 }
 
 // t[v] = (5 - e_v) + floor(P'_accu - 0.51 log2 max(c_v, 1)) with c_v the sum over the K ranges of
@@ -96,34 +96,32 @@ template <typename T>
 hipError_t launch_accurate_prescale(const T *A, int64_t lda, bool a_k_contiguous, const T *B,
                                     int64_t ldb, bool b_k_contiguous, int64_t m, int64_t n,
                                     int64_t k, int ranges, void *scratch, int8_t *Abar, int8_t *Bbar,
-                                    int64_t Mp, int64_t Np, int64_t Kp, bool small, hipStream_t stream) {
+                                    int64_t Mp, int64_t Np, int64_t Kp, bool fused, hipStream_t stream) {
     if (ranges < 1 || ranges > kMaxKRanges) return hipErrorInvalidValue;
     const Scratch s = carve(scratch, m, n);
-    if (small) {                                          // both factors per launch
-        if (hipError_t e = launch_small_maxbits<T>(A, lda, a_k_contiguous, B, ldb, b_k_contiguous, m, n, k,
-                                                   s.amax, s.bmax, stream))
-            return e;
-        hipLaunchKernelGGL(k_preshift, dim3(blocks_for(m + n)), dim3(256), 0, stream, s.amax, m + n, ranges,
-                           s.preA, s.cmax);
-        return launch_small_magnitudes<T>(A, lda, a_k_contiguous, B, ldb, b_k_contiguous, m, n, k, s.preA,
-                                          s.preB, Abar, Bbar, Mp, Np, Kp, stream);
+    // Factors whose vectors fit a workgroup: everything in one launch for both.
+    const bool use[2] = {fused && fused_applies(Kp, a_k_contiguous), fused && fused_applies(Kp, b_k_contiguous)};
+    const bool kc[2] = {a_k_contiguous, b_k_contiguous};
+    if (use[0] || use[1]) {
+        const FusedFactor<T> fa{use[0] ? A : nullptr, lda, kc[0], m, k, s.preA, Abar, Mp, Kp, s.amax, s.cmax, m + n, ranges};
+        const FusedFactor<T> fb{use[1] ? B : nullptr, ldb, kc[1], n, k, s.preB, Bbar, Np, Kp, s.bmax, s.cmax + m, m + n, ranges};
+        if (hipError_t e = launch_fused_magnitudes<T>(fa, fb, fused_plan(Kp, use, kc, sizeof(T)), stream)) return e;
     }
-    // A vector of the product (a row of op(A), a column of op(B)) is either contiguous in
-    // memory (one workgroup per vector) or strided by the leading dimension (column kernels).
-    if (a_k_contiguous)
-        hipLaunchKernelGGL((k_row_maxbits<T>), dim3((unsigned)m), dim3(256), 0, stream, A, lda, k, s.amax);
-    else if (hipError_t e = launch_col_maxbits<T>(A, lda, k, m, s.amax, stream)) return e;
-    if (b_k_contiguous)
-        hipLaunchKernelGGL((k_row_maxbits<T>), dim3((unsigned)n), dim3(256), 0, stream, B, ldb, k, s.bmax);
-    else if (hipError_t e = launch_col_maxbits<T>(B, ldb, k, n, s.bmax, stream)) return e;
-    // amax | bmax, preA | preB and the row | column maxima adjoin: one launch for both factors
-    hipLaunchKernelGGL(k_preshift, dim3(blocks_for(m + n)), dim3(256), 0, stream, s.amax, m + n, ranges, s.preA,
-                       s.cmax);
-    if (hipError_t e = a_k_contiguous ? launch_magnitudes<T>(A, lda, m, k, s.preA, Abar, Mp, Kp, stream)
-                                      : launch_magnitudes_cols<T>(A, lda, k, m, s.preA, Abar, Mp, Kp, stream))
-        return e;
-    return b_k_contiguous ? launch_magnitudes<T>(B, ldb, n, k, s.preB, Bbar, Np, Kp, stream)
-                          : launch_magnitudes_cols<T>(B, ldb, k, n, s.preB, Bbar, Np, Kp, stream);
+    // The others: maxima, then pre-shifts (and the cleared maxima of Cbar), then magnitudes.  A vector of
+    // the product (a row of op(A), a column of op(B)) is either contiguous in memory (one workgroup per
+    // vector) or strided by the leading dimension (column kernels).
+    auto general = [&](const T *X, int64_t ld, bool k_contiguous, int64_t vecs, unsigned long long *maxbits, int32_t *pre,
+                       int32_t *cmax, int8_t *out, int64_t vecs_pad) -> hipError_t {
+        if (k_contiguous)
+            hipLaunchKernelGGL((k_row_maxbits<T>), dim3((unsigned)vecs), dim3(256), 0, stream, X, ld, k, maxbits);
+        else if (hipError_t e = launch_col_maxbits<T>(X, ld, k, vecs, maxbits, stream)) return e;
+        hipLaunchKernelGGL(k_preshift, dim3(blocks_for(vecs)), dim3(256), 0, stream, maxbits, vecs, m + n, ranges, pre, cmax);
+        return k_contiguous ? launch_magnitudes<T>(X, ld, vecs, k, pre, out, vecs_pad, Kp, stream)
+                            : launch_magnitudes_cols<T>(X, ld, k, vecs, pre, out, vecs_pad, Kp, stream);
+    };
+    if (!use[0])
+        if (hipError_t e = general(A, lda, a_k_contiguous, m, s.amax, s.preA, s.cmax, Abar, Mp)) return e;
+    return use[1] ? hipSuccess : general(B, ldb, b_k_contiguous, n, s.bmax, s.preB, s.cmax + m, Bbar, Np);
 }
 
 void accurate_maxima(void *scratch, int64_t m, int64_t n, int range, int **row_max, int **col_max) {

@@ -35,7 +35,7 @@ struct oz2_context {
     bool profiling = false;
     bool int32_products = false;           // diagnostic form: keep C'_s as int32
     bool overlap = false;                  // conversion of later panels beside the GEMMs (run_overlapped)
-    bool small_conversion = true;          // fused conversion launches for small problems (oz2_small.hip)
+    bool small_conversion = true;          // fused conversion launches (oz2_fused.hip, oz2_small.hip)
     bool cut_launches = true;              // GEMM launches of a large product cut into parts (launch_panels)
     hipEvent_t ev[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
     bool ev_recorded = false;
@@ -320,9 +320,12 @@ oz2_status gemm_impl(Ctx &g, int opA, int opB, int64_t m, int64_t n, int64_t k, 
     int8_t *rB = reinterpret_cast<int8_t *>(g.ws + L.off_rb);
     void *prod = g.ws + L.off_prod;
 
-    // Small problems: the conversion of both factors in two launches instead of seven (and
-    // likewise the passes of accurate mode that precede Cbar).
-    const bool small = g.small_conversion && small_conversion_applies(m, n, k);
+    // Factors whose vectors fit a workgroup are converted in one launch and one read (their shifts
+    // then count as residues in the stage times); likewise the passes of accurate mode that precede Cbar.
+    // The overlapped form needs the shifts first.
+    const bool kc[2] = {a_kc, b_kc};
+    const bool fusing = g.small_conversion && !accurate && !overlapped;
+    const bool fuse[2] = {fusing && fused_applies(L.Kp, a_kc), fusing && fused_applies(L.Kp, b_kc)};
     if (oz2_status st = mark(g, 0, stream)) return st;
     if (accurate) {
         // Section 4.2, accurate mode: 7-bit matrices into slice 0; of Cbar only the row and
@@ -332,7 +335,7 @@ oz2_status gemm_impl(Ctx &g, int opA, int opB, int64_t m, int64_t n, int64_t k, 
         // inequalities behind the scale vectors needs.
         const int ranges = (int)((L.Kp + OZ2_MAX_K - 1) / OZ2_MAX_K);
         OZ2_TRY(launch_accurate_prescale<T>(A, lda, a_kc, B, ldb, b_kc, m, n, k, ranges, scratch, rA, rB, L.Mp,
-                                            L.Np, L.Kp, small, stream));
+                                            L.Np, L.Kp, g.small_conversion, stream));
         const GemmPanel all{0, L.Mp, 0, L.Np, L.Np, L.Mp * L.Np};      // nothing is stored: no panels needed
         for (int r = 0; r < ranges; ++r) {
             int *row_max = nullptr, *col_max = nullptr;
@@ -342,11 +345,9 @@ oz2_status gemm_impl(Ctx &g, int opA, int opB, int64_t m, int64_t n, int64_t k, 
                                             all, m, n, row_max, col_max, stream));
         }
         OZ2_TRY(launch_accurate_finish(m, n, ranges, make_accu_shift_args(tab), scratch, tA, tB, stream));
-    } else if (small) {
-        OZ2_TRY(launch_small_shifts<T>(A, lda, a_kc, B, ldb, b_kc, m, n, k, sa, tA, tB, stream));
     } else {
-        OZ2_TRY(launch_fast_shifts<T>(A, lda, a_kc, m, k, sa, scratch, tA, stream));
-        OZ2_TRY(launch_fast_shifts<T>(B, ldb, b_kc, n, k, sa, scratch, tB, stream));
+        if (!fuse[0]) OZ2_TRY(launch_fast_shifts<T>(A, lda, a_kc, m, k, sa, scratch, tA, stream));
+        if (!fuse[1]) OZ2_TRY(launch_fast_shifts<T>(B, ldb, b_kc, n, k, sa, scratch, tB, stream));
     }
     if (oz2_status st = mark(g, 1, stream)) return st;
     if (overlapped) {
@@ -356,12 +357,17 @@ oz2_status gemm_impl(Ctx &g, int opA, int opB, int64_t m, int64_t n, int64_t k, 
         g.ev_recorded = g.profiling;
         return OZ2_OK;
     }
-    if (small) {
+    if (accurate && g.small_conversion && small_conversion_applies(m, n, k)) {
         OZ2_TRY(launch_small_residues<T>(A, lda, a_kc, B, ldb, b_kc, m, n, k, ma, tA, tB, rA, rB, L.Mp, L.Np,
                                          L.Kp, stream));
     } else {
-        OZ2_TRY(launch_any_residues<T>(A, lda, a_kc, m, k, tA, ma, rA, L.Mp, L.Kp, stream));
-        OZ2_TRY(launch_any_residues<T>(B, ldb, b_kc, n, k, tB, ma, rB, L.Np, L.Kp, stream));
+        if (fuse[0] || fuse[1]) {
+            const FusedFactor<T> fa{fuse[0] ? A : nullptr, lda, a_kc, m, k, tA, rA, L.Mp, L.Kp, nullptr, nullptr, 0, 0};
+            const FusedFactor<T> fb{fuse[1] ? B : nullptr, ldb, b_kc, n, k, tB, rB, L.Np, L.Kp, nullptr, nullptr, 0, 0};
+            OZ2_TRY(launch_fused_conversion<T>(fa, fb, fused_plan(L.Kp, fuse, kc, sizeof(T)), sa, ma, stream));
+        }
+        if (!fuse[0]) OZ2_TRY(launch_any_residues<T>(A, lda, a_kc, m, k, tA, ma, rA, L.Mp, L.Kp, stream));
+        if (!fuse[1]) OZ2_TRY(launch_any_residues<T>(B, ldb, b_kc, n, k, tB, ma, rB, L.Np, L.Kp, stream));
     }
     if (oz2_status st = mark(g, 2, stream)) return st;
     if (oz2_status st = run_products<T>(g, L, P, rA, rB, tA, tB, prod, ma, alpha, beta, C, ldc, stream)) return st;

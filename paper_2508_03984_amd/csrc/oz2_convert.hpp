@@ -26,8 +26,7 @@ __device__ inline uint64_t wave_sum(uint64_t v) {
 // ----------------------------------------------------------------------------------------
 // Residues.  x' = trunc(x 2^t) is an integer-valued FP64 number below 2^77.  Its
 // symmetric residue modulo p comes from rounds of  y <- fma(-rint(y * (1/p)), p, y),
-// the reduction of Section 4.2 kept in FP64 throughout (FP64 and FP32 FMA run at the
-// same rate on this chip, so there is nothing to gain from dropping to FP32):
+// the reduction of Section 4.2 kept in FP64 throughout:
 //   the first round is exact (the difference is an integer below 2^26 in magnitude) and leaves
 //   |y| <= p/2 + 2^-52 |x'|;  for |x'| < 2^46 the quotient estimate is within 2^-13 of
 //   x'/p, closer than any integer/p can be to a half-integer for odd p, so rint returns
@@ -43,9 +42,45 @@ __device__ inline uint64_t wave_sum(uint64_t v) {
 __device__ inline double group_reduce(double x, double M, double Minv) {
     return fma(-rint(x * Minv), M, x);
 }
-__device__ inline int residue_of(double y, double p, double pinv) {
-    return (int)fma(-rint(y * pinv), p, y);
+
+// The one-round case for 8 numbers at a time, only the low byte of y - p rint(y/p) being wanted:
+// one FP64 FMA leaves 1.5 * 2^52 + rint(y/p), whose low half holds the quotient modulo 2^32, and the rest
+// is 16-bit integer arithmetic on two numbers per instruction.  (The FMA rounds y/p once where a
+// multiplication followed by rint rounds twice; the quotient is the same, since y/p is further from a
+// half-integer than either error for odd p, and p = 256 divides exactly.)  9 cycles per wavefront,
+// number and modulus where multiply, rint, FMA, conversion and byte insertion took 22.
+typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+constexpr double kRintMagic = 6755399441055744.0;                     // 1.5 * 2^52
+__device__ __forceinline__ uint32_t low_word(double x) { return (uint32_t)__double_as_longlong(x); }
+__device__ __forceinline__ us2 low_halves(double x0, double x1) {     // the low 16 bits of both
+    return __builtin_bit_cast(us2, __builtin_amdgcn_perm(low_word(x1), low_word(x0), 0x05040100u));
 }
+
+struct ResidueInput {
+    double y[8];                                                      // |y| < 2^46, integers
+    us2 low[4];                                                       // their low 16 bits
+    __device__ __forceinline__ void set_low() {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) low[i] = low_halves(y[2 * i] + kRintMagic, y[2 * i + 1] + kRintMagic);
+    }
+    // the residues modulo p of the 8 numbers as 8 bytes
+    __device__ __forceinline__ uint2 residues(int p, double pinv) const {
+        const us2 neg_p = {(unsigned short)-p, (unsigned short)-p};
+        uint32_t w[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            us2 r[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int e = 4 * h + 2 * i;
+                r[i] = low_halves(fma(y[e], pinv, kRintMagic), fma(y[e + 1], pinv, kRintMagic)) * neg_p + low[e / 2];
+            }
+            w[h] = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, r[1]), __builtin_bit_cast(uint32_t, r[0]),
+                                         0x06040200u);
+        }
+        return make_uint2(w[0], w[1]);
+    }
+};
 
 constexpr int kResPerThread = 8;     // consecutive elements per thread -> 8-byte stores
 
@@ -110,21 +145,14 @@ __device__ __forceinline__ void residues_block(int64_t block, const T *__restric
     }
     const int s_end = group_hi < (ma.n + kModGroup - 1) / kModGroup ? group_hi * kModGroup : ma.n;
     for (int s0 = group_lo * kModGroup; s0 < s_end; s0 += kModGroup) {
-        double y[kResPerThread];
+        ResidueInput in;
 #pragma unroll
         for (int i = 0; i < kResPerThread; ++i)
-            y[i] = ROUNDS == 2 ? group_reduce(v[i], ma.group_mod[s0 / kModGroup], ma.group_inv[s0 / kModGroup]) : v[i];
+            in.y[i] = ROUNDS == 2 ? group_reduce(v[i], ma.group_mod[s0 / kModGroup], ma.group_inv[s0 / kModGroup]) : v[i];
+        in.set_low();
         const int s1 = s0 + kModGroup < ma.n ? s0 + kModGroup : ma.n;
-        for (int s = s0; s < s1; ++s) {
-            const double p = (double)ma.p[s], pinv = ma.pinv[s];
-            uint32_t w[2] = {0u, 0u};
-#pragma unroll
-            for (int i = 0; i < kResPerThread; ++i) {
-                uint32_t b = (uint32_t)residue_of(y[i], p, pinv) & 0xffu;
-                w[i >> 2] |= b << (8 * (i & 3));
-            }
-            *reinterpret_cast<uint2 *>(o + (int64_t)s * plane) = make_uint2(w[0], w[1]);
-        }
+        for (int s = s0; s < s1; ++s)
+            *reinterpret_cast<uint2 *>(o + (int64_t)s * plane) = in.residues(ma.p[s], ma.pinv[s]);
     }
 }
 
@@ -173,27 +201,28 @@ __device__ __forceinline__ void residues_cols_block(int64_t block_x, int64_t blo
     const int n_slices = group_hi < (n_all + kGroup - 1) / kGroup ? group_hi * kGroup : n_all;
     for (int s0 = group_lo * kGroup; s0 < n_slices; s0 += kGroup) {
         const int ns = n_slices - s0 < kGroup ? n_slices - s0 : kGroup;
-        double y[2][8];
-#pragma unroll
-        for (int half = 0; half < 2; ++half)
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                y[half][i] = (KIND == 0 && ROUNDS == 2)
-                                 ? group_reduce(v[half][i], ma.group_mod[s0 / kGroup], ma.group_inv[s0 / kGroup])
-                                 : v[half][i];
-        for (int g = 0; g < ns; ++g) {
-            const double p = (double)ma.p[s0 + g], pinv = ma.pinv[s0 + g];
+        if (KIND == 1) {
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
                 uint32_t w[2] = {0u, 0u};
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    uint32_t b = (KIND == 0 ? (uint32_t)residue_of(y[half][i], p, pinv)
-                                            : (uint32_t)(int)y[half][i]) & 0xffu;
-                    w[i >> 2] |= b << (8 * (i & 3));
-                }
-                stage[g][wave + 4 * half][lane] = make_uint2(w[0], w[1]);
+                for (int i = 0; i < 8; ++i) w[i >> 2] |= ((uint32_t)(int)v[half][i] & 0xffu) << (8 * (i & 3));
+                stage[0][wave + 4 * half][lane] = make_uint2(w[0], w[1]);
             }
+        } else {
+            ResidueInput in[2];
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    in[half].y[i] = ROUNDS == 2 ? group_reduce(v[half][i], ma.group_mod[s0 / kGroup], ma.group_inv[s0 / kGroup])
+                                                : v[half][i];
+                in[half].set_low();
+            }
+            for (int g = 0; g < ns; ++g)
+#pragma unroll
+                for (int half = 0; half < 2; ++half)
+                    stage[g][wave + 4 * half][lane] = in[half].residues(ma.p[s0 + g], ma.pinv[s0 + g]);
         }
         __syncthreads();
         for (int g = 0; g < ns; ++g) {

@@ -1,0 +1,259 @@
+// Algorithm 1 lines 1-5 in one launch and one read of the operands: scale vector and residues.
+// A workgroup owns whole vectors (V rows, or a strip of V columns, of a factor) and keeps them in
+// registers between the three things that are done to them: the maximum of |x|, the exact sum of
+// squares behind the shift (fast mode of Section 4.2), and the reduction modulo all N moduli.  The
+// general kernels (oz2_prepost.hip, oz2_columns.hip) do these in two to six launches and two or three
+// reads; their results are the same bit for bit.  fused_plan (oz2_plan.hpp) says which vectors fit.
+//
+// Layout: after the load, thread `tid` holds in piece c the 8 consecutive elements of number
+//   q = c THREADS + tid = ((kb V + vec) 8 + piece),  element h = 64 kb + 8 piece + {0..7} of vector vec,
+// so that the 8-byte pieces of residues which a wavefront stores are 512 contiguous bytes of the K-blocked
+// slice (for V >= 8).  Rows are loaded that way directly.  A strip of columns is loaded along its rows
+// (64-byte segments for V = 8 in FP64) and exchanged through LDS, once per element and not once per
+// modulus.
+//
+// KIND 1 is the first half of accurate mode: the maximum, the pre-shift 5 - e and the 7-bit magnitudes
+// ceil(|x| 2^(5-e)) (slice 0); the maxima of Cbar are cleared on the way.
+//
+// Bound: HBM (reads and N bytes per element written) for large vectors, launch and load latency for
+// small ones.
+#include <algorithm>
+
+#include "oz2_convert.hpp"
+#include "oz2_kernels.hpp"
+
+namespace oz2 {
+namespace {
+
+using namespace dev;
+
+constexpr int kMaxLogV = 5;
+
+template <typename T>
+struct Side {
+    const T *X;
+    int64_t ld, vecs, len;      // `vecs` vectors of `len` elements: X[v ld + h] (k_contiguous) or X[h ld + v]
+    int32_t *t;                 // [vecs] shifts (KIND 1: pre-shifts)
+    unsigned long long *maxbits;   // KIND 1: [vecs] bits of max |x|
+    int32_t *cmax;              // KIND 1: [ranges][cmax_stride], cleared
+    int64_t cmax_stride;
+    int8_t *out;                // slices [N][len_pad/64][vecs_pad][64]
+    int64_t vecs_pad, len_pad;
+    int ranges;
+    int k_contiguous, log_v;    // vectors per workgroup = 2^log_v
+    unsigned blocks;            // workgroups of this side
+};
+
+__device__ inline uint64_t abs_bits(double x) { return (uint64_t)__double_as_longlong(fabs(x)); }
+
+template <typename T, int THREADS, int CH, int ROUNDS, int KIND>
+__global__ __launch_bounds__(THREADS) void k_convert(Side<T> a, Side<T> b, ShiftArgs sa, ModArgs ma) {
+    __shared__ T tile[THREADS * 9];                                   // one piece per thread, padded (columns only)
+    __shared__ unsigned long long red_max[1 << kMaxLogV], red_sum[1 << kMaxLogV];
+    const bool first = blockIdx.x < a.blocks;
+    const Side<T> s = first ? a : b;
+    unsigned blk = first ? blockIdx.x : blockIdx.x - a.blocks;
+    // Workgroups go to the 8 XCDs round-robin: neighbouring vectors, which share 128-byte lines of the
+    // operand (strips of columns) or of the slices (single rows), are given to one XCD.
+    if ((s.blocks & 7u) == 0) blk = (blk & 7u) * (s.blocks >> 3) + (blk >> 3);
+    const int tid = threadIdx.x, lane = tid & 63, lv = s.log_v, V = 1 << lv;
+    const int64_t v0 = (int64_t)blk << lv;
+    const int vec = (tid >> 3) & (V - 1), piece = tid & 7;
+    const bool valid = v0 + vec < s.vecs;
+    if (tid < V) { red_max[tid] = 0; red_sum[tid] = 0; }
+
+    double x[CH][8];
+    const int kb0 = tid >> (3 + lv), kb_step = THREADS >> (3 + lv);   // K block of piece c: kb0 + c kb_step
+    if (s.k_contiguous) {
+        const T *row = s.X + (v0 + vec) * s.ld;
+        const bool aligned = (reinterpret_cast<uintptr_t>(row) & 15) == 0;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            const int64_t h0 = (int64_t)(kb0 + c * kb_step) * kBlockK + piece * 8;
+            if (valid && aligned && h0 + 8 <= s.len) {
+                constexpr int kVec = 16 / sizeof(T);
+                typedef T vec_t __attribute__((ext_vector_type(kVec)));
+#pragma unroll
+                for (int i = 0; i < 8 / kVec; ++i) {
+                    const vec_t w = reinterpret_cast<const vec_t *>(row + h0)[i];
+#pragma unroll
+                    for (int e = 0; e < kVec; ++e) x[c][i * kVec + e] = (double)w[e];
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) x[c][i] = valid && h0 + i < s.len ? (double)row[h0 + i] : 0.0;
+            }
+        }
+    } else {
+        // thread -> column tid & (V - 1) and, a constant stride apart, the rows (tid >> lv) + j (THREADS >> lv)
+        const int col = tid & (V - 1), step = THREADS >> lv;
+        const T *src = s.X + v0 + col + (int64_t)(tid >> lv) * s.ld;
+        const int64_t src_step = step * s.ld;
+        T raw[CH][8];
+        int left = v0 + col < s.vecs ? (int)s.len - (tid >> lv) : 0;  // rows from this thread's to the last
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                raw[c][i] = left > 0 ? *src : T(0);
+                src += src_step;
+                left -= step;
+            }
+        const int group = 9 * V;                                      // 8 rows of V elements, and V of padding
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int r = (i * THREADS + tid) >> lv;
+                tile[(r >> 3) * group + (r & 7) * V + col] = raw[c][i];
+            }
+            __syncthreads();
+            const T *mine = tile + (kb0 * 8 + piece) * group + vec;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[c][i] = (double)mine[i * V];
+        }
+    }
+
+    // maximum of |x| per vector
+    uint64_t mx = 0;
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const uint64_t bits = abs_bits(x[c][i]);
+            mx = bits > mx ? bits : mx;
+        }
+    auto over_lanes = [&](auto op, uint64_t v) {                      // lanes of this wavefront with the same vector
+        for (int off = 1; off < 8; off <<= 1) v = op(v, (uint64_t)__shfl_xor(v, off, kWave));
+        for (int off = 8 << lv; off < kWave; off <<= 1) v = op(v, (uint64_t)__shfl_xor(v, off, kWave));
+        return v;
+    };
+    const bool leader = piece == 0 && (lane >> (3 + lv)) == 0;        // one lane per wavefront and vector
+    mx = over_lanes([](uint64_t p, uint64_t q) { return p > q ? p : q; }, mx);
+    __syncthreads();                                                  // red_max is cleared
+    if (leader) atomicMax(&red_max[vec], (unsigned long long)mx);
+    __syncthreads();
+    mx = red_max[vec];
+    const int e = mx ? floor_log2_of_bits(mx) : 0;
+    const bool writes = tid < 8 * V && piece == 0 && valid;           // one thread per vector
+
+    if (KIND == 1) {
+        const int pre = mx ? 5 - e : 0;
+        if (writes) {
+            s.maxbits[v0 + vec] = mx;
+            s.t[v0 + vec] = pre;
+            for (int r = 0; r < s.ranges; ++r) s.cmax[r * s.cmax_stride + v0 + vec] = 0;
+        }
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            const int64_t kb = kb0 + c * kb_step;
+            if (kb * kBlockK >= s.len_pad) continue;
+            uint32_t w[2] = {0u, 0u};
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                w[i >> 2] |= ((uint32_t)(int)ceil(ldexp(fabs(x[c][i]), pre)) & 0xffu) << (8 * (i & 3));
+            *reinterpret_cast<uint2 *>(s.out + (kb * s.vecs_pad + v0 + vec) * kBlockK + piece * 8) = make_uint2(w[0], w[1]);
+        }
+        return;
+    }
+
+    // T = sum of ceil(|x| 2^(15-e))^2: integers of at most 2^32, whose sum (at most 2^53) FP64 holds exactly
+    double sum = 0.0;
+    if (mx) {
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const double q = ceil(ldexp(fabs(x[c][i]), 15 - e));
+                sum = fma(q, q, sum);
+            }
+    }
+    const uint64_t part = over_lanes([](uint64_t p, uint64_t q) { return p + q; }, (uint64_t)sum);
+    if (leader) atomicAdd(&red_sum[vec], (unsigned long long)part);
+    __syncthreads();
+    int t = 0;
+    if (mx) {
+        const uint64_t T_ = red_sum[vec];
+        int j = 0;
+        while (j < sa.levels - 1 && T_ > sa.theta[j]) ++j;
+        t = (sa.f_max - j) - e;
+    }
+    if (writes) s.t[v0 + vec] = t;
+
+    const int64_t plane = s.vecs_pad * s.len_pad;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        const int64_t kb = kb0 + c * kb_step;
+        if (kb * kBlockK >= s.len_pad) continue;
+        int8_t *o = s.out + (kb * s.vecs_pad + v0 + vec) * kBlockK + piece * 8;
+        double v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = trunc(ldexp(x[c][i], t));
+        for (int s0 = 0; s0 < ma.n; s0 += kModGroup) {
+            ResidueInput in;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                in.y[i] = ROUNDS == 2 ? group_reduce(v[i], ma.group_mod[s0 / kModGroup], ma.group_inv[s0 / kModGroup]) : v[i];
+            in.set_low();
+            const int s1 = s0 + kModGroup < ma.n ? s0 + kModGroup : ma.n;
+            for (int m = s0; m < s1; ++m)
+                *reinterpret_cast<uint2 *>(o + (int64_t)m * plane) = in.residues(ma.p[m], ma.pinv[m]);
+        }
+    }
+}
+
+template <typename T>
+Side<T> side_of(const FusedFactor<T> &f, const FusedPlan &plan, int side) {
+    Side<T> s{};
+    if (!f.X) return s;                                               // no workgroups
+    s.X = f.X; s.ld = f.ld; s.vecs = f.vecs; s.len = f.len; s.t = f.t; s.maxbits = f.maxbits;
+    s.cmax = f.cmax; s.cmax_stride = f.cmax_stride; s.ranges = f.ranges;
+    s.out = f.out; s.vecs_pad = f.vecs_pad; s.len_pad = f.len_pad;
+    s.k_contiguous = f.k_contiguous ? 1 : 0;
+    s.log_v = plan.log_v[side];
+    s.blocks = (unsigned)(f.vecs_pad >> s.log_v);
+    return s;
+}
+
+template <typename T, int ROUNDS, int KIND>
+hipError_t launch_kind(const Side<T> &a, const Side<T> &b, const FusedPlan &plan, const ShiftArgs &sa, const ModArgs &ma,
+                       hipStream_t stream) {
+    const dim3 grid(a.blocks + b.blocks);
+#define OZ2_CONVERT(THREADS, CH)                                                                              \
+    if (plan.threads == THREADS && plan.pieces == CH) {                                                       \
+        hipLaunchKernelGGL((k_convert<T, THREADS, CH, ROUNDS, KIND>), grid, dim3(THREADS), 0, stream, a, b, sa, ma); \
+        return hipGetLastError();                                                                             \
+    }
+    OZ2_CONVERT(256, 1) OZ2_CONVERT(256, 2) OZ2_CONVERT(512, 2) OZ2_CONVERT(512, 3) OZ2_CONVERT(512, 4)
+    OZ2_CONVERT(1024, 3) OZ2_CONVERT(1024, 4)
+#undef OZ2_CONVERT
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+template <typename T>
+hipError_t launch_fused_conversion(const FusedFactor<T> &A, const FusedFactor<T> &B, const FusedPlan &plan,
+                                   const ShiftArgs &sa, const ModArgs &ma, hipStream_t stream) {
+    const Side<T> a = side_of(A, plan, 0), b = side_of(B, plan, 1);
+    return ma.rounds == 1 ? launch_kind<T, 1, 0>(a, b, plan, sa, ma, stream) : launch_kind<T, 2, 0>(a, b, plan, sa, ma, stream);
+}
+
+template <typename T>
+hipError_t launch_fused_magnitudes(const FusedFactor<T> &A, const FusedFactor<T> &B, const FusedPlan &plan,
+                                   hipStream_t stream) {
+    const Side<T> a = side_of(A, plan, 0), b = side_of(B, plan, 1);
+    return launch_kind<T, 1, 1>(a, b, plan, ShiftArgs{}, ModArgs{}, stream);
+}
+
+#define OZ2_INSTANTIATE_FUSED(T)                                                                              \
+    template hipError_t launch_fused_conversion<T>(const FusedFactor<T> &, const FusedFactor<T> &,            \
+                                                   const FusedPlan &, const ShiftArgs &, const ModArgs &,     \
+                                                   hipStream_t);                                              \
+    template hipError_t launch_fused_magnitudes<T>(const FusedFactor<T> &, const FusedFactor<T> &,            \
+                                                   const FusedPlan &, hipStream_t);
+OZ2_INSTANTIATE_FUSED(double)
+OZ2_INSTANTIATE_FUSED(float)
+
+}  // namespace oz2

@@ -89,40 +89,50 @@ hipError_t launch_residues_cols(const T *X, int64_t ld, int64_t rows, int64_t co
                                 const ModArgs &ma, int8_t *out, int64_t cols_pad, int64_t rows_pad,
                                 hipStream_t stream, int64_t cols_stride = 0);   // stride: as in launch_residues
 
-// Algorithm 1 lines 1-5 (fast mode) for SMALL problems, where the number of dependent launches
-// sets the time: one launch for the shifts of both factors and one for their residues, with the
-// results of the launchers above.  A is the left factor (m vectors of k elements: its rows when
-// a_k_contiguous, else its columns), B the right one (n vectors); slices as in launch_residues.
-// small_conversion_applies (oz2_plan.hpp) says for which shapes these launchers may be used.
+// Algorithm 1 lines 1-5 (fast mode) for one or both factors in ONE launch that reads them once
+// (oz2_fused.hip), with the results of the launchers above: the shifts t and the residue slices.
+// A factor has `vecs` vectors of `len` elements, contiguous (k_contiguous) or strided by ld; a factor
+// with X == nullptr takes no part.  fused_applies / fused_plan (oz2_plan.hpp): which vectors can be
+// converted this way, and how.  launch_fused_magnitudes is the first half of accurate mode: maxbits,
+// the pre-shifts (in t) and the 7-bit magnitude matrix (slice 0 of out), and cmax cleared for `ranges`
+// K ranges cmax_stride apart.
 template <typename T>
-hipError_t launch_small_shifts(const T *A, int64_t lda, bool a_k_contiguous, const T *B, int64_t ldb,
-                               bool b_k_contiguous, int64_t m, int64_t n, int64_t k, const ShiftArgs &sa,
-                               int32_t *tA, int32_t *tB, hipStream_t stream);
+struct FusedFactor {
+    const T *X;
+    int64_t ld;
+    bool k_contiguous;
+    int64_t vecs, len;
+    int32_t *t;
+    int8_t *out;
+    int64_t vecs_pad, len_pad;
+    unsigned long long *maxbits;         // launch_fused_magnitudes only, like the following
+    int32_t *cmax;
+    int64_t cmax_stride;
+    int ranges;
+};
+template <typename T>
+hipError_t launch_fused_conversion(const FusedFactor<T> &A, const FusedFactor<T> &B, const FusedPlan &plan,
+                                   const ShiftArgs &sa, const ModArgs &ma, hipStream_t stream);
+template <typename T>
+hipError_t launch_fused_magnitudes(const FusedFactor<T> &A, const FusedFactor<T> &B, const FusedPlan &plan,
+                                   hipStream_t stream);
+
+// The residues of both factors in one launch where the shifts are known (accurate mode) and the
+// problem is small: slices as in launch_residues.  small_conversion_applies (oz2_plan.hpp) says for
+// which shapes.
 template <typename T>
 hipError_t launch_small_residues(const T *A, int64_t lda, bool a_k_contiguous, const T *B, int64_t ldb,
                                  bool b_k_contiguous, int64_t m, int64_t n, int64_t k, const ModArgs &ma,
                                  const int32_t *tA, const int32_t *tB, int8_t *rA, int8_t *rB, int64_t Mp,
                                  int64_t Np, int64_t Kp, hipStream_t stream);
 
-// The same for accurate mode: the bits of max |.| per vector of both factors in one launch, and
-// the 7-bit magnitude matrices ceil(|x| 2^pre) of both (slice 0 of the residue buffers) in one.
-template <typename T>
-hipError_t launch_small_maxbits(const T *A, int64_t lda, bool a_k_contiguous, const T *B, int64_t ldb,
-                                bool b_k_contiguous, int64_t m, int64_t n, int64_t k,
-                                unsigned long long *amax, unsigned long long *bmax, hipStream_t stream);
-template <typename T>
-hipError_t launch_small_magnitudes(const T *A, int64_t lda, bool a_k_contiguous, const T *B, int64_t ldb,
-                                   bool b_k_contiguous, int64_t m, int64_t n, int64_t k, const int32_t *preA,
-                                   const int32_t *preB, int8_t *Abar, int8_t *Bbar, int64_t Mp, int64_t Np,
-                                   int64_t Kp, hipStream_t stream);
-
 // Accurate mode (Section 4.2, second half).  All vectors live in `scratch`
 // (accurate_scratch_bytes(m, n) bytes); the 7-bit matrices go to slice 0 of the residue
 // buffers (same K-blocked layout); Cbar itself is never stored:
 //   launch_accurate_prescale   max|.| per row of A / column of B, mu' = 2^(5-e), nu', and
 //                              Abar = ceil(mu' |A|), Bbar = ceil(|B| nu') as int8; clears the
-//                              maxima of Cbar for `ranges` K ranges.  small: with the fused
-//                              launches for small problems
+//                              maxima of Cbar for `ranges` K ranges.  fused: factors that
+//                              launch_fused_magnitudes can take go there
 //   (the caller then runs launch_int8_gemm_maxima on Cbar_r = Abar * Bbar over each K range r)
 //   launch_accurate_finish     t = (5 - e) + floor(P'_accu - 0.51 log2 c), c = the sum over the
 //                              ranges of the maxima of Cbar_r (one range: the maximum of Cbar, the
@@ -131,7 +141,7 @@ template <typename T>
 hipError_t launch_accurate_prescale(const T *A, int64_t lda, bool a_k_contiguous, const T *B,
                                     int64_t ldb, bool b_k_contiguous, int64_t m, int64_t n,
                                     int64_t k, int ranges, void *scratch, int8_t *Abar, int8_t *Bbar,
-                                    int64_t Mp, int64_t Np, int64_t Kp, bool small, hipStream_t stream);
+                                    int64_t Mp, int64_t Np, int64_t Kp, bool fused, hipStream_t stream);
 // Where the maxima of Cbar_r live in `scratch` (m row maxima, then n column maxima; the caller
 // fills them with launch_int8_gemm_maxima); _finish turns them into the shifts.
 void accurate_maxima(void *scratch, int64_t m, int64_t n, int range, int **row_max, int **col_max);

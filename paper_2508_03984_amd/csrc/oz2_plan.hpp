@@ -34,6 +34,35 @@ inline bool small_conversion_applies(int64_t m, int64_t n, int64_t k) {
     return k <= 4096 && m <= 8192 && n <= 8192 && (m + n) * k <= (int64_t)2 * 2048 * 2048;
 }
 
+// The fused conversion (oz2_fused.hip): a workgroup of `threads` threads holds 8 `pieces` elements per
+// thread, i.e. 2^log_v whole vectors of Kp elements.  8 vectors make a wavefront's stores 512
+// contiguous bytes and a strip of FP64 columns 64-byte segments, so the smallest workgroup with room
+// for 8 vectors is taken (for strips of FP32 columns: 16, up to the largest workgroup).  Longer rows
+// go down to one vector of 32768 elements.  Columns of more than 4096 elements are left to the
+// general kernels: fewer than 8 of them would be read in segments of 32 bytes and less.
+struct FusedPlan {
+    int threads, pieces;
+    int log_v[2];                          // of the left and of the right factor
+};
+constexpr int kFusedElements = 32768;      // 1024 threads, 4 pieces
+
+inline bool fused_applies(int64_t Kp, bool k_contiguous) { return Kp <= (k_contiguous ? kFusedElements : kFusedElements / 8); }
+
+// use[i]: the factor takes part; k_contiguous[i]: its vectors are contiguous.
+inline FusedPlan fused_plan(int64_t Kp, const bool use[2], const bool k_contiguous[2], size_t element) {
+    static const int shapes[][2] = {{256, 1}, {256, 2}, {512, 2}, {512, 3}, {512, 4}, {1024, 3}, {1024, 4}};
+    const bool strips = (use[0] && !k_contiguous[0]) || (use[1] && !k_contiguous[1]);
+    const int64_t want = Kp * (strips && element == 4 ? 16 : 8);
+    FusedPlan p{1024, 4, {0, 0}};
+    for (const auto &s : shapes)
+        if ((int64_t)s[0] * s[1] * 8 >= want) { p.threads = s[0]; p.pieces = s[1]; break; }
+    const int64_t room = (int64_t)p.threads * p.pieces * 8;
+    int lv = 0;
+    while (lv < 5 && (Kp << (lv + 1)) <= room && (16 << lv) <= p.threads) ++lv;
+    p.log_v[0] = p.log_v[1] = lv;
+    return p;
+}
+
 inline bool supported(int64_t k, int N) {
     return N >= OZ2_MIN_MODULI && N <= OZ2_MAX_MODULI && k <= OZ2_MAX_K_BLOCKED;
 }
