@@ -101,11 +101,10 @@ hipError_t launch_accurate_prescale(const T *A, int64_t lda, bool a_k_contiguous
     const Scratch s = carve(scratch, m, n);
     // Factors whose vectors fit a workgroup: everything in one launch for both.
     const bool use[2] = {fused && fused_applies(Kp, a_k_contiguous), fused && fused_applies(Kp, b_k_contiguous)};
-    const bool kc[2] = {a_k_contiguous, b_k_contiguous};
     if (use[0] || use[1]) {
-        const FusedFactor<T> fa{use[0] ? A : nullptr, lda, kc[0], m, k, s.preA, Abar, Mp, Kp, s.amax, s.cmax, m + n, ranges};
-        const FusedFactor<T> fb{use[1] ? B : nullptr, ldb, kc[1], n, k, s.preB, Bbar, Np, Kp, s.bmax, s.cmax + m, m + n, ranges};
-        if (hipError_t e = launch_fused_magnitudes<T>(fa, fb, fused_plan(Kp, use, kc, sizeof(T)), stream)) return e;
+        const FusedFactor<T> fa{use[0] ? A : nullptr, lda, a_k_contiguous, m, k, s.preA, Abar, Mp, Kp, s.amax, s.cmax, m + n, ranges};
+        const FusedFactor<T> fb{use[1] ? B : nullptr, ldb, b_k_contiguous, n, k, s.preB, Bbar, Np, Kp, s.bmax, s.cmax + m, m + n, ranges};
+        if (hipError_t e = launch_fused_magnitudes<T>(fa, fb, stream)) return e;
     }
     // The others: maxima, then pre-shifts (and the cleared maxima of Cbar), then magnitudes.  A vector of
     // the product (a row of op(A), a column of op(B)) is either contiguous in memory (one workgroup per

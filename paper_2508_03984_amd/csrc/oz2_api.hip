@@ -323,7 +323,6 @@ oz2_status gemm_impl(Ctx &g, int opA, int opB, int64_t m, int64_t n, int64_t k, 
     // Factors whose vectors fit a workgroup are converted in one launch and one read (their shifts
     // then count as residues in the stage times); likewise the passes of accurate mode that precede Cbar.
     // The overlapped form needs the shifts first.
-    const bool kc[2] = {a_kc, b_kc};
     const bool fusing = g.small_conversion && !accurate && !overlapped;
     const bool fuse[2] = {fusing && fused_applies(L.Kp, a_kc), fusing && fused_applies(L.Kp, b_kc)};
     if (oz2_status st = mark(g, 0, stream)) return st;
@@ -364,7 +363,7 @@ oz2_status gemm_impl(Ctx &g, int opA, int opB, int64_t m, int64_t n, int64_t k, 
         if (fuse[0] || fuse[1]) {
             const FusedFactor<T> fa{fuse[0] ? A : nullptr, lda, a_kc, m, k, tA, rA, L.Mp, L.Kp, nullptr, nullptr, 0, 0};
             const FusedFactor<T> fb{fuse[1] ? B : nullptr, ldb, b_kc, n, k, tB, rB, L.Np, L.Kp, nullptr, nullptr, 0, 0};
-            OZ2_TRY(launch_fused_conversion<T>(fa, fb, fused_plan(L.Kp, fuse, kc, sizeof(T)), sa, ma, stream));
+            OZ2_TRY(launch_fused_conversion<T>(fa, fb, sa, ma, stream));
         }
         if (!fuse[0]) OZ2_TRY(launch_any_residues<T>(A, lda, a_kc, m, k, tA, ma, rA, L.Mp, L.Kp, stream));
         if (!fuse[1]) OZ2_TRY(launch_any_residues<T>(B, ldb, b_kc, n, k, tB, ma, rB, L.Np, L.Kp, stream));
@@ -414,11 +413,16 @@ oz2_status prepare_impl(int side, int op, int64_t rows, int64_t k, const T *X, i
     o->mem = static_cast<char *>(p);
     o->t = reinterpret_cast<int32_t *>(o->mem);
     o->res = reinterpret_cast<int8_t *>(o->mem + off_res);
-    hipError_t e = launch_fast_shifts<T>(X, ld, k_contiguous, rows, k, make_shift_args(tab),
-                                         o->mem + off_scratch, o->t, stream);
-    if (e == hipSuccess)
-        e = launch_any_residues<T>(X, ld, k_contiguous, rows, k, o->t, make_mod_args(tab, false), o->res,
-                                   o->rows_pad, o->Kp, stream);
+    hipError_t e = hipSuccess;
+    if (fused_applies(o->Kp, k_contiguous)) {
+        const FusedFactor<T> f{X, ld, k_contiguous, rows, k, o->t, o->res, o->rows_pad, o->Kp, nullptr, nullptr, 0, 0};
+        e = launch_fused_conversion<T>(f, FusedFactor<T>{}, make_shift_args(tab), make_mod_args(tab, false), stream);
+    } else {
+        e = launch_fast_shifts<T>(X, ld, k_contiguous, rows, k, make_shift_args(tab), o->mem + off_scratch, o->t, stream);
+        if (e == hipSuccess)
+            e = launch_any_residues<T>(X, ld, k_contiguous, rows, k, o->t, make_mod_args(tab, false), o->res,
+                                       o->rows_pad, o->Kp, stream);
+    }
     if (e != hipSuccess) { (void)hipFree(o->mem); delete o; return OZ2_HIP_ERROR; }
     *out = o;
     return OZ2_OK;

@@ -23,6 +23,26 @@ __device__ inline uint64_t wave_sum(uint64_t v) {
     return v;
 }
 
+// f = f_max - j, j = the number of thresholds below v (the table is sorted and filled up with the largest
+// number; at most levels - 1): all comparisons at once instead of a search whose every step waits for a
+// scalar load.
+__device__ __forceinline__ int shift_exponent(uint64_t v, const ShiftArgs &sa) {
+    int j = 0;
+#pragma unroll
+    for (int i = 0; i < kMaxLevels; ++i) j += v > sa.theta[i] ? 1 : 0;
+    return sa.f_max - (j < sa.levels - 1 ? j : sa.levels - 1);
+}
+
+// v of another lane: bits 1:0 of the lane number flipped by the quad permutations, the others by
+// mirroring groups of 8 or 16 lanes (the callers have made the lanes of a group equal before).
+constexpr int kDppXor1 = 0xb1, kDppXor2 = 0x4e, kDppMirror8 = 0x141, kDppMirror16 = 0x140;
+template <int CTRL>
+__device__ __forceinline__ uint64_t dpp64(uint64_t v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), CTRL, 0xf, 0xf, false);
+    return (uint64_t)(uint32_t)lo | ((uint64_t)(uint32_t)hi << 32);
+}
+
 // ----------------------------------------------------------------------------------------
 // Residues.  x' = trunc(x 2^t) is an integer-valued FP64 number below 2^77.  Its
 // symmetric residue modulo p comes from rounds of  y <- fma(-rint(y * (1/p)), p, y),
@@ -83,6 +103,21 @@ struct ResidueInput {
 };
 
 constexpr int kResPerThread = 8;     // consecutive elements per thread -> 8-byte stores
+
+// store(s, bytes) for the moduli s0 <= s < n of one group.  The constants of all of them are requested
+// together (s0 + 4 < kMaxModuli always): where few wavefronts are resident, one that waits for each
+// modulus' own scalar loads takes about twice as long.
+template <typename Store>
+__device__ __forceinline__ void emit_group(const ResidueInput &in, const ModArgs &ma, int s0, int n, Store store) {
+    int p[kModGroup];
+    double pinv[kModGroup];
+#pragma unroll
+    for (int g = 0; g < kModGroup; ++g) { p[g] = ma.p[s0 + g]; pinv[g] = ma.pinv[s0 + g]; }
+#pragma unroll
+    for (int g = 0; g < kModGroup; ++g)
+        if (s0 + g < n) store(s0 + g, in.residues(p[g], pinv[g]));
+}
+static_assert(kMaxModuli % kModGroup == 0, "emit_group reads the constants of whole groups");
 
 // KIND 0: residues of trunc(x 2^t) for all moduli.  KIND 1 (accurate mode): the single
 // 7-bit magnitude matrix ceil(|x| 2^t), written as slice 0.
@@ -150,14 +185,13 @@ __device__ __forceinline__ void residues_block(int64_t block, const T *__restric
         for (int i = 0; i < kResPerThread; ++i)
             in.y[i] = ROUNDS == 2 ? group_reduce(v[i], ma.group_mod[s0 / kModGroup], ma.group_inv[s0 / kModGroup]) : v[i];
         in.set_low();
-        const int s1 = s0 + kModGroup < ma.n ? s0 + kModGroup : ma.n;
-        for (int s = s0; s < s1; ++s)
-            *reinterpret_cast<uint2 *>(o + (int64_t)s * plane) = in.residues(ma.p[s], ma.pinv[s]);
+        emit_group(in, ma, s0, ma.n, [&](int s, uint2 w) { *reinterpret_cast<uint2 *>(o + (int64_t)s * plane) = w; });
     }
 }
 
 // KIND as in the row kernel: 0 = residues for all moduli, 1 = the 7-bit magnitudes (slice 0).
-template <typename T, int ROUNDS, int KIND>
+// THREADS: 512 (one piece of 8 elements per thread) or 256 (two).
+template <typename T, int ROUNDS, int KIND, int THREADS>
 __device__ __forceinline__ void residues_cols_block(int64_t block_x, int64_t block_y,
                                                     const T *__restrict__ X, int64_t ld, int64_t rows,
                                                     int64_t cols, const int32_t *__restrict__ t,
@@ -174,16 +208,17 @@ __device__ __forceinline__ void residues_cols_block(int64_t block_x, int64_t blo
     // resident workgroups) independent of N; a group is also what shares the first reduction
     // round when two are needed.
     constexpr int kGroup = kModGroup;
+    constexpr int kWaves = THREADS / kWave, kHalves = 8 / kWaves;     // pieces wave, wave + kWaves
     __shared__ uint2 stage[kGroup][8][65];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t c = block_x * kColStrip + lane;                     // column of X = row of the output
     const int64_t kb = block_y;                                       // K block
     const int sh = c < cols ? t[c] : 0;
 
-    double v[2][8];                                                   // pieces wave and wave + 4
+    double v[kHalves][8];
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-        const int64_t h0 = kb * kBlockK + (wave + 4 * half) * 8;
+    for (int half = 0; half < kHalves; ++half) {
+        const int64_t h0 = kb * kBlockK + (wave + kWaves * half) * 8;
 #pragma unroll
         for (int i = 0; i < 8; ++i)
             v[half][i] = !(c < cols && h0 + i < rows) ? 0.0
@@ -194,8 +229,9 @@ __device__ __forceinline__ void residues_cols_block(int64_t block_x, int64_t blo
     // Write-out: per modulus the 64 columns x 64 bytes of this tile are contiguous in
     // out[s][kb][c0 .. c0+63][64]; thread -> (column, 16-byte quarter).
     const int64_t plane = cols_stride * rows_pad;
-    const int col = threadIdx.x >> 2, quarter = threadIdx.x & 3;
-    int8_t *dst = out + (kb * cols_stride + block_x * kColStrip) * kBlockK + threadIdx.x * 16;
+    const int part = threadIdx.x & 255, col = part >> 2, quarter = part & 3;
+    const int g0 = threadIdx.x >> 8;                                  // 512 threads: two moduli at a time
+    int8_t *dst = out + (kb * cols_stride + block_x * kColStrip) * kBlockK + part * 16;
 
     const int n_all = KIND == 0 ? ma.n : 1;
     const int n_slices = group_hi < (n_all + kGroup - 1) / kGroup ? group_hi * kGroup : n_all;
@@ -203,29 +239,29 @@ __device__ __forceinline__ void residues_cols_block(int64_t block_x, int64_t blo
         const int ns = n_slices - s0 < kGroup ? n_slices - s0 : kGroup;
         if (KIND == 1) {
 #pragma unroll
-            for (int half = 0; half < 2; ++half) {
+            for (int half = 0; half < kHalves; ++half) {
                 uint32_t w[2] = {0u, 0u};
 #pragma unroll
                 for (int i = 0; i < 8; ++i) w[i >> 2] |= ((uint32_t)(int)v[half][i] & 0xffu) << (8 * (i & 3));
-                stage[0][wave + 4 * half][lane] = make_uint2(w[0], w[1]);
+                stage[0][wave + kWaves * half][lane] = make_uint2(w[0], w[1]);
             }
         } else {
-            ResidueInput in[2];
+            ResidueInput in[kHalves];
 #pragma unroll
-            for (int half = 0; half < 2; ++half) {
+            for (int half = 0; half < kHalves; ++half) {
 #pragma unroll
                 for (int i = 0; i < 8; ++i)
                     in[half].y[i] = ROUNDS == 2 ? group_reduce(v[half][i], ma.group_mod[s0 / kGroup], ma.group_inv[s0 / kGroup])
                                                 : v[half][i];
                 in[half].set_low();
             }
-            for (int g = 0; g < ns; ++g)
 #pragma unroll
-                for (int half = 0; half < 2; ++half)
-                    stage[g][wave + 4 * half][lane] = in[half].residues(ma.p[s0 + g], ma.pinv[s0 + g]);
+            for (int half = 0; half < kHalves; ++half)
+                emit_group(in[half], ma, s0, s0 + ns,
+                           [&](int s, uint2 w) { stage[s - s0][wave + kWaves * half][lane] = w; });
         }
         __syncthreads();
-        for (int g = 0; g < ns; ++g) {
+        for (int g = g0; g < ns; g += THREADS / 256) {
             const uint2 lo = stage[g][2 * quarter][col];
             const uint2 hi = stage[g][2 * quarter + 1][col];
             *reinterpret_cast<uint4 *>(dst + (int64_t)(s0 + g) * plane) = make_uint4(lo.x, lo.y, hi.x, hi.y);

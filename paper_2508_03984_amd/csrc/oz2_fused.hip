@@ -125,8 +125,12 @@ __global__ __launch_bounds__(THREADS) void k_convert(Side<T> a, Side<T> b, Shift
             mx = bits > mx ? bits : mx;
         }
     auto over_lanes = [&](auto op, uint64_t v) {                      // lanes of this wavefront with the same vector
-        for (int off = 1; off < 8; off <<= 1) v = op(v, (uint64_t)__shfl_xor(v, off, kWave));
-        for (int off = 8 << lv; off < kWave; off <<= 1) v = op(v, (uint64_t)__shfl_xor(v, off, kWave));
+        v = op(v, dpp64<kDppXor1>(v));
+        v = op(v, dpp64<kDppXor2>(v));
+        v = op(v, dpp64<kDppMirror8>(v));
+        if (lv < 1) v = op(v, dpp64<kDppMirror16>(v));
+        if (lv < 2) v = op(v, (uint64_t)__shfl_xor(v, 16, kWave));
+        if (lv < 3) v = op(v, (uint64_t)__shfl_xor(v, 32, kWave));
         return v;
     };
     const bool leader = piece == 0 && (lane >> (3 + lv)) == 0;        // one lane per wavefront and vector
@@ -172,13 +176,7 @@ __global__ __launch_bounds__(THREADS) void k_convert(Side<T> a, Side<T> b, Shift
     const uint64_t part = over_lanes([](uint64_t p, uint64_t q) { return p + q; }, (uint64_t)sum);
     if (leader) atomicAdd(&red_sum[vec], (unsigned long long)part);
     __syncthreads();
-    int t = 0;
-    if (mx) {
-        const uint64_t T_ = red_sum[vec];
-        int j = 0;
-        while (j < sa.levels - 1 && T_ > sa.theta[j]) ++j;
-        t = (sa.f_max - j) - e;
-    }
+    const int t = mx ? shift_exponent(red_sum[vec], sa) - e : 0;
     if (writes) s.t[v0 + vec] = t;
 
     const int64_t plane = s.vecs_pad * s.len_pad;
@@ -196,36 +194,43 @@ __global__ __launch_bounds__(THREADS) void k_convert(Side<T> a, Side<T> b, Shift
             for (int i = 0; i < 8; ++i)
                 in.y[i] = ROUNDS == 2 ? group_reduce(v[i], ma.group_mod[s0 / kModGroup], ma.group_inv[s0 / kModGroup]) : v[i];
             in.set_low();
-            const int s1 = s0 + kModGroup < ma.n ? s0 + kModGroup : ma.n;
-            for (int m = s0; m < s1; ++m)
-                *reinterpret_cast<uint2 *>(o + (int64_t)m * plane) = in.residues(ma.p[m], ma.pinv[m]);
+            emit_group(in, ma, s0, ma.n, [&](int m, uint2 w) { *reinterpret_cast<uint2 *>(o + (int64_t)m * plane) = w; });
         }
     }
 }
 
 template <typename T>
-Side<T> side_of(const FusedFactor<T> &f, const FusedPlan &plan, int side) {
+Side<T> side_of(const FusedFactor<T> &f, const FusedPlan &plan) {
     Side<T> s{};
     if (!f.X) return s;                                               // no workgroups
     s.X = f.X; s.ld = f.ld; s.vecs = f.vecs; s.len = f.len; s.t = f.t; s.maxbits = f.maxbits;
     s.cmax = f.cmax; s.cmax_stride = f.cmax_stride; s.ranges = f.ranges;
     s.out = f.out; s.vecs_pad = f.vecs_pad; s.len_pad = f.len_pad;
     s.k_contiguous = f.k_contiguous ? 1 : 0;
-    s.log_v = plan.log_v[side];
+    s.log_v = plan.log_v;
     s.blocks = (unsigned)(f.vecs_pad >> s.log_v);
     return s;
 }
 
 template <typename T, int ROUNDS, int KIND>
-hipError_t launch_kind(const Side<T> &a, const Side<T> &b, const FusedPlan &plan, const ShiftArgs &sa, const ModArgs &ma,
+hipError_t launch_kind(const FusedFactor<T> &A, const FusedFactor<T> &B, const ShiftArgs &sa, const ModArgs &ma,
                        hipStream_t stream) {
+    const int64_t Kp = A.X ? A.len_pad : B.len_pad;
+    const bool strips = (A.X && !A.k_contiguous) || (B.X && !B.k_contiguous);
+    if (A.X && B.X && A.k_contiguous != B.k_contiguous && Kp > kFusedShareLaunch) {
+        const FusedFactor<T> none{};
+        if (hipError_t e = launch_kind<T, ROUNDS, KIND>(A, none, sa, ma, stream)) return e;
+        return launch_kind<T, ROUNDS, KIND>(none, B, sa, ma, stream);
+    }
+    const FusedPlan plan = fused_plan(Kp, strips);
+    const Side<T> a = side_of(A, plan), b = side_of(B, plan);
     const dim3 grid(a.blocks + b.blocks);
 #define OZ2_CONVERT(THREADS, CH)                                                                              \
     if (plan.threads == THREADS && plan.pieces == CH) {                                                       \
         hipLaunchKernelGGL((k_convert<T, THREADS, CH, ROUNDS, KIND>), grid, dim3(THREADS), 0, stream, a, b, sa, ma); \
         return hipGetLastError();                                                                             \
     }
-    OZ2_CONVERT(256, 1) OZ2_CONVERT(256, 2) OZ2_CONVERT(512, 2) OZ2_CONVERT(512, 3) OZ2_CONVERT(512, 4)
+    OZ2_CONVERT(256, 1) OZ2_CONVERT(512, 1) OZ2_CONVERT(512, 2) OZ2_CONVERT(512, 3) OZ2_CONVERT(512, 4)
     OZ2_CONVERT(1024, 3) OZ2_CONVERT(1024, 4)
 #undef OZ2_CONVERT
     return hipErrorInvalidValue;
@@ -234,25 +239,20 @@ hipError_t launch_kind(const Side<T> &a, const Side<T> &b, const FusedPlan &plan
 }  // namespace
 
 template <typename T>
-hipError_t launch_fused_conversion(const FusedFactor<T> &A, const FusedFactor<T> &B, const FusedPlan &plan,
-                                   const ShiftArgs &sa, const ModArgs &ma, hipStream_t stream) {
-    const Side<T> a = side_of(A, plan, 0), b = side_of(B, plan, 1);
-    return ma.rounds == 1 ? launch_kind<T, 1, 0>(a, b, plan, sa, ma, stream) : launch_kind<T, 2, 0>(a, b, plan, sa, ma, stream);
+hipError_t launch_fused_conversion(const FusedFactor<T> &A, const FusedFactor<T> &B, const ShiftArgs &sa,
+                                   const ModArgs &ma, hipStream_t stream) {
+    return ma.rounds == 1 ? launch_kind<T, 1, 0>(A, B, sa, ma, stream) : launch_kind<T, 2, 0>(A, B, sa, ma, stream);
 }
 
 template <typename T>
-hipError_t launch_fused_magnitudes(const FusedFactor<T> &A, const FusedFactor<T> &B, const FusedPlan &plan,
-                                   hipStream_t stream) {
-    const Side<T> a = side_of(A, plan, 0), b = side_of(B, plan, 1);
-    return launch_kind<T, 1, 1>(a, b, plan, ShiftArgs{}, ModArgs{}, stream);
+hipError_t launch_fused_magnitudes(const FusedFactor<T> &A, const FusedFactor<T> &B, hipStream_t stream) {
+    return launch_kind<T, 1, 1>(A, B, ShiftArgs{}, ModArgs{}, stream);
 }
 
 #define OZ2_INSTANTIATE_FUSED(T)                                                                              \
     template hipError_t launch_fused_conversion<T>(const FusedFactor<T> &, const FusedFactor<T> &,            \
-                                                   const FusedPlan &, const ShiftArgs &, const ModArgs &,     \
-                                                   hipStream_t);                                              \
-    template hipError_t launch_fused_magnitudes<T>(const FusedFactor<T> &, const FusedFactor<T> &,            \
-                                                   const FusedPlan &, hipStream_t);
+                                                   const ShiftArgs &, const ModArgs &, hipStream_t);          \
+    template hipError_t launch_fused_magnitudes<T>(const FusedFactor<T> &, const FusedFactor<T> &, hipStream_t);
 OZ2_INSTANTIATE_FUSED(double)
 OZ2_INSTANTIATE_FUSED(float)
 

@@ -89,11 +89,11 @@ hipError_t launch_residues_cols(const T *X, int64_t ld, int64_t rows, int64_t co
                                 const ModArgs &ma, int8_t *out, int64_t cols_pad, int64_t rows_pad,
                                 hipStream_t stream, int64_t cols_stride = 0);   // stride: as in launch_residues
 
-// Algorithm 1 lines 1-5 (fast mode) for one or both factors in ONE launch that reads them once
-// (oz2_fused.hip), with the results of the launchers above: the shifts t and the residue slices.
+// Algorithm 1 lines 1-5 (fast mode) for one or both factors in one launch that reads them once
+// (two launches for long vectors of different forms; oz2_fused.hip), with the results of the launchers above: the shifts t and the residue slices.
 // A factor has `vecs` vectors of `len` elements, contiguous (k_contiguous) or strided by ld; a factor
-// with X == nullptr takes no part.  fused_applies / fused_plan (oz2_plan.hpp): which vectors can be
-// converted this way, and how.  launch_fused_magnitudes is the first half of accurate mode: maxbits,
+// with X == nullptr takes no part.  fused_applies (oz2_plan.hpp) says which vectors can be converted
+// this way.  launch_fused_magnitudes is the first half of accurate mode: maxbits,
 // the pre-shifts (in t) and the 7-bit magnitude matrix (slice 0 of out), and cmax cleared for `ranges`
 // K ranges cmax_stride apart.
 template <typename T>
@@ -111,11 +111,10 @@ struct FusedFactor {
     int ranges;
 };
 template <typename T>
-hipError_t launch_fused_conversion(const FusedFactor<T> &A, const FusedFactor<T> &B, const FusedPlan &plan,
-                                   const ShiftArgs &sa, const ModArgs &ma, hipStream_t stream);
+hipError_t launch_fused_conversion(const FusedFactor<T> &A, const FusedFactor<T> &B, const ShiftArgs &sa,
+                                   const ModArgs &ma, hipStream_t stream);
 template <typename T>
-hipError_t launch_fused_magnitudes(const FusedFactor<T> &A, const FusedFactor<T> &B, const FusedPlan &plan,
-                                   hipStream_t stream);
+hipError_t launch_fused_magnitudes(const FusedFactor<T> &A, const FusedFactor<T> &B, hipStream_t stream);
 
 // The residues of both factors in one launch where the shifts are known (accurate mode) and the
 // problem is small: slices as in launch_residues.  small_conversion_applies (oz2_plan.hpp) says for

@@ -35,33 +35,37 @@ inline bool small_conversion_applies(int64_t m, int64_t n, int64_t k) {
 }
 
 // The fused conversion (oz2_fused.hip): a workgroup of `threads` threads holds 8 `pieces` elements per
-// thread, i.e. 2^log_v whole vectors of Kp elements.  8 vectors make a wavefront's stores 512
-// contiguous bytes and a strip of FP64 columns 64-byte segments, so the smallest workgroup with room
-// for 8 vectors is taken (for strips of FP32 columns: 16, up to the largest workgroup).  Longer rows
-// go down to one vector of 32768 elements.  Columns of more than 4096 elements are left to the
-// general kernels: fewer than 8 of them would be read in segments of 32 bytes and less.
+// thread, i.e. 2^log_v whole vectors of Kp elements.
 struct FusedPlan {
-    int threads, pieces;
-    int log_v[2];                          // of the left and of the right factor
+    int threads, pieces, log_v;
 };
-constexpr int kFusedElements = 32768;      // 1024 threads, 4 pieces
+constexpr int64_t kFusedElements = 32768;  // 1024 threads, 4 pieces
+constexpr int64_t kFusedMaxRow = kFusedElements / 2, kFusedMaxColumn = kFusedElements / 8;
 
-inline bool fused_applies(int64_t Kp, bool k_contiguous) { return Kp <= (k_contiguous ? kFusedElements : kFusedElements / 8); }
+// Rows of up to 16384 elements (two per workgroup: 128-byte lines of the slices; one per workgroup measured
+// 1.8 ms for 2^28 elements and 15 moduli against 1.6 ms for the general kernels) and columns of up to
+// 4096 (eight per workgroup: 64-byte segments of the operand in FP64).
+inline bool fused_applies(int64_t Kp, bool k_contiguous) { return Kp <= (k_contiguous ? kFusedMaxRow : kFusedMaxColumn); }
 
-// use[i]: the factor takes part; k_contiguous[i]: its vectors are contiguous.
-inline FusedPlan fused_plan(int64_t Kp, const bool use[2], const bool k_contiguous[2], size_t element) {
-    static const int shapes[][2] = {{256, 1}, {256, 2}, {512, 2}, {512, 3}, {512, 4}, {1024, 3}, {1024, 4}};
-    const bool strips = (use[0] && !k_contiguous[0]) || (use[1] && !k_contiguous[1]);
-    const int64_t want = Kp * (strips && element == 4 ? 16 : 8);
-    FusedPlan p{1024, 4, {0, 0}};
+// The smallest workgroup with room for the vectors above; strips of columns of more than 1024
+// elements take 16 where they fit.  Measured (us, both factors, N = 15 in FP64): rows of 4096, 4096^2
+// each, 512 threads and 2 rows 148, 1024 threads and 8 rows 171 (several workgroups per compute
+// unit overlap one's loads with another's stores); columns of 2048, 2048^2 each, 16 per workgroup 42, 8 52;
+// columns of 1024, 1024^2 each, 8 per workgroup 16.8, 16 21.4.
+inline FusedPlan fused_plan(int64_t Kp, bool strips) {
+    static const int shapes[][2] = {{256, 1}, {512, 1}, {512, 2}, {512, 3}, {512, 4}, {1024, 3}, {1024, 4}};
+    const int64_t want = strips ? Kp * (Kp <= 1024 ? 8 : 16) : Kp * 2;
+    FusedPlan p{1024, 4, 0};
     for (const auto &s : shapes)
         if ((int64_t)s[0] * s[1] * 8 >= want) { p.threads = s[0]; p.pieces = s[1]; break; }
     const int64_t room = (int64_t)p.threads * p.pieces * 8;
-    int lv = 0;
-    while (lv < 5 && (Kp << (lv + 1)) <= room && (16 << lv) <= p.threads) ++lv;
-    p.log_v[0] = p.log_v[1] = lv;
+    while (p.log_v < 5 && (Kp << (p.log_v + 1)) <= room && (16 << p.log_v) <= p.threads) ++p.log_v;
     return p;
 }
+
+// A factor of rows and one of columns share a launch up to here; beyond, the two forms want different
+// workgroups and a launch more costs less.
+constexpr int64_t kFusedShareLaunch = 2048;
 
 inline bool supported(int64_t k, int N) {
     return N >= OZ2_MIN_MODULI && N <= OZ2_MAX_MODULI && k <= OZ2_MAX_K_BLOCKED;
