@@ -5,35 +5,28 @@
 // power-of-two arithmetic, so the shifts are bit-reproducible; the floor(P'_accu - 0.51 log2 c)
 // of the paper is a table lookup on the integer maximum c (built on the host from that
 // formula, see oz2_constants.cpp).
+#include "oz2_convert.hpp"
 #include "oz2_kernels.hpp"
 
 namespace oz2 {
 namespace {
 
-__device__ inline uint64_t wave_max_u64(uint64_t v) {
-    for (int off = 32; off > 0; off >>= 1) {
-        uint64_t o = __shfl_xor(v, off, 64);
-        v = o > v ? o : v;
-    }
-    return v;
-}
-
 // rowmax[r] = max_h bits(|X[r][h]|): one workgroup per row.
+constexpr int kRowThreads = 512;
 template <typename T>
-__global__ __launch_bounds__(256) void k_row_maxbits(const T *__restrict__ X, int64_t ld,
-                                                     int64_t len, unsigned long long *rowmax) {
-    __shared__ uint64_t part[4];
-    const T *x = X + (int64_t)blockIdx.x * ld;
+__global__ __launch_bounds__(kRowThreads) void k_row_maxbits(const T *__restrict__ X, int64_t ld,
+                                                             int64_t len, unsigned long long *rowmax) {
+    __shared__ uint64_t part[kRowThreads / dev::kWave];
     uint64_t mx = 0;
-    for (int64_t h = threadIdx.x; h < len; h += 256) {
-        uint64_t b = (uint64_t)__double_as_longlong(fabs((double)x[h]));
+    dev::scan_row<T, kRowThreads>(X + (int64_t)blockIdx.x * ld, len, [&](double v) {
+        const uint64_t b = dev::abs_bits(v);
         mx = b > mx ? b : mx;
-    }
-    mx = wave_max_u64(mx);
+    });
+    mx = dev::wave_max(mx);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = mx;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < 4; ++w) mx = part[w] > mx ? part[w] : mx;
+        for (int w = 1; w < kRowThreads / dev::kWave; ++w) mx = part[w] > mx ? part[w] : mx;
         rowmax[blockIdx.x] = mx;
     }
 }
@@ -112,7 +105,8 @@ hipError_t launch_accurate_prescale(const T *A, int64_t lda, bool a_k_contiguous
     auto general = [&](const T *X, int64_t ld, bool k_contiguous, int64_t vecs, unsigned long long *maxbits, int32_t *pre,
                        int32_t *cmax, int8_t *out, int64_t vecs_pad) -> hipError_t {
         if (k_contiguous)
-            hipLaunchKernelGGL((k_row_maxbits<T>), dim3((unsigned)vecs), dim3(256), 0, stream, X, ld, k, maxbits);
+            hipLaunchKernelGGL((k_row_maxbits<T>), dim3((unsigned)vecs), dim3(kRowThreads), 0, stream, X, ld, k,
+                               maxbits);
         else if (hipError_t e = launch_col_maxbits<T>(X, ld, k, vecs, maxbits, stream)) return e;
         hipLaunchKernelGGL(k_preshift, dim3(blocks_for(vecs)), dim3(256), 0, stream, maxbits, vecs, m + n, ranges, pre, cmax);
         return k_contiguous ? launch_magnitudes<T>(X, ld, vecs, k, pre, out, vecs_pad, Kp, stream)

@@ -47,14 +47,25 @@ constexpr int64_t kFusedMaxRow = kFusedElements / 2, kFusedMaxColumn = kFusedEle
 // 4096 (eight per workgroup: 64-byte segments of the operand in FP64).
 inline bool fused_applies(int64_t Kp, bool k_contiguous) { return Kp <= (k_contiguous ? kFusedMaxRow : kFusedMaxColumn); }
 
-// The smallest workgroup with room for the vectors above; strips of columns of more than 1024
-// elements take 16 where they fit.  Measured (us, both factors, N = 15 in FP64): rows of 4096, 4096^2
+// The smallest workgroup with room for two rows (four of up to 1024 elements) or eight columns; strips of
+// columns of more than 1024 elements take 16 where they fit.  Measured (us, both factors, N = 15 in FP64): rows of 4096, 4096^2
 // each, 512 threads and 2 rows 148, 1024 threads and 8 rows 171 (several workgroups per compute
 // unit overlap one's loads with another's stores); columns of 2048, 2048^2 each, 16 per workgroup 42, 8 52;
 // columns of 1024, 1024^2 each, 8 per workgroup 16.8, 16 21.4.
-inline FusedPlan fused_plan(int64_t Kp, bool strips) {
+// Beyond 2048 a strip of 8 columns fills a compute unit, and the launch runs in rounds of 256 strips; of strips of
+// 4 two or three are resident.  Those are read less well (1.1 times the time in FP64, 1.3 in FP32, from
+// columns of 4096 and 2048), so they are taken where they save more than that in the last round (1500 + 1111
+// columns of 3001: 71 -> 40 us).
+// vectors: padded number of vectors in the launch.
+inline FusedPlan fused_plan(int64_t Kp, bool strips, int64_t vectors, size_t element) {
     static const int shapes[][2] = {{256, 1}, {512, 1}, {512, 2}, {512, 3}, {512, 4}, {1024, 3}, {1024, 4}};
-    const int64_t want = strips ? Kp * (Kp <= 1024 ? 8 : 16) : Kp * 2;
+    int64_t want = strips ? Kp * (Kp <= 1024 ? 8 : 16) : Kp * (Kp <= 1024 ? 4 : 2);
+    if (strips && Kp > 2048) {
+        const int64_t resident = 4 * Kp <= 512 * 3 * 8 ? 3 : 2;
+        const double by8 = (double)((vectors / 8 + 255) / 256) * 8;
+        const double by4 = (double)((vectors / 4 + 256 * resident - 1) / (256 * resident) * resident) * 4 * (element == 8 ? 1.1 : 1.3);
+        want = Kp * (by4 < by8 ? 4 : 8);
+    }
     FusedPlan p{1024, 4, 0};
     for (const auto &s : shapes)
         if ((int64_t)s[0] * s[1] * 8 >= want) { p.threads = s[0]; p.pieces = s[1]; break; }

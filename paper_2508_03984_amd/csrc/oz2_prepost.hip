@@ -64,52 +64,45 @@ using namespace dev;
 // bit patterns), pass 2 sums q^2 with q = ceil(|x| 2^(15-e)) <= 2^16 in 64-bit integers, which
 // is exact and independent of the order of summation.  f comes from the threshold table,
 // t = f - e.  k_shifts re-reads the row for pass 2 (rows of any length); k_shifts_cached
-// further down keeps rows of up to 16384 elements in registers between the passes.
+// further down keeps rows of up to 49152 elements in registers between the passes.
 // ----------------------------------------------------------------------------------------
+constexpr int kShiftThreads = 512;
+
 template <typename T>
-__global__ __launch_bounds__(256) void k_shifts(const T *__restrict__ X, int64_t ld, int64_t len,
-                                                ShiftArgs sa, int32_t *__restrict__ t) {
-    __shared__ uint64_t part[4];
-    __shared__ uint64_t bcast;
+__global__ __launch_bounds__(kShiftThreads) void k_shifts(const T *__restrict__ X, int64_t ld, int64_t len,
+                                                          ShiftArgs sa, int32_t *__restrict__ t) {
+    constexpr int kWaves = kShiftThreads / kWave;
+    __shared__ uint64_t part_max[kWaves], part_sum[kWaves];
     const T *x = X + (int64_t)blockIdx.x * ld;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 
     uint64_t mx = 0;
-    for (int64_t h = threadIdx.x; h < len; h += 256) {
-        uint64_t b = (uint64_t)__double_as_longlong(fabs((double)x[h]));
+    scan_row<T, kShiftThreads>(x, len, [&](double v) {
+        const uint64_t b = abs_bits(v);
         mx = b > mx ? b : mx;
-    }
+    });
     mx = wave_max(mx);
-    if (lane == 0) part[wave] = mx;
+    if (lane == 0) part_max[wave] = mx;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint64_t m = part[0];
-        for (int w = 1; w < 4; ++w) m = part[w] > m ? part[w] : m;
-        bcast = m;
-    }
-    __syncthreads();
-    mx = bcast;
+    for (int w = 0; w < kWaves; ++w) mx = part_max[w] > mx ? part_max[w] : mx;
     if (mx == 0) {                                                    // all-zero row
         if (threadIdx.x == 0) t[blockIdx.x] = 0;
         return;
     }
     const int e = floor_log2_of_bits(mx);
 
-    uint64_t sum = 0;
-    for (int64_t h = threadIdx.x; h < len; h += 256) {
-        double q = ceil(ldexp(fabs((double)x[h]), 15 - e));
-        uint64_t qi = (uint64_t)q;
-        sum += qi * qi;
-    }
-    sum = wave_sum(sum);
-    __syncthreads();                                                  // part[] is reused
-    if (lane == 0) part[wave] = sum;
+    double sum = 0.0;                                                 // exact: integers, at most 2^53 in all
+    scan_row<T, kShiftThreads>(x, len, [&](double v) {
+        const double q = ceil(ldexp(fabs(v), 15 - e));
+        sum = fma(q, q, sum);
+    });
+    const uint64_t s = wave_sum((uint64_t)sum);
+    if (lane == 0) part_sum[wave] = s;
     __syncthreads();
     if (threadIdx.x == 0) {
-        uint64_t T_ = part[0] + part[1] + part[2] + part[3];
-        int j = 0;
-        while (j < sa.levels - 1 && T_ > sa.theta[j]) ++j;
-        t[blockIdx.x] = (sa.f_max - j) - e;
+        uint64_t T_ = 0;
+        for (int w = 0; w < kWaves; ++w) T_ += part_sum[w];
+        t[blockIdx.x] = shift_exponent(T_, sa) - e;
     }
 }
 
@@ -123,12 +116,12 @@ __global__ __launch_bounds__(256) void k_residues(const T *__restrict__ X, int64
 }
 
 // ----------------------------------------------------------------------------------------
-// Shifts of rows of up to 16384 elements, reading each row once: the row is held in registers
+// Shifts of rows of up to 49152 elements, reading each row once: the row is held in registers
 // (CH pieces of 8 elements per thread, 8 threads per 64 elements), its maximum and then its
 // integer sum of squares come from two workgroup reductions.  Same result as k_shifts, half
-// its memory traffic (0.34 against 0.67 ms at 16384^2 FP64).  (Computing the residues from
-// the same registers as well was measured: no faster than the separate residue kernel, because
-// a workgroup that owns one row writes 64-byte pieces 1 MiB apart.)
+// its memory traffic (0.34 against 0.67 ms at 16384^2 FP64; 0.105 against 0.226 ms for 1536 rows of 40000).  (Rows of up to 16384 elements get their
+// residues from the same registers, oz2_fused.hip; a workgroup that owns a single longer row would
+// write them in 64-byte pieces, which is slower than a kernel of its own.)
 // ----------------------------------------------------------------------------------------
 template <typename T, int THREADS, int CH>
 __global__ __launch_bounds__(THREADS) void k_shifts_cached(const T *__restrict__ X, int64_t ld,
@@ -140,29 +133,34 @@ __global__ __launch_bounds__(THREADS) void k_shifts_cached(const T *__restrict__
     __shared__ uint64_t bcast;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const T *x = X + (int64_t)blockIdx.x * ld;
-    const bool aligned = (reinterpret_cast<uintptr_t>(x) & 15) == 0;
 
+    // all loads first (pieces beyond the row's end read its first elements, or nothing if it has no 8)
+    constexpr int kVec = 16 / sizeof(T);
+    Vec16<T> w[CH][kPer / kVec];
+    if (len >= kPer) {
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            const int64_t h0 = ((int64_t)c * THREADS + threadIdx.x) * kPer;
+            const T *src = h0 + kPer <= len ? x + h0 : x;
+#pragma unroll
+            for (int i = 0; i < kPer / kVec; ++i) w[c][i] = reinterpret_cast<const Vec16<T> *>(src)[i];
+        }
+    }
     double v[CH][kPer];
     uint64_t mx = 0;
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
         const int64_t h0 = ((int64_t)c * THREADS + threadIdx.x) * kPer;
-        if (h0 + kPer <= len && aligned) {
-            constexpr int kVec = 16 / sizeof(T);
-            typedef T vec_t __attribute__((ext_vector_type(kVec)));
+        const bool whole = h0 + kPer <= len;
 #pragma unroll
-            for (int i = 0; i < kPer / kVec; ++i) {
-                const vec_t q = reinterpret_cast<const vec_t *>(x + h0)[i];
+        for (int i = 0; i < kPer; ++i) v[c][i] = whole ? (double)w[c][i / kVec][i % kVec] : 0.0;
+        if (!whole && h0 < len) {
 #pragma unroll
-                for (int e = 0; e < kVec; ++e) v[c][i * kVec + e] = (double)q[e];
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < kPer; ++i) v[c][i] = (h0 + i < len) ? (double)x[h0 + i] : 0.0;
+            for (int i = 0; i < kPer; ++i) v[c][i] = h0 + i < len ? (double)x[h0 + i] : 0.0;
         }
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
-            const uint64_t bits = (uint64_t)__double_as_longlong(fabs(v[c][i]));
+            const uint64_t bits = abs_bits(v[c][i]);
             mx = bits > mx ? bits : mx;
         }
     }
@@ -181,24 +179,22 @@ __global__ __launch_bounds__(THREADS) void k_shifts_cached(const T *__restrict__
         return;
     }
     const int e = floor_log2_of_bits(mx);
-    uint64_t sum = 0;
+    double sum = 0.0;                                                 // exact: integers, at most 2^53 in all
 #pragma unroll
     for (int c = 0; c < CH; ++c)
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
-            const uint64_t qi = (uint64_t)ceil(ldexp(fabs(v[c][i]), 15 - e));
-            sum += qi * qi;
+            const double q = ceil(ldexp(fabs(v[c][i]), 15 - e));
+            sum = fma(q, q, sum);
         }
-    sum = wave_sum(sum);
+    const uint64_t s = wave_sum((uint64_t)sum);
     __syncthreads();                                                  // part[] is reused
-    if (lane == 0) part[wave] = sum;
+    if (lane == 0) part[wave] = s;
     __syncthreads();
     if (threadIdx.x == 0) {
         uint64_t T_ = 0;
         for (int w = 0; w < kWaves; ++w) T_ += part[w];
-        int j = 0;
-        while (j < sa.levels - 1 && T_ > sa.theta[j]) ++j;
-        t_out[blockIdx.x] = (sa.f_max - j) - e;
+        t_out[blockIdx.x] = shift_exponent(T_, sa) - e;
     }
 }
 
@@ -334,8 +330,8 @@ inline unsigned blocks_for(int64_t threads) { return (unsigned)((threads + 255) 
 template <typename T>
 hipError_t launch_shifts(const T *X, int64_t ld, int64_t rows, int64_t len, const ShiftArgs &sa,
                          int32_t *t, hipStream_t stream) {
-    // rows of up to 16384 elements are read once (pieces of 8 elements: 128 threads hold 1024
-    // elements per piece, 512 threads 4096); longer rows are read twice
+    // rows of up to 49152 elements are read once (pieces of 8 elements: 128 threads hold 1024
+    // elements per piece, 512 threads 4096, 1024 threads 8192); longer rows are read twice
     auto cached = [&](auto threads, auto ch) {
         hipLaunchKernelGGL((k_shifts_cached<T, decltype(threads)::value, decltype(ch)::value>), dim3((unsigned)rows),
                            dim3(decltype(threads)::value), 0, stream, X, ld, len, sa, t);
@@ -347,7 +343,11 @@ hipError_t launch_shifts(const T *X, int64_t ld, int64_t rows, int64_t len, cons
     else if (len <= 8192) cached(integral_constant<int, 512>{}, integral_constant<int, 2>{});
     else if (len <= 12288) cached(integral_constant<int, 512>{}, integral_constant<int, 3>{});
     else if (len <= 16384) cached(integral_constant<int, 512>{}, integral_constant<int, 4>{});
-    else hipLaunchKernelGGL((k_shifts<T>), dim3((unsigned)rows), dim3(256), 0, stream, X, ld, len, sa, t);
+    else if (len <= 24576) cached(integral_constant<int, 1024>{}, integral_constant<int, 3>{});
+    else if (len <= 32768) cached(integral_constant<int, 1024>{}, integral_constant<int, 4>{});
+    else if (len <= 40960) cached(integral_constant<int, 1024>{}, integral_constant<int, 5>{});
+    else if (len <= 49152) cached(integral_constant<int, 1024>{}, integral_constant<int, 6>{});
+    else hipLaunchKernelGGL((k_shifts<T>), dim3((unsigned)rows), dim3(kShiftThreads), 0, stream, X, ld, len, sa, t);
     return hipGetLastError();
 }
 
