@@ -29,6 +29,7 @@
 
 #include "oz2_bytemod.hpp"
 #include "oz2_kernels.hpp"
+#include "oz2_tilemap.hpp"
 
 namespace oz2 {
 namespace {
@@ -56,33 +57,6 @@ constexpr int vmcnt_imm(int n) { return (n & 0xf) | ((n >> 4) << 14) | (0x7 << 4
 template <int CPR>
 __device__ inline int swizzle_mask(int row) {
     return (row / (16 / CPR)) & (CPR - 1);
-}
-
-struct TileMap {
-    int tiles_m, tiles_n;      // tiles per slice
-    int swizzled;              // 1: tiles_m and tiles_n are multiples of 16
-};
-
-// Workgroup id -> (slice, tile row, tile column).  Workgroups are handed to the 8 XCDs
-// round-robin by id, and 256 run at a time (one per CU).  In the swizzled map the 256
-// co-resident workgroups cover one 16 x 16-tile region of one slice, and the 32 that share
-// an XCD (and its L2) cover an 8 x 4 sub-block of it, so an A tile row is fetched into that
-// L2 once for 4 workgroups and a B tile row once for 8.
-__device__ inline void map_tile(const TileMap &tm, int id, int &s, int &tr, int &tc) {
-    if (tm.swizzled) {
-        const int xcd = id & 7, local = id >> 3;
-        const int pos = local & 31, region = local >> 5;
-        const int regions_n = tm.tiles_n / 16, regions = (tm.tiles_m / 16) * regions_n;
-        s = region / regions;
-        const int r = region % regions;
-        tr = (r / regions_n) * 16 + (xcd >> 2) * 8 + (pos >> 2);
-        tc = (r % regions_n) * 16 + (xcd & 3) * 4 + (pos & 3);
-    } else {
-        const int per = tm.tiles_m * tm.tiles_n;
-        s = id / per;
-        tr = (id % per) / tm.tiles_n;
-        tc = id % tm.tiles_n;
-    }
 }
 
 // What the store phase writes (Algorithm 1 lines 6-7):
@@ -464,7 +438,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_int8_gemm_persistent(const int
                                                    void *__restrict__ C, int64_t Mp,
                                                    int64_t Np, int64_t KB, int kb0, int KT,
                                                    int64_t c_ld, int64_t c_plane,
-                                                   TileMap tmap, int total_tiles, GemmMods mods) {
+                                                   TileMap tmap, GemmMods mods) {
     typedef GemmCore<WM, WN, TM, TN, BK, STAGES> Core;
     static_assert(OUT != kOutMax, "the maxima form runs one workgroup per tile");
     const Core core(Mp, Np);
@@ -474,23 +448,24 @@ __global__ __launch_bounds__(64 * WM * WN) void k_int8_gemm_persistent(const int
     const int8_t *src = core.tile_source(A, B, s, tile_r, tile_c, Mp, Np, KB, kb0);
     core.issue_head(src, KT);
     for (;;) {
+        // Where the next tile starts is worked out while the head of this one travels.
+        const int next = tile + (int)gridDim.x;
+        int s_next = 0, tile_r_next = 0, tile_c_next = 0;
+        const int8_t *src_next = nullptr;
+        if (next < tmap.total) {
+            map_tile(tmap, next, s_next, tile_r_next, tile_c_next);
+            src_next = core.tile_source(A, B, s_next, tile_r_next, tile_c_next, Mp, Np, KB, kb0);
+        }
         v16i acc[TM][TN];
         Core::fill(acc, first_acc(OUT));
         core.contract(src, KT, acc);
         // Every wavefront has passed the last barrier, so nothing reads the LDS stages any more:
         // the head of this workgroup's next tile is requested now and travels while the results
         // of this one are reduced and stored.
-        const int next = tile + (int)gridDim.x;
-        int s_next = 0, tile_r_next = 0, tile_c_next = 0;
-        const int8_t *src_next = nullptr;
-        if (next < total_tiles) {
-            map_tile(tmap, next, s_next, tile_r_next, tile_c_next);
-            src_next = core.tile_source(A, B, s_next, tile_r_next, tile_c_next, Mp, Np, KB, kb0);
-            core.issue_head(src_next, KT);
-        }
+        if (next < tmap.total) core.issue_head(src_next, KT);
         core.template store<OUT>(acc, C, s, (int64_t)tile_r * Core::BM, (int64_t)tile_c * Core::BN, c_ld, c_plane,
                                  mods);
-        if (next >= total_tiles) break;                    // uniform over the workgroup
+        if (next >= tmap.total) break;                    // uniform over the workgroup
         tile = next; s = s_next; tile_r = tile_r_next; tile_c = tile_c_next; src = src_next;
     }
 }
@@ -525,19 +500,16 @@ hipError_t launch_persistent(const int8_t *A, const int8_t *B, void *C, int batc
         if (e != hipSuccess) return e;
         attr_device = dev;
     }
-    TileMap tm;
-    tm.tiles_m = (int)(pn.rows / BM);
-    tm.tiles_n = (int)(pn.cols / BN);
-    tm.swizzled = (tm.tiles_m % 16 == 0 && tm.tiles_n % 16 == 0) ? 1 : 0;
-    const int64_t total = (int64_t)tm.tiles_m * tm.tiles_n * batch;
+    const int64_t total = (pn.rows / BM) * (pn.cols / BN) * batch;
     if (total > 0x7fff0000) return hipErrorInvalidValue;      // tile ids (plus one grid stride) fit an int
+    const TileMap tm = make_tile_map((int)(pn.rows / BM), (int)(pn.cols / BN), (int)total);
     // The grid is a multiple of 8, so that tile id -> XCD stays id mod 8 as in the tile map.
     const int64_t units = compute_units() / 8 * 8;
     if (units < 8) return hipErrorInvalidValue;
     hipLaunchKernelGGL((k_int8_gemm_persistent<WM, WN, TM, TN, BK, STAGES, OUT>),
                        dim3((unsigned)std::min(total, units)), dim3(64 * WM * WN), lds_bytes, stream,
                        A + pn.row0 * BK, B + pn.col0 * BK, C, Mp, Np, Kp / BK, (int)(k_begin / BK),
-                       (int)(k_len / BK), pn.c_ld, pn.c_plane, tm, (int)total, mods);
+                       (int)(k_len / BK), pn.c_ld, pn.c_plane, tm, mods);
     return hipGetLastError();
 }
 
@@ -557,12 +529,9 @@ hipError_t launch(const int8_t *A, const int8_t *B, void *C, int batch, int64_t 
         if (e != hipSuccess) return e;
         attr_device = dev;
     }
-    TileMap tm;
-    tm.tiles_m = (int)(pn.rows / BM);
-    tm.tiles_n = (int)(pn.cols / BN);
-    tm.swizzled = (tm.tiles_m % 16 == 0 && tm.tiles_n % 16 == 0) ? 1 : 0;
-    const int64_t total = (int64_t)tm.tiles_m * tm.tiles_n * batch;
-    if (total > 0x7fffffff) return hipErrorInvalidValue;
+    const int64_t total = (pn.rows / BM) * (pn.cols / BN) * batch;
+    if (total > 0x7fff0000) return hipErrorInvalidValue;      // tile ids fit an int
+    const TileMap tm = make_tile_map((int)(pn.rows / BM), (int)(pn.cols / BN), (int)total);
     hipLaunchKernelGGL((k_int8_gemm<WM, WN, TM, TN, BK, STAGES, OUT>), dim3((unsigned)total),
                        dim3(64 * WM * WN), lds_bytes, stream, A + pn.row0 * BK, B + pn.col0 * BK, C, Mp,
                        Np, Kp / BK, (int)(k_begin / BK), (int)(k_len / BK), pn.c_ld, pn.c_plane, tm, mods);
