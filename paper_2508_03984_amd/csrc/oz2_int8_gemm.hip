@@ -210,7 +210,10 @@ struct GemmCore {
     // do not, so there is no branch per load; the LDS stage offsets are carried along, not
     // recomputed (measured against the same pipeline with a branch and a readfirstlane per load:
     // 3.5 % faster at 16 x 4096 x 4096 x 16384).
-    __device__ __forceinline__ void contract(const int8_t *src_tile, int KT, v16i (&acc)[TM][TN]) const {
+    // STORES: vector stores that may have been issued between the head and this call, if `stores` says so.
+    template <int STORES = 0>
+    __device__ __forceinline__ void contract(const int8_t *src_tile, int KT, v16i (&acc)[TM][TN],
+                                             bool stores = false) const {
         v4i fa[2][TM], fb[2][TN];
         const char *const lds_bytes = reinterpret_cast<const char *>(lds);
         auto load_frags = [&](int buf, int stage_off, int kk) {
@@ -223,11 +226,16 @@ struct GemmCore {
                 fb[buf][j] = *reinterpret_cast<const v4i *>(st + b_addr[kk] + j * 32 * CPR * 16);
         };
 
-        // K tiles 0 and 1 must have landed before the first fragment reads.  (In the persistent
-        // kernel the stores of this workgroup's previous tile are outstanding as well; they were
-        // issued after these loads, and loads complete in order, so "at most the youngest K tile
-        // outstanding" still implies that K tiles 0 and 1 are complete.)
-        if (KT >= STAGES - 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm((STAGES - 3) * LPT));
+        // K tiles 0 and 1 must have landed before the first fragment reads.  In the persistent
+        // kernel the stores of this workgroup's previous tile were issued after these loads.  Loads and
+        // stores leave the counter in the order in which they were issued, so the youngest K tile and all
+        // of the stores may stay outstanding: waiting for the stores here and after the first K tile
+        // cost a write's way to memory per tile (STORE_WAIT_FIGURES).
+        constexpr int kYoungest = (STAGES - 3) * LPT;
+        static_assert(kYoungest + STORES < 64, "vmcnt is a 6-bit counter");
+        const bool lenient = STORES > 0 && stores && KT >= STAGES;
+        if (lenient) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kYoungest + STORES));
+        else if (KT >= STAGES - 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kYoungest));
         else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
         __builtin_amdgcn_s_barrier();
         load_frags(0, 0, 0);
@@ -237,7 +245,7 @@ struct GemmCore {
         // two halves, each behind the second MFMA row of a K step.
         int cur_off = 0;
         const int8_t *src_ld = src_tile + (int64_t)(STAGES - 1) * tile_step;
-        auto iteration = [&](auto issued_c, bool last) {
+        auto iteration = [&](auto issued_c, bool last, bool after_stores = false) {
             constexpr bool issued = decltype(issued_c)::value;
             const int nxt_off = cur_off + STAGE_BYTES == STAGES * STAGE_BYTES ? 0 : cur_off + STAGE_BYTES;
             const int ld_off = cur_off == 0 ? (STAGES - 1) * STAGE_BYTES : cur_off - STAGE_BYTES;
@@ -269,14 +277,15 @@ struct GemmCore {
             }
             // Tile kt + 2 must be complete (and visible to every wavefront) before iteration
             // kt + 1 prefetches fragments from it; the barrier also frees the stage just read.
-            if (issued) __builtin_amdgcn_s_waitcnt(vmcnt_imm((STAGES - 3) * LPT));
+            if (issued && after_stores) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kYoungest + STORES));
+            else if (issued) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kYoungest));
             else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
             __builtin_amdgcn_s_barrier();
             cur_off = nxt_off;
             src_ld += tile_step;
         };
         int kt = 0;
-        for (; kt + STAGES - 1 < KT; ++kt) iteration(std::true_type{}, false);
+        for (; kt + STAGES - 1 < KT; ++kt) iteration(std::true_type{}, false, STORES > 0 && lenient && kt == 0);
         for (; kt < KT; ++kt) iteration(std::false_type{}, kt + 1 == KT);
     }
 
@@ -447,6 +456,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_int8_gemm_persistent(const int
     map_tile(tmap, tile, s, tile_r, tile_c);
     const int8_t *src = core.tile_source(A, B, s, tile_r, tile_c, Mp, Np, KB, kb0);
     core.issue_head(src, KT);
+    bool stores = false;                                   // the previous tile's stores may be on their way
     for (;;) {
         // Where the next tile starts is worked out while the head of this one travels.
         const int next = tile + (int)gridDim.x;
@@ -458,7 +468,9 @@ __global__ __launch_bounds__(64 * WM * WN) void k_int8_gemm_persistent(const int
         }
         v16i acc[TM][TN];
         Core::fill(acc, first_acc(OUT));
-        core.contract(src, KT, acc);
+        // (The fold forms also load what they add to, and wait for it themselves.)
+        constexpr int kStores = OUT == kOutU8 ? TM * TN : 0;
+        core.template contract<kStores>(src, KT, acc, stores);
         // Every wavefront has passed the last barrier, so nothing reads the LDS stages any more:
         // the head of this workgroup's next tile is requested now and travels while the results
         // of this one are reduced and stored.
@@ -466,6 +478,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_int8_gemm_persistent(const int
         core.template store<OUT>(acc, C, s, (int64_t)tile_r * Core::BM, (int64_t)tile_c * Core::BN, c_ld, c_plane,
                                  mods);
         if (next >= tmap.total) break;                    // uniform over the workgroup
+        stores = true;
         tile = next; s = s_next; tile_r = tile_r_next; tile_c = tile_c_next; src = src_next;
     }
 }
