@@ -168,6 +168,13 @@ oz2_status run_products(Ctx &g, const Layout &L, const Panels &P, const int8_t *
     // contraction up to 2^17.)
     const size_t entry = L.prod_u8 ? 1 : 4;
     int64_t done = 0;
+    if (L.prod_u8 && P.count == 1 && tiny_product_applies(L.m, L.n, L.Kp, L.N)) {
+        ++g.last_gemm_launches;                               // (the accumulation is part of it)
+        OZ2_TRY(launch_tiny_product<T>(rA, rB, static_cast<uint8_t *>(prod), L.Mp, L.Np, L.Kp, L.m, L.n, tA, tB, ma, alpha, beta,
+                                       C, ldc, stream));
+        if (oz2_status st = mark(g, 3, stream)) return st;
+        return mark(g, 4, stream);
+    }
     for (int64_t row0 = 0; row0 < L.Mp; row0 += P.pr)
         for (int64_t col0 = 0; col0 < L.Np; col0 += P.pc) {
             const int64_t rows = std::min(P.pr, L.Mp - row0), cols = std::min(P.pc, L.Np - col0);

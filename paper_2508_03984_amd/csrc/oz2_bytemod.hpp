@@ -34,8 +34,11 @@ inline ByteMod make_byte_mod(int p) {
     // x = u - 2^31, so t = -2^31 - h (mod p)
     const int t = p == 256 ? 0 : (int)((((int64_t)p << 32) - ((int64_t)1 << 31) - h) % p);
     b.base = 0x4b000000u + (uint32_t)t;
-    int j = 0;
-    if (p % 2) while ((unsigned)(-p * j - h) & 0xffu) ++j;
+    // -p j = h (mod 256): the inverse of an odd p modulo 256 by Newton's iteration (3, 6, 12 bits)
+    uint32_t inverse = (uint32_t)p;
+    inverse *= 2u - (uint32_t)p * inverse;
+    inverse *= 2u - (uint32_t)p * inverse;
+    const uint32_t j = p % 2 ? (0u - inverse * (uint32_t)h) & 0xffu : 0u;
     b.pinv = 1.0f / (float)p;
     b.magic = 12582912.0f + (float)j;
     b.neg_p = -p;

@@ -1,0 +1,43 @@
+// Device code shared by the kernels that end a product (Algorithm 1 lines 6-12): residues of the INT32
+// sums as bytes, and the last steps of an entry of C.
+#pragma once
+#include "oz2_bytemod.hpp"
+#include "oz2_kernels.hpp"
+
+namespace oz2 {
+
+// byte_mod_word on the device: with its share of the packing 15 cycles per wavefront and entry where
+// the mulhi form of mod_small takes 26.  Measured for whole calls, mulhi form -> this one: 8192 x 8192 x
+// 512, N = 15, 1299 -> 1245 us; 4096 x 3072 x 2048 prepared 454 -> 435 us; 4096^3, N = 14, 1142 -> 1121 us; no
+// difference at 16384^3, where the store phase is 2 % of a tile.
+__device__ __forceinline__ uint32_t byte_mod_word_dev(int acc, const ByteMod &b) {
+    const uint32_t f = __builtin_amdgcn_udot4((uint32_t)acc, b.coef, b.base, false);
+    const float q = __builtin_fmaf(__builtin_bit_cast(float, f) - 8388608.0f, b.pinv, b.magic);
+    return (uint32_t)__mul24(__builtin_bit_cast(int, q), b.neg_p) + f;
+}
+
+// The low bytes of four words in one.
+__device__ __forceinline__ uint32_t pack_low_bytes(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3) {
+    const uint32_t lo = __builtin_amdgcn_perm(w1, w0, 0x0c0c0400u), hi = __builtin_amdgcn_perm(w3, w2, 0x0c0c0400u);
+    return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+}
+
+template <typename OutT>
+__device__ inline OutT finish(double c, double alpha, double beta, const OutT *Cin) {
+    double r;
+    if (beta == 0.0) r = (alpha == 1.0) ? c : alpha * c;
+    else r = fma(alpha, c, beta * (double)*Cin);
+    return (OutT)r;
+}
+
+// Q = rint(P_inv C1), C'' = fma(-P2, Q, fma(-P1, Q, C1) + C2), c = C'' 2^-(tA_i + tB_j), then alpha and beta.
+template <typename OutT>
+__device__ __forceinline__ OutT crt_entry(double C1, double C2, int shift, const ModArgs &ma, double alpha, double beta,
+                                          const OutT *Cin) {
+    const double Q = rint(ma.Pinv * C1);
+    const double T_ = fma(-ma.P1, Q, C1);
+    const double Cpp = fma(-ma.P2, Q, T_ + C2);
+    return finish<OutT>(ldexp(Cpp, -shift), alpha, beta, Cin);
+}
+
+}  // namespace oz2

@@ -27,7 +27,7 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "oz2_bytemod.hpp"
+#include "oz2_epilogue.hpp"
 #include "oz2_kernels.hpp"
 #include "oz2_tilemap.hpp"
 
@@ -96,22 +96,6 @@ struct GemmMods {                       // moduli of the slices and what their r
 
 // The uint8 forms start their accumulators at -2^31 (see oz2_bytemod.hpp), the others at 0.
 constexpr int first_acc(int out) { return out == kOutU8 || out == kOutU8Fold ? (int)0x80000000 : 0; }
-
-// byte_mod_word on the device: with its share of the packing 15 cycles per wavefront and entry where
-// the mulhi form of mod_small takes 26.  Measured for whole calls, mulhi form -> this one: 8192 x 8192 x
-// 512, N = 15, 1299 -> 1245 us; 4096 x 3072 x 2048 prepared 454 -> 435 us; 4096^3, N = 14, 1142 -> 1121 us; no
-// difference at 16384^3, where the store phase is 2 % of a tile.
-__device__ __forceinline__ uint32_t byte_mod_word_dev(int acc, const ByteMod &b) {
-    const uint32_t f = __builtin_amdgcn_udot4((uint32_t)acc, b.coef, b.base, false);
-    const float q = __builtin_fmaf(__builtin_bit_cast(float, f) - 8388608.0f, b.pinv, b.magic);
-    return (uint32_t)__mul24(__builtin_bit_cast(int, q), b.neg_p) + f;
-}
-
-// The low bytes of four words in one.
-__device__ __forceinline__ uint32_t pack_low_bytes(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3) {
-    const uint32_t lo = __builtin_amdgcn_perm(w1, w0, 0x0c0c0400u), hi = __builtin_amdgcn_perm(w3, w2, 0x0c0c0400u);
-    return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
-}
 
 // The LDS of a workgroup: STAGES stages of (A rows | B rows) x 64 bytes.  Declared here, not
 // passed around, so that every access is an offset from a base the compiler knows.
@@ -230,7 +214,7 @@ struct GemmCore {
         // kernel the stores of this workgroup's previous tile were issued after these loads.  Loads and
         // stores leave the counter in the order in which they were issued, so the youngest K tile and all
         // of the stores may stay outstanding: waiting for the stores here and after the first K tile
-        // cost a write's way to memory per tile (STORE_WAIT_FIGURES).
+        // cost a write's way to memory per tile (8192 x 8192 x 512, N = 15: 1107 -> 1095 us for the call).
         constexpr int kYoungest = (STAGES - 3) * LPT;
         static_assert(kYoungest + STORES < 64, "vmcnt is a 6-bit counter");
         const bool lenient = STORES > 0 && stores && KT >= STAGES;
@@ -551,6 +535,19 @@ hipError_t launch(const int8_t *A, const int8_t *B, void *C, int batch, int64_t 
     return hipGetLastError();
 }
 
+// Problems of fewer than 128 large tiles: 128 x 128 tiles, so that more workgroups exist.  Up to 256 of them
+// have a compute unit each: 8 wavefronts and 6 stages there (2048^3 in accurate mode, the one slice of Cbar:
+// 4 wavefronts and 4 stages 21.6 us, 4 and 6 20.6, 8 and 6 19.8, 8 and 9 19.2 but slower for short
+// contractions; 500 x 300 x 777, 8 slices: 8.4, 7.6, 7.8, 8.1); of more, two share one.
+template <int OUT>
+hipError_t launch_small(const int8_t *A, const int8_t *B, void *C, int batch, int64_t Mp, int64_t Np,
+                        int64_t Kp, int64_t k_begin, int64_t k_len, const GemmPanel &pn,
+                        const GemmMods &mods, hipStream_t stream) {
+    if (pn.rows * pn.cols * batch <= (int64_t)128 * 128 * 256)
+        return launch<2, 4, 2, 1, 64, 6, OUT>(A, B, C, batch, Mp, Np, Kp, k_begin, k_len, pn, mods, stream);
+    return launch<2, 2, 2, 2, 64, 4, OUT>(A, B, C, batch, Mp, Np, Kp, k_begin, k_len, pn, mods, stream);
+}
+
 template <int OUT>
 hipError_t launch_out(const int8_t *A, const int8_t *B, void *C, int batch, int64_t Mp, int64_t Np,
                       int64_t Kp, int64_t k_begin, int64_t k_len, const GemmPanel &pn,
@@ -559,7 +556,7 @@ hipError_t launch_out(const int8_t *A, const int8_t *B, void *C, int batch, int6
     // (measured at N = 14: 512^3, 56 large tiles, 11.4 against 17.3 us; 1024^3, 224 large tiles,
     // 31.2 against 26.8 us, so from there on the large tile wins although it leaves units idle).
     if (pn.rows * pn.cols * batch < (int64_t)256 * 256 * 128)
-        return launch<2, 2, 2, 2, 64, 4, OUT>(A, B, C, batch, Mp, Np, Kp, k_begin, k_len, pn, mods, stream);
+        return launch_small<OUT>(A, B, C, batch, Mp, Np, Kp, k_begin, k_len, pn, mods, stream);
     // 8 wavefronts (2 per SIMD), each 128 x 64: measured against 4 wavefronts of 128 x 128 on
     // the same device it is 2 % faster at 16 x 16384^3 -- a wavefront that is held up issuing
     // a load leaves the matrix core to its SIMD partner.
@@ -586,7 +583,7 @@ hipError_t launch_int8_gemm_maxima(const int8_t *A, const int8_t *B, int64_t Mp,
     q.c_plane = col_max - row_max;
     const GemmMods none{};
     if (pn.rows * pn.cols < (int64_t)256 * 256 * 128)        // as in launch_out
-        return launch<2, 2, 2, 2, 64, 4, kOutMax>(A, B, row_max, 1, Mp, Np, Kp, k_begin, k_len, q, none, stream);
+        return launch_small<kOutMax>(A, B, row_max, 1, Mp, Np, Kp, k_begin, k_len, q, none, stream);
     return launch<2, 4, 4, 2, 64, 4, kOutMax>(A, B, row_max, 1, Mp, Np, Kp, k_begin, k_len, q, none, stream);
 }
 

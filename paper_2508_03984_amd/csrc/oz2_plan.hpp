@@ -228,6 +228,15 @@ inline int64_t launch_k_len(int64_t Kp, int N, const Panels &Q) {
     return std::min<int64_t>(len, OZ2_MAX_K);
 }
 
+// The smallest products run their GEMMs and the accumulation as one launch (oz2_tiny.hip): at most one 32 x 32
+// tile of C per compute unit, at most 512 elements of k in a row for a wavefront (each of the 16 takes every
+// 16th modulus), and few enough operands for a compute unit to load (64 Kp N bytes).  Measured (us on the GPU, two
+// launches | one; a launch less also saves the host about 4 us): 256^3 N = 14 10.1 | 7.9, 400 x 400 x 384 N = 8 9.7 | 8.2,
+// 1000 x 250 x 256 N = 15 11.9 | 10.3; not taken: 100 x 100 x 500 N = 15 10.2 | 14.8, 512^3 N = 15 13.0 | 13.0.
+inline bool tiny_product_applies(int64_t m, int64_t n, int64_t Kp, int N) {
+    return (m + 31) / 32 * ((n + 31) / 32) <= 256 && (N + 15) / 16 * Kp <= 512 && Kp * N <= 4096;
+}
+
 // Side of a panel of the overlapped form: the INT8 GEMM loses nothing down to 4096 x 4096.
 constexpr int64_t kOverlapPanel = 4096;
 

@@ -5,6 +5,7 @@
 #include <type_traits>
 
 #include "oz2_convert.hpp"
+#include "oz2_epilogue.hpp"
 #include "oz2_kernels.hpp"
 
 namespace oz2 {
@@ -205,14 +206,6 @@ __global__ __launch_bounds__(THREADS) void k_shifts_cached(const T *__restrict__
 // One thread per 4 consecutive columns (16-byte loads of the int32 planes).
 // ----------------------------------------------------------------------------------------
 
-template <typename OutT>
-__device__ inline OutT finish(double c, double alpha, double beta, const OutT *Cin) {
-    double r;
-    if (beta == 0.0) r = (alpha == 1.0) ? c : alpha * c;
-    else r = fma(alpha, c, beta * (double)*Cin);
-    return (OutT)r;
-}
-
 // IN_U8: the GEMM already reduced its sums (prod holds U_s as uint8, 4 bytes per thread and
 // modulus); otherwise prod holds int32 sums (possibly folded partial sums) reduced here.
 template <typename OutT, bool IN_U8>
@@ -280,11 +273,7 @@ __device__ __forceinline__ void epilogue_block(int64_t block, const void *__rest
 #pragma unroll
     for (int c = 0; c < W; ++c) {
         if (j0 + c < n) {
-            double Q = rint(ma.Pinv * C1[c]);
-            double T_ = fma(-ma.P1, Q, C1[c]);
-            double Cpp = fma(-ma.P2, Q, T_ + C2[c]);
-            double val = ldexp(Cpp, -(ta + tB[j0 + c]));
-            res[c] = finish<OutT>(val, alpha, beta, dst + c);
+            res[c] = crt_entry<OutT>(C1[c], C2[c], ta + tB[j0 + c], ma, alpha, beta, dst + c);
         }
     }
     if (j0 + W <= n && (reinterpret_cast<uintptr_t>(dst) & 15) == 0) {      // 16-byte stores

@@ -1,0 +1,72 @@
+"""Sizes on both sides of the limits where a call takes another kernel or another shape of one."""
+import numpy as np
+import pytest
+
+import synth_inputs as S
+from test_gpu_ops_panels import stored
+from test_gpu_parity import assert_parity, gpu_gemm, oz  # noqa: F401  (fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("m,n,k,N,dtype", [
+    (1, 1, 1, 2, np.float64),                        # one entry, one chunk of k, two moduli
+    (31, 33, 128, 16, np.float64),                   # tile edges; a modulus per wavefront
+    (33, 64, 129, 16, np.float64),                   # two chunks
+    (100, 100, 200, 17, np.float32),                 # Kp N just beyond 4096: two launches
+    (100, 100, 120, 17, np.float32),                 # a second modulus for one wavefront
+    (512, 500, 250, 8, np.float32),                  # 256 tiles, the most of the one-launch form
+    (513, 500, 250, 8, np.float32),                  # one row more: two launches
+    (64, 40, 500, 8, np.float64),                    # four chunks: the longest in a row for a wavefront
+    (64, 40, 513, 7, np.float64),                    # longer: two launches
+    (255, 257, 127, 20, np.float64),                 # all moduli
+])
+def test_products_around_the_one_launch_form(oz, oracle, m, n, k, N, dtype):
+    """The smallest products run GEMMs and accumulation as one launch: every stage and C against the
+    oracle, with alpha and beta too."""
+    is_double = dtype == np.float64
+    A, B = S.gemm_inputs(m, n, k, 1.0, seed=900 + m + k, dtype=dtype)
+    assert_parity(gpu_gemm(oz, A, B, N), oracle.gemm(A, B, N, is_double=is_double), is_double)
+    Cin = S.matrix(m, n, 0.5, seed=7, dtype=dtype)
+    assert_parity(gpu_gemm(oz, A, B, N, 0.5, -1.25, Cin, ldc=n + 3),
+                  oracle.gemm(A, B, N, 0.5, -1.25, Cin, is_double=is_double), is_double)
+
+
+@pytest.mark.parametrize("m,n,k,opA,opB", [
+    (5, 3, 7, 0, 1), (5, 3, 7, 1, 0),                # rows shorter than one 8-element piece
+    (37, 300, 129, 0, 0), (300, 37, 511, 1, 1),      # smallest workgroups, ragged rows and columns
+    (40, 50, 1025, 0, 1), (40, 50, 1025, 1, 0),      # beyond 1024: other shapes for rows and for columns
+    (30, 600, 2049, 0, 0),                           # beyond 2048: a launch per form
+    (1500, 1111, 2900, 1, 0),                        # strips of 4 columns
+    (20, 30, 4096, 1, 0), (20, 30, 4097, 1, 0),      # the longest columns, and beyond: the general column kernels
+    (9, 270, 16384, 0, 1), (9, 270, 16385, 0, 1),    # the longest rows, and beyond: rows held for their shifts only
+    (3, 4, 40961, 0, 1), (3, 4, 49153, 0, 1),        # ... by the largest workgroup; read twice
+])
+@pytest.mark.parametrize("dtype,N,accurate", [(np.float64, 16, False), (np.float32, 8, False), (np.float64, 9, True)])
+def test_conversion_forms_agree(oz, m, n, k, opA, opB, dtype, N, accurate):
+    """The fused conversion against the general kernels (which the oracle checks elsewhere): shifts, slices with
+    their padding, and C are equal bit for bit; leading dimensions leave rows unaligned."""
+    import torch
+    from paper_2508_03984_amd import binding as b
+    A, B = S.gemm_inputs(m, n, k, 2.0, seed=31 + k, dtype=dtype)
+    A[m // 2, :] = 0.0
+    B[:, n // 3] = 0.0
+    is_double = dtype == np.float64
+    dt = torch.float64 if is_double else torch.float32
+    dA, lda = stored(A, opA, 3, dt)
+    dB, ldb = stored(B, opB, 5, dt)
+    fn = oz.oz2_dgemm_op if is_double else oz.oz2_sgemm_op
+    got = {}
+    try:
+        for fused in (True, False):
+            oz.oz2_set_small_conversion(fused)
+            dC = torch.full((m, n), float("nan"), dtype=dt, device="cuda")
+            fn(opA, opB, accurate, m, n, k, 1.0, dA, lda, dB, ldb, 0.0, dC, n, N)
+            torch.cuda.synchronize()
+            got[fused] = [dC] + [oz.stage_tensor(st) for st in (b.OZ2_STAGE_SHIFT_A, b.OZ2_STAGE_SHIFT_B,
+                                                                b.OZ2_STAGE_RES_A, b.OZ2_STAGE_RES_B)]
+    finally:
+        oz.oz2_set_small_conversion(True)
+    for x, y, name in zip(got[True], got[False], ("C", "tA", "tB", "residues of A", "residues of B")):
+        assert torch.equal(x, y), name
+    assert bool(torch.isfinite(got[True][0]).all())
