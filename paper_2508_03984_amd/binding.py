@@ -7,11 +7,12 @@ from __future__ import annotations
 
 import ctypes as C
 import os
-from typing import Optional, Tuple
+from typing import Tuple
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(HERE, "liboz2.so")
 _lib = None
+_torch = None          # the torch module, once something needs it (a call costs a few microseconds: no import in it)
 
 OZ2_STAGE_SHIFT_A, OZ2_STAGE_SHIFT_B, OZ2_STAGE_RES_A, OZ2_STAGE_RES_B, OZ2_STAGE_PROD, OZ2_STAGE_U = range(6)
 
@@ -147,23 +148,43 @@ def load():
     return lib
 
 
-def _stream(stream) -> C.c_void_p:
-    if stream is None:
+_raw_stream = None     # (handle of the current stream of a device, the current device) without wrapper objects
+
+
+def _th():
+    global _torch
+    if _torch is None:
         import torch
-        stream = torch.cuda.current_stream().cuda_stream
-    elif hasattr(stream, "cuda_stream"):
+        _torch = torch
+    return _torch
+
+
+def _stream(stream) -> int:
+    """The handle of a stream: torch's current one on the current device if none is given."""
+    global _raw_stream
+    if stream is None:
+        if _raw_stream is None:
+            torch = _th()
+            handle = torch.cuda.current_stream().cuda_stream       # initialises the device if nothing has
+            get = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+            if None in get:
+                return handle
+            _raw_stream = get
+        return _raw_stream[0](_raw_stream[1]())
+    if hasattr(stream, "cuda_stream"):
         stream = stream.cuda_stream
-    return C.c_void_p(int(stream))
+    return int(stream)
 
 
-def _dev(t, dtype=None) -> C.c_void_p:
+def _dev(t, dtype=None) -> int:
+    """The address of a device tensor, 0 for None."""
     if t is None:
-        return C.c_void_p(0)
+        return 0
     if not t.is_cuda:
         raise ValueError("device tensor expected")
-    if dtype is not None and t.dtype != dtype:
+    if dtype is not None and t.dtype is not dtype:
         raise ValueError(f"tensor of dtype {dtype} expected, got {t.dtype}")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _check(status: int, where: str) -> None:
@@ -176,7 +197,7 @@ def oz2_status_string(status: int) -> str:
 
 
 def oz2_dgemm(m, n, k, alpha, A, lda, B, ldb, beta, C_, ldc, num_moduli, stream=None) -> None:
-    import torch
+    torch = _th()
     _check(load().oz2_dgemm(m, n, k, float(alpha), _dev(A, torch.float64), lda,
                             _dev(B, torch.float64), ldb, float(beta), _dev(C_, torch.float64), ldc,
                             int(num_moduli), _stream(stream)), "oz2_dgemm")
@@ -186,21 +207,21 @@ OZ2_NOALLOC_WORKSPACE_BYTES = 64 * 1024 * 1024
 
 
 def oz2_dgemm_noalloc(m, n, k, alpha, A, lda, B, ldb, beta, C_, ldc, num_moduli, stream=None) -> None:
-    import torch
+    torch = _th()
     _check(load().oz2_dgemm_noalloc(m, n, k, float(alpha), _dev(A, torch.float64), lda,
                                     _dev(B, torch.float64), ldb, float(beta), _dev(C_, torch.float64), ldc,
                                     int(num_moduli), _stream(stream)), "oz2_dgemm_noalloc")
 
 
 def oz2_sgemm(m, n, k, alpha, A, lda, B, ldb, beta, C_, ldc, num_moduli, stream=None) -> None:
-    import torch
+    torch = _th()
     _check(load().oz2_sgemm(m, n, k, float(alpha), _dev(A, torch.float32), lda,
                             _dev(B, torch.float32), ldb, float(beta), _dev(C_, torch.float32), ldc,
                             int(num_moduli), _stream(stream)), "oz2_sgemm")
 
 
 def oz2_dgemm_accurate(m, n, k, alpha, A, lda, B, ldb, beta, C_, ldc, num_moduli, stream=None) -> None:
-    import torch
+    torch = _th()
     _check(load().oz2_dgemm_accurate(m, n, k, float(alpha), _dev(A, torch.float64), lda,
                                      _dev(B, torch.float64), ldb, float(beta),
                                      _dev(C_, torch.float64), ldc, int(num_moduli), _stream(stream)),
@@ -208,7 +229,7 @@ def oz2_dgemm_accurate(m, n, k, alpha, A, lda, B, ldb, beta, C_, ldc, num_moduli
 
 
 def oz2_sgemm_accurate(m, n, k, alpha, A, lda, B, ldb, beta, C_, ldc, num_moduli, stream=None) -> None:
-    import torch
+    torch = _th()
     _check(load().oz2_sgemm_accurate(m, n, k, float(alpha), _dev(A, torch.float32), lda,
                                      _dev(B, torch.float32), ldb, float(beta),
                                      _dev(C_, torch.float32), ldc, int(num_moduli), _stream(stream)),
@@ -217,7 +238,7 @@ def oz2_sgemm_accurate(m, n, k, alpha, A, lda, B, ldb, beta, C_, ldc, num_moduli
 
 def oz2_dgemm_op(opA, opB, accurate, m, n, k, alpha, A, lda, B, ldb, beta, C_, ldc, num_moduli,
                  stream=None) -> None:
-    import torch
+    torch = _th()
     _check(load().oz2_dgemm_op(int(opA), int(opB), int(bool(accurate)), m, n, k, float(alpha),
                                _dev(A, torch.float64), lda, _dev(B, torch.float64), ldb, float(beta),
                                _dev(C_, torch.float64), ldc, int(num_moduli), _stream(stream)),
@@ -226,7 +247,7 @@ def oz2_dgemm_op(opA, opB, accurate, m, n, k, alpha, A, lda, B, ldb, beta, C_, l
 
 def oz2_sgemm_op(opA, opB, accurate, m, n, k, alpha, A, lda, B, ldb, beta, C_, ldc, num_moduli,
                  stream=None) -> None:
-    import torch
+    torch = _th()
     _check(load().oz2_sgemm_op(int(opA), int(opB), int(bool(accurate)), m, n, k, float(alpha),
                                _dev(A, torch.float32), lda, _dev(B, torch.float32), ldb, float(beta),
                                _dev(C_, torch.float32), ldc, int(num_moduli), _stream(stream)),
@@ -235,7 +256,7 @@ def oz2_sgemm_op(opA, opB, accurate, m, n, k, alpha, A, lda, B, ldb, beta, C_, l
 
 def oz2_dgemm_colmajor(opA, opB, accurate, m, n, k, alpha, A, lda, B, ldb, beta, C_, ldc, num_moduli,
                        stream=None) -> None:
-    import torch
+    torch = _th()
     _check(load().oz2_dgemm_colmajor(int(opA), int(opB), int(bool(accurate)), m, n, k, float(alpha),
                                      _dev(A, torch.float64), lda, _dev(B, torch.float64), ldb, float(beta),
                                      _dev(C_, torch.float64), ldc, int(num_moduli), _stream(stream)),
@@ -244,7 +265,7 @@ def oz2_dgemm_colmajor(opA, opB, accurate, m, n, k, alpha, A, lda, B, ldb, beta,
 
 def oz2_sgemm_colmajor(opA, opB, accurate, m, n, k, alpha, A, lda, B, ldb, beta, C_, ldc, num_moduli,
                        stream=None) -> None:
-    import torch
+    torch = _th()
     _check(load().oz2_sgemm_colmajor(int(opA), int(opB), int(bool(accurate)), m, n, k, float(alpha),
                                      _dev(A, torch.float32), lda, _dev(B, torch.float32), ldb, float(beta),
                                      _dev(C_, torch.float32), ldc, int(num_moduli), _stream(stream)),
@@ -281,12 +302,12 @@ def _prepare(fn_name, dtype, side, op, rows, k, X, ld, num_moduli, stream) -> Op
 
 
 def oz2_prepare_d(side, op, rows, k, X, ld, num_moduli, stream=None) -> Operand:
-    import torch
+    torch = _th()
     return _prepare("oz2_prepare_d", torch.float64, side, op, rows, k, X, ld, num_moduli, stream)
 
 
 def oz2_prepare_s(side, op, rows, k, X, ld, num_moduli, stream=None) -> Operand:
-    import torch
+    torch = _th()
     return _prepare("oz2_prepare_s", torch.float32, side, op, rows, k, X, ld, num_moduli, stream)
 
 
@@ -299,14 +320,14 @@ def oz2_operand_bytes(operand: Operand) -> int:
 
 
 def oz2_dgemm_prepared(left: Operand, right: Operand, alpha, beta, C_, ldc, stream=None) -> None:
-    import torch
+    torch = _th()
     _check(load().oz2_dgemm_prepared(C.c_void_p(left.handle), C.c_void_p(right.handle), float(alpha),
                                      float(beta), _dev(C_, torch.float64), ldc, _stream(stream)),
            "oz2_dgemm_prepared")
 
 
 def oz2_sgemm_prepared(left: Operand, right: Operand, alpha, beta, C_, ldc, stream=None) -> None:
-    import torch
+    torch = _th()
     _check(load().oz2_sgemm_prepared(C.c_void_p(left.handle), C.c_void_p(right.handle), float(alpha),
                                      float(beta), _dev(C_, torch.float32), ldc, _stream(stream)),
            "oz2_sgemm_prepared")
@@ -392,7 +413,7 @@ def oz2_stage_ptr(stage: int) -> Tuple[int, Tuple[int, int, int, int]]:
 
 
 def oz2_int8_gemm(A, B, C_, batch, Mp, Np, Kp, stream=None) -> None:
-    import torch
+    torch = _th()
     _check(load().oz2_int8_gemm(_dev(A, torch.int8), _dev(B, torch.int8), _dev(C_, torch.int32),
                                 int(batch), Mp, Np, Kp, _stream(stream)), "oz2_int8_gemm")
 
@@ -469,7 +490,7 @@ def oz2_ctx_set_option(ctx, option: int, value) -> None:
 
 def oz2_ctx_dgemm(ctx, opA, opB, accurate, m, n, k, alpha, A, lda, B, ldb, beta, C_, ldc, num_moduli,
                   stream=None) -> None:
-    import torch
+    torch = _th()
     _check(load().oz2_ctx_dgemm(_ctx(ctx), int(opA), int(opB), int(bool(accurate)), m, n, k, float(alpha),
                                 _dev(A, torch.float64), lda, _dev(B, torch.float64), ldb, float(beta),
                                 _dev(C_, torch.float64), ldc, int(num_moduli), _stream(stream)),
@@ -478,7 +499,7 @@ def oz2_ctx_dgemm(ctx, opA, opB, accurate, m, n, k, alpha, A, lda, B, ldb, beta,
 
 def oz2_ctx_sgemm(ctx, opA, opB, accurate, m, n, k, alpha, A, lda, B, ldb, beta, C_, ldc, num_moduli,
                   stream=None) -> None:
-    import torch
+    torch = _th()
     _check(load().oz2_ctx_sgemm(_ctx(ctx), int(opA), int(opB), int(bool(accurate)), m, n, k, float(alpha),
                                 _dev(A, torch.float32), lda, _dev(B, torch.float32), ldb, float(beta),
                                 _dev(C_, torch.float32), ldc, int(num_moduli), _stream(stream)),
@@ -486,14 +507,14 @@ def oz2_ctx_sgemm(ctx, opA, opB, accurate, m, n, k, alpha, A, lda, B, ldb, beta,
 
 
 def oz2_ctx_dgemm_prepared(ctx, left: Operand, right: Operand, alpha, beta, C_, ldc, stream=None) -> None:
-    import torch
+    torch = _th()
     _check(load().oz2_ctx_dgemm_prepared(_ctx(ctx), C.c_void_p(left.handle), C.c_void_p(right.handle),
                                          float(alpha), float(beta), _dev(C_, torch.float64), ldc,
                                          _stream(stream)), "oz2_ctx_dgemm_prepared")
 
 
 def oz2_ctx_sgemm_prepared(ctx, left: Operand, right: Operand, alpha, beta, C_, ldc, stream=None) -> None:
-    import torch
+    torch = _th()
     _check(load().oz2_ctx_sgemm_prepared(_ctx(ctx), C.c_void_p(left.handle), C.c_void_p(right.handle),
                                          float(alpha), float(beta), _dev(C_, torch.float32), ldc,
                                          _stream(stream)), "oz2_ctx_sgemm_prepared")
@@ -617,7 +638,7 @@ def matmul(A, B, num_moduli: int, alpha: float = 1.0, beta: float = 0.0, out=Non
            accurate: bool = False, ctx=None):
     """C = alpha * A @ B + beta * out for device tensors that are row-major or transposed views
     (`X.t()`) of row-major ones, via oz2_ctx_dgemm / oz2_ctx_sgemm (ctx None: the default context)."""
-    import torch
+    torch = _th()
     if A.dim() != 2 or B.dim() != 2 or A.shape[1] != B.shape[0] or A.dtype != B.dtype:
         raise ValueError("A (m x k) and B (k x n) of one dtype expected")
     m, k = A.shape
