@@ -412,13 +412,12 @@ oz2_status oz2_mfma_probe(int random_operands, double seconds, double *tops, int
 void oz2_set_overlap(int on);
 
 /*
- * Small problems (on by default).  Below about 2048^3 a call is bound by the latency of its
- * dependent kernel launches.  For calls with k <= 4096, m, n <= 8192 and
- * (m + n) * k <= 2 * 2048^2 the conversion of Algorithm 1 lines 1-5 therefore runs as two
- * launches that cover both factors (the shifts; the residues) instead of seven, and in
- * accurate mode the passes that precede Cbar (maxima; Abar and Bbar) likewise.  The result
- * and every stage are bit-identical.  oz2_set_small_conversion(0) uses the general kernels
- * at every size.
+ * Fused conversion (on by default).  A factor whose vectors fit a workgroup (rows of up to 16384, columns
+ * of up to 4096 elements, padded to a multiple of 128) goes through Algorithm 1 lines 1-5 in one launch
+ * and one read, both factors in the same launch where they can share it; in accurate mode the
+ * passes that precede Cbar (maxima; Abar or Bbar) likewise, and the residues of both factors take one
+ * launch where k <= 4096, m, n <= 8192 and (m + n) * k <= 2 * 2048^2.  The result and every stage are
+ * bit-identical.  oz2_set_small_conversion(0) uses the general kernels at every size.
  */
 void oz2_set_small_conversion(int on);
 
@@ -426,7 +425,9 @@ void oz2_set_small_conversion(int on);
  * Per-stage timing.  With profiling on, each call records HIP events around its
  * stages on the call's stream; oz2_last_stage_times_ms waits for the last call
  * and writes { scale+exponent, residues, INT8 GEMM, epilogue } in milliseconds
- * to a HOST array.  Off by default (no events are recorded then).  For an overlapped call
+ * to a HOST array.  Off by default (no events are recorded then).  Shifts that come from the launch of
+ * the residues (see oz2_set_small_conversion) count as residues, and for the smallest products the
+ * accumulation, which shares the GEMMs' launch, counts as GEMM.  For an overlapped call
  * (see oz2_set_overlap) the four numbers are: the shifts; the part of the residues that
  * precedes the first GEMM; the sum of the GEMM launches of all panels (events on `stream`
  * around each); the rest of the call (the accumulations, waits for residues).

@@ -11,7 +11,7 @@
 namespace oz2 {
 
 int residue_rounds(const Table &t, bool accurate) {
-    // One reduction round gives the canonical residue while |x'| < 2^46 (see residue_of).
+    // One reduction round gives the canonical residue while |x'| < 2^46 (see ResidueInput).
     // Fast mode: |x| < 2^(e+1) and t = f - e with f <= f_max, so |x'| < 2^(f_max+1).
     // Accurate mode: mu' brings |x| below 2^6 and the second factor is at most 2^accu_f_max
     // (reached when the maximum of Cbar is 0 or 1), so |x'| < 2^(accu_f_max+6).

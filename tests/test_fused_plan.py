@@ -1,0 +1,43 @@
+"""The workgroup shapes of the fused conversion (fused_plan in csrc/oz2_plan.hpp), built for the host: every vector that
+fused_applies accepts fits the registers of its workgroup, whatever the form, the type and the number of vectors."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2508_03984_amd", "csrc")
+
+MAIN = r"""
+#include <cstdio>
+#include "oz2_plan.hpp"
+using namespace oz2;
+int main() {
+    long bad = 0, seen = 0;
+    for (int64_t Kp = kPadK; Kp <= kFusedMaxRow + 4 * kPadK; Kp += kPadK)
+        for (int strips = 0; strips < 2; ++strips)
+            for (int64_t vectors = kPadMN; vectors <= 65536; vectors += vectors < 8192 ? 256 : 3328)
+                for (size_t element : {(size_t)4, (size_t)8}) {
+                    if (!fused_applies(Kp, !strips)) continue;
+                    const FusedPlan p = fused_plan(Kp, strips, vectors, element);
+                    const int64_t V = (int64_t)1 << p.log_v;
+                    const bool ok = V * Kp <= (int64_t)p.threads * p.pieces * 8      // the vectors fit
+                                    && 8 * V <= p.threads                              // a thread holds one vector's pieces
+                                    && p.log_v <= 5 && kPadMN % V == 0                 // whole workgroups, LDS arrays
+                                    && (strips ? V >= 4 : V >= 2);                     // whole lines, see fused_plan
+                    ++seen;
+                    if (!ok && ++bad < 10)
+                        std::printf("Kp %lld strips %d vectors %lld: %d x %d, log_v %d\n", (long long)Kp, strips,
+                                    (long long)vectors, p.threads, p.pieces, p.log_v);
+                }
+    std::printf("bad=%ld\n", bad);
+    return bad != 0 || seen < 1000;
+}
+"""
+
+
+def test_vectors_fit_their_workgroups(tmp_path):
+    src = tmp_path / "fused_plan_main.cpp"
+    src.write_text(MAIN)
+    exe = tmp_path / "fused_plan"
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-I", CSRC, str(src), "-o", str(exe)])
+    out = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert out.returncode == 0 and out.stdout.strip() == "bad=0", out.stdout
