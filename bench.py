@@ -709,8 +709,10 @@ def main() -> int:
     gemm_tops = gemm_ops / (stage_ms[2] * 1e-3) / 1e12            # stage_ms[2]: all GEMM launches of a step
     E = 4 if args.sgemm else 8
     PB = 4 if args.int32_products else 1                        # bytes per product entry
+    # factors whose vectors fit a workgroup get their shifts from the launch of the residues (fast mode)
+    a_fused, b_fused = not args.accurate and Kp <= 16384, not args.accurate and Kp <= 4096
     stage_bytes = [
-        E * (m * k + 2 * k * n) + 4 * (m + n),                  # shifts: A once, B twice (max, then sum)
+        E * ((0 if a_fused else m * k) + (0 if b_fused else 2 * k * n)) + 4 * (m + n),   # shifts: A once, B twice (max, then sum)
         E * (m * k + k * n) + N * (Mp * Kp + Np * Kp),          # residues
         N * (Mp * Kp + Np * Kp) + PB * N * Mp * Np,             # GEMM compulsory traffic
         PB * N * m * n + E * m * n,                             # epilogue
