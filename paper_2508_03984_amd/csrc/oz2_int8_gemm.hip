@@ -97,6 +97,12 @@ struct GemmMods {                       // moduli of the slices and what their r
 // The uint8 forms start their accumulators at -2^31 (see oz2_bytemod.hpp), the others at 0.
 constexpr int first_acc(int out) { return out == kOutU8 || out == kOutU8Fold ? (int)0x80000000 : 0; }
 
+// No memory access moves across this in the compiler (no instruction; the hardware issues in order).
+__device__ __forceinline__ void pin_memory_order() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // The LDS of a workgroup: STAGES stages of (A rows | B rows) x 64 bytes.  Declared here, not
 // passed around, so that every access is an offset from a base the compiler knows.
 extern __shared__ v4i lds[];                              // [STAGES][ROWS][CPR]
@@ -194,7 +200,8 @@ struct GemmCore {
     // do not, so there is no branch per load; the LDS stage offsets are carried along, not
     // recomputed (measured against the same pipeline with a branch and a readfirstlane per load:
     // 3.5 % faster at 16 x 4096 x 4096 x 16384).
-    // STORES: vector stores that may have been issued between the head and this call, if `stores` says so.
+    // STORES: the vector stores that were issued after the head and before this call, if `stores` says so:
+    // no fewer than that, or the relaxed wait below would pass K tiles that have not landed.
     template <int STORES = 0>
     __device__ __forceinline__ void contract(const int8_t *src_tile, int KT, v16i (&acc)[TM][TN],
                                              bool stores = false) const {
@@ -452,15 +459,19 @@ __global__ __launch_bounds__(64 * WM * WN) void k_int8_gemm_persistent(const int
         }
         v16i acc[TM][TN];
         Core::fill(acc, first_acc(OUT));
-        // (The fold forms also load what they add to, and wait for it themselves.)
+        // kStores: the number of store instructions of store<kOutU8>, one of 16 bytes per 32 x 32 block of a
+        // wavefront.  (The fold forms also load what they add to, and wait for it themselves.)
         constexpr int kStores = OUT == kOutU8 ? TM * TN : 0;
         core.template contract<kStores>(src, KT, acc, stores);
         // Every wavefront has passed the last barrier, so nothing reads the LDS stages any more:
         // the head of this workgroup's next tile is requested now and travels while the results
         // of this one are reduced and stored.
         if (next < tmap.total) core.issue_head(src_next, KT);
+        // contract<kStores> takes the stores for younger than all of the head's loads: none may move across.
+        pin_memory_order();
         core.template store<OUT>(acc, C, s, (int64_t)tile_r * Core::BM, (int64_t)tile_c * Core::BN, c_ld, c_plane,
                                  mods);
+        pin_memory_order();
         if (next >= tmap.total) break;                    // uniform over the workgroup
         stores = true;
         tile = next; s = s_next; tile_r = tile_r_next; tile_c = tile_c_next; src = src_next;

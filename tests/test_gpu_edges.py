@@ -32,6 +32,15 @@ def test_products_around_the_one_launch_form(oz, oracle, m, n, k, N, dtype):
                   oracle.gemm(A, B, N, 0.5, -1.25, Cin, is_double=is_double), is_double)
 
 
+@pytest.mark.parametrize("k", [128, 129, 256, 257])
+def test_short_contractions_with_several_tiles_per_workgroup(oz, oracle, k):
+    """480 tiles of 256 x 256 for the persistent GEMM's workgroups, and K tiles around its pipeline: 2 (the head is
+    shorter than the pipeline), 4 (one prefetching iteration, which takes the relaxed wait) and 6."""
+    m, n, N = 1100, 1500, 16
+    A, B = S.gemm_inputs(m, n, k, 1.0, seed=700 + k)
+    assert_parity(gpu_gemm(oz, A, B, N), oracle.gemm(A, B, N), True)
+
+
 @pytest.mark.parametrize("m,n,k,opA,opB", [
     (5, 3, 7, 0, 1), (5, 3, 7, 1, 0),                # rows shorter than one 8-element piece
     (37, 300, 129, 0, 0), (300, 37, 511, 1, 1),      # smallest workgroups, ragged rows and columns
