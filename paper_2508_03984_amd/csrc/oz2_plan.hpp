@@ -47,7 +47,7 @@ constexpr int64_t kFusedMaxRow = kFusedElements / 2, kFusedMaxColumn = kFusedEle
 // 4096 (eight per workgroup: 64-byte segments of the operand in FP64).
 inline bool fused_applies(int64_t Kp, bool k_contiguous) { return Kp <= (k_contiguous ? kFusedMaxRow : kFusedMaxColumn); }
 
-// The smallest workgroup with room for two rows (four of up to 1024 elements) or eight columns; strips of
+// For many vectors the smallest workgroup with room for two rows (four of up to 1024 elements) or eight columns; strips of
 // columns of more than 1024 elements take 16 where they fit.  Measured (us, both factors, N = 15 in FP64): rows of 4096, 4096^2
 // each, 512 threads and 2 rows 148, 1024 threads and 8 rows 171 (several workgroups per compute
 // unit overlap one's loads with another's stores); columns of 2048, 2048^2 each, 16 per workgroup 42, 8 52;
@@ -56,16 +56,22 @@ inline bool fused_applies(int64_t Kp, bool k_contiguous) { return Kp <= (k_conti
 // 4 two or three are resident.  Those are read less well (1.1 times the time in FP64, 1.3 in FP32, from
 // columns of 4096 and 2048), so they are taken where they save more than that in the last round (1500 + 1111
 // columns of 3001: 71 -> 40 us).
+// Few vectors: narrower workgroups until there is one per compute unit.  Their operands come from the caches, where
+// partial lines cost less than idle units (whole calls, N = 15 in FP64, us, 8 or 16 columns per workgroup whatever their
+// number | this rule | at least 2: 256 x 256 x 2048 45.6 | 28.6 | 28.8, 64 x 64 x 4096 62.6 | 46.6 | 49.8,
+// 512 x 256 x 2048 45.2 | 31.5 | 31.6; the kernels of oz2_prepost.hip and oz2_columns.hip took 40.4, 55.9 and 44.3).
 // vectors: padded number of vectors in the launch.
 inline FusedPlan fused_plan(int64_t Kp, bool strips, int64_t vectors, size_t element) {
     static const int shapes[][2] = {{256, 1}, {512, 1}, {512, 2}, {512, 3}, {512, 4}, {1024, 3}, {1024, 4}};
-    int64_t want = strips ? Kp * (Kp <= 1024 ? 8 : 16) : Kp * (Kp <= 1024 ? 4 : 2);
+    int64_t per = strips ? (Kp <= 1024 ? 8 : 16) : (Kp <= 1024 ? 4 : 2);
     if (strips && Kp > 2048) {
         const int64_t resident = 4 * Kp <= 512 * 3 * 8 ? 3 : 2;
         const double by8 = (double)((vectors / 8 + 255) / 256) * 8;
         const double by4 = (double)((vectors / 4 + 256 * resident - 1) / (256 * resident) * resident) * 4 * (element == 8 ? 1.1 : 1.3);
-        want = Kp * (by4 < by8 ? 4 : 8);
+        per = by4 < by8 ? 4 : 8;
     }
+    while (per > 1 && vectors < per * 256) per /= 2;
+    const int64_t want = Kp * per;
     FusedPlan p{1024, 4, 0};
     for (const auto &s : shapes)
         if ((int64_t)s[0] * s[1] * 8 >= want) { p.threads = s[0]; p.pieces = s[1]; break; }

@@ -1,5 +1,6 @@
 """The workgroup shapes of the fused conversion (fused_plan in csrc/oz2_plan.hpp), built for the host: every vector that
-fused_applies accepts fits the registers of its workgroup, whatever the form, the type and the number of vectors."""
+fused_applies accepts fits the registers of its workgroup, whatever the form, the type and the number of vectors, and
+few vectors are spread over the chip."""
 import os
 import subprocess
 
@@ -22,7 +23,9 @@ int main() {
                     const bool ok = V * Kp <= (int64_t)p.threads * p.pieces * 8      // the vectors fit
                                     && 8 * V <= p.threads                              // a thread holds one vector's pieces
                                     && p.log_v <= 5 && kPadMN % V == 0                 // whole workgroups, LDS arrays
-                                    && (strips ? V >= 4 : V >= 2);                     // whole lines, see fused_plan
+                                    && ((strips ? V >= 4 : V >= 2) || vectors < 2 * V * 256)   // whole lines, see fused_plan
+                                    // a workgroup for each of 256 compute units, unless it is the smallest there is
+                                    && (vectors / V >= 256 || V == 1 || (p.threads == 256 && p.pieces == 1));
                     ++seen;
                     if (!ok && ++bad < 10)
                         std::printf("Kp %lld strips %d vectors %lld: %d x %d, log_v %d\n", (long long)Kp, strips,

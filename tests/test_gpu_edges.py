@@ -46,6 +46,7 @@ def test_short_contractions_with_several_tiles_per_workgroup(oz, oracle, k):
     (37, 300, 129, 0, 0), (300, 37, 511, 1, 1),      # smallest workgroups, ragged rows and columns
     (40, 50, 1025, 0, 1), (40, 50, 1025, 1, 0),      # beyond 1024: other shapes for rows and for columns
     (30, 600, 2049, 0, 0),                           # beyond 2048: a launch per form
+    (300, 700, 2048, 1, 0), (5, 3, 1500, 0, 0),      # few vectors: 4 and 2 per workgroup where many take 16
     (1500, 1111, 2900, 1, 0),                        # strips of 4 columns
     (20, 30, 4096, 1, 0), (20, 30, 4097, 1, 0),      # the longest columns, and beyond: the general column kernels
     (9, 270, 16384, 0, 1), (9, 270, 16385, 0, 1),    # the longest rows, and beyond: rows held for their shifts only
