@@ -93,8 +93,9 @@ __global__ __launch_bounds__(64 * kWaves) void k_tiny_product(const int8_t *__re
     const int shift = (i < m ? tA[i] : 0) + (j < n ? tB[j] : 0);
     __syncthreads();
 
-    // accumulation: one entry per thread, moduli in ascending order
-    if (i >= m || j >= n) return;
+    // Accumulation: one entry per thread, moduli in ascending order.  Also in the lanes beyond C: FP64 instructions of a
+    // wavefront with 16 lanes or fewer at work take longer (128 x 100 x 64, N = 15: 10.6 us with 4 columns' lanes alone
+    // in the last tile, 7.3 us with all, as for 128 columns).
     const uint8_t *u = reinterpret_cast<const uint8_t *>(&u_lds[0][r][0]) + c;
     double C1 = 0.0, C2 = 0.0;
     for (int s0 = 0; s0 < ma.n; s0 += kModGroup) {          // the constants and bytes of a group requested together
@@ -113,6 +114,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_tiny_product(const int8_t *__re
                 C2 = fma(s2[g], (double)v[g], C2);
             }
     }
+    if (i >= m || j >= n) return;
     OutT *dst = C + i * ldc + j;
     *dst = crt_entry<OutT>(C1, C2, shift, ma, alpha, beta, dst);
 }
