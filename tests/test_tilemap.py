@@ -31,6 +31,13 @@ int main(int argc, char **argv) {
                     seen[(s * m + r) * n + c] = 1;
                 }
             }
+    // the divisions of the map
+    for (int64_t d = 1; d < (1ll << 31); d += d < 4096 ? 1 : d / 3) {
+        const oz2::Divisor by = oz2::make_divisor((int)d);
+        for (int64_t q : {(int64_t)0, (int64_t)1, (int64_t)2, 0x7fffffff / d / 2, 0x7fffffff / d - 1, 0x7fffffff / d})
+            for (int64_t x : {q * d - 1, q * d, q * d + 1, q * d + d - 1, (int64_t)0x7fffffff})
+                if (x >= 0 && x <= 0x7fffffff && oz2::divide((int)x, by) != x / d) ++bad;
+    }
     std::printf("bad=%ld\n", bad);
     return bad != 0;
 }
