@@ -205,7 +205,7 @@ hipError_t launch_epilogue(const void *prod, bool prod_is_u8, int64_t Mp, int64_
                            double beta, OutT *C, int64_t ldc, hipStream_t stream);
 
 // launch_int8_gemm (uint8 form) and launch_epilogue in one launch, for products that
-// tiny_product_applies (oz2_plan.hpp) accepts: U (the tiles that hold entries of C) and C.
+// tiny_product_applies (oz2_plan.hpp) accepts: U with its padding, and C.
 template <typename OutT>
 hipError_t launch_tiny_product(const int8_t *A, const int8_t *B, uint8_t *U, int64_t Mp, int64_t Np, int64_t Kp,
                                int64_t m, int64_t n, const int32_t *tA, const int32_t *tB, const ModArgs &ma,

@@ -9,6 +9,7 @@
 #include "oz2_convert.hpp"
 #include "oz2_epilogue.hpp"
 #include "oz2_kernels.hpp"
+#include "oz2_tilemap.hpp"
 
 namespace oz2 {
 namespace {
@@ -30,11 +31,30 @@ __global__ __launch_bounds__(64 * kWaves) void k_tiny_product(const int8_t *__re
                                                                  int64_t Kp, int64_t m, int64_t n,
                                                                  const int32_t *__restrict__ tA,
                                                                  const int32_t *__restrict__ tB, ModArgs ma, TinyMods tm,
-                                                                 double alpha, double beta, OutT *C, int64_t ldc) {
+                                                                 double alpha, double beta, OutT *C, int64_t ldc,
+                                                                 int tiles_n, Divisor by_tiles_n, int tiles) {
     __shared__ v4i u_lds[kMaxModuli][kTile][kTile / 16];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lrow = lane & 31, lhalf = lane >> 5;
-    const int64_t row0 = (int64_t)blockIdx.y * kTile, col0 = (int64_t)blockIdx.x * kTile;
+    const int64_t plane = Mp * Np;
+    if ((int)blockIdx.x >= tiles) {
+        // Padding of U, zero as from the products of zero residues: 32 rows of a block of 256 columns, all planes.  First
+        // the last blocks of the rows of tiles (beside the tiles), then all blocks of the rows below.  (Tiles that clear what
+        // lies beside them take longer: 1 x 1 x 64, N = 15, 9.6 us, this way 7.1; padding in 32 x 32 tiles writes partial
+        // lines: 8000 x 1 x 64 50 us, this way 13.6.)
+        const int id = (int)blockIdx.x - tiles, columns = (int)(Np / kPadMN), live = tiles_n * kTile;
+        const int tiles_m = divide(tiles, by_tiles_n), beside = Np > live ? tiles_m : 0;
+        const bool right = id < beside;
+        const int row = right ? id : tiles_m + (id - beside) / columns, block = right ? columns - 1 : (id - beside) % columns;
+        const int64_t col = (int64_t)block * kPadMN + (tid & 15) * 16;
+        uint8_t *const u = U + ((int64_t)row * kTile + (tid >> 4 & 31)) * Np + col;
+        if (!right || col >= live)
+            for (int s = tid >> 9; s < ma.n; s += 2) *reinterpret_cast<v4i *>(u + s * plane) = v4i{0, 0, 0, 0};
+        return;
+    }
+    const int tile_r = divide((int)blockIdx.x, by_tiles_n), tile_c = (int)blockIdx.x - tile_r * tiles_n;
+    const int64_t row0 = (int64_t)tile_r * kTile, col0 = (int64_t)tile_c * kTile;
+    uint8_t *const u_out = U + (row0 + lrow) * Np + col0 + 16 * lhalf;
 
     // Chunk number c of this wavefront: modulus wave + 16 (c / chunks), elements 128 (c % chunks) ...
     const int chunks = (int)(Kp / kChunk), total = (ma.n - wave + kWaves - 1) / kWaves * chunks;
@@ -78,7 +98,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_tiny_product(const int8_t *__re
                     const auto s1 = __builtin_amdgcn_permlane32_swap(d[1], d[3], false, false);
                     const v4i q = v4i{(int)s0[0], (int)s0[1], (int)s1[0], (int)s1[1]};
                     u_lds[s][lrow][lhalf] = q;
-                    *reinterpret_cast<v4i *>(U + ((int64_t)s * Mp + row0 + lrow) * Np + col0 + 16 * lhalf) = q;
+                    *reinterpret_cast<v4i *>(u_out + s * plane) = q;
                     s += kWaves;
                     left = chunks;
 #pragma unroll
@@ -127,9 +147,10 @@ hipError_t launch_tiny_product(const int8_t *A, const int8_t *B, uint8_t *U, int
                                double alpha, double beta, OutT *C, int64_t ldc, hipStream_t stream) {
     TinyMods tm{};
     for (int i = 0; i < ma.n; ++i) tm.byte_mod[i] = make_byte_mod(ma.p[i]);
-    const dim3 grid((unsigned)((n + kTile - 1) / kTile), (unsigned)((m + kTile - 1) / kTile));
-    hipLaunchKernelGGL((k_tiny_product<OutT>), grid, dim3(64 * kWaves), 0, stream, A, B, U, Mp, Np, Kp, m, n, tA, tB, ma, tm,
-                       alpha, beta, C, ldc);
+    const int tiles_m = (int)((m + kTile - 1) / kTile), tiles_n = (int)((n + kTile - 1) / kTile), tiles = tiles_m * tiles_n;
+    const int64_t padding = (Mp / kTile - tiles_m) * (Np / kPadMN) + (Np > (int64_t)tiles_n * kTile ? tiles_m : 0);
+    hipLaunchKernelGGL((k_tiny_product<OutT>), dim3((unsigned)(tiles + padding)), dim3(64 * kWaves), 0, stream, A, B, U, Mp, Np,
+                       Kp, m, n, tA, tB, ma, tm, alpha, beta, C, ldc, tiles_n, make_divisor(tiles_n), tiles);
     return hipGetLastError();
 }
 

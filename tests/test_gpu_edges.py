@@ -32,6 +32,27 @@ def test_products_around_the_one_launch_form(oz, oracle, m, n, k, N, dtype):
                   oracle.gemm(A, B, N, 0.5, -1.25, Cin, is_double=is_double), is_double)
 
 
+@pytest.mark.parametrize("m,n", [(1, 1), (33, 250), (256, 100), (300, 31)])
+def test_padding_of_the_smallest_products_is_zero(oz, m, n):
+    """U_s beyond m x n holds zeros, whatever the workspace held before."""
+    import torch
+    from paper_2508_03984_amd import binding as b
+    k, N = 100, 15
+    A, B = S.gemm_inputs(m, n, k, 1.0, seed=41)
+    dA, dB = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+    dC = torch.empty((m, n), dtype=torch.float64, device="cuda")
+    ws = torch.full((oz.oz2_workspace_bytes(m, n, k, N),), 0x5A, dtype=torch.int8, device="cuda")
+    oz.oz2_set_workspace(ws)
+    try:
+        oz.oz2_dgemm(m, n, k, 1.0, dA, k, dB, n, 0.0, dC, n, N)
+        torch.cuda.synchronize()
+        U = oz.stage_tensor(b.OZ2_STAGE_U).clone()
+    finally:
+        oz.oz2_set_workspace(None)
+    assert U.shape == (N, 256 if m <= 256 else 512, 256)
+    assert not U[:, m:, :].any() and not U[:, :, n:].any()
+
+
 @pytest.mark.parametrize("k", [128, 129, 256, 257])
 def test_short_contractions_with_several_tiles_per_workgroup(oz, oracle, k):
     """480 tiles of 256 x 256 for the persistent GEMM's workgroups, and K tiles around its pipeline: 2 (the head is
