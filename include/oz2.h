@@ -417,7 +417,8 @@ void oz2_set_overlap(int on);
  * and one read, both factors in the same launch where they can share it; in accurate mode the
  * passes that precede Cbar (maxima; Abar or Bbar) likewise, and the residues of both factors take one
  * launch where k <= 4096, m, n <= 8192 and (m + n) * k <= 2 * 2048^2.  The result and every stage are
- * bit-identical.  oz2_set_small_conversion(0) uses the general kernels at every size.
+ * bit-identical.  oz2_set_small_conversion(0) uses the general kernels at every size, for the products of the
+ * default context and for oz2_prepare_*.
  */
 void oz2_set_small_conversion(int on);
 

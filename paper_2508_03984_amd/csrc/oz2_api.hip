@@ -397,6 +397,11 @@ struct oz2_operand {
 
 namespace {
 
+bool fused_conversion_on(Ctx &g) {
+    std::lock_guard<std::mutex> lock(g.mu);
+    return g.small_conversion;
+}
+
 template <typename T>
 oz2_status prepare_impl(int side, int op, int64_t rows, int64_t k, const T *X, int64_t ld, int N,
                         hipStream_t stream, oz2_operand **out) {
@@ -421,7 +426,7 @@ oz2_status prepare_impl(int side, int op, int64_t rows, int64_t k, const T *X, i
     o->t = reinterpret_cast<int32_t *>(o->mem);
     o->res = reinterpret_cast<int8_t *>(o->mem + off_res);
     hipError_t e = hipSuccess;
-    if (fused_applies(o->Kp, k_contiguous)) {
+    if (fused_conversion_on(default_context()) && fused_applies(o->Kp, k_contiguous)) {
         const FusedFactor<T> f{X, ld, k_contiguous, rows, k, o->t, o->res, o->rows_pad, o->Kp, nullptr, nullptr, 0, 0};
         e = launch_fused_conversion<T>(f, FusedFactor<T>{}, make_shift_args(tab), make_mod_args(tab, false), stream);
     } else {

@@ -101,3 +101,34 @@ def test_conversion_forms_agree(oz, m, n, k, opA, opB, dtype, N, accurate):
     for x, y, name in zip(got[True], got[False], ("C", "tA", "tB", "residues of A", "residues of B")):
         assert torch.equal(x, y), name
     assert bool(torch.isfinite(got[True][0]).all())
+
+
+@pytest.mark.parametrize("m,n,k,opA,opB", [
+    (20, 30, 4096, 1, 0), (20, 30, 4097, 1, 0),      # both factors by columns: the longest that are fused, and beyond
+    (9, 270, 16384, 0, 1), (9, 270, 16385, 0, 1),    # both by rows
+])
+@pytest.mark.parametrize("dtype,N", [(np.float64, 16), (np.float32, 8)])
+def test_prepared_operands_of_both_conversions(oz, m, n, k, opA, opB, dtype, N):
+    """A product of prepared operands equals the plain call bit for bit, whichever kernels converted them."""
+    import torch
+    A, B = S.gemm_inputs(m, n, k, 2.0, seed=61 + k, dtype=dtype)
+    is_double = dtype == np.float64
+    dt = torch.float64 if is_double else torch.float32
+    dA, lda = stored(A, opA, 3, dt)
+    dB, ldb = stored(B, opB, 5, dt)
+    fn = oz.oz2_dgemm_op if is_double else oz.oz2_sgemm_op
+    prepare = oz.oz2_prepare_d if is_double else oz.oz2_prepare_s
+    product = oz.oz2_dgemm_prepared if is_double else oz.oz2_sgemm_prepared
+    want = torch.full((m, n), float("nan"), dtype=dt, device="cuda")
+    fn(opA, opB, False, m, n, k, 1.0, dA, lda, dB, ldb, 0.0, want, n, N)
+    try:
+        for fused in (True, False):
+            oz.oz2_set_small_conversion(fused)
+            left, right = prepare(0, opA, m, k, dA, lda, N), prepare(1, opB, n, k, dB, ldb, N)
+            got = torch.full((m, n), float("nan"), dtype=dt, device="cuda")
+            product(left, right, 1.0, 0.0, got, n)
+            torch.cuda.synchronize()
+            assert torch.equal(got, want), fused
+            left.free(); right.free()
+    finally:
+        oz.oz2_set_small_conversion(True)
