@@ -1,5 +1,5 @@
 // Device code of the conversion to INT8 residues (Algorithm 1 lines 2-5) shared by the row
-// kernels, the column kernels and the fused kernels for small problems: the reduction of an
+// kernels, the column kernels, the fused conversion and accurate mode's residue launch for small problems: the reduction of an
 // integer-valued FP64 number modulo the moduli of Section 4.1, and the work of one workgroup
 // of the row form (residues_block) and of the column form (residues_cols_block).
 #pragma once
@@ -10,6 +10,10 @@ namespace dev {
 
 constexpr int kWave = 64;
 constexpr int kColStrip = 64;        // columns per workgroup of the column form (one per lane)
+
+// The sums of squares behind the shifts are sums of integers of at most 2^32 in FP64: exact up to this many.
+constexpr int64_t kMaxSquares = (int64_t)1 << (53 - 32);
+static_assert(OZ2_MAX_K_BLOCKED <= kMaxSquares, "sums of squares beyond 2^53 would be rounded");
 
 // 16 bytes of elements for one load at element alignment, which the hardware's global loads take.
 template <typename T>
@@ -88,8 +92,8 @@ __device__ __forceinline__ uint64_t dpp64(uint64_t v) {
 //   difference is an integer, |y| <= M/2 + 2^-51 |x'| < 2^45) and y = x' (mod M) implies
 //   y = x' (mod p) for every p that divides M; the second round, on |y| < 2^46, is the
 //   one-round case above for each of these p.
-// p = 256: 1/p is exact, y lands in [-128, 128] and the int8 cast wraps 128 to -128,
-// which is the same class (Section 4.1).
+// p = 256: 1/p is exact, y lands in [-128, 128], and of 128 and -128, which are the same class (Section 4.1),
+// only the low byte is kept: 0x80 for both.
 // ----------------------------------------------------------------------------------------
 __device__ inline double group_reduce(double x, double M, double Minv) {
     return fma(-rint(x * Minv), M, x);
@@ -99,8 +103,9 @@ __device__ inline double group_reduce(double x, double M, double Minv) {
 // one FP64 FMA leaves 1.5 * 2^52 + rint(y/p), whose low half holds the quotient modulo 2^32, and the rest
 // is 16-bit integer arithmetic on two numbers per instruction.  (The FMA rounds y/p once where a
 // multiplication followed by rint rounds twice; the quotient is the same, since y/p is further from a
-// half-integer than either error for odd p, and p = 256 divides exactly.)  9 cycles per wavefront,
-// number and modulus where multiply, rint, FMA, conversion and byte insertion took 22.
+// half-integer than either error for odd p, and p = 256 divides exactly.)  Per number and modulus one FP64 FMA, half a
+// packed multiply-add and three quarters of a byte permute, where multiplication, rint, FMA, conversion (all FP64) and the
+// insertion of a byte were five and more.
 typedef unsigned short us2 __attribute__((ext_vector_type(2)));
 constexpr double kRintMagic = 6755399441055744.0;                     // 1.5 * 2^52
 __device__ __forceinline__ uint32_t low_word(double x) { return (uint32_t)__double_as_longlong(x); }

@@ -6,8 +6,8 @@
 
 namespace oz2 {
 
-// byte_mod_word on the device: with its share of the packing 15 cycles per wavefront and entry where
-// the mulhi form of mod_small takes 26.  Measured for whole calls, mulhi form -> this one: 8192 x 8192 x
+// byte_mod_word on the device: with its share of the packing 4.75 vector instructions per entry, none of them a
+// 32-bit multiplication (the mulhi form of mod_small has two).  Measured for whole calls, mulhi form -> this one: 8192 x 8192 x
 // 512, N = 15, 1299 -> 1245 us; 4096 x 3072 x 2048 prepared 454 -> 435 us; 4096^3, N = 14, 1142 -> 1121 us; no
 // difference at 16384^3, where the store phase is 2 % of a tile.
 __device__ __forceinline__ uint32_t byte_mod_word_dev(int acc, const ByteMod &b) {

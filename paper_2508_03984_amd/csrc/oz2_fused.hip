@@ -172,7 +172,7 @@ __global__ __launch_bounds__(THREADS) void k_convert(Side<T> a, Side<T> b, Shift
         return;
     }
 
-    // T = sum of ceil(|x| 2^(15-e))^2: integers of at most 2^32, whose sum (at most 2^53) FP64 holds exactly
+    // T = sum of ceil(|x| 2^(15-e))^2: integers of at most 2^32, whose sum FP64 holds exactly (kMaxSquares)
     double sum = 0.0;
     if (mx) {
 #pragma unroll

@@ -27,9 +27,8 @@ inline size_t column_scratch_bytes(int64_t cols) { return (size_t)cols * 16; }
 // pre-shift (4) and one maximum of Cbar per K range (4 each).
 inline size_t accurate_scratch_bytes(int64_t m, int64_t n) { return (size_t)(m + n) * (12 + 4 * kMaxKRanges); }
 
-// Shapes whose conversion (Algorithm 1 lines 1-5) runs as two fused launches: both operands
-// within 2 x 2048^2 elements (they and their slices then sit in the caches) and columns short
-// enough for one workgroup per strip.
+// Shapes whose residues of both factors come from one launch once the shifts are known (accurate mode, oz2_small.hip):
+// both operands within 2 x 2048^2 elements, so that they and their slices sit in the caches.
 inline bool small_conversion_applies(int64_t m, int64_t n, int64_t k) {
     return k <= 4096 && m <= 8192 && n <= 8192 && (m + n) * k <= (int64_t)2 * 2048 * 2048;
 }
@@ -53,9 +52,11 @@ inline bool fused_applies(int64_t Kp, bool k_contiguous) { return Kp <= (k_conti
 // unit overlap one's loads with another's stores); columns of 2048, 2048^2 each, 16 per workgroup 42, 8 52;
 // columns of 1024, 1024^2 each, 8 per workgroup 16.8, 16 21.4.
 // Beyond 2048 a strip of 8 columns fills a compute unit, and the launch runs in rounds of 256 strips; of strips of
-// 4 two or three are resident.  Those are read less well (1.1 times the time in FP64, 1.3 in FP32, from
-// columns of 4096 and 2048), so they are taken where they save more than that in the last round (1500 + 1111
-// columns of 3001: 71 -> 40 us).
+// 4 two or three are resident.  Those are read less well, so they are taken where they save more than their price in the last
+// round (1500 + 1111 columns of 3001: 71 -> 40 us).  The prices, 1.1 in FP64 and 1.3 in FP32, are on the safe side of what long
+// launches show (strips of 4 against 8, us, 16384 columns of 2100 | 3072 | 4096: FP64 N = 15 206 : 189 | 274 : 270 | 384 : 369,
+// FP32 N = 8 130 : 130 | 196 : 179 | 266 : 225; 8192 columns 111 : 96 | 146 : 133 | 203 : 185 and 45 : 54 | 97 : 84 | 132 : 108).
+// Where operand and slices stay in the caches strips of 4 would also win with whole rounds of 8: FP32, 5120 columns of 3072 41 : 49.
 // Few vectors: narrower workgroups until there is one per compute unit.  Their operands come from the caches, where
 // partial lines cost less than idle units (whole calls, N = 15 in FP64, us, 8 or 16 columns per workgroup whatever their
 // number | this rule | at least 2: 256 x 256 x 2048 45.6 | 28.6 | 28.8, 64 x 64 x 4096 62.6 | 46.6 | 49.8,

@@ -62,8 +62,8 @@ using namespace dev;
 
 // ----------------------------------------------------------------------------------------
 // Shifts.  One workgroup per row: pass 1 finds max|x| (as an integer compare of the FP64
-// bit patterns), pass 2 sums q^2 with q = ceil(|x| 2^(15-e)) <= 2^16 in 64-bit integers, which
-// is exact and independent of the order of summation.  f comes from the threshold table,
+// bit patterns), pass 2 sums q^2 with q = ceil(|x| 2^(15-e)) <= 2^16 by FP64 FMA: integers whose sum
+// stays within 2^53 (kMaxSquares), so the sum is exact and independent of the order.  f comes from the threshold table,
 // t = f - e.  k_shifts re-reads the row for pass 2 (rows of any length); k_shifts_cached
 // further down keeps rows of up to 49152 elements in registers between the passes.
 // ----------------------------------------------------------------------------------------
@@ -92,7 +92,7 @@ __global__ __launch_bounds__(kShiftThreads) void k_shifts(const T *__restrict__ 
     }
     const int e = floor_log2_of_bits(mx);
 
-    double sum = 0.0;                                                 // exact: integers, at most 2^53 in all
+    double sum = 0.0;                                                 // exact: see kMaxSquares
     scan_row<T, kShiftThreads>(x, len, [&](double v) {
         const double q = ceil(ldexp(fabs(v), 15 - e));
         sum = fma(q, q, sum);
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(THREADS) void k_shifts_cached(const T *__restrict__
         return;
     }
     const int e = floor_log2_of_bits(mx);
-    double sum = 0.0;                                                 // exact: integers, at most 2^53 in all
+    double sum = 0.0;                                                 // exact: see kMaxSquares
 #pragma unroll
     for (int c = 0; c < CH; ++c)
 #pragma unroll

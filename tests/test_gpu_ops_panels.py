@@ -493,8 +493,8 @@ def test_random_shapes_modes_and_operand_forms_against_the_oracle(oz, oracle):
     (1000, 1024, 4095, 9, np.float32, 0, 1),       # both factors by rows
 ])
 def test_small_conversion_equals_the_general_kernels(oz, m, n, k, N, dtype, opA, opB, accurate):
-    """Up to (m + n) k = 2 x 2048^2 the shifts and residues of both factors come from two fused
-    launches; every stage and C must equal what the general kernels give, bit for bit (those
+    """The fused conversion, and up to (m + n) k = 2 x 2048^2 accurate mode's residues of both factors in one
+    launch: every stage and C must equal what the general kernels give, bit for bit (those
     are checked against the oracle at these sizes by the sampled tests)."""
     import torch
     from paper_2508_03984_amd import binding as b
