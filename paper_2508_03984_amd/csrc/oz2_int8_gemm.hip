@@ -547,16 +547,14 @@ hipError_t launch(const int8_t *A, const int8_t *B, void *C, int batch, int64_t 
 }
 
 // Problems of fewer than 128 large tiles: 128 x 128 tiles, so that more workgroups exist.  Up to 256 of them
-// have a compute unit each, and 8 wavefronts with 6 stages hide more of the loads' way there than 4 with 4 do, of which
-// two share one; but they are slower to start.  Measured, 4 x 4 | 8 x 6, us: prepared operands, N = 9, 512 x 512 x 1024 10.7 | 11.2,
-// x 4096 24.1 | 21.3; N = 15, 64 x 64 x 1024 10.2 | 10.4, x 2048 13.05 | 13.45; N = 14, 256 x 256 x 4096 23.7 | 20.2; the maxima of
-// accurate mode (whole calls, N = 15) 512 x 512 x 512 38.4 | 35.1, 1024^3 65.5 | 61.9, 2048^3 209.8 | 208.7.
-constexpr int64_t kFewTilesMinK = 2560;
+// have a compute unit each: 8 wavefronts and 6 stages there (2048^3 in accurate mode, the one slice of Cbar:
+// 4 wavefronts and 4 stages 21.6 us, 4 and 6 20.6, 8 and 6 19.8, 8 and 9 19.2 but slower for short
+// contractions; 500 x 300 x 777, 8 slices: 8.4, 7.6, 7.8, 8.1); of more, two share one.
 template <int OUT>
 hipError_t launch_small(const int8_t *A, const int8_t *B, void *C, int batch, int64_t Mp, int64_t Np,
                         int64_t Kp, int64_t k_begin, int64_t k_len, const GemmPanel &pn,
                         const GemmMods &mods, hipStream_t stream) {
-    if (pn.rows * pn.cols * batch <= (int64_t)128 * 128 * 256 && (OUT == kOutMax || k_len > kFewTilesMinK))
+    if (pn.rows * pn.cols * batch <= (int64_t)128 * 128 * 256)
         return launch<2, 4, 2, 1, 64, 6, OUT>(A, B, C, batch, Mp, Np, Kp, k_begin, k_len, pn, mods, stream);
     return launch<2, 2, 2, 2, 64, 4, OUT>(A, B, C, batch, Mp, Np, Kp, k_begin, k_len, pn, mods, stream);
 }
