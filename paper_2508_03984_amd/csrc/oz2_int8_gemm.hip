@@ -547,9 +547,10 @@ hipError_t launch(const int8_t *A, const int8_t *B, void *C, int batch, int64_t 
 }
 
 // Problems of fewer than 128 large tiles: 128 x 128 tiles, so that more workgroups exist.  Up to 256 of them
-// have a compute unit each: 8 wavefronts and 6 stages there (2048^3 in accurate mode, the one slice of Cbar:
-// 4 wavefronts and 4 stages 21.6 us, 4 and 6 20.6, 8 and 6 19.8, 8 and 9 19.2 but slower for short
-// contractions; 500 x 300 x 777, 8 slices: 8.4, 7.6, 7.8, 8.1); of more, two share one.
+// have a compute unit each: 8 wavefronts and 6 stages there; of more, two share one.  Measured, 4 wavefronts and 4 stages | 4 and 6 |
+// 8 and 6, us, prepared operands, others in each call: 500 x 300 x 777 FP32 N = 8 12.0 | 11.5 | 11.6; N = 15, 256 x 256 x 1024
+// 13.5 | 12.7 | 12.8, 512 x 512 x 2048 22.5 | 19.5 | 19.8; accurate mode 512^3 N = 15 (whole call, the one slice of Cbar)
+// - | 40.6 | 37.7.  (The same operands again and again stay in the L2s: 4 and 4 is then 0.1 to 0.4 us faster up to k of about 2500.)
 template <int OUT>
 hipError_t launch_small(const int8_t *A, const int8_t *B, void *C, int batch, int64_t Mp, int64_t Np,
                         int64_t Kp, int64_t k_begin, int64_t k_len, const GemmPanel &pn,
