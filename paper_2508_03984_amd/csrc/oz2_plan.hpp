@@ -237,9 +237,12 @@ inline int64_t launch_k_len(int64_t Kp, int N, const Panels &Q) {
 
 // The smallest products run their GEMMs and the accumulation as one launch (oz2_tiny.hip): at most one 32 x 32
 // tile of C per compute unit, at most 512 elements of k in a row for a wavefront (each of the 16 takes every
-// 16th modulus), and few enough operands for a compute unit to load (64 Kp N bytes).  Measured (us on the GPU, two
-// launches | one; a launch less also saves the host about 4 us): 256^3 N = 14 10.1 | 7.9, 400 x 400 x 384 N = 8 9.7 | 8.2,
-// 1000 x 250 x 256 N = 15 11.9 | 10.3; not taken: 100 x 100 x 500 N = 15 10.2 | 14.8, 512^3 N = 15 13.0 | 13.0.
+// 16th modulus), and few enough operands for a compute unit to load (64 Kp N bytes).  Measured on the GPU, two launches | one,
+// us, other operands in each call; prepared operands: 256^3 N = 15 9.5 | 8.9, 1000 x 250 x 256 N = 15 12.1 | 10.6, 400 x 400 x 384
+// FP32 N = 8 9.3 | 9.1, not taken 100 x 100 x 512 N = 15 11.0 | 11.8, 512^3 N = 15 13.0 | 13.4; whole calls: 256^3 N = 15 14.9 | 14.1,
+// 256 x 256 x 128 FP32 N = 6 11.4 | 9.3, 1000 x 250 x 256 18.7 | 18.7, and with more than about 64 tiles 400 x 400 x 256 N = 15
+// 17.1 | 17.6, 400 x 400 x 384 FP32 N = 8 14.2 | 15.6.  A launch less also saves the host about 4 us, which bounds calls one after
+// another at these sizes.
 inline bool tiny_product_applies(int64_t m, int64_t n, int64_t Kp, int N) {
     return (m + 31) / 32 * ((n + 31) / 32) <= 256 && (N + 15) / 16 * Kp <= 512 && Kp * N <= 4096;
 }
