@@ -383,7 +383,7 @@ oz2_status oz2_int8_gemm(const int8_t *dev_A, const int8_t *dev_B, int32_t *dev_
 
 /*
  * Diagnostics: the rate of the INT8 matrix cores on their own (the instruction of the
- * GEMM of Algorithm 1 line 6, v_mfma_i32_32x32x32_i8, issued back to back from registers by
+ * GEMM of Algorithm 1 line 6, v_mfma_i32_16x16x64_i8, issued back to back from registers by
  * two wavefronts per SIMD, no memory traffic), sustained over about `seconds` (0 < seconds
  * <= 5) on the current device's default stream; blocks until done.
  * random_operands = 0: constant operands; 1: pseudo-random bytes, which is what residues

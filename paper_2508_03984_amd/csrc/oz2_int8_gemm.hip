@@ -9,17 +9,23 @@
 // and every MFMA operand is a 16-byte K-run read with one ds_read_b128.
 //
 // Tiling: workgroup = WM x WN wavefronts, block tile (32 TM WM) x (32 TN WN) x 64, each
-// wavefront owns (32 TM) x (32 TN) = TM x TN v_mfma_i32_32x32x32_i8 accumulators.  The
+// wavefront owns (32 TM) x (32 TN), in 2 TM x 2 TN accumulators of v_mfma_i32_16x16x64_i8.  The
 // large configuration is 2 x 4 wavefronts of 128 x 64 (a 256 x 256 block, 128 accumulator
 // registers per lane, two wavefronts per SIMD).
+//
+// Bound: board power for large products of random residues (the clock falls to 1.6 GHz), so the instruction that
+// spends less energy per operation is the faster one: from registers 16x16x64 sustains 4.1 POP/s on
+// random operands and 32x32x32, which reads and writes twice the accumulators per operation, 3.5 (4.95 both on
+// constant ones).  Products of prepared operands, 32x32x32 -> 16x16x64, us: 8192^3 N = 14 6410 -> 5540, 4096^3 N = 14
+// 858 -> 765, 2048^3 FP32 N = 7 69.8 -> 61.9, 8192 x 8192 x 512 N = 15 978 -> 922; 16384^3 N = 16 whole 56.7 -> 52.0 ms.
 //
 // Data movement: global_load_lds_dwordx4 copies HBM/L2 straight into a ring of STAGES LDS
 // stages, STAGES-1 tiles ahead of the math, so no VGPRs or ds_write instructions are spent
 // on staging.  A wavefront's 64 lanes fill 64 consecutive 16-byte LDS chunks per
 // instruction; the XOR swizzle that keeps the fragment reads free of bank conflicts is
-// applied on the global side (which 16 bytes of a row a lane fetches).  MFMA operands are
-// double-buffered in registers and fetched one 32-deep K step ahead, across stage
-// boundaries, so LDS latency is covered by 16 MFMAs.
+// applied on the global side (which 16 bytes of a row a lane fetches).  MFMA operands are fetched into registers
+// shortly before they are used, across stage boundaries: A's in two sets of two rows in turn, B's in place.  (More of
+// them, four rows at a time or a second set for B with the loop unrolled over two K tiles, measured 0.5 to 1 % slower.)
 //
 // Synchronisation per K tile: one s_waitcnt vmcnt(n) that leaves the youngest tiles in
 // flight, then one s_barrier.  The compiler does not track LDS writes made by
@@ -41,7 +47,6 @@ constexpr int64_t kMaxExactK = (int64_t)1 << 17;   // Section 4.3: no INT32 over
 constexpr int64_t kPersistentMaxK = OZ2_PERSISTENT_MAX_K;   // contractions up to here run as a persistent grid
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
 typedef __attribute__((address_space(3))) void *lds_ptr_t;
 typedef const __attribute__((address_space(1))) void *global_ptr_t;
 
@@ -49,14 +54,15 @@ typedef const __attribute__((address_space(1))) void *global_ptr_t;
 // 15:14, expcnt 6:4 and lgkmcnt 11:8 left at their maxima).
 constexpr int vmcnt_imm(int n) { return (n & 0xf) | ((n >> 4) << 14) | (0x7 << 4) | (0xf << 8); }
 
-// LDS on this chip is 64 banks x 4 B: a 256-byte line is 16 slots of 16 B, and a
-// ds_read_b128 is served 16 lanes per clock.  A tile row is CPR slots, so rows r and
-// r + 16/CPR start in the same slot; XOR-ing the chunk index with (row / (16/CPR)) spreads
-// the 32 rows that a fragment read touches over all 16 slots in every group of lanes the
-// hardware serves together (measured: 230 B/clk/CU against 125 with a 128-byte-line swizzle).
-template <int CPR>
+// LDS on this chip is 64 banks x 4 B: a 256-byte line is 16 slots of 16 B, and a ds_read_b128 is served 16
+// lanes per clock: lanes {0-3, 12-15, 20-27} together, then {4-11, 16-19, 28-31}, likewise in the upper half.  A
+// tile row is 4 slots, so the rows r and r + 4 start in the same slot and a fragment read (16 rows; lane l reads
+// row l % 16, chunk l / 16) has four rows, in two chunks, that want the same slots in each such group.  XOR-ing the chunk index with
+// 0, 2, 3, 1 for the row quads 0 to 3 gives each of the 16 lanes a slot of its own (0 conflict cycles per read in the
+// counters; 0, 1, 2, 3, which suits fragments of 32 rows, 4 of 8).
 __device__ inline int swizzle_mask(int row) {
-    return (row / (16 / CPR)) & (CPR - 1);
+    const int quad = row >> 2;
+    return ((quad ^ (quad >> 1)) & 1) << 1 | (quad >> 1 & 1);
 }
 
 // What the store phase writes (Algorithm 1 lines 6-7):
@@ -118,7 +124,7 @@ struct GemmCore {
     static constexpr int ROWS = BM + BN;                      // A rows then B rows in one LDS stage
     static constexpr int CHUNKS = ROWS * CPR;
     static constexpr int LPT = CHUNKS / THREADS;              // LDS-direct loads per lane and tile
-    static constexpr int KK = BK / 32;                        // MFMA K steps per tile
+    static constexpr int FM = 2 * TM, FN = 2 * TN;            // 16 x 16 fragments of a wavefront
     static constexpr int STAGE_BYTES = CHUNKS * 16;
     static constexpr int ROWS_PER_LOAD = 64 / CPR;            // rows one wavefront-wide load covers
     static constexpr int SRC_STEP = ROWS_PER_LOAD * BK;
@@ -127,9 +133,11 @@ struct GemmCore {
     static_assert(BK == kBlockK, "the K tile is the K block of the operand layout");
     static_assert(CPR == 4, "the load-side swizzle below assumes one mask per lane");
     static_assert(STAGES >= 3 && (STAGES - 3) * LPT < 64, "vmcnt is a 6-bit counter");
-    static_assert(KK >= 2, "operand double-buffering assumes an even number of K steps");
+    static constexpr int RB = 2, NB = FM / RB;                // blocks of rows that the K loop takes one after another
+    static_assert(FM % (2 * RB) == 0 && LPT >= 2 && LPT <= 4, "fragments of two blocks in turn; loads in two halves");
+    static_assert(FN == 2 || FN == 4, "the store phase transposes groups of four blocks");
 
-    int wm, wn, lrow, lhalf;
+    int wm, wn, lrow, lquad;
     // Load i of this wavefront fills LDS chunks [64 q, 64 q + 64) of a stage, q = wave*LPT + i,
     // i.e. rows q*ROWS_PER_LOAD ...; lane -> (row, physical chunk) -> logical chunk to fetch.
     // In the blocked layout those 64 chunks are 1 KiB of contiguous memory, so the LPT loads of a
@@ -141,9 +149,9 @@ struct GemmCore {
     bool from_a;                                              // uniform over the wavefront
     int64_t tile_step;                                        // next K block of the same rows
     int my_dst;                                               // uniform: byte offset within a stage
-    // Fragment addressing: lane l reads row (l % 32) of a 32-row fragment, 16-byte chunk
-    // 2*kk + l/32 of the K tile.  The swizzle mask depends on l % 32 only.
-    int a_addr[KK], b_addr[KK];                               // byte offsets within a stage, per K step
+    // Fragment addressing: lane l reads row (l % 16) of a 16-row fragment, 16-byte chunk l / 16 of the
+    // K tile (one MFMA takes all 64 of its k).  The swizzle mask depends on l % 16 only.
+    int a_addr, b_addr;                                       // byte offsets within a stage
 
     __device__ __forceinline__ GemmCore(int64_t Mp, int64_t Np) {
         const int tid = threadIdx.x, lane = tid & 63;
@@ -152,18 +160,14 @@ struct GemmCore {
         wm = wave / WN; wn = wave % WN;
         const int row0u = wave * LPT * ROWS_PER_LOAD;
         row0 = row0u + lane / CPR;
-        ch = (lane % CPR) ^ swizzle_mask<CPR>(row0);
+        ch = (lane % CPR) ^ swizzle_mask(row0);
         from_a = row0u < BM;
         tile_step = (from_a ? Mp : Np) * BK;
         my_dst = wave * LPT * 1024;
-        lrow = lane & 31; lhalf = lane >> 5;
-        const int mask = swizzle_mask<CPR>(lrow);
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-            const int c = (kk * 2 + lhalf) ^ mask;
-            a_addr[kk] = ((wm * 32 * TM + lrow) * CPR + c) * 16;
-            b_addr[kk] = ((BM + wn * 32 * TN + lrow) * CPR + c) * 16;
-        }
+        lrow = lane & 15; lquad = lane >> 4;
+        const int c = lquad ^ swizzle_mask(lrow);
+        a_addr = ((wm * 32 * TM + lrow) * CPR + c) * 16;
+        b_addr = ((BM + wn * 32 * TN + lrow) * CPR + c) * 16;
     }
 
     // Where this lane's loads of tile (s, tr, tc) start.  KB = K blocks per slice; the launch
@@ -176,15 +180,18 @@ struct GemmCore {
     }
 
     // Loads [I0, I1) of the K tile whose loads start at src_t, into the stage at byte offset
-    // stage_off (uniform).
+    // stage_off (uniform).  In assembly (nothing is returned to registers), because the compiler takes the
+    // builtin for one that may complete out of order with LDS reads, and then waits for all of those
+    // where the next of them is used.  M0 takes one wait state before it is read.
     template <int I0, int I1>
     __device__ __forceinline__ void issue_loads(const int8_t *src_t, int stage_off) const {
-        if constexpr (I0 < I1) {
-            __builtin_amdgcn_global_load_lds((global_ptr_t)src_t,
-                                             (lds_ptr_t)(reinterpret_cast<char *>(lds) + stage_off + my_dst), 16,
-                                             I0 * 1024, 0);
-            issue_loads<I0 + 1, I1>(src_t, stage_off);
-        }
+        static_assert(I1 - I0 >= 1 && I1 - I0 <= 4, "");
+        const uint32_t dst = (uint32_t)(uintptr_t)(lds_ptr_t)lds + stage_off + my_dst;
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off offset:%2" ::"s"(dst), "v"(src_t),
+                     "n"(I0 * 1024) : "memory", "m0");
+        if constexpr (I1 - I0 > 1) asm volatile("global_load_lds_dwordx4 %0, off offset:%1" ::"v"(src_t), "n"((I0 + 1) * 1024) : "memory", "m0");
+        if constexpr (I1 - I0 > 2) asm volatile("global_load_lds_dwordx4 %0, off offset:%1" ::"v"(src_t), "n"((I0 + 2) * 1024) : "memory", "m0");
+        if constexpr (I1 - I0 > 3) asm volatile("global_load_lds_dwordx4 %0, off offset:%1" ::"v"(src_t), "n"((I0 + 3) * 1024) : "memory", "m0");
     }
 
     // The first STAGES - 1 K tiles of a tile.  KT >= 2: every K range is a multiple of 128.
@@ -203,18 +210,15 @@ struct GemmCore {
     // STORES: the vector stores that were issued after the head and before this call, if `stores` says so:
     // no fewer than that, or the relaxed wait below would pass K tiles that have not landed.
     template <int STORES = 0>
-    __device__ __forceinline__ void contract(const int8_t *src_tile, int KT, v16i (&acc)[TM][TN],
+    __device__ __forceinline__ void contract(const int8_t *src_tile, int KT, v4i (&acc)[FM][FN],
                                              bool stores = false) const {
-        v4i fa[2][TM], fb[2][TN];
+        v4i fa[2 * RB], fb[FN];
         const char *const lds_bytes = reinterpret_cast<const char *>(lds);
-        auto load_frags = [&](int buf, int stage_off, int kk) {
-            const char *st = lds_bytes + stage_off;
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-                fa[buf][i] = *reinterpret_cast<const v4i *>(st + a_addr[kk] + i * 32 * CPR * 16);
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-                fb[buf][j] = *reinterpret_cast<const v4i *>(st + b_addr[kk] + j * 32 * CPR * 16);
+        auto load_a = [&](int stage_off, int i) {
+            fa[i % (2 * RB)] = *reinterpret_cast<const v4i *>(lds_bytes + stage_off + a_addr + i * 16 * CPR * 16);
+        };
+        auto load_b = [&](int stage_off, int j) {
+            fb[j] = *reinterpret_cast<const v4i *>(lds_bytes + stage_off + b_addr + j * 16 * CPR * 16);
         };
 
         // K tiles 0 and 1 must have landed before the first fragment reads.  In the persistent
@@ -229,42 +233,43 @@ struct GemmCore {
         else if (KT >= STAGES - 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kYoungest));
         else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
         __builtin_amdgcn_s_barrier();
-        load_frags(0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < FN; ++j) load_b(0, j);
+#pragma unroll
+        for (int i = 0; i < 2 * RB; ++i) load_a(0, i);
 
-        // One K tile: it is read from the stage at cur_off, the K tile STAGES - 1 ahead is
-        // requested into the stage read during the previous iteration.  Its LPT loads go out in
-        // two halves, each behind the second MFMA row of a K step.
+        // One K tile, in blocks of RB rows of MFMAs.  Behind a block the fragments of A of the block after the next one
+        // are requested into its registers, and behind each column of the last block the next K tile's fragment of
+        // B, so that LDS latency is covered by a block of MFMAs.  The K tile STAGES - 1 ahead is requested into the
+        // stage read during the previous iteration; its LPT loads go out in two halves, behind a quarter and three
+        // quarters of the MFMAs.
         int cur_off = 0;
         const int8_t *src_ld = src_tile + (int64_t)(STAGES - 1) * tile_step;
-        auto iteration = [&](auto issued_c, bool last, bool after_stores = false) {
-            constexpr bool issued = decltype(issued_c)::value;
+        auto iteration = [&](auto issued_c, auto last_c, bool after_stores = false) {
+            constexpr bool issued = decltype(issued_c)::value, last = decltype(last_c)::value;
             const int nxt_off = cur_off + STAGE_BYTES == STAGES * STAGE_BYTES ? 0 : cur_off + STAGE_BYTES;
             const int ld_off = cur_off == 0 ? (STAGES - 1) * STAGE_BYTES : cur_off - STAGE_BYTES;
 #pragma unroll
-            for (int kk = 0; kk < KK; ++kk) {
-                const int cur = kk & 1, nxt = cur ^ 1;
-                // The first MFMA row runs before the next operands are requested: its operands
-                // were requested a whole K step ago, so waiting for them (the LDS counter is
-                // waited down to zero at that point) does not wait for the new requests.
+            for (int p = 0; p < NB; ++p) {
 #pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[0][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[cur][j], fa[cur][0], acc[0][j], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-                if (kk + 1 < KK) load_frags(nxt, cur_off, kk + 1);
-                else if (!last) load_frags(nxt, nxt_off, 0);
-                __builtin_amdgcn_sched_barrier(0);
+                for (int j = 0; j < FN; ++j) {
 #pragma unroll
-                for (int i = 1; i < TM; ++i) {
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[cur][j], fa[cur][i], acc[i][j], 0, 0, 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (issued && i == 1) {
-                        if (kk == 0) issue_loads<0, LPT / 2>(src_ld, ld_off);
-                        if (kk == KK - 1) issue_loads<LPT / 2, LPT>(src_ld, ld_off);
+                    for (int rr = 0; rr < RB; ++rr) {
+                        const int i = p * RB + (j & 1 ? RB - 1 - rr : rr);   // a column starts with the row the last one ended with
+                        acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fb[j], fa[i % (2 * RB)], acc[i][j], 0, 0, 0);
                     }
                     __builtin_amdgcn_sched_barrier(0);
+                    if (p == NB - 1 && !last) load_b(nxt_off, j);
+                    if (issued && p * FN + j == NB * FN / 4 - 1) issue_loads<0, LPT / 2>(src_ld, ld_off);
+                    if (issued && p * FN + j == 3 * NB * FN / 4 - 1) issue_loads<LPT / 2, LPT>(src_ld, ld_off);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
+#pragma unroll
+                for (int r = 0; r < RB; ++r) {
+                    if (p + 2 < NB) load_a(cur_off, (p + 2) * RB + r);
+                    else if (!last) load_a(nxt_off, (p + 2 - NB) * RB + r);
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
             // Tile kt + 2 must be complete (and visible to every wavefront) before iteration
             // kt + 1 prefetches fragments from it; the barrier also frees the stage just read.
@@ -275,123 +280,123 @@ struct GemmCore {
             cur_off = nxt_off;
             src_ld += tile_step;
         };
+        constexpr std::true_type yes{};
+        constexpr std::false_type no{};
         int kt = 0;
-        for (; kt + STAGES - 1 < KT; ++kt) iteration(std::true_type{}, false, STORES > 0 && lenient && kt == 0);
-        for (; kt < KT; ++kt) iteration(std::false_type{}, kt + 1 == KT);
+        for (; kt + STAGES - 1 < KT; ++kt) iteration(yes, no, STORES > 0 && lenient && kt == 0);
+        for (; kt + 1 < KT; ++kt) iteration(no, no);
+        iteration(no, yes);
     }
 
     // Row and column maxima of the tile (kOutMax).  Entries are sums of products of non-negative
     // 7-bit numbers (k <= 2^17: below 2^29), the maxima start at 0 and zero entries (all the
     // padding) are skipped, so integer atomic maxima give the exact result whatever the order.  A
-    // lane holds, per 32 x 32 block, 16 columns of one row: the row maximum is completed by the
-    // lane 32 further on, a column maximum by the 32 lanes of the same half-wavefront.
-    __device__ __forceinline__ void store_maxima(const v16i (&acc)[TM][TN], int *rmax, int *cmax, int64_t bm,
+    // lane holds, per 16 x 16 block, 4 columns of one row: the row maximum is completed by the
+    // lanes 16, 32 and 48 further on, a column maximum by the 16 lanes of the same quarter.
+    __device__ __forceinline__ void store_maxima(const v4i (&acc)[FM][FN], int *rmax, int *cmax, int64_t bm,
                                                  int64_t bn, int valid_rows, int valid_cols) const {
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
+        for (int i = 0; i < FM; ++i) {
             int v = 0;
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
+            for (int j = 0; j < FN; ++j)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) v = acc[i][j][r] > v ? acc[i][j][r] : v;
-            const int o = __shfl_xor(v, 32, 64);
-            v = o > v ? o : v;
-            const int row = (int)bm + wm * 32 * TM + i * 32 + lrow;
-            if (lhalf == 0 && v > 0 && row < valid_rows) atomicMax(&rmax[row], v);
+                for (int r = 0; r < 4; ++r) v = acc[i][j][r] > v ? acc[i][j][r] : v;
+#pragma unroll
+            for (int off = 16; off < 64; off <<= 1) {
+                const int o = __shfl_xor(v, off, 64);
+                v = o > v ? o : v;
+            }
+            const int row = (int)bm + wm * 32 * TM + i * 16 + lrow;
+            if (lquad == 0 && v > 0 && row < valid_rows) atomicMax(&rmax[row], v);
         }
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+        for (int j = 0; j < FN; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
+            for (int r = 0; r < 4; ++r) {
                 int v = 0;
 #pragma unroll
-                for (int i = 0; i < TM; ++i) v = acc[i][j][r] > v ? acc[i][j][r] : v;
+                for (int i = 0; i < FM; ++i) v = acc[i][j][r] > v ? acc[i][j][r] : v;
 #pragma unroll
-                for (int off = 1; off < 32; off <<= 1) {
+                for (int off = 1; off < 16; off <<= 1) {
                     const int o = __shfl_xor(v, off, 64);
                     v = o > v ? o : v;
                 }
-                const int col = (int)bn + wn * 32 * TN + j * 32 + 8 * (r >> 2) + 4 * lhalf + (r & 3);
+                const int col = (int)bn + wn * 32 * TN + j * 16 + 4 * lquad + r;
                 if (lrow == 0 && v > 0 && col < valid_cols) atomicMax(&cmax[col], v);
             }
     }
 
     // The store phase (Algorithm 1 lines 6-7 in the forms listed at kOut...).  The B fragment is
-    // the MFMA's first operand, so the 32x32 accumulator is the transposed block: lane l holds
-    // row (l % 32) of the C block and, in registers 4g .. 4g+3, the four consecutive columns
-    // 8g + 4*(l / 32) + {0,1,2,3}.  The reduction to bytes is that of oz2_bytemod.hpp; the int32
-    // forms use the mulhi reduction of Section 4.3.
+    // the MFMA's first operand, so the 16x16 accumulator is the transposed block: lane l holds
+    // row (l % 16) of the C block and the four consecutive columns 4 * (l / 16) + {0,1,2,3}.  The
+    // reduction to bytes is that of oz2_bytemod.hpp; the int32 forms use the mulhi reduction of Section 4.3.
     template <int OUT>
-    __device__ __forceinline__ void store(const v16i (&acc)[TM][TN], void *C, int s, int64_t bm, int64_t bn,
+    __device__ __forceinline__ void store(const v4i (&acc)[FM][FN], void *C, int s, int64_t bm, int64_t bn,
                                           int64_t c_ld, int64_t c_plane, const GemmMods &mods) const {
         const int p = mods.p[s], pv = mods.pinv_prime[s];
         const int64_t c_off = (int64_t)s * c_plane + bm * c_ld + bn;   // C: [slice][row][column]
         if (OUT == kOutU8 || OUT == kOutU8Fold) {
             const ByteMod b = mods.byte_mod[s];
-            // Four residues per register quad pack into one dword; the two half-wavefronts hold
-            // alternating dwords of a row (columns 8g + 4*(l/32) ...), so they swap two dwords
-            // each (lanes 0-31 end up with columns 0-15 of the block row, lanes 32-63 with 16-31)
-            // and every lane stores 16 contiguous bytes: a lane pair completes a 32-byte
-            // sector of the row, and the L2 does not have to fetch lines to merge 4-byte stores.
+            // The four residues a lane holds of a block pack into one dword; the lanes l, l + 16, l + 32 and
+            // l + 48 hold the four dwords of a row.  Four blocks (side by side, or two by two) are exchanged
+            // as a 4 x 4 transposition among these lanes, after which each of them holds a row of one block and
+            // stores 16 contiguous bytes: whole 32- or 64-byte sectors of a row per instruction, and the L2
+            // does not have to fetch lines to merge 4-byte stores.
             // (Staging the whole uint8 tile through LDS to store 64-byte row segments was measured
             // 3.5 ms slower per launch at 16 x 16384^3.)
+            constexpr int ROWS_PER = 4 / FN;                  // block rows per group of four blocks
+            const int row = wm * 32 * TM + (FN == 2 ? (lquad >> 1) * 16 : 0) + lrow;
+            const int col = wn * 32 * TN + (FN == 2 ? lquad & 1 : lquad) * 16;
+            uint8_t *const dst0 = static_cast<uint8_t *>(C) + c_off + (int64_t)row * c_ld + col;
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+            for (int i = 0; i < FM; i += ROWS_PER) {
+                uint32_t d[4];
 #pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    uint32_t d[4];
-#pragma unroll
-                    for (int g = 0; g < 4; ++g)
-                        d[g] = pack_low_bytes(byte_mod_word_dev(acc[i][j][4 * g], b), byte_mod_word_dev(acc[i][j][4 * g + 1], b),
-                                              byte_mod_word_dev(acc[i][j][4 * g + 2], b),
-                                              byte_mod_word_dev(acc[i][j][4 * g + 3], b));
-                    // v_permlane32_swap(a, b): the upper half of a and the lower half of b change
-                    // places, so lanes 0-31 get (d0 | d0 of lane + 32) and lanes 32-63 (d2 of lane
-                    // - 32 | d2) in (a, b): the row's dwords in column order, no selects needed.
-                    const auto s0 = __builtin_amdgcn_permlane32_swap(d[0], d[2], false, false);
-                    const auto s1 = __builtin_amdgcn_permlane32_swap(d[1], d[3], false, false);
-                    v4i q = v4i{(int)s0[0], (int)s0[1], (int)s1[0], (int)s1[1]};
-                    const int row = wm * 32 * TM + i * 32 + lrow;
-                    const int col = wn * 32 * TN + j * 32 + 16 * lhalf;
-                    v4i *dst = reinterpret_cast<v4i *>(static_cast<uint8_t *>(C) + c_off + (int64_t)row * c_ld + col);
-                    if (OUT == kOutU8Fold) {               // a further K range: (old + new) mod p_s, byte by byte
-                        const v4i old = *dst;
-#pragma unroll
-                        for (int w = 0; w < 4; ++w) q[w] = (int)add_mod_bytes((uint32_t)q[w], (uint32_t)old[w], p);
-                    }
-                    *dst = q;
+                for (int g = 0; g < 4; ++g) {
+                    const v4i &x = acc[i + g / FN][g % FN];
+                    d[g] = pack_low_bytes(byte_mod_word_dev(x[0], b), byte_mod_word_dev(x[1], b), byte_mod_word_dev(x[2], b),
+                                          byte_mod_word_dev(x[3], b));
                 }
+                // v_permlane32_swap(a, b): the upper half of a and the lower half of b change places;
+                // v_permlane16_swap(a, b): the odd quarters of a and the even quarters of b.
+                const auto s02 = __builtin_amdgcn_permlane32_swap(d[0], d[2], false, false);
+                const auto s13 = __builtin_amdgcn_permlane32_swap(d[1], d[3], false, false);
+                const auto lo = __builtin_amdgcn_permlane16_swap(s02[0], s13[0], false, false);
+                const auto hi = __builtin_amdgcn_permlane16_swap(s02[1], s13[1], false, false);
+                v4i q = v4i{(int)lo[0], (int)lo[1], (int)hi[0], (int)hi[1]};
+                v4i *dst = reinterpret_cast<v4i *>(dst0 + (int64_t)(i * 16) * c_ld);
+                if (OUT == kOutU8Fold) {                   // a further K range: (old + new) mod p_s, byte by byte
+                    const v4i old = *dst;
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) q[w] = (int)add_mod_bytes((uint32_t)q[w], (uint32_t)old[w], p);
+                }
+                *dst = q;
+            }
             return;
         }
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < FM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
+            for (int j = 0; j < FN; ++j) {
+                const int row = wm * 32 * TM + i * 16 + lrow;
+                const int col = wn * 32 * TN + j * 16 + 4 * lquad;
+                v4i v = acc[i][j];
+                v4i *dst = reinterpret_cast<v4i *>(static_cast<int32_t *>(C) + c_off + (int64_t)row * c_ld + col);
+                if (OUT == kOutI32Fold) {
+                    const v4i old = *dst;
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int row = wm * 32 * TM + i * 32 + lrow;
-                    const int col = wn * 32 * TN + j * 32 + 8 * g + 4 * lhalf;
-                    const int64_t at = c_off + (int64_t)row * c_ld + col;
-                    int v[4];
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) v[c] = acc[i][j][4 * g + c];
-                    v4i *dst = reinterpret_cast<v4i *>(static_cast<int32_t *>(C) + at);
-                    if (OUT == kOutI32Fold) {
-                        const v4i old = *dst;
-#pragma unroll
-                        for (int c = 0; c < 4; ++c) v[c] = mod_small(old[c], p, pv) + mod_small(v[c], p, pv);
-                    }
-                    *dst = v4i{v[0], v[1], v[2], v[3]};
+                    for (int c = 0; c < 4; ++c) v[c] = mod_small(old[c], p, pv) + mod_small(v[c], p, pv);
                 }
+                *dst = v;
+            }
     }
 
-    static __device__ __forceinline__ void fill(v16i (&acc)[TM][TN], int v) {
+    static __device__ __forceinline__ void fill(v4i (&acc)[FM][FN], int v) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < FM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = v;
+            for (int j = 0; j < FN; ++j) acc[i][j] = v4i{v, v, v, v};
     }
 };
 
@@ -411,7 +416,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_int8_gemm(const int8_t *__rest
     map_tile(tmap, (int)blockIdx.x, s, tile_r, tile_c);
     const int8_t *src = core.tile_source(A, B, s, tile_r, tile_c, Mp, Np, KB, kb0);
     core.issue_head(src, KT);
-    v16i acc[TM][TN];
+    v4i acc[Core::FM][Core::FN];
     Core::fill(acc, first_acc(OUT));
     core.contract(src, KT, acc);
     const int64_t bm = (int64_t)tile_r * Core::BM, bn = (int64_t)tile_c * Core::BN;
@@ -457,7 +462,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_int8_gemm_persistent(const int
             map_tile(tmap, next, s_next, tile_r_next, tile_c_next);
             src_next = core.tile_source(A, B, s_next, tile_r_next, tile_c_next, Mp, Np, KB, kb0);
         }
-        v16i acc[TM][TN];
+        v4i acc[Core::FM][Core::FN];
         Core::fill(acc, first_acc(OUT));
         // kStores: the number of store instructions of store<kOutU8>, one of 16 bytes per 32 x 32 block of a
         // wavefront.  (The fold forms also load what they add to, and wait for it themselves.)

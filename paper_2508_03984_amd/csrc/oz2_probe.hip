@@ -10,10 +10,9 @@
 namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr int kProbeThreads = 256;     // one wavefront per SIMD
-constexpr int kProbeAcc = 8;           // independent accumulators per wavefront
+constexpr int kProbeAcc = 16;          // independent accumulators per wavefront
 constexpr int kProbeOps = 8;           // distinct operand registers per side
 
 __device__ inline uint32_t mix(uint32_t x) {      // integer hash (xorshift-multiply rounds)
@@ -23,7 +22,7 @@ __device__ inline uint32_t mix(uint32_t x) {      // integer hash (xorshift-mult
     return x;
 }
 
-// Every wavefront issues iters * kProbeAcc * kProbeOps v_mfma_i32_32x32x32_i8 back to back.
+// Every wavefront issues iters * kProbeAcc * kProbeOps v_mfma_i32_16x16x64_i8 (the GEMM's instruction) back to back.
 // Consecutive instructions of the pipeline see different operand registers, so with
 // random contents the multiplier inputs toggle the way a stream of residues makes them.
 __global__ __launch_bounds__(kProbeThreads) void k_mfma_probe(int *out, int iters, int random_operands) {
@@ -36,23 +35,23 @@ __global__ __launch_bounds__(kProbeThreads) void k_mfma_probe(int *out, int iter
             a[i][c] = random_operands ? (int)mix(id * 64u + i * 8u + c) : 0x01010101;
             b[i][c] = random_operands ? (int)mix(id * 64u + i * 8u + c + 4u) : 0x01010101;
         }
-    v16i acc[kProbeAcc];
+    v4i acc[kProbeAcc];
 #pragma unroll
     for (int i = 0; i < kProbeAcc; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][r] = 0;
+        for (int r = 0; r < 4; ++r) acc[i][r] = 0;
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
         for (int o = 0; o < kProbeOps; ++o)
 #pragma unroll
             for (int i = 0; i < kProbeAcc; ++i)
-                acc[i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[(o + i) % kProbeOps], b[o], acc[i], 0, 0, 0);
+                acc[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[(o + i) % kProbeOps], b[o], acc[i], 0, 0, 0);
     }
     int s = 0;
 #pragma unroll
     for (int i = 0; i < kProbeAcc; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s += acc[i][r];
+        for (int r = 0; r < 4; ++r) s += acc[i][r];
     out[id] = s;
 }
 
@@ -73,7 +72,7 @@ extern "C" oz2_status oz2_mfma_probe(int random_operands, double seconds, double
     hipEvent_t e0 = nullptr, e1 = nullptr;
     oz2_status st = OZ2_HIP_ERROR;
     float ms = 0.f;
-    const double ops_per_iter = (double)blocks * (kProbeThreads / 64) * kProbeAcc * kProbeOps * 65536.0;
+    const double ops_per_iter = (double)blocks * (kProbeThreads / 64) * kProbeAcc * kProbeOps * 32768.0;
     // One short launch sizes the timed one (the sustained clock is what is being measured,
     // so the timed launch has to last long enough for the power management to settle).
     int iters = 2000;
