@@ -182,16 +182,22 @@ struct GemmCore {
     // Loads [I0, I1) of the K tile whose loads start at src_t, into the stage at byte offset
     // stage_off (uniform).  In assembly (nothing is returned to registers), because the compiler takes the
     // builtin for one that may complete out of order with LDS reads, and then waits for all of those
-    // where the next of them is used.  M0 takes one wait state before it is read.
+    // where the next of them is used.  M0, which is nobody else's in these kernels, takes one wait state before it is read.
     template <int I0, int I1>
     __device__ __forceinline__ void issue_loads(const int8_t *src_t, int stage_off) const {
-        static_assert(I1 - I0 >= 1 && I1 - I0 <= 4, "");
+        static_assert(I1 - I0 == 1 || I1 - I0 == 2 || I1 - I0 == 4, "");
         const uint32_t dst = (uint32_t)(uintptr_t)(lds_ptr_t)lds + stage_off + my_dst;
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off offset:%2" ::"s"(dst), "v"(src_t),
-                     "n"(I0 * 1024) : "memory", "m0");
-        if constexpr (I1 - I0 > 1) asm volatile("global_load_lds_dwordx4 %0, off offset:%1" ::"v"(src_t), "n"((I0 + 1) * 1024) : "memory", "m0");
-        if constexpr (I1 - I0 > 2) asm volatile("global_load_lds_dwordx4 %0, off offset:%1" ::"v"(src_t), "n"((I0 + 2) * 1024) : "memory", "m0");
-        if constexpr (I1 - I0 > 3) asm volatile("global_load_lds_dwordx4 %0, off offset:%1" ::"v"(src_t), "n"((I0 + 3) * 1024) : "memory", "m0");
+        if constexpr (I1 - I0 == 1)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off offset:%2" ::"s"(dst), "v"(src_t),
+                         "n"(I0 * 1024) : "memory");
+        else if constexpr (I1 - I0 == 2)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off offset:%2\n\t"
+                         "global_load_lds_dwordx4 %1, off offset:%3" ::"s"(dst), "v"(src_t), "n"(I0 * 1024),
+                         "n"(I0 * 1024 + 1024) : "memory");
+        else {
+            issue_loads<I0, I0 + 2>(src_t, stage_off);
+            issue_loads<I0 + 2, I1>(src_t, stage_off);
+        }
     }
 
     // The first STAGES - 1 K tiles of a tile.  KT >= 2: every K range is a multiple of 128.
