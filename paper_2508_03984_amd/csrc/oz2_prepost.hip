@@ -7,6 +7,7 @@
 #include "oz2_convert.hpp"
 #include "oz2_epilogue.hpp"
 #include "oz2_kernels.hpp"
+#include "oz2_tilemap.hpp"
 
 namespace oz2 {
 
@@ -200,107 +201,138 @@ __global__ __launch_bounds__(THREADS) void k_shifts_cached(const T *__restrict__
 }
 
 // ----------------------------------------------------------------------------------------
-// Epilogue: for each (i, j) read the N int32 products once, U_s = mod(C'_s, p_s) by the
-// mulhi reduction of Section 4.3, C1 += s_s1 U_s, C2 += s_s2 U_s (s = 1..N, one FMA each),
+// Epilogue: for each (i, j) read U_s once (or the N int32 products, U_s = mod(C'_s, p_s) by the
+// mulhi reduction of Section 4.3), C1 += s_s1 U_s, C2 += s_s2 U_s (s = 1..N, one FMA each),
 // Q = rint(P_inv C1), C'' = fma(-P2, Q, fma(-P1, Q, C1) + C2), c = C'' 2^-(tA_i + tB_j).
-// One thread per 4 consecutive columns (16-byte loads of the int32 planes).
+// One thread per 4 consecutive columns: one 4-byte (uint8 input) or 16-byte (int32 input) load
+// per modulus; 8 columns per thread measured slower (2.4 against 1.9 ms at 16384^2, N = 16).
 // ----------------------------------------------------------------------------------------
+constexpr int kEpilogueColumns = 4;
 
-// IN_U8: the GEMM already reduced its sums (prod holds U_s as uint8, 4 bytes per thread and
-// modulus); otherwise prod holds int32 sums (possibly folded partial sums) reduced here.
-template <typename OutT, bool IN_U8>
-__device__ __forceinline__ void epilogue_block(int64_t block, const void *__restrict__ prod_, int64_t Mp,
-                                               int64_t Np, int64_t m, int64_t n,
-                                               const int32_t *__restrict__ tA,
-                                               const int32_t *__restrict__ tB, const ModArgs &ma,
-                                               double alpha, double beta, OutT *C, int64_t ldc) {
-    // 4 consecutive columns per thread: one 4-byte (uint8 input) or 16-byte (int32 input) load
-    // per modulus; 8 columns per thread measured slower (2.4 against 1.9 ms at 16384^2, N = 16).
-    // Np is a multiple of 256.
-    constexpr int W = 4;
-    const int64_t groups = (n + W - 1) / W;
-    const int64_t idx = block * 256 + threadIdx.x;
-    if (idx >= m * groups) return;
-    const int64_t i = idx / groups, j0 = (idx % groups) * W;
+// A thread's place: row i of C and its first column, by a 32-bit division that is a multiplication: a 64-bit
+// division and its remainder took about a quarter of a thread's vector instructions.
+struct EpiloguePlace {
+    int64_t i, j0;
+    bool valid;
+    __device__ __forceinline__ EpiloguePlace(int64_t m, int groups, Divisor by_groups) {
+        const int idx = (int)(blockIdx.x * 256 + threadIdx.x), row = divide(idx, by_groups);
+        i = row; j0 = (int64_t)(idx - row * groups) * kEpilogueColumns;
+        valid = row < m;
+    }
+};
 
-    const int64_t plane = Mp * Np;
-    const int64_t at = i * Np + j0;
+// The end of an entry for the four columns of a thread; `old`: C before the call if `beta` needs it and it was
+// loaded as 16-byte pieces (whole, aligned groups of columns).
+template <typename OutT>
+struct EpilogueTail {
+    static constexpr int W = kEpilogueColumns, kVec = 16 / sizeof(OutT);
+    typedef OutT vec_t __attribute__((ext_vector_type(kVec)));
+    OutT *dst;
+    int shift[W], columns;
+    bool vector;
+    vec_t old[W / kVec];
+    __device__ __forceinline__ EpilogueTail(const EpiloguePlace &at, int64_t n, const int32_t *tA, const int32_t *tB, double beta,
+                                            OutT *C, int64_t ldc) {
+        dst = C + at.i * ldc + at.j0;
+        columns = n - at.j0 < W ? (int)(n - at.j0) : W;
+        vector = columns == W && (reinterpret_cast<uintptr_t>(dst) & 15) == 0;
+        const int ta = tA[at.i];
+#pragma unroll
+        for (int c = 0; c < W; ++c) shift[c] = ta + (c < columns ? tB[at.j0 + c] : 0);
+        if (vector && beta != 0.0) {
+#pragma unroll
+            for (int q = 0; q < W / kVec; ++q) old[q] = reinterpret_cast<const vec_t *>(dst)[q];
+        }
+    }
+    __device__ __forceinline__ void store(const double (&C1)[W], const double (&C2)[W], const ModArgs &ma, double alpha, double beta) {
+        if (vector) {
+#pragma unroll
+            for (int c = 0; c < W; ++c) {
+                const OutT before = old[c / kVec][c % kVec];  // (read if beta is not 0)
+                old[c / kVec][c % kVec] = crt_entry<OutT>(C1[c], C2[c], shift[c], ma, alpha, beta, &before);
+            }
+#pragma unroll
+            for (int q = 0; q < W / kVec; ++q) reinterpret_cast<vec_t *>(dst)[q] = old[q];
+        } else {
+#pragma unroll
+            for (int c = 0; c < W; ++c)
+                if (c < columns) dst[c] = crt_entry<OutT>(C1[c], C2[c], shift[c], ma, alpha, beta, dst + c);
+        }
+    }
+};
+
+// The uint8 form for N moduli: everything it reads, C for beta != 0 included, is requested before anything is used.  Bound: HBM
+// for large C (8192^2, N = 15, beta = 1: 389 us, 5.3 TB/s).  With groups of 8, 4, 2 and 1 moduli that waited for their loads, C
+// read at the end and 64-bit divisions it took 450 us; 4096^2, N = 14, 76 -> 68; 2048^2, N = 15, 20.8 -> 18.8; 1024^2 8.5 -> 7.2.
+template <typename OutT, int N>
+__global__ __launch_bounds__(256) void k_epilogue(const uint8_t *__restrict__ U, int64_t plane, int64_t Np, int64_t m, int64_t n,
+                                                  const int32_t *__restrict__ tA, const int32_t *__restrict__ tB, ModArgs ma,
+                                                  double alpha, double beta, OutT *C, int64_t ldc, int groups, Divisor by_groups) {
+    constexpr int W = kEpilogueColumns;
+    const EpiloguePlace at(m, groups, by_groups);
+    if (!at.valid) return;
+    const uint8_t *u = U + at.i * Np + at.j0;                 // Np is a multiple of 256: aligned, and within the row
+    uint32_t x[N];
+#pragma unroll
+    for (int s = 0; s < N; ++s) { x[s] = *reinterpret_cast<const uint32_t *>(u); u += plane; }
+    EpilogueTail<OutT> tail(at, n, tA, tB, beta, C, ldc);
     double C1[W], C2[W];
 #pragma unroll
     for (int c = 0; c < W; ++c) C1[c] = C2[c] = 0.0;
-    // Moduli s0 .. s0 + CNT - 1: all loads first (CNT of them in flight), then the FMAs in
-    // ascending order of s, which is the order the accumulation of C'(2) is defined in.
-    auto group = [&](int s0, auto cnt) {
-        constexpr int CNT = decltype(cnt)::value;
-        int us[CNT][W];
+    // ascending order of s, in which the accumulation of C'(2) is defined
 #pragma unroll
-        for (int g = 0; g < CNT; ++g) {
-            const int s = s0 + g;
-            if (IN_U8) {
-                const uint32_t x = *reinterpret_cast<const uint32_t *>(
-                    static_cast<const uint8_t *>(prod_) + (int64_t)s * plane + at);
+    for (int s = 0; s < N; ++s) {
+        const double s1 = ma.s1[s], s2 = ma.s2[s];
 #pragma unroll
-                for (int c = 0; c < 4; ++c) us[g][c] = (int)((x >> (8 * c)) & 0xffu);
-            } else {
-                const int4 x = *reinterpret_cast<const int4 *>(
-                    static_cast<const int32_t *>(prod_) + (int64_t)s * plane + at);
-                const int p = ma.p[s], pv = (int)ma.pinv_prime[s];
-                us[g][0] = mod_small(x.x, p, pv); us[g][1] = mod_small(x.y, p, pv);
-                us[g][2] = mod_small(x.z, p, pv); us[g][3] = mod_small(x.w, p, pv);
-            }
-        }
-#pragma unroll
-        for (int g = 0; g < CNT; ++g) {
-            const double s1 = ma.s1[s0 + g], s2 = ma.s2[s0 + g];
-#pragma unroll
-            for (int c = 0; c < W; ++c) {
-                const double u = (double)us[g][c];
-                C1[c] = fma(s1, u, C1[c]);
-                C2[c] = fma(s2, u, C2[c]);
-            }
-        }
-    };
-    // groups of 8, then 4, 2, 1: a count that is not a multiple of 8 costs at most three more
-    // rounds of load latency (a plain remainder loop cost 0.15 ms at 16384^2 for N = 14, 15)
-    int s = 0;
-    for (; s + 8 <= ma.n; s += 8) group(s, std::integral_constant<int, 8>{});
-    if (s + 4 <= ma.n) { group(s, std::integral_constant<int, 4>{}); s += 4; }
-    if (s + 2 <= ma.n) { group(s, std::integral_constant<int, 2>{}); s += 2; }
-    if (s < ma.n) group(s, std::integral_constant<int, 1>{});
-    const int ta = tA[i];
-    OutT *dst = C + i * ldc + j0;
-    OutT res[W];
-#pragma unroll
-    for (int c = 0; c < W; ++c) {
-        if (j0 + c < n) {
-            res[c] = crt_entry<OutT>(C1[c], C2[c], ta + tB[j0 + c], ma, alpha, beta, dst + c);
+        for (int c = 0; c < W; ++c) {
+            const double v = (double)(int)((x[s] >> (8 * c)) & 0xffu);
+            C1[c] = fma(s1, v, C1[c]);
+            C2[c] = fma(s2, v, C2[c]);
         }
     }
-    if (j0 + W <= n && (reinterpret_cast<uintptr_t>(dst) & 15) == 0) {      // 16-byte stores
-        constexpr int kVec = 16 / sizeof(OutT);
-        typedef OutT vec_t __attribute__((ext_vector_type(kVec)));
-#pragma unroll
-        for (int q = 0; q < W / kVec; ++q) {
-            vec_t v;
-#pragma unroll
-            for (int c = 0; c < kVec; ++c) v[c] = res[q * kVec + c];
-            reinterpret_cast<vec_t *>(dst)[q] = v;
-        }
-    } else {
-#pragma unroll
-        for (int c = 0; c < W; ++c)
-            if (j0 + c < n) dst[c] = res[c];
-    }
+    tail.store(C1, C2, ma, alpha, beta);
 }
 
-template <typename OutT, bool IN_U8>
-__global__ __launch_bounds__(256) void k_epilogue(const void *__restrict__ prod_, int64_t Mp,
-                                                  int64_t Np, int64_t m, int64_t n,
-                                                  const int32_t *__restrict__ tA,
-                                                  const int32_t *__restrict__ tB, ModArgs ma,
-                                                  double alpha, double beta, OutT *C,
-                                                  int64_t ldc) {
-    epilogue_block<OutT, IN_U8>(blockIdx.x, prod_, Mp, Np, m, n, tA, tB, ma, alpha, beta, C, ldc);
+// The form for int32 sums (possibly folded partial sums), which are reduced here.
+template <typename OutT>
+__global__ __launch_bounds__(256) void k_epilogue_i32(const int32_t *__restrict__ prod, int64_t plane, int64_t Np, int64_t m,
+                                                      int64_t n, const int32_t *__restrict__ tA,
+                                                      const int32_t *__restrict__ tB, ModArgs ma, double alpha, double beta,
+                                                      OutT *C, int64_t ldc, int groups, Divisor by_groups) {
+    constexpr int W = kEpilogueColumns;
+    const EpiloguePlace at(m, groups, by_groups);
+    if (!at.valid) return;
+    const int32_t *u = prod + at.i * Np + at.j0;
+    double C1[W], C2[W];
+#pragma unroll
+    for (int c = 0; c < W; ++c) C1[c] = C2[c] = 0.0;
+#pragma unroll 4
+    for (int s = 0; s < ma.n; ++s) {
+        const int4 x = *reinterpret_cast<const int4 *>(u + s * plane);
+        const int p = ma.p[s], pv = (int)ma.pinv_prime[s];
+        const int us[W] = {mod_small(x.x, p, pv), mod_small(x.y, p, pv), mod_small(x.z, p, pv), mod_small(x.w, p, pv)};
+        const double s1 = ma.s1[s], s2 = ma.s2[s];
+#pragma unroll
+        for (int c = 0; c < W; ++c) {
+            C1[c] = fma(s1, (double)us[c], C1[c]);
+            C2[c] = fma(s2, (double)us[c], C2[c]);
+        }
+    }
+    EpilogueTail<OutT>(at, n, tA, tB, beta, C, ldc).store(C1, C2, ma, alpha, beta);
+}
+
+template <typename OutT, int N>
+hipError_t launch_epilogue_u8(const uint8_t *U, int64_t plane, int64_t Np, int64_t m, int64_t n, const int32_t *tA,
+                              const int32_t *tB, const ModArgs &ma, double alpha, double beta, OutT *C, int64_t ldc, int groups,
+                              unsigned blocks, hipStream_t stream) {
+    if constexpr (N <= kMaxModuli) {
+        if (ma.n != N)
+            return launch_epilogue_u8<OutT, N + 1>(U, plane, Np, m, n, tA, tB, ma, alpha, beta, C, ldc, groups, blocks, stream);
+        hipLaunchKernelGGL((k_epilogue<OutT, N>), dim3(blocks), dim3(256), 0, stream, U, plane, Np, m, n, tA, tB, ma, alpha, beta, C,
+                           ldc, groups, make_divisor(groups));
+        return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
 }
 
 template <typename OutT>
@@ -369,14 +401,25 @@ template <typename OutT>
 hipError_t launch_epilogue(const void *prod, bool prod_is_u8, int64_t Mp, int64_t Np, int64_t m,
                            int64_t n, const int32_t *tA, const int32_t *tB, const ModArgs &ma,
                            double alpha, double beta, OutT *C, int64_t ldc, hipStream_t stream) {
-    const int64_t threads = m * ((n + 3) / 4);
-    if (prod_is_u8)
-        hipLaunchKernelGGL((k_epilogue<OutT, true>), dim3(blocks_for(threads)), dim3(256), 0, stream,
-                           prod, Mp, Np, m, n, tA, tB, ma, alpha, beta, C, ldc);
-    else
-        hipLaunchKernelGGL((k_epilogue<OutT, false>), dim3(blocks_for(threads)), dim3(256), 0, stream,
-                           prod, Mp, Np, m, n, tA, tB, ma, alpha, beta, C, ldc);
-    return hipGetLastError();
+    const int64_t groups = (n + kEpilogueColumns - 1) / kEpilogueColumns, plane = Mp * Np;
+    if (groups > 0x3fffffff) return hipErrorInvalidValue;     // (a row of U of 4 GiB per modulus)
+    const int64_t rows = std::max<int64_t>(1, ((int64_t)0x7fffff00 - 256) / groups);   // of a launch: its thread numbers fit 31 bits
+    for (int64_t r = 0; r < m; r += rows) {
+        const int64_t count = std::min(rows, m - r);
+        const unsigned blocks = blocks_for(count * groups);
+        hipError_t e;
+        if (prod_is_u8) {
+            e = launch_epilogue_u8<OutT, OZ2_MIN_MODULI>(static_cast<const uint8_t *>(prod) + r * Np, plane, Np, count, n, tA + r, tB, ma,
+                                                         alpha, beta, C + r * ldc, ldc, (int)groups, blocks, stream);
+        } else {
+            hipLaunchKernelGGL((k_epilogue_i32<OutT>), dim3(blocks), dim3(256), 0, stream,
+                               static_cast<const int32_t *>(prod) + r * Np, plane, Np, count, n, tA + r, tB, ma, alpha, beta,
+                               C + r * ldc, ldc, (int)groups, make_divisor((int)groups));
+            e = hipGetLastError();
+        }
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 template <typename OutT>
