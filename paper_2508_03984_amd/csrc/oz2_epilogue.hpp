@@ -6,20 +6,30 @@
 
 namespace oz2 {
 
-// byte_mod_word on the device: with its share of the packing 4.75 vector instructions per entry, none of them a
-// 32-bit multiplication (the mulhi form of mod_small has two).  Measured for whole calls, mulhi form -> this one: 8192 x 8192 x
-// 512, N = 15, 1299 -> 1245 us; 4096 x 3072 x 2048 prepared 454 -> 435 us; 4096^3, N = 14, 1142 -> 1121 us; no
-// difference at 16384^3, where the store phase is 2 % of a tile.
-__device__ __forceinline__ uint32_t byte_mod_word_dev(int acc, const ByteMod &b) {
-    const uint32_t f = __builtin_amdgcn_udot4((uint32_t)acc, b.coef, b.base, false);
-    const float q = __builtin_fmaf(__builtin_bit_cast(float, f) - 8388608.0f, b.pinv, b.magic);
-    return (uint32_t)__mul24(__builtin_bit_cast(int, q), b.neg_p) + f;
-}
-
 // The low bytes of four words in one.
 __device__ __forceinline__ uint32_t pack_low_bytes(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3) {
     const uint32_t lo = __builtin_amdgcn_perm(w1, w0, 0x0c0c0400u), hi = __builtin_amdgcn_perm(w3, w2, 0x0c0c0400u);
     return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+}
+
+// byte_mod_word on the device, for four sums, whose residues come packed: 3.75 vector instructions per entry, none of them a
+// 32-bit multiplication (the mulhi form of mod_small has two).  All four v_dot4 first, because what reads the result of one has
+// to stay three instructions behind it.  Measured for whole calls, us, mulhi form -> this one with the dot product converted by a
+// subtraction: 8192 x 8192 x 512, N = 15, 1299 -> 1245; 4096 x 3072 x 2048 prepared 454 -> 435; then, prepared, without the
+// subtraction and without writing the accumulators before the first K tile: 8192 x 8192 x 128 623 -> 590, x 512 924 -> 904, 2048^3
+// N = 15 132.5 -> 129.7, 4096^3 N = 14 765 -> 757; no difference at 16384^3, where the store phase is 2 % of a tile.
+__device__ __forceinline__ uint32_t byte_mod_pack(int a0, int a1, int a2, int a3, const ByteMod &b) {
+    const int acc[4] = {a0, a1, a2, a3};
+    uint32_t f[4], w[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) f[c] = __builtin_amdgcn_udot4((uint32_t)acc[c], b.coef, b.base, false);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const float q = __builtin_fmaf(__builtin_bit_cast(float, f[c]), b.pinv, b.magic);
+        w[c] = (uint32_t)__mul24(__builtin_bit_cast(int, q), b.neg_p) + f[c];
+    }
+    return pack_low_bytes(w[0], w[1], w[2], w[3]);
 }
 
 template <typename OutT>

@@ -100,7 +100,7 @@ struct GemmMods {                       // moduli of the slices and what their r
     ByteMod byte_mod[kMaxModuli];       // reduction to bytes (uint8 forms)
 };
 
-// The uint8 forms start their accumulators at -2^31 (see oz2_bytemod.hpp), the others at 0.
+// The uint8 forms start their sums at -2^31 (see oz2_bytemod.hpp), the others at 0.
 constexpr int first_acc(int out) { return out == kOutU8 || out == kOutU8Fold ? (int)0x80000000 : 0; }
 
 // No memory access moves across this in the compiler (no instruction; the hardware issues in order).
@@ -207,7 +207,7 @@ struct GemmCore {
             if (t < KT) issue_loads<0, LPT>(src_tile + (int64_t)t * tile_step, t * STAGE_BYTES);
     }
 
-    // The K loop over a tile whose head has been requested: acc += A tile * B tile^T.
+    // The K loop over a tile whose head has been requested: acc = first + A tile * B tile^T.
     // It is written so that the instruction stream between the MFMAs stays as short as it can be:
     // the loop is split into iterations that prefetch (all but the last STAGES - 1) and ones that
     // do not, so there is no branch per load; the LDS stage offsets are carried along, not
@@ -216,8 +216,9 @@ struct GemmCore {
     // STORES: the vector stores that were issued after the head and before this call, if `stores` says so:
     // no fewer than that, or the relaxed wait below would pass K tiles that have not landed.
     template <int STORES = 0>
-    __device__ __forceinline__ void contract(const int8_t *src_tile, int KT, v4i (&acc)[FM][FN],
+    __device__ __forceinline__ void contract(const int8_t *src_tile, int KT, int first, v4i (&acc)[FM][FN],
                                              bool stores = false) const {
+        const v4i start = {first, first, first, first};
         v4i fa[2 * RB], fb[FN];
         const char *const lds_bytes = reinterpret_cast<const char *>(lds);
         auto load_a = [&](int stage_off, int i) {
@@ -251,8 +252,8 @@ struct GemmCore {
         // quarters of the MFMAs.
         int cur_off = 0;
         const int8_t *src_ld = src_tile + (int64_t)(STAGES - 1) * tile_step;
-        auto iteration = [&](auto issued_c, auto last_c, bool after_stores = false) {
-            constexpr bool issued = decltype(issued_c)::value, last = decltype(last_c)::value;
+        auto iteration = [&](auto opens_c, auto issued_c, auto last_c, bool after_stores = false) {
+            constexpr bool opens = decltype(opens_c)::value, issued = decltype(issued_c)::value, last = decltype(last_c)::value;
             const int nxt_off = cur_off + STAGE_BYTES == STAGES * STAGE_BYTES ? 0 : cur_off + STAGE_BYTES;
             const int ld_off = cur_off == 0 ? (STAGES - 1) * STAGE_BYTES : cur_off - STAGE_BYTES;
 #pragma unroll
@@ -262,7 +263,7 @@ struct GemmCore {
 #pragma unroll
                     for (int rr = 0; rr < RB; ++rr) {
                         const int i = p * RB + (j & 1 ? RB - 1 - rr : rr);   // a column starts with the row the last one ended with
-                        acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fb[j], fa[i % (2 * RB)], acc[i][j], 0, 0, 0);
+                        acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fb[j], fa[i % (2 * RB)], opens ? start : acc[i][j], 0, 0, 0);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                     if (p == NB - 1 && !last) load_b(nxt_off, j);
@@ -279,7 +280,7 @@ struct GemmCore {
             }
             // Tile kt + 2 must be complete (and visible to every wavefront) before iteration
             // kt + 1 prefetches fragments from it; the barrier also frees the stage just read.
-            if (issued && after_stores) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kYoungest + STORES));
+            if (STORES > 0 && issued && after_stores) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kYoungest + STORES));
             else if (issued) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kYoungest));
             else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
             __builtin_amdgcn_s_barrier();
@@ -288,10 +289,13 @@ struct GemmCore {
         };
         constexpr std::true_type yes{};
         constexpr std::false_type no{};
-        int kt = 0;
-        for (; kt + STAGES - 1 < KT; ++kt) iteration(yes, no, STORES > 0 && lenient && kt == 0);
-        for (; kt + 1 < KT; ++kt) iteration(no, no);
-        iteration(no, yes);
+        // The first K tile starts from `start` in every entry: no register of the accumulators is written beforehand.
+        if (KT >= STAGES) iteration(yes, yes, no, lenient);
+        else iteration(yes, no, no);
+        int kt = 1;
+        for (; kt + STAGES - 1 < KT; ++kt) iteration(no, yes, no);
+        for (; kt + 1 < KT; ++kt) iteration(no, no, no);
+        iteration(no, no, yes);
     }
 
     // Row and column maxima of the tile (kOutMax).  Entries are sums of products of non-negative
@@ -361,8 +365,7 @@ struct GemmCore {
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     const v4i &x = acc[i + g / FN][g % FN];
-                    d[g] = pack_low_bytes(byte_mod_word_dev(x[0], b), byte_mod_word_dev(x[1], b), byte_mod_word_dev(x[2], b),
-                                          byte_mod_word_dev(x[3], b));
+                    d[g] = byte_mod_pack(x[0], x[1], x[2], x[3], b);
                 }
                 // v_permlane32_swap(a, b): the upper half of a and the lower half of b change places;
                 // v_permlane16_swap(a, b): the odd quarters of a and the even quarters of b.
@@ -397,13 +400,6 @@ struct GemmCore {
                 *dst = v;
             }
     }
-
-    static __device__ __forceinline__ void fill(v4i (&acc)[FM][FN], int v) {
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-            for (int j = 0; j < FN; ++j) acc[i][j] = v4i{v, v, v, v};
-    }
 };
 
 // One workgroup per output tile.  For kOutMax the arguments mean: C = the row maxima of the
@@ -423,8 +419,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_int8_gemm(const int8_t *__rest
     const int8_t *src = core.tile_source(A, B, s, tile_r, tile_c, Mp, Np, KB, kb0);
     core.issue_head(src, KT);
     v4i acc[Core::FM][Core::FN];
-    Core::fill(acc, first_acc(OUT));
-    core.contract(src, KT, acc);
+    core.contract(src, KT, first_acc(OUT), acc);
     const int64_t bm = (int64_t)tile_r * Core::BM, bn = (int64_t)tile_c * Core::BN;
     if (OUT == kOutMax) {
         int *rmax = static_cast<int *>(C);
@@ -469,11 +464,10 @@ __global__ __launch_bounds__(64 * WM * WN) void k_int8_gemm_persistent(const int
             src_next = core.tile_source(A, B, s_next, tile_r_next, tile_c_next, Mp, Np, KB, kb0);
         }
         v4i acc[Core::FM][Core::FN];
-        Core::fill(acc, first_acc(OUT));
         // kStores: the number of store instructions of store<kOutU8>, one of 16 bytes per 32 x 32 block of a
         // wavefront.  (The fold forms also load what they add to, and wait for it themselves.)
         constexpr int kStores = OUT == kOutU8 ? TM * TN : 0;
-        core.template contract<kStores>(src, KT, acc, stores);
+        core.template contract<kStores>(src, KT, first_acc(OUT), acc, stores);
         // Every wavefront has passed the last barrier, so nothing reads the LDS stages any more:
         // the head of this workgroup's next tile is requested now and travels while the results
         // of this one are reduced and stored.

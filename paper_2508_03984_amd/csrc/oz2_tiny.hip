@@ -97,8 +97,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_tiny_product(const int8_t *__re
                     uint32_t d[4];
 #pragma unroll
                     for (int g = 0; g < 4; ++g)
-                        d[g] = pack_low_bytes(byte_mod_word_dev(acc[4 * g], bm), byte_mod_word_dev(acc[4 * g + 1], bm),
-                                              byte_mod_word_dev(acc[4 * g + 2], bm), byte_mod_word_dev(acc[4 * g + 3], bm));
+                        d[g] = byte_mod_pack(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3], bm);
                     const auto s0 = __builtin_amdgcn_permlane32_swap(d[0], d[2], false, false);
                     const auto s1 = __builtin_amdgcn_permlane32_swap(d[1], d[3], false, false);
                     const v4i q = v4i{(int)s0[0], (int)s0[1], (int)s1[0], (int)s1[1]};
