@@ -134,7 +134,7 @@ struct GemmCore {
     static_assert(CPR == 4, "the load-side swizzle below assumes one mask per lane");
     static_assert(STAGES >= 3 && (STAGES - 3) * LPT < 64, "vmcnt is a 6-bit counter");
     static constexpr int RB = 2, NB = FM / RB;                // blocks of rows that the K loop takes one after another
-    static_assert(FM % (2 * RB) == 0 && LPT >= 2 && LPT <= 4, "fragments of two blocks in turn; loads in two halves");
+    static_assert(FM % (2 * RB) == 0 && LPT >= 2 && LPT <= 4, "fragments of two blocks in turn");
     static_assert(FN == 2 || FN == 4, "the store phase transposes groups of four blocks");
 
     int wm, wn, lrow, lquad;
@@ -179,32 +179,27 @@ struct GemmCore {
         return (from_a ? Ab + (int64_t)row0 * BK : Bb + (int64_t)(row0 - BM) * BK) + ch * 16;
     }
 
-    // Loads [I0, I1) of the K tile whose loads start at src_t, into the stage at byte offset
-    // stage_off (uniform).  In assembly (nothing is returned to registers), because the compiler takes the
-    // builtin for one that may complete out of order with LDS reads, and then waits for all of those
-    // where the next of them is used.  M0, which is nobody else's in these kernels, takes one wait state before it is read.
-    template <int I0, int I1>
+    // The loads of the K tile that start at src_t, into the stage at byte offset stage_off (uniform).  In assembly
+    // (nothing is returned to registers), because the compiler takes the builtin for one that may complete out of
+    // order with LDS reads, and then waits for all of those where the next of them is used.  M0, which is
+    // nobody else's in these kernels, takes one wait state before it is read.
     __device__ __forceinline__ void issue_loads(const int8_t *src_t, int stage_off) const {
-        static_assert(I1 - I0 == 1 || I1 - I0 == 2 || I1 - I0 == 4, "");
+        static_assert(LPT == 2 || LPT == 4, "");
         const uint32_t dst = (uint32_t)(uintptr_t)(lds_ptr_t)lds + stage_off + my_dst;
-        if constexpr (I1 - I0 == 1)
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off offset:%2" ::"s"(dst), "v"(src_t),
-                         "n"(I0 * 1024) : "memory");
-        else if constexpr (I1 - I0 == 2)
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off offset:%2\n\t"
-                         "global_load_lds_dwordx4 %1, off offset:%3" ::"s"(dst), "v"(src_t), "n"(I0 * 1024),
-                         "n"(I0 * 1024 + 1024) : "memory");
-        else {
-            issue_loads<I0, I0 + 2>(src_t, stage_off);
-            issue_loads<I0 + 2, I1>(src_t, stage_off);
-        }
+        if constexpr (LPT == 2)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\t"
+                         "global_load_lds_dwordx4 %1, off offset:1024" ::"s"(dst), "v"(src_t) : "memory");
+        else
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\t"
+                         "global_load_lds_dwordx4 %1, off offset:1024\n\tglobal_load_lds_dwordx4 %1, off offset:2048\n\t"
+                         "global_load_lds_dwordx4 %1, off offset:3072" ::"s"(dst), "v"(src_t) : "memory");
     }
 
     // The first STAGES - 1 K tiles of a tile.  KT >= 2: every K range is a multiple of 128.
     __device__ __forceinline__ void issue_head(const int8_t *src_tile, int KT) const {
 #pragma unroll
         for (int t = 0; t < STAGES - 1; ++t)
-            if (t < KT) issue_loads<0, LPT>(src_tile + (int64_t)t * tile_step, t * STAGE_BYTES);
+            if (t < KT) issue_loads(src_tile + (int64_t)t * tile_step, t * STAGE_BYTES);
     }
 
     // The K loop over a tile whose head has been requested: acc = first + A tile * B tile^T.
@@ -248,8 +243,9 @@ struct GemmCore {
         // One K tile, in blocks of RB rows of MFMAs.  Behind a block the fragments of A of the block after the next one
         // are requested into its registers, and behind each column of the last block the next K tile's fragment of
         // B, so that LDS latency is covered by a block of MFMAs.  The K tile STAGES - 1 ahead is requested into the
-        // stage read during the previous iteration; its LPT loads go out in two halves, behind a quarter and three
-        // quarters of the MFMAs.
+        // stage read during the previous iteration, all of it behind a quarter of the MFMAs (prepared operands, us, at 1/8 | 1/4 |
+        // 1/2 | 3/4, and half at 1/4 and half at 3/4: 16384 x 8192 x 16384 N = 8 12420 | 12220 | 12460 | 12550, 12335; 8192^3 N = 8
+        // 3246 | 3200 | 3255 | 3280, 3222; the A tile at 1/4 and the B tile at 5/8 12725 and 3294).
         int cur_off = 0;
         const int8_t *src_ld = src_tile + (int64_t)(STAGES - 1) * tile_step;
         auto iteration = [&](auto opens_c, auto issued_c, auto last_c, bool after_stores = false) {
@@ -267,8 +263,7 @@ struct GemmCore {
                     }
                     __builtin_amdgcn_sched_barrier(0);
                     if (p == NB - 1 && !last) load_b(nxt_off, j);
-                    if (issued && p * FN + j == NB * FN / 4 - 1) issue_loads<0, LPT / 2>(src_ld, ld_off);
-                    if (issued && p * FN + j == 3 * NB * FN / 4 - 1) issue_loads<LPT / 2, LPT>(src_ld, ld_off);
+                    if (issued && p * FN + j == NB * FN * 3 / 16) issue_loads(src_ld, ld_off);
                     __builtin_amdgcn_sched_barrier(0);
                 }
 #pragma unroll
