@@ -50,7 +50,10 @@ inline bool fused_applies(int64_t Kp, bool k_contiguous) { return Kp <= (k_conti
 // columns of more than 1024 elements take 16 where they fit.  Measured (us, both factors, N = 15 in FP64): rows of 4096, 4096^2
 // each, 512 threads and 2 rows 148, 1024 threads and 8 rows 171 (several workgroups per compute
 // unit overlap one's loads with another's stores); columns of 2048, 2048^2 each, 16 per workgroup 42, 8 52;
-// columns of 1024, 1024^2 each, 8 per workgroup 16.8, 16 21.4.
+// columns of 1024, 1024^2 each, 8 per workgroup 16.8, 16 21.4.  Columns of up to 1024 in FP64 go by 4 while the launch has
+// few workgroups, two of which then overlap on a compute unit (conversion stage, N = 15, us, by 8 | by 4: 1024 x 1024 x 1024 21.7 |
+// 20.4, 1500 x 1500 x 1000 25.2 | 23.7, 2500 x 2500 x 1024 41.2 | 37.8; 4096 x 4096 x 1024 53.0 | 54.1, 8192 x 8192 x 512 46.4 | 47.6;
+// FP32, whose segments would be 16 bytes, 1024 x 1024 x 1024 N = 8 21.8 | 22.4).
 // Beyond 2048 a strip of 8 columns fills a compute unit, and the launch runs in rounds of 256 strips; of strips of
 // 4 two or three are resident.  Those are read less well, so they are taken where they save more than their price in the last
 // round (1500 + 1111 columns of 3001: 71 -> 40 us).  The prices, 1.1 in FP64 and 1.3 in FP32, are on the safe side of what long
@@ -64,7 +67,7 @@ inline bool fused_applies(int64_t Kp, bool k_contiguous) { return Kp <= (k_conti
 // vectors: padded number of vectors in the launch.
 inline FusedPlan fused_plan(int64_t Kp, bool strips, int64_t vectors, size_t element) {
     static const int shapes[][2] = {{256, 1}, {512, 1}, {512, 2}, {512, 3}, {512, 4}, {1024, 3}, {1024, 4}};
-    int64_t per = strips ? (Kp <= 1024 ? 8 : 16) : (Kp <= 1024 ? 4 : 2);
+    int64_t per = strips ? (Kp <= 1024 ? (element == 8 && vectors <= 6144 ? 4 : 8) : 16) : (Kp <= 1024 ? 4 : 2);
     if (strips && Kp > 2048) {
         const int64_t resident = 4 * Kp <= 512 * 3 * 8 ? 3 : 2;
         const double by8 = (double)((vectors / 8 + 255) / 256) * 8;
