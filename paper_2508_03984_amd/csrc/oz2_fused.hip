@@ -44,7 +44,8 @@ struct Side {
     unsigned blocks;            // workgroups of this side
 };
 
-template <typename T, int THREADS, int CH, int ROUNDS, int KIND>
+// SPLIT: workgroup row y of the launch produces the moduli of group y only.
+template <typename T, int THREADS, int CH, int ROUNDS, int KIND, bool SPLIT>
 __global__ __launch_bounds__(THREADS) void k_convert(Side<T> a, Side<T> b, ShiftArgs sa, ModArgs ma) {
     __shared__ T tile[THREADS * 9];                                   // one piece per thread, padded (columns only)
     __shared__ unsigned long long red_max[1 << kMaxLogV], red_sum[1 << kMaxLogV];
@@ -187,7 +188,7 @@ __global__ __launch_bounds__(THREADS) void k_convert(Side<T> a, Side<T> b, Shift
     if (leader) atomicAdd(&red_sum[vec], (unsigned long long)part);
     __syncthreads();
     const int t = mx ? shift_exponent(red_sum[vec], sa) - e : 0;
-    if (writes) s.t[v0 + vec] = t;
+    if (writes && (!SPLIT || blockIdx.y == 0)) s.t[v0 + vec] = t;
 
     const int64_t plane = s.vecs_pad * s.len_pad;
 #pragma unroll
@@ -198,7 +199,8 @@ __global__ __launch_bounds__(THREADS) void k_convert(Side<T> a, Side<T> b, Shift
         double v[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) v[i] = trunc(ldexp(x[c][i], t));
-        for (int s0 = 0; s0 < ma.n; s0 += kModGroup) {
+        const int first = SPLIT ? (int)blockIdx.y * kModGroup : 0, end = SPLIT ? first + 1 : ma.n;
+        for (int s0 = first; s0 < end; s0 += kModGroup) {
             ResidueInput in;
 #pragma unroll
             for (int i = 0; i < 8; ++i)
@@ -234,10 +236,28 @@ hipError_t launch_kind(const FusedFactor<T> &A, const FusedFactor<T> &B, const S
     }
     const FusedPlan plan = fused_plan(Kp, strips, (A.X ? A.vecs_pad : 0) + (B.X ? B.vecs_pad : 0), sizeof(T));
     const Side<T> a = side_of(A, plan), b = side_of(B, plan);
-    const dim3 grid(a.blocks + b.blocks);
+    // The smallest launches leave compute units idle while each thread walks through all moduli: where there is one for
+    // each, every group of moduli gets workgroups of its own, which read the operands again, from the caches (whole calls
+    // repeated in a graph, other operands in each, us: 256^3 N = 14 13.1 -> 12.0, 64^3 N = 15 12.5 -> 11.4, 200^3 N = 15 14.7 -> 13.6).
+    const unsigned blocks = a.blocks + b.blocks, groups = (unsigned)((ma.n + kModGroup - 1) / kModGroup);
+    if constexpr (KIND == 0) {
+        if (groups > 1 && blocks * groups <= 256) {
+            const dim3 grid(blocks, groups);
+#define OZ2_CONVERT_SPLIT(THREADS, CH)                                                                        \
+    if (plan.threads == THREADS && plan.pieces == CH) {                                                       \
+        hipLaunchKernelGGL((k_convert<T, THREADS, CH, ROUNDS, KIND, true>), grid, dim3(THREADS), 0, stream, a, b, sa, ma); \
+        return hipGetLastError();                                                                             \
+    }
+            OZ2_CONVERT_SPLIT(256, 1) OZ2_CONVERT_SPLIT(512, 1) OZ2_CONVERT_SPLIT(512, 2) OZ2_CONVERT_SPLIT(512, 3)
+            OZ2_CONVERT_SPLIT(512, 4) OZ2_CONVERT_SPLIT(1024, 3) OZ2_CONVERT_SPLIT(1024, 4)
+#undef OZ2_CONVERT_SPLIT
+            return hipErrorInvalidValue;
+        }
+    }
+    const dim3 grid(blocks);
 #define OZ2_CONVERT(THREADS, CH)                                                                              \
     if (plan.threads == THREADS && plan.pieces == CH) {                                                       \
-        hipLaunchKernelGGL((k_convert<T, THREADS, CH, ROUNDS, KIND>), grid, dim3(THREADS), 0, stream, a, b, sa, ma); \
+        hipLaunchKernelGGL((k_convert<T, THREADS, CH, ROUNDS, KIND, false>), grid, dim3(THREADS), 0, stream, a, b, sa, ma); \
         return hipGetLastError();                                                                             \
     }
     OZ2_CONVERT(256, 1) OZ2_CONVERT(512, 1) OZ2_CONVERT(512, 2) OZ2_CONVERT(512, 3) OZ2_CONVERT(512, 4)
