@@ -32,6 +32,18 @@ __device__ __forceinline__ uint32_t byte_mod_pack(int a0, int a1, int a2, int a3
     return pack_low_bytes(w[0], w[1], w[2], w[3]);
 }
 
+// The 4 x 4 transposition of words among the lanes l, l + 16, l + 32 and l + 48 (quarters 0 to 3): quarter q gets the four
+// quarters' d[q], in ascending order.  v_permlane32_swap(a, b): the upper half of a and the lower half of b change places;
+// v_permlane16_swap(a, b): the odd quarters of a and the even quarters of b.
+typedef int exchanged_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ exchanged_t exchange_quarters(const uint32_t (&d)[4]) {
+    const auto s02 = __builtin_amdgcn_permlane32_swap(d[0], d[2], false, false);
+    const auto s13 = __builtin_amdgcn_permlane32_swap(d[1], d[3], false, false);
+    const auto lo = __builtin_amdgcn_permlane16_swap(s02[0], s13[0], false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(s02[1], s13[1], false, false);
+    return exchanged_t{(int)lo[0], (int)lo[1], (int)hi[0], (int)hi[1]};
+}
+
 template <typename OutT>
 __device__ inline OutT finish(double c, double alpha, double beta, const OutT *Cin) {
     double r;

@@ -362,13 +362,7 @@ struct GemmCore {
                     const v4i &x = acc[i + g / FN][g % FN];
                     d[g] = byte_mod_pack(x[0], x[1], x[2], x[3], b);
                 }
-                // v_permlane32_swap(a, b): the upper half of a and the lower half of b change places;
-                // v_permlane16_swap(a, b): the odd quarters of a and the even quarters of b.
-                const auto s02 = __builtin_amdgcn_permlane32_swap(d[0], d[2], false, false);
-                const auto s13 = __builtin_amdgcn_permlane32_swap(d[1], d[3], false, false);
-                const auto lo = __builtin_amdgcn_permlane16_swap(s02[0], s13[0], false, false);
-                const auto hi = __builtin_amdgcn_permlane16_swap(s02[1], s13[1], false, false);
-                v4i q = v4i{(int)lo[0], (int)lo[1], (int)hi[0], (int)hi[1]};
+                v4i q = exchange_quarters(d);
                 v4i *dst = reinterpret_cast<v4i *>(dst0 + (int64_t)(i * 16) * c_ld);
                 if (OUT == kOutU8Fold) {                   // a further K range: (old + new) mod p_s, byte by byte
                     const v4i old = *dst;

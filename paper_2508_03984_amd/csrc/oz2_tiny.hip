@@ -1,10 +1,13 @@
 // Algorithm 1 lines 6-12 in one launch for the smallest products: the INT8 GEMMs of all moduli, U_s and
-// the accumulation.  A workgroup owns a 32 x 32 tile of C; its 16 wavefronts take the moduli in turn, load
+// the accumulation.  A workgroup owns a 16 x 16 or 32 x 32 tile of C; its 16 wavefronts take the moduli in turn, load
 // their operands straight from the residue slices (no LDS: nothing is shared between moduli), keep
 // U_s in LDS for the accumulation and write it to the product buffer as the general form does.
 //
-// Bound: a launch, the way of the first operands, and then the loads of a compute unit, 64 Kp N bytes at
-// about 64 bytes per clock.  tiny_product_applies (oz2_plan.hpp) draws the line and says what it measured.
+// Bound: a launch, the way of the first operands, and then the loads of a compute unit, 32 Kp N or 64 Kp N bytes at
+// about 60 bytes per clock.  tiny_product_applies (oz2_plan.hpp) draws the line and says what it measured.
+#include <algorithm>
+#include <type_traits>
+
 #include "oz2_bytemod.hpp"
 #include "oz2_convert.hpp"
 #include "oz2_epilogue.hpp"
@@ -15,32 +18,33 @@ namespace oz2 {
 namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
 
-constexpr int kTile = 32, kWaves = 16;
-constexpr int kChunk = 128;              // elements of k loaded at a time: four MFMA K steps, 32 registers
-constexpr int kFlight = 2;               // chunks on the way per wavefront
+constexpr int kWaves = 16;
+constexpr int kChunk = 128;              // elements of k loaded at a time: two MFMA K steps
 
 struct TinyMods {
     ByteMod byte_mod[kMaxModuli];
 };
 
-template <typename OutT>
+template <typename OutT, int BLOCKS>
 __global__ __launch_bounds__(64 * kWaves) void k_tiny_product(const int8_t *__restrict__ A, const int8_t *__restrict__ B,
                                                                  uint8_t *__restrict__ U, int64_t Mp, int64_t Np,
                                                                  int64_t Kp, int64_t m, int64_t n,
                                                                  const int32_t *__restrict__ tA,
                                                                  const int32_t *__restrict__ tB, ModArgs ma, TinyMods tm,
                                                                  double alpha, double beta, OutT *C, int64_t ldc,
-                                                                 int tiles_n, Divisor by_tiles_n, int tiles) {
-    __shared__ v4i u_lds[kMaxModuli][kTile][kTile / 16];
+                                                                 int tiles_n, Divisor by_tiles_n, int tiles, int tiles_short,
+                                                                 Divisor by_short) {
+    constexpr int kTile = 16 * BLOCKS;                        // BLOCKS x BLOCKS blocks of 16 x 16
+    constexpr int kFlight = 4 / BLOCKS;                       // chunks on the way per wavefront: 16 loads
+    __shared__ v4i u_lds[kMaxModuli][kTile][BLOCKS];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int lrow = lane & 31, lhalf = lane >> 5;
+    const int lrow = lane & 15, lquad = lane >> 4;
     // All of the arguments that the way to the first loads needs are requested before any branch: one wait for the
     // argument buffer instead of three (256^3 prepared, N = 14, other operands in
     // each call: 9.0 -> 8.7 us).
     asm volatile("" ::"s"(A), "s"(B), "s"(U), "s"(Mp), "s"(Np), "s"(Kp), "s"(m), "s"(tA), "s"(tB), "s"(ma.n), "s"(tiles_n),
-                 "s"(by_tiles_n.mul), "s"(by_tiles_n.shift), "s"(tiles));
+                 "s"(by_short.mul), "s"(by_short.shift), "s"(tiles), "s"(tiles_short));
     const int64_t plane = Mp * Np;
     if ((int)blockIdx.x >= tiles) {
         // Padding of U, zero as from the products of zero residues: 32 rows of a block of 256 columns, all planes.  First
@@ -52,36 +56,53 @@ __global__ __launch_bounds__(64 * kWaves) void k_tiny_product(const int8_t *__re
         const bool right = id < beside;
         const int row = right ? id : tiles_m + (id - beside) / columns, block = right ? columns - 1 : (id - beside) % columns;
         const int64_t col = (int64_t)block * kPadMN + (tid & 15) * 16;
-        uint8_t *const u = U + ((int64_t)row * kTile + (tid >> 4 & 31)) * Np + col;
+        uint8_t *const u = U + ((int64_t)row * kTile + (tid >> 4) % kTile) * Np + col;
         if (!right || col >= live)
-            for (int s = tid >> 9; s < ma.n; s += 2) *reinterpret_cast<v4i *>(u + s * plane) = v4i{0, 0, 0, 0};
+            for (int s = (tid >> 4) / kTile; s < ma.n; s += kWaves * 4 / kTile) *reinterpret_cast<v4i *>(u + s * plane) = v4i{0, 0, 0, 0};
         return;
     }
-    const int tile_r = divide((int)blockIdx.x, by_tiles_n), tile_c = (int)blockIdx.x - tile_r * tiles_n;
+    // Ids are dealt to the 8 XCDs round-robin: each XCD gets consecutive tiles across the shorter side of C, so that a row of the
+    // longer factor is fetched by one XCD (64 x 1000 x 256, N = 15: 14.7 us for the call, 18.2 with tiles along the longer side, 16.0
+    // with neighbouring tiles on different XCDs).
+    const int xcd = (int)blockIdx.x & 7, more = tiles & 7;
+    const int id = xcd * (tiles >> 3) + (xcd < more ? xcd : more) + ((int)blockIdx.x >> 3);
+    const int line = divide(id, by_short), at = id - line * tiles_short;
+    const int tile_r = tiles_short == tiles_n ? line : at, tile_c = tiles_short == tiles_n ? at : line;
     const int64_t row0 = (int64_t)tile_r * kTile, col0 = (int64_t)tile_c * kTile;
-    uint8_t *const u_out = U + (row0 + lrow) * Np + col0 + 16 * lhalf;
+    // Where this lane's 16 bytes (BLOCKS 1: 4 bytes) of a modulus go in the tile: see the exchange below
+    const int u_row = BLOCKS == 2 ? 16 * (lquad >> 1) + lrow : lrow, u_col = BLOCKS == 2 ? 16 * (lquad & 1) : 4 * lquad;
+    uint8_t *const u_out = U + (row0 + u_row) * Np + col0 + u_col;
 
-    // Chunk number c of this wavefront: modulus wave + 16 (c / chunks), elements 128 (c % chunks) ...
+    // Chunk number c of this wavefront: modulus wave + 16 (c / chunks), elements 128 (c % chunks) ...  Lane l holds
+    // row l % 16 of a block of 16 rows and 16 consecutive k of the K block's 64, number l / 16.
     const int chunks = (int)(Kp / kChunk), total = (ma.n - wave + kWaves - 1) / kWaves * chunks;
-    const int8_t *pa = A + (row0 + lrow) * kBlockK + lhalf * 16, *pb = B + (col0 + lrow) * kBlockK + lhalf * 16;
-    v4i fa[kFlight][4], fb[kFlight][4];
+    const int8_t *pa = A + (row0 + lrow) * kBlockK + lquad * 16, *pb = B + (col0 + lrow) * kBlockK + lquad * 16;
+    v4i fa[kFlight][2][BLOCKS], fb[kFlight][2][BLOCKS];
     auto load = [&](int buf, int c) {
         const int64_t s = wave + (int64_t)kWaves * (c / chunks), kb = 2 * (int64_t)(c % chunks);
         const int8_t *a = pa + (s * (Kp / kBlockK) + kb) * Mp * kBlockK, *b = pb + (s * (Kp / kBlockK) + kb) * Np * kBlockK;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            fa[buf][i] = *reinterpret_cast<const v4i *>(a + (i >> 1) * Mp * kBlockK + (i & 1) * 32);
-            fb[buf][i] = *reinterpret_cast<const v4i *>(b + (i >> 1) * Np * kBlockK + (i & 1) * 32);
-        }
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int i = 0; i < BLOCKS; ++i) {
+                fa[buf][h][i] = *reinterpret_cast<const v4i *>(a + (h * Mp + i * 16) * kBlockK);
+                fb[buf][h][i] = *reinterpret_cast<const v4i *>(b + (h * Np + i * 16) * kBlockK);
+            }
     };
     if (total > 0) {
         // (indices beyond the last chunk load it again: no branch around a load)
 #pragma unroll
         for (int b = 0; b < kFlight; ++b) load(b, b < total ? b : total - 1);
-        v16i acc;
+        const v4i start = {(int)0x80000000, (int)0x80000000, (int)0x80000000, (int)0x80000000};
+        v4i acc[BLOCKS][BLOCKS];
         int left = chunks, s = wave;                        // chunks left of the current modulus
+        auto restart = [&] {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = (int)0x80000000;
+            for (int i = 0; i < BLOCKS; ++i)
+#pragma unroll
+                for (int j = 0; j < BLOCKS; ++j) acc[i][j] = start;
+        };
+        restart();
         for (int c0 = 0; c0 < total; c0 += kFlight) {
             const bool more = c0 + kFlight < total;
 #pragma unroll
@@ -89,38 +110,49 @@ __global__ __launch_bounds__(64 * kWaves) void k_tiny_product(const int8_t *__re
                 const int c = c0 + b;
                 if (c >= total) break;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[b][i], fa[b][i], acc, 0, 0, 0);
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int i = 0; i < BLOCKS; ++i)
+#pragma unroll
+                        for (int j = 0; j < BLOCKS; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fb[b][h][j], fa[b][h][i], acc[i][j], 0, 0, 0);
                 if (more) load(b, c + kFlight < total ? c + kFlight : total - 1);
                 if (--left == 0) {
-                    // lane l holds row l % 32 and columns 8 g + 4 (l / 32) + {0..3} of the tile (as in GemmCore::store)
+                    // lane l holds row l % 16 and columns 4 (l / 16) + {0..3} of each block (as in GemmCore::store)
                     const ByteMod bm = tm.byte_mod[s];
                     uint32_t d[4];
 #pragma unroll
-                    for (int g = 0; g < 4; ++g)
-                        d[g] = byte_mod_pack(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3], bm);
-                    const auto s0 = __builtin_amdgcn_permlane32_swap(d[0], d[2], false, false);
-                    const auto s1 = __builtin_amdgcn_permlane32_swap(d[1], d[3], false, false);
-                    const v4i q = v4i{(int)s0[0], (int)s0[1], (int)s1[0], (int)s1[1]};
-                    u_lds[s][lrow][lhalf] = q;
-                    *reinterpret_cast<v4i *>(u_out + s * plane) = q;
+                    for (int g = 0; g < BLOCKS * BLOCKS; ++g) {
+                        const v4i &x = acc[g / BLOCKS][g % BLOCKS];
+                        d[g] = byte_mod_pack(x[0], x[1], x[2], x[3], bm);
+                    }
+                    uint8_t *const u = reinterpret_cast<uint8_t *>(&u_lds[s][u_row][0]) + u_col;
+                    if constexpr (BLOCKS == 2) {
+                        const v4i q = exchange_quarters(d);
+                        *reinterpret_cast<v4i *>(u) = q;
+                        *reinterpret_cast<v4i *>(u_out + s * plane) = q;
+                    } else {
+                        *reinterpret_cast<uint32_t *>(u) = d[0];
+                        *reinterpret_cast<uint32_t *>(u_out + s * plane) = d[0];
+                    }
                     s += kWaves;
                     left = chunks;
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[r] = (int)0x80000000;
+                    restart();
                 }
             }
         }
     }
     // what the accumulation needs from memory travels meanwhile
-    const int r = tid >> 5, c = tid & 31;
+    const int r = tid / kTile, c = tid % kTile;             // (threads beyond the tile's entries: below)
     const int64_t i = row0 + r, j = col0 + c;
-    const int shift = (i < m ? tA[i] : 0) + (j < n ? tB[j] : 0);
+    const int shift = (r < kTile && i < m ? tA[i] : 0) + (j < n ? tB[j] : 0);
     __syncthreads();
 
     // Accumulation: one entry per thread, moduli in ascending order.  Also in the lanes beyond C: FP64 instructions of a
     // wavefront with 16 lanes or fewer at work take longer (128 x 100 x 64, N = 15: 10.6 us with 4 columns' lanes alone
     // in the last tile, 7.3 us with all, as for 128 columns).
-    if (row0 + 2 * wave >= m) return;                       // both rows of the wavefront
+    const int wave_row = wave * (64 / kTile);               // its first row
+    if (wave_row >= kTile || row0 + wave_row >= m) return;
     const uint8_t *u = reinterpret_cast<const uint8_t *>(&u_lds[0][r][0]) + c;
     double C1 = 0.0, C2 = 0.0;
     for (int s0 = 0; s0 < ma.n; s0 += kModGroup) {          // the constants and bytes of a group requested together
@@ -152,11 +184,23 @@ hipError_t launch_tiny_product(const int8_t *A, const int8_t *B, uint8_t *U, int
                                double alpha, double beta, OutT *C, int64_t ldc, hipStream_t stream) {
     TinyMods tm{};
     for (int i = 0; i < ma.n; ++i) tm.byte_mod[i] = make_byte_mod(ma.p[i]);
-    const int tiles_m = (int)((m + kTile - 1) / kTile), tiles_n = (int)((n + kTile - 1) / kTile), tiles = tiles_m * tiles_n;
-    const int64_t padding = (Mp / kTile - tiles_m) * (Np / kPadMN) + (Np > (int64_t)tiles_n * kTile ? tiles_m : 0);
-    hipLaunchKernelGGL((k_tiny_product<OutT>), dim3((unsigned)(tiles + padding)), dim3(64 * kWaves), 0, stream, A, B, U, Mp, Np,
-                       Kp, m, n, tA, tB, ma, tm, alpha, beta, C, ldc, tiles_n, make_divisor(tiles_n), tiles);
-    return hipGetLastError();
+    struct Grid { int tiles_n, tiles; int64_t padding; };
+    auto grid_of = [&](int tile) {
+        const int tiles_m = (int)((m + tile - 1) / tile), tiles_n = (int)((n + tile - 1) / tile);
+        return Grid{tiles_n, tiles_m * tiles_n, (Mp / tile - tiles_m) * (Np / kPadMN) + (Np > (int64_t)tiles_n * tile ? tiles_m : 0)};
+    };
+    auto go = [&](auto blocks, const Grid &g) {
+        hipLaunchKernelGGL((k_tiny_product<OutT, decltype(blocks)::value>), dim3((unsigned)(g.tiles + g.padding)), dim3(64 * kWaves), 0,
+                           stream, A, B, U, Mp, Np, Kp, m, n, tA, tB, ma, tm, alpha, beta, C, ldc, g.tiles_n, make_divisor(g.tiles_n),
+                           g.tiles, std::min(g.tiles_n, g.tiles / g.tiles_n), make_divisor(std::min(g.tiles_n, g.tiles / g.tiles_n)));
+        return hipGetLastError();
+    };
+    // Tiles of 16 x 16 where these and the padding have a compute unit each: four times as many units fetch operands and
+    // accumulate (whole calls repeated in a graph, other operands in each, us, 32 x 32 | 16 x 16: 256^3 N = 14 13.0 | 12.1, 200^3
+    // N = 15 14.2 | 13.6, 128^3 N = 14 12.5 | 11.5, 256 x 256 x 512 FP32 N = 6 11.6 | 10.1).
+    const Grid small = grid_of(16);
+    if (small.tiles + small.padding <= 256) return go(std::integral_constant<int, 1>{}, small);
+    return go(std::integral_constant<int, 2>{}, grid_of(32));
 }
 
 #define OZ2_INSTANTIATE_TINY(T)                                                                                   \
