@@ -541,7 +541,7 @@ hipError_t launch(const int8_t *A, const int8_t *B, void *C, int batch, int64_t 
 }
 
 // Problems of fewer than 128 large tiles: 128 x 128 tiles, so that more workgroups exist.  Up to 256 of them
-// have a compute unit each: 8 wavefronts and 6 stages there; of more, two share one.  Measured, 4 wavefronts and 4 stages | 4 and 6 |
+// have a compute unit each: 8 wavefronts and 6 stages there; of more, two share one.  Measured with 32x32x32 MFMAs, 4 wavefronts and 4 stages | 4 and 6 |
 // 8 and 6, us, prepared operands, others in each call: 500 x 300 x 777 FP32 N = 8 12.0 | 11.5 | 11.6; N = 15, 256 x 256 x 1024
 // 13.5 | 12.7 | 12.8, 512 x 512 x 2048 22.5 | 19.5 | 19.8; accurate mode 512^3 N = 15 (whole call, the one slice of Cbar)
 // - | 40.6 | 37.7.  (The same operands again and again stay in the L2s: 4 and 4 is then 0.1 to 0.4 us faster up to k of about 2500.)

@@ -240,7 +240,7 @@ inline int64_t launch_k_len(int64_t Kp, int N, const Panels &Q) {
 
 // The smallest products run their GEMMs and the accumulation as one launch (oz2_tiny.hip): at most one 32 x 32
 // tile of C per compute unit, at most 512 elements of k in a row for a wavefront (each of the 16 takes every
-// 16th modulus), and few enough operands for a compute unit to load (64 Kp N bytes).  Measured on the GPU, two launches | one,
+// 16th modulus), and few enough operands for a compute unit to load (64 Kp N bytes).  Measured on the GPU with tiles of 32 x 32 only, two launches | one,
 // us, other operands in each call; prepared operands: 256^3 N = 15 9.5 | 8.9, 1000 x 250 x 256 N = 15 12.1 | 10.6, 400 x 400 x 384
 // FP32 N = 8 9.3 | 9.1, not taken 100 x 100 x 512 N = 15 11.0 | 11.8, 512^3 N = 15 13.0 | 13.4; whole calls: 256^3 N = 15 14.9 | 14.1,
 // 256 x 256 x 128 FP32 N = 6 11.4 | 9.3, 1000 x 250 x 256 18.7 | 18.7, and with more than about 64 tiles 400 x 400 x 256 N = 15
