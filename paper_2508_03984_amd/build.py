@@ -23,12 +23,19 @@ FLAGS = [
     "-mllvm", "-amdgpu-mfma-vgpr-form",        # accumulators in plain VGPRs: the store phase reads them without copies
     "-Wall", "-Wno-unused-function",
 ]
+# After any extra flags: the reduction of sums to bytes (csrc/oz2_bytemod.hpp) computes with subnormal binary32 numbers, and
+# kernels that flush them to zero would return wrong residues.
+LAST_FLAGS = ["-fno-gpu-flush-denormals-to-zero", "-Xclang", "-fdenormal-fp-math-f32=ieee"]
+
+
+def compile_flags() -> list:
+    extra = os.environ.get("OZ2_EXTRA_HIPCC_FLAGS", "").split()      # for experiments
+    return FLAGS + extra + LAST_FLAGS
 
 
 def build_library(verbose: bool = False) -> str:
     """Compile every source for gfx950 and link liboz2.so; always rebuilds."""
-    extra = os.environ.get("OZ2_EXTRA_HIPCC_FLAGS", "").split()      # for experiments
-    cmd = [HIPCC] + FLAGS + extra + ["-x", "hip"] + [os.path.join(CSRC, s) for s in SOURCES] + ["-o", LIB]
+    cmd = [HIPCC] + compile_flags() + ["-x", "hip"] + [os.path.join(CSRC, s) for s in SOURCES] + ["-o", LIB]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
