@@ -248,7 +248,7 @@ struct EpilogueTail {
         if (vector) {
 #pragma unroll
             for (int c = 0; c < W; ++c) {
-                const OutT before = old[c / kVec][c % kVec];  // (read if beta is not 0)
+                const OutT before = beta != 0.0 ? old[c / kVec][c % kVec] : OutT(0);
                 old[c / kVec][c % kVec] = crt_entry<OutT>(C1[c], C2[c], shift[c], ma, alpha, beta, &before);
             }
 #pragma unroll
