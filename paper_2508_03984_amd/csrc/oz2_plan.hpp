@@ -250,6 +250,16 @@ inline bool tiny_product_applies(int64_t m, int64_t n, int64_t Kp, int N) {
     return (m + 31) / 32 * ((n + 31) / 32) <= 256 && (N + 15) / 16 * Kp <= 512 && Kp * N <= 4096;
 }
 
+// The accumulation gives each thread kEpilogueColumns consecutive columns of a row, in workgroups of kEpilogueThreads, and works
+// out a thread's place from its number in 31 bits: a launch covers at most this many rows (0: a row of U that takes
+// 4 GiB per modulus, which is refused).
+constexpr int kEpilogueColumns = 4, kEpilogueThreads = 256;
+constexpr int64_t kEpilogueMaxThreads = (int64_t)0x7fffff00;     // whole workgroups below 2^31
+inline int64_t epilogue_groups(int64_t n) { return (n + kEpilogueColumns - 1) / kEpilogueColumns; }
+inline int64_t epilogue_rows(int64_t groups, int64_t max_threads = kEpilogueMaxThreads) {
+    return groups > 0x3fffffff ? 0 : max_threads / groups;
+}
+
 // Side of a panel of the overlapped form: the INT8 GEMM loses nothing down to 4096 x 4096.
 constexpr int64_t kOverlapPanel = 4096;
 

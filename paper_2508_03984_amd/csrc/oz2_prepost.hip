@@ -207,15 +207,13 @@ __global__ __launch_bounds__(THREADS) void k_shifts_cached(const T *__restrict__
 // One thread per 4 consecutive columns: one 4-byte (uint8 input) or 16-byte (int32 input) load
 // per modulus; 8 columns per thread measured slower (2.4 against 1.9 ms at 16384^2, N = 16).
 // ----------------------------------------------------------------------------------------
-constexpr int kEpilogueColumns = 4;
-
 // A thread's place: row i of C and its first column, by a 32-bit division that is a multiplication: a 64-bit
 // division and its remainder took about a quarter of a thread's vector instructions.
 struct EpiloguePlace {
     int64_t i, j0;
     bool valid;
     __device__ __forceinline__ EpiloguePlace(int64_t m, int groups, Divisor by_groups) {
-        const int idx = (int)(blockIdx.x * 256 + threadIdx.x), row = divide(idx, by_groups);
+        const int idx = (int)(blockIdx.x * kEpilogueThreads + threadIdx.x), row = divide(idx, by_groups);
         i = row; j0 = (int64_t)(idx - row * groups) * kEpilogueColumns;
         valid = row < m;
     }
@@ -265,7 +263,7 @@ struct EpilogueTail {
 // for large C (8192^2, N = 15, beta = 1: 389 us, 5.3 TB/s).  With groups of 8, 4, 2 and 1 moduli that waited for their loads, C
 // read at the end and 64-bit divisions it took 450 us; 4096^2, N = 14, 76 -> 68; 2048^2, N = 15, 20.8 -> 18.8; 1024^2 8.5 -> 7.2.
 template <typename OutT, int N>
-__global__ __launch_bounds__(256) void k_epilogue(const uint8_t *__restrict__ U, int64_t plane, int64_t Np, int64_t m, int64_t n,
+__global__ __launch_bounds__(kEpilogueThreads) void k_epilogue(const uint8_t *__restrict__ U, int64_t plane, int64_t Np, int64_t m, int64_t n,
                                                   const int32_t *__restrict__ tA, const int32_t *__restrict__ tB, ModArgs ma,
                                                   double alpha, double beta, OutT *C, int64_t ldc, int groups, Divisor by_groups) {
     constexpr int W = kEpilogueColumns;
@@ -295,7 +293,7 @@ __global__ __launch_bounds__(256) void k_epilogue(const uint8_t *__restrict__ U,
 
 // The form for int32 sums (possibly folded partial sums), which are reduced here.
 template <typename OutT>
-__global__ __launch_bounds__(256) void k_epilogue_i32(const int32_t *__restrict__ prod, int64_t plane, int64_t Np, int64_t m,
+__global__ __launch_bounds__(kEpilogueThreads) void k_epilogue_i32(const int32_t *__restrict__ prod, int64_t plane, int64_t Np, int64_t m,
                                                       int64_t n, const int32_t *__restrict__ tA,
                                                       const int32_t *__restrict__ tB, ModArgs ma, double alpha, double beta,
                                                       OutT *C, int64_t ldc, int groups, Divisor by_groups) {
@@ -328,7 +326,7 @@ hipError_t launch_epilogue_u8(const uint8_t *U, int64_t plane, int64_t Np, int64
     if constexpr (N <= kMaxModuli) {
         if (ma.n != N)
             return launch_epilogue_u8<OutT, N + 1>(U, plane, Np, m, n, tA, tB, ma, alpha, beta, C, ldc, groups, blocks, stream);
-        hipLaunchKernelGGL((k_epilogue<OutT, N>), dim3(blocks), dim3(256), 0, stream, U, plane, Np, m, n, tA, tB, ma, alpha, beta, C,
+        hipLaunchKernelGGL((k_epilogue<OutT, N>), dim3(blocks), dim3(kEpilogueThreads), 0, stream, U, plane, Np, m, n, tA, tB, ma, alpha, beta, C,
                            ldc, groups, make_divisor(groups));
         return hipGetLastError();
     }
@@ -401,18 +399,17 @@ template <typename OutT>
 hipError_t launch_epilogue(const void *prod, bool prod_is_u8, int64_t Mp, int64_t Np, int64_t m,
                            int64_t n, const int32_t *tA, const int32_t *tB, const ModArgs &ma,
                            double alpha, double beta, OutT *C, int64_t ldc, hipStream_t stream) {
-    const int64_t groups = (n + kEpilogueColumns - 1) / kEpilogueColumns, plane = Mp * Np;
-    if (groups > 0x3fffffff) return hipErrorInvalidValue;     // (a row of U of 4 GiB per modulus)
-    const int64_t rows = std::max<int64_t>(1, ((int64_t)0x7fffff00 - 256) / groups);   // of a launch: its thread numbers fit 31 bits
+    const int64_t groups = epilogue_groups(n), plane = Mp * Np, rows = epilogue_rows(groups);
+    if (rows < 1) return hipErrorInvalidValue;
     for (int64_t r = 0; r < m; r += rows) {
         const int64_t count = std::min(rows, m - r);
-        const unsigned blocks = blocks_for(count * groups);
+        const unsigned blocks = (unsigned)((count * groups + kEpilogueThreads - 1) / kEpilogueThreads);
         hipError_t e;
         if (prod_is_u8) {
             e = launch_epilogue_u8<OutT, OZ2_MIN_MODULI>(static_cast<const uint8_t *>(prod) + r * Np, plane, Np, count, n, tA + r, tB, ma,
                                                          alpha, beta, C + r * ldc, ldc, (int)groups, blocks, stream);
         } else {
-            hipLaunchKernelGGL((k_epilogue_i32<OutT>), dim3(blocks), dim3(256), 0, stream,
+            hipLaunchKernelGGL((k_epilogue_i32<OutT>), dim3(blocks), dim3(kEpilogueThreads), 0, stream,
                                static_cast<const int32_t *>(prod) + r * Np, plane, Np, count, n, tA + r, tB, ma, alpha, beta,
                                C + r * ldc, ldc, (int)groups, make_divisor((int)groups));
             e = hipGetLastError();

@@ -84,24 +84,28 @@ print(json.dumps(out))
 """
 
 
-@pytest.fixture(scope="module")
-def prepare_launches(tmp_path_factory):
+def run_on_stand_in(d, caller, stand_in=STAND_IN):
+    """What `caller` prints (JSON) about a library whose HIP runtime is the stand-in, in a process of its own."""
     import paper_2508_03984_amd as oz
     if not os.path.exists(oz.lib_path()):
         from paper_2508_03984_amd.build import build_library
         build_library()
-    d = tmp_path_factory.mktemp("routes")
     needed = subprocess.run(["readelf", "-d", oz.lib_path()], capture_output=True, text=True, check=True).stdout
     soname = next(line.split("[")[1].split("]")[0] for line in needed.splitlines() if "libamdhip64" in line)
-    (d / "fake.c").write_text(STAND_IN)
+    (d / "fake.c").write_text(stand_in)
     (d / "fake.map").write_text("hip_4.2 { global: *; };\nhip_6.0 { global: hipGetDevicePropertiesR0600; } hip_4.2;\n")
-    (d / "caller.py").write_text(CALLER)
+    (d / "caller.py").write_text(caller)
     fake = d / "libfake.so"
     subprocess.check_call(["gcc", "-std=gnu99", "-O1", "-shared", "-fPIC", "-Wl,-soname," + soname,
                            "-Wl,--version-script=" + str(d / "fake.map"), str(d / "fake.c"), "-o", str(fake)])
     run = subprocess.run([sys.executable, str(d / "caller.py"), str(fake), oz.lib_path()], capture_output=True, text=True)
     assert run.returncode == 0, run.stderr
     return json.loads(run.stdout)
+
+
+@pytest.fixture(scope="module")
+def prepare_launches(tmp_path_factory):
+    return run_on_stand_in(tmp_path_factory.mktemp("routes"), CALLER)
 
 
 def test_prepared_operands_follow_the_conversion_option(prepare_launches):
