@@ -291,7 +291,13 @@ __global__ __launch_bounds__(kEpilogueThreads) void k_epilogue(const uint8_t *__
     tail.store(C1, C2, ma, alpha, beta);
 }
 
-// The form for int32 sums (possibly folded partial sums), which are reduced here.
+// The form for int32 sums (possibly folded partial sums), which are reduced here.  Bound: HBM.  Moduli in groups of 8, then 4, 2
+// and 1, a group's loads first.  Planes beyond the memory-side cache are read better by fewer wavefronts: LDS that nobody uses keeps
+// them to 4 per SIMD there.  us, loops of 4 moduli and single ones at the end | groups | groups, 4 wavefronts: 8192^2 N = 16 980 |
+// 972 | 954, 4096^2 N = 14 242 | 241 | 233, with beta = 1 264 | 262 | 255, FP32 N = 8 145 | 144 | 136; from the cache 2048^2 N = 15
+// 51 | 52 | 54, 1024^2 15.8 | 15.9 | 15.9.
+constexpr int64_t kMemorySideCache = (int64_t)256 << 20;
+constexpr unsigned kLdsFor4Waves = 40 * 1024;             // a quarter of a compute unit's, per workgroup of 4 wavefronts
 template <typename OutT>
 __global__ __launch_bounds__(kEpilogueThreads) void k_epilogue_i32(const int32_t *__restrict__ prod, int64_t plane, int64_t Np, int64_t m,
                                                       int64_t n, const int32_t *__restrict__ tA,
@@ -304,18 +310,29 @@ __global__ __launch_bounds__(kEpilogueThreads) void k_epilogue_i32(const int32_t
     double C1[W], C2[W];
 #pragma unroll
     for (int c = 0; c < W; ++c) C1[c] = C2[c] = 0.0;
-#pragma unroll 4
-    for (int s = 0; s < ma.n; ++s) {
-        const int4 x = *reinterpret_cast<const int4 *>(u + s * plane);
-        const int p = ma.p[s], pv = (int)ma.pinv_prime[s];
-        const int us[W] = {mod_small(x.x, p, pv), mod_small(x.y, p, pv), mod_small(x.z, p, pv), mod_small(x.w, p, pv)};
-        const double s1 = ma.s1[s], s2 = ma.s2[s];
+    // moduli s0 .. s0 + CNT - 1, the FMAs in ascending order of s
+    auto group = [&](int s0, auto cnt) {
+        constexpr int CNT = decltype(cnt)::value;
+        int4 x[CNT];
 #pragma unroll
-        for (int c = 0; c < W; ++c) {
-            C1[c] = fma(s1, (double)us[c], C1[c]);
-            C2[c] = fma(s2, (double)us[c], C2[c]);
+        for (int g = 0; g < CNT; ++g) x[g] = *reinterpret_cast<const int4 *>(u + (s0 + g) * plane);
+#pragma unroll
+        for (int g = 0; g < CNT; ++g) {
+            const int p = ma.p[s0 + g], pv = (int)ma.pinv_prime[s0 + g];
+            const int us[W] = {mod_small(x[g].x, p, pv), mod_small(x[g].y, p, pv), mod_small(x[g].z, p, pv), mod_small(x[g].w, p, pv)};
+            const double s1 = ma.s1[s0 + g], s2 = ma.s2[s0 + g];
+#pragma unroll
+            for (int c = 0; c < W; ++c) {
+                C1[c] = fma(s1, (double)us[c], C1[c]);
+                C2[c] = fma(s2, (double)us[c], C2[c]);
+            }
         }
-    }
+    };
+    int s = 0;
+    for (; s + 8 <= ma.n; s += 8) group(s, std::integral_constant<int, 8>{});
+    if (s + 4 <= ma.n) { group(s, std::integral_constant<int, 4>{}); s += 4; }
+    if (s + 2 <= ma.n) { group(s, std::integral_constant<int, 2>{}); s += 2; }
+    if (s < ma.n) group(s, std::integral_constant<int, 1>{});
     EpilogueTail<OutT>(at, n, tA, tB, beta, C, ldc).store(C1, C2, ma, alpha, beta);
 }
 
@@ -409,7 +426,8 @@ hipError_t launch_epilogue(const void *prod, bool prod_is_u8, int64_t Mp, int64_
             e = launch_epilogue_u8<OutT, OZ2_MIN_MODULI>(static_cast<const uint8_t *>(prod) + r * Np, plane, Np, count, n, tA + r, tB, ma,
                                                          alpha, beta, C + r * ldc, ldc, (int)groups, blocks, stream);
         } else {
-            hipLaunchKernelGGL((k_epilogue_i32<OutT>), dim3(blocks), dim3(kEpilogueThreads), 0, stream,
+            const unsigned lds_bytes = 4 * ma.n * plane > kMemorySideCache ? kLdsFor4Waves : 0;
+            hipLaunchKernelGGL((k_epilogue_i32<OutT>), dim3(blocks), dim3(kEpilogueThreads), lds_bytes, stream,
                                static_cast<const int32_t *>(prod) + r * Np, plane, Np, count, n, tA + r, tB, ma, alpha, beta,
                                C + r * ldc, ldc, (int)groups, make_divisor((int)groups));
             e = hipGetLastError();
