@@ -241,17 +241,10 @@ hipError_t launch_kind(const FusedFactor<T> &A, const FusedFactor<T> &B, const S
     // repeated in a graph, other operands in each, us: 256^3 N = 14 13.1 -> 12.0, 64^3 N = 15 12.5 -> 11.4, 200^3 N = 15 14.7 -> 13.6).
     const unsigned blocks = a.blocks + b.blocks, groups = (unsigned)((ma.n + kModGroup - 1) / kModGroup);
     if constexpr (KIND == 0) {
-        if (groups > 1 && blocks * groups <= 256) {
-            const dim3 grid(blocks, groups);
-#define OZ2_CONVERT_SPLIT(THREADS, CH)                                                                        \
-    if (plan.threads == THREADS && plan.pieces == CH) {                                                       \
-        hipLaunchKernelGGL((k_convert<T, THREADS, CH, ROUNDS, KIND, true>), grid, dim3(THREADS), 0, stream, a, b, sa, ma); \
-        return hipGetLastError();                                                                             \
-    }
-            OZ2_CONVERT_SPLIT(256, 1) OZ2_CONVERT_SPLIT(512, 1) OZ2_CONVERT_SPLIT(512, 2) OZ2_CONVERT_SPLIT(512, 3)
-            OZ2_CONVERT_SPLIT(512, 4) OZ2_CONVERT_SPLIT(1024, 3) OZ2_CONVERT_SPLIT(1024, 4)
-#undef OZ2_CONVERT_SPLIT
-            return hipErrorInvalidValue;
+        if (fused_split_applies(plan, blocks, groups)) {
+            hipLaunchKernelGGL((k_convert<T, kFusedSplitThreads, kFusedSplitPieces, ROUNDS, KIND, true>), dim3(blocks, groups),
+                               dim3(kFusedSplitThreads), 0, stream, a, b, sa, ma);
+            return hipGetLastError();
         }
     }
     const dim3 grid(blocks);

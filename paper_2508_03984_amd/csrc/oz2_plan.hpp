@@ -84,6 +84,13 @@ inline FusedPlan fused_plan(int64_t Kp, bool strips, int64_t vectors, size_t ele
     return p;
 }
 
+// Groups of moduli get workgroups of their own where every one of those has a compute unit.  Only the smallest shape can have
+// that few workgroups: the others have 256 at least.
+constexpr int kFusedSplitThreads = 256, kFusedSplitPieces = 1;
+inline bool fused_split_applies(const FusedPlan &p, int64_t workgroups, int64_t groups) {
+    return groups > 1 && workgroups * groups <= 256 && p.threads == kFusedSplitThreads && p.pieces == kFusedSplitPieces;
+}
+
 // A factor of rows and one of columns share a launch up to here; beyond, the two forms want different
 // workgroups and a launch more costs less.
 constexpr int64_t kFusedShareLaunch = 2048;
