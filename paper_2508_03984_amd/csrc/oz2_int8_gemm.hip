@@ -48,7 +48,6 @@ constexpr int64_t kPersistentMaxK = OZ2_PERSISTENT_MAX_K;   // contractions up t
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void *lds_ptr_t;
-typedef const __attribute__((address_space(1))) void *global_ptr_t;
 
 // s_waitcnt immediate that waits for vmcnt <= n only (gfx9 encoding: vmcnt in bits 3:0 and
 // 15:14, expcnt 6:4 and lgkmcnt 11:8 left at their maxima).
@@ -127,7 +126,6 @@ struct GemmCore {
     static constexpr int FM = 2 * TM, FN = 2 * TN;            // 16 x 16 fragments of a wavefront
     static constexpr int STAGE_BYTES = CHUNKS * 16;
     static constexpr int ROWS_PER_LOAD = 64 / CPR;            // rows one wavefront-wide load covers
-    static constexpr int SRC_STEP = ROWS_PER_LOAD * BK;
     static_assert(CHUNKS % THREADS == 0 && (BM * CPR) % (64 * LPT) == 0,
                   "each wavefront must load from one operand only");
     static_assert(BK == kBlockK, "the K tile is the K block of the operand layout");
