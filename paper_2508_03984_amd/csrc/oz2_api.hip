@@ -168,7 +168,7 @@ oz2_status run_products(Ctx &g, const Layout &L, const Panels &P, const int8_t *
     // contraction up to 2^17.)
     const size_t entry = L.prod_u8 ? 1 : 4;
     int64_t done = 0;
-    if (L.prod_u8 && P.count == 1 && tiny_product_applies(L.m, L.n, L.Kp, L.N)) {
+    if (L.prod_u8 && P.count == 1 && tiny_product_applies(L.m, L.n, L.Kp, L.N, !L.with_operands)) {
         ++g.last_gemm_launches;                               // (the accumulation is part of it)
         OZ2_TRY(launch_tiny_product<T>(rA, rB, static_cast<uint8_t *>(prod), L.Mp, L.Np, L.Kp, L.m, L.n, tA, tB, ma, alpha, beta,
                                        C, ldc, stream));

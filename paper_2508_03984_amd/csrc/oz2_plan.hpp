@@ -126,6 +126,7 @@ struct Layout {
     int64_t m, n, k, Mp, Np, Kp;
     int N;
     bool prod_u8;
+    bool with_operands;                    // the call converts its factors itself
     size_t off_bt, off_ta, off_tb, off_ra, off_rb, off_prod;
     size_t prod_whole, prod_min;           // product part: all of C at once / one 256 x 256 panel
 };
@@ -135,7 +136,7 @@ inline size_t bytes_per_entry(int N, bool prod_u8) { return (size_t)N * (prod_u8
 
 inline Layout make_layout(int64_t m, int64_t n, int64_t k, int N, bool prod_u8, bool with_operands = true) {
     Layout L{};
-    L.m = m; L.n = n; L.k = k; L.N = N; L.prod_u8 = prod_u8;
+    L.m = m; L.n = n; L.k = k; L.N = N; L.prod_u8 = prod_u8; L.with_operands = with_operands;
     L.Mp = round_up(m, kPadMN); L.Np = round_up(n, kPadMN); L.Kp = round_up(k, kPadK);
     size_t o = 0;
     if (with_operands) {
@@ -245,16 +246,44 @@ inline int64_t launch_k_len(int64_t Kp, int N, const Panels &Q) {
     return std::min<int64_t>(len, OZ2_MAX_K);
 }
 
-// The smallest products run their GEMMs and the accumulation as one launch (oz2_tiny.hip): at most one 32 x 32
-// tile of C per compute unit, at most 512 elements of k in a row for a wavefront (each of the 16 takes every
-// 16th modulus), and few enough operands for a compute unit to load (64 Kp N bytes).  Measured on the GPU with tiles of 32 x 32 only, two launches | one,
-// us, other operands in each call; prepared operands: 256^3 N = 15 9.5 | 8.9, 1000 x 250 x 256 N = 15 12.1 | 10.6, 400 x 400 x 384
-// FP32 N = 8 9.3 | 9.1, not taken 100 x 100 x 512 N = 15 11.0 | 11.8, 512^3 N = 15 13.0 | 13.4; whole calls: 256^3 N = 15 14.9 | 14.1,
-// 256 x 256 x 128 FP32 N = 6 11.4 | 9.3, 1000 x 250 x 256 18.7 | 18.7, and with more than about 64 tiles 400 x 400 x 256 N = 15
-// 17.1 | 17.6, 400 x 400 x 384 FP32 N = 8 14.2 | 15.6.  A launch less also saves the host about 4 us, which bounds calls one after
-// another at these sizes.
-inline bool tiny_product_applies(int64_t m, int64_t n, int64_t Kp, int N) {
-    return (m + 31) / 32 * ((n + 31) / 32) <= 256 && (N + 15) / 16 * Kp <= 512 && Kp * N <= 4096;
+// The smallest products run their GEMMs and the accumulation as one launch (oz2_tiny.hip): tiles of 16 x 16 where these and
+// the padding have a compute unit each, else of 32 x 32.
+struct TinyGrid {
+    int64_t tiles_m, tiles_n, padding;     // padding: workgroups that clear it
+    int64_t tiles() const { return tiles_m * tiles_n; }
+};
+inline TinyGrid tiny_grid(int64_t m, int64_t n, int tile) {
+    const int64_t tiles_m = (m + tile - 1) / tile, tiles_n = (n + tile - 1) / tile;
+    const int64_t Mp = round_up(m, kPadMN), Np = round_up(n, kPadMN);
+    return TinyGrid{tiles_m, tiles_n, (Mp / tile - tiles_m) * (Np / kPadMN) + (Np > tiles_n * tile ? tiles_m : 0)};
+}
+inline bool tiny_small_tiles(int64_t m, int64_t n) {
+    const TinyGrid g = tiny_grid(m, n, 16);
+    return g.tiles() + g.padding <= 256;
+}
+
+// Which products: at most one 32 x 32 tile of C per compute unit, at most 512 elements of k in a row for a wavefront (each of
+// the 16 takes every 16th modulus), and few enough operands for a compute unit to load (32 Kp N or 64 Kp N bytes).  Prepared operands
+// gain there nearly throughout (us, other operands in each call, two launches | one: 256^3 N = 14 8.1 | 7.3, 256 x 256 x 512 FP32 N = 8 8.3 | 5.6,
+// 400 x 400 x 256 N = 15 9.4 | 8.7, 400 x 400 x 384 FP32 N = 8 8.3 | 7.8, 512 x 512 x 256 N = 15 9.9 | 8.9; with Kp = 128, N = 15 and tiles of
+// 16 x 16 6.7 | 6.9).  Beyond the limits it is uneven: 200 x 200 x 1024 FP32 N = 8 9.5 | 7.3, but 500 x 300 x 777 9.6 | 11.2,
+// 400 x 400 x 1024 10.6 | 11.4, 128 x 128 x 1024 N = 14 10.0 | 10.2.
+//
+// A call that converts its factors itself gains less, and nothing where C is about as wide as high and the moduli are many
+// (whole calls, graph | one after another from Python, us, two launches -> one; taken back to two: 300 x 300 x 128 N = 15 12.3 -> 13.6 | 12.6 -> 13.5, 320 x 320 x 256
+// N = 16 +1.0 | +0.7, 400 x 400 x 384 FP32 N = 8 13.3 -> 13.8 | 13.4 -> 13.9, 512 x 300 x 128 N = 16 +0.7 | +1.0, with tiles of 16 x 16 200^3 N = 16 +1.0 | +1.4;
+// taken: 256^3 N = 14 0 | -0.6, 128^3 N = 14 +0.3 | -0.7, 400 x 400 x 128 FP32 N = 8 10.7 -> 9.9 | 11.8 -> 10.3, 512 x 512 x 512 FP32 N = 6
+// 14.3 -> 13.2 | 14.2 -> 13.0, 512 x 512 x 256 N = 15 16.5 -> 16.0 | 16.4 -> 15.8, 1000 x 250 x 256 17.3 -> 15.3 | 17.6 -> 15.3, 8000 x 30 x 64 27.5 -> 20.5).
+// Of those taken, N = 14 and 15 with Kp = 256 and tiles of 16 x 16 are even in a graph and lose up to 0.9 one after another,
+// Kp = 384 with N = 8 to 10 and C wider than 448 loses up to 1.7.  Accurate mode shows the same signs.
+inline bool tiny_product_applies(int64_t m, int64_t n, int64_t Kp, int N, bool prepared) {
+    if ((m + 31) / 32 * ((n + 31) / 32) > 256 || (N + 15) / 16 * Kp > 512 || Kp * N > 4096) return false;
+    const int64_t longer = std::max(m, n);
+    if (prepared || longer >= 4 * std::min(m, n)) return true;
+    if (tiny_small_tiles(m, n)) return N <= 15 || longer <= 64;
+    if (N <= 6 || (N <= 10 && Kp <= 256)) return true;
+    if (N > 16) return longer > 384;       // the INT8 GEMM of the other form has a second round
+    return Kp > 128 && longer > 448;
 }
 
 // The accumulation gives each thread kEpilogueColumns consecutive columns of a row, in workgroups of kEpilogueThreads, and works

@@ -184,23 +184,18 @@ hipError_t launch_tiny_product(const int8_t *A, const int8_t *B, uint8_t *U, int
                                double alpha, double beta, OutT *C, int64_t ldc, hipStream_t stream) {
     TinyMods tm{};
     for (int i = 0; i < ma.n; ++i) tm.byte_mod[i] = make_byte_mod(ma.p[i]);
-    struct Grid { int tiles_n, tiles; int64_t padding; };
-    auto grid_of = [&](int tile) {
-        const int tiles_m = (int)((m + tile - 1) / tile), tiles_n = (int)((n + tile - 1) / tile);
-        return Grid{tiles_n, tiles_m * tiles_n, (Mp / tile - tiles_m) * (Np / kPadMN) + (Np > (int64_t)tiles_n * tile ? tiles_m : 0)};
-    };
-    auto go = [&](auto blocks, const Grid &g) {
-        hipLaunchKernelGGL((k_tiny_product<OutT, decltype(blocks)::value>), dim3((unsigned)(g.tiles + g.padding)), dim3(64 * kWaves), 0,
-                           stream, A, B, U, Mp, Np, Kp, m, n, tA, tB, ma, tm, alpha, beta, C, ldc, g.tiles_n, make_divisor(g.tiles_n),
-                           g.tiles, std::min(g.tiles_n, g.tiles / g.tiles_n), make_divisor(std::min(g.tiles_n, g.tiles / g.tiles_n)));
+    auto go = [&](auto blocks, const TinyGrid &g) {
+        const int tiles_n = (int)g.tiles_n, tiles = (int)g.tiles(), tiles_short = (int)std::min(g.tiles_m, g.tiles_n);
+        hipLaunchKernelGGL((k_tiny_product<OutT, decltype(blocks)::value>), dim3((unsigned)(tiles + g.padding)), dim3(64 * kWaves), 0,
+                           stream, A, B, U, Mp, Np, Kp, m, n, tA, tB, ma, tm, alpha, beta, C, ldc, tiles_n, make_divisor(tiles_n),
+                           tiles, tiles_short, make_divisor(tiles_short));
         return hipGetLastError();
     };
     // Tiles of 16 x 16 where these and the padding have a compute unit each: four times as many units fetch operands and
     // accumulate (whole calls repeated in a graph, other operands in each, us, 32 x 32 | 16 x 16: 256^3 N = 14 13.0 | 12.1, 200^3
     // N = 15 14.2 | 13.6, 128^3 N = 14 12.5 | 11.5, 256 x 256 x 512 FP32 N = 6 11.6 | 10.1).
-    const Grid small = grid_of(16);
-    if (small.tiles + small.padding <= 256) return go(std::integral_constant<int, 1>{}, small);
-    return go(std::integral_constant<int, 2>{}, grid_of(32));
+    if (tiny_small_tiles(m, n)) return go(std::integral_constant<int, 1>{}, tiny_grid(m, n, 16));
+    return go(std::integral_constant<int, 2>{}, tiny_grid(m, n, 32));
 }
 
 #define OZ2_INSTANTIATE_TINY(T)                                                                                   \

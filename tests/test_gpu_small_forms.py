@@ -5,6 +5,7 @@ import pytest
 
 import synth_inputs as S
 from test_gpu_parity import assert_parity, gpu_gemm, oz  # noqa: F401  (fixture)
+from test_launch_routes import ONE, TWO
 
 pytestmark = pytest.mark.gpu
 
@@ -33,3 +34,28 @@ def test_smallest_products(oz, oracle, m, n, k, N, dtype):
     Cin = S.matrix(m, n, 0.5, seed=8, dtype=dtype)
     assert_parity(gpu_gemm(oz, A, B, N, -1.0, 0.75, Cin, ldc=n + 1),
                   oracle.gemm(A, B, N, -1.0, 0.75, Cin, is_double=is_double), is_double)
+
+
+@pytest.mark.parametrize("t,m,n,k,N", TWO + ONE)
+def test_one_launch_and_two_give_the_same_bits(oz, t, m, n, k, N):
+    """Prepared operands take the one-launch form where a call that converts its factors may take two launches: C, with and
+    without a C that is read, is equal, and the padding of U_s is zero in both forms of the calls."""
+    import torch
+    from paper_2508_03984_amd import binding as b
+    dtype = torch.float64 if t == "d" else torch.float32
+    A, B = (torch.from_numpy(x).cuda() for x in S.gemm_inputs(m, n, k, 1.0, seed=m + k, dtype=np.float64 if t == "d" else np.float32))
+    prepare, product = (oz.oz2_prepare_d, oz.oz2_dgemm_prepared) if t == "d" else (oz.oz2_prepare_s, oz.oz2_sgemm_prepared)
+    left, right = prepare(0, 0, m, k, A, k, N), prepare(1, 0, n, k, B, n, N)
+    try:
+        for alpha, beta in ((1.0, 0.0), (-0.5, 1.25)):
+            plain, one = (torch.full((m, n), 3.0, dtype=dtype, device="cuda") for _ in range(2))
+            oz.matmul(A, B, N, alpha=alpha, beta=beta, out=plain)
+            torch.cuda.synchronize()
+            U = oz.stage_tensor(b.OZ2_STAGE_U)
+            assert not U[:, m:, :].any() and not U[:, :, n:].any()
+            product(left, right, alpha, beta, one, n)
+            torch.cuda.synchronize()
+            assert torch.equal(plain, one), (alpha, beta)
+    finally:
+        left.free()
+        right.free()

@@ -84,7 +84,7 @@ print(json.dumps(out))
 """
 
 
-def run_on_stand_in(d, caller, stand_in=STAND_IN):
+def run_on_stand_in(d, caller, stand_in=STAND_IN, data=None):
     """What `caller` prints (JSON) about a library whose HIP runtime is the stand-in, in a process of its own."""
     import paper_2508_03984_amd as oz
     if not os.path.exists(oz.lib_path()):
@@ -98,7 +98,8 @@ def run_on_stand_in(d, caller, stand_in=STAND_IN):
     fake = d / "libfake.so"
     subprocess.check_call(["gcc", "-std=gnu99", "-O1", "-shared", "-fPIC", "-Wl,-soname," + soname,
                            "-Wl,--version-script=" + str(d / "fake.map"), str(d / "fake.c"), "-o", str(fake)])
-    run = subprocess.run([sys.executable, str(d / "caller.py"), str(fake), oz.lib_path()], capture_output=True, text=True)
+    run = subprocess.run([sys.executable, str(d / "caller.py"), str(fake), oz.lib_path()], input=data, capture_output=True,
+                         text=True)
     assert run.returncode == 0, run.stderr
     return json.loads(run.stdout)
 
@@ -122,3 +123,61 @@ def test_prepared_operands_follow_the_conversion_option(prepare_launches):
             assert len(names) == 1 and fused, (case, names)
         else:
             assert not fused and len(names) >= 2, (case, names)
+
+
+PRODUCTS = r"""
+import ctypes as C, json, sys
+fake = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+fake.launched.restype = C.c_char_p
+lib = C.CDLL(sys.argv[2])
+vp, i64 = C.c_void_p, C.c_int64
+for t, real in (("d", C.c_double), ("s", C.c_float)):
+    getattr(lib, "oz2_prepare_" + t).argtypes = [C.c_int, C.c_int, i64, i64, vp, i64, C.c_int, vp, C.POINTER(vp)]
+    getattr(lib, "oz2_%sgemm_prepared" % t).argtypes = [vp, vp, real, real, vp, i64, vp]
+    getattr(lib, "oz2_%sgemm_op" % t).argtypes = [C.c_int, C.c_int, C.c_int, i64, i64, i64, real, vp, i64, vp, i64, real, vp, i64, C.c_int, vp]
+lib.oz2_operand_free.argtypes = [vp]
+out = {}
+X = 1 << 20                                               # nothing reads it
+for case in json.loads(sys.stdin.read()):
+    t, m, n, k, N = case
+    got = []
+    for accurate in (0, 1):
+        fake.forget()
+        assert getattr(lib, "oz2_%sgemm_op" % t)(0, 0, accurate, m, n, k, 1.0, X, k, X, n, 0.0, X, n, N, None) == 0
+        got.append(fake.launched().decode().split("\n")[:-1])
+    a, b = vp(), vp()
+    assert getattr(lib, "oz2_prepare_" + t)(0, 0, m, k, X, k, N, None, C.byref(a)) == 0
+    assert getattr(lib, "oz2_prepare_" + t)(1, 0, n, k, X, n, N, None, C.byref(b)) == 0
+    fake.forget()
+    assert getattr(lib, "oz2_%sgemm_prepared" % t)(a, b, 1.0, 0.0, X, n, None) == 0
+    got.append(fake.launched().decode().split("\n")[:-1])
+    lib.oz2_operand_free(a); lib.oz2_operand_free(b)
+    out["%s %d %d %d %d" % tuple(case)] = got
+print(json.dumps(out))
+"""
+
+# A product that converts its factors in two launches (GEMMs, accumulation) or one; prepared operands take one for all of these.
+TWO = [("d", 300, 300, 128, 15), ("d", 400, 400, 256, 15), ("s", 400, 400, 384, 8), ("d", 448, 448, 256, 16), ("d", 200, 200, 256, 16),
+       ("d", 65, 66, 100, 16), ("d", 384, 384, 128, 17), ("d", 512, 512, 128, 16), ("d", 512, 130, 128, 16), ("s", 300, 300, 257, 7)]
+ONE = [("d", 256, 256, 256, 14), ("d", 256, 256, 256, 15), ("d", 64, 64, 64, 20), ("d", 512, 128, 128, 16), ("d", 100, 401, 256, 16),
+       ("d", 449, 449, 256, 16), ("d", 385, 385, 128, 17), ("s", 400, 400, 256, 8), ("s", 400, 400, 256, 10), ("s", 300, 300, 512, 6),
+       ("s", 449, 300, 500, 8), ("d", 8000, 30, 64, 15), ("d", 1, 1, 1, 2)]
+
+
+@pytest.fixture(scope="module")
+def product_launches(tmp_path_factory):
+    return run_on_stand_in(tmp_path_factory.mktemp("products"), PRODUCTS, data=json.dumps(TWO + ONE + [("d", 100, 100, 513, 7)]))
+
+
+def test_one_launch_form_where_it_gains(product_launches):
+    """The one-launch form of the smallest products is taken by calls that convert their factors only where it is the
+    faster one, by prepared operands throughout."""
+    for case in TWO + ONE:
+        fast, accurate, prepared = product_launches["%s %d %d %d %d" % case]
+        one = case in ONE
+        assert ("k_tiny_product" in " ".join(fast)) == one and ("k_epilogue" in " ".join(fast)) != one, case
+        assert ("k_tiny_product" in " ".join(accurate)) == one and ("k_epilogue" in " ".join(accurate)) != one, case
+        assert len(prepared) == 1 and "k_tiny_product" in prepared[0], case
+        assert len(fast) == (2 if one else 3), (case, fast)
+    for names in product_launches["d 100 100 513 7"]:     # beyond the limits of the form
+        assert "k_tiny_product" not in " ".join(names) and "k_epilogue" in names[-1]
