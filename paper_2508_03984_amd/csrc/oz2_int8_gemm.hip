@@ -538,16 +538,12 @@ hipError_t launch(const int8_t *A, const int8_t *B, void *C, int batch, int64_t 
     return hipGetLastError();
 }
 
-// Problems of fewer than 128 large tiles: 128 x 128 tiles, so that more workgroups exist.  Up to 256 of them
-// have a compute unit each: 8 wavefronts and 6 stages there; of more, two share one.  Measured with 32x32x32 MFMAs, 4 wavefronts and 4 stages | 4 and 6 |
-// 8 and 6, us, prepared operands, others in each call: 500 x 300 x 777 FP32 N = 8 12.0 | 11.5 | 11.6; N = 15, 256 x 256 x 1024
-// 13.5 | 12.7 | 12.8, 512 x 512 x 2048 22.5 | 19.5 | 19.8; accurate mode 512^3 N = 15 (whole call, the one slice of Cbar)
-// - | 40.6 | 37.7.  (The same operands again and again stay in the L2s: 4 and 4 is then 0.1 to 0.4 us faster up to k of about 2500.)
+// Tiles of 128 x 128 (gemm_small_tiles, oz2_plan.hpp).
 template <int OUT>
 hipError_t launch_small(const int8_t *A, const int8_t *B, void *C, int batch, int64_t Mp, int64_t Np,
                         int64_t Kp, int64_t k_begin, int64_t k_len, const GemmPanel &pn,
                         const GemmMods &mods, hipStream_t stream) {
-    if (pn.rows * pn.cols * batch <= (int64_t)128 * 128 * 256)
+    if (gemm_one_tile_per_unit(pn.rows, pn.cols, batch))
         return launch<2, 4, 2, 1, 64, 6, OUT>(A, B, C, batch, Mp, Np, Kp, k_begin, k_len, pn, mods, stream);
     return launch<2, 2, 2, 2, 64, 4, OUT>(A, B, C, batch, Mp, Np, Kp, k_begin, k_len, pn, mods, stream);
 }
@@ -556,10 +552,7 @@ template <int OUT>
 hipError_t launch_out(const int8_t *A, const int8_t *B, void *C, int batch, int64_t Mp, int64_t Np,
                       int64_t Kp, int64_t k_begin, int64_t k_len, const GemmPanel &pn,
                       const GemmMods &mods, hipStream_t stream) {
-    // Problems of fewer than 128 large tiles get the 128 x 128 tile so that more workgroups exist
-    // (measured at N = 14: 512^3, 56 large tiles, 11.4 against 17.3 us; 1024^3, 224 large tiles,
-    // 31.2 against 26.8 us, so from there on the large tile wins although it leaves units idle).
-    if (pn.rows * pn.cols * batch < (int64_t)256 * 256 * 128)
+    if (gemm_small_tiles(pn.rows, pn.cols, batch))
         return launch_small<OUT>(A, B, C, batch, Mp, Np, Kp, k_begin, k_len, pn, mods, stream);
     // 8 wavefronts (2 per SIMD), each 128 x 64: measured against 4 wavefronts of 128 x 128 on
     // the same device it is 2 % faster at 16 x 16384^3 -- a wavefront that is held up issuing
@@ -586,7 +579,7 @@ hipError_t launch_int8_gemm_maxima(const int8_t *A, const int8_t *B, int64_t Mp,
     q.c_ld = valid_rows | (valid_cols << 32);
     q.c_plane = col_max - row_max;
     const GemmMods none{};
-    if (pn.rows * pn.cols < (int64_t)256 * 256 * 128)        // as in launch_out
+    if (gemm_small_tiles(pn.rows, pn.cols, 1))
         return launch_small<kOutMax>(A, B, row_max, 1, Mp, Np, Kp, k_begin, k_len, q, none, stream);
     return launch<2, 4, 4, 2, 64, 4, kOutMax>(A, B, row_max, 1, Mp, Np, Kp, k_begin, k_len, q, none, stream);
 }

@@ -296,6 +296,23 @@ inline int64_t epilogue_rows(int64_t groups, int64_t max_threads = kEpilogueMaxT
     return groups > 0x3fffffff ? 0 : max_threads / groups;
 }
 
+// The INT8 GEMM takes tiles of 128 x 128 where there would be at most 128 tiles of 256 x 256: those leave half of the compute units
+// without one, and up to there every unit has work with two of the small ones.  Prepared operands, other ones in
+// each call, us, 128 x 128 | 256 x 256: 96 large tiles (1024^3 FP32 N = 6) 19.4 | 21.9; 112 19.8 | 22.7; 120 (2048 x 256 x 1024 N = 15) 20.5 | 22.8; 128
+// (1024^3 FP32 N = 8) 21.4 | 23.9, (512 x 1024 x 8192 N = 16) 87.4 | 92.2, (2048^3 N = 2) 33.2 | 37.2; 135 (768 x 768 x 1024 N = 15) 26.8 | 24.0; 140
+// 29.3 | 25.3; 168 (1024 x 768 x 1024 N = 14) 27.2 | 23.5; 224 (1024^3 N = 14) 33.5 | 28.1; 448 (2048^3 FP32 N = 7) 78.6 | 66.3.  Accurate mode's one slice, whole
+// calls: 128 (2048 x 4096 x 2048 FP32 N = 6) 174 | 179, 144 (2304 x 4096 x 2048) 207 | 203.
+inline bool gemm_small_tiles(int64_t rows, int64_t cols, int64_t batch) {
+    return rows * cols * batch <= (int64_t)256 * 256 * 128;
+}
+// Of those, at most one per compute unit run with 8 wavefronts and 6 stages of LDS, more with 4 and 4, so that two share a unit.  us as
+// above, 4 and 4 | 8 and 6: 256 x 256 x 1024 N = 15 10.7 | 10.2, x 4096 30.7 | 26.0, 500 x 300 x 777 FP32 N = 8 9.9 | 9.6, 512 x 512 x 2048 N = 15 20.8 | 19.6, 512^3
+// N = 14 10.8 | 10.7, N = 16 (256 tiles) 11.6 | 11.5, N = 17 (272) 12.6 | 14.9, 768 x 768 x 512 N = 8 (288) 13.1 | 15.4; accurate mode, whole calls, 512^3
+// N = 15 35.9 | 34.7, 1024^3 63.1 | 61.4.
+inline bool gemm_one_tile_per_unit(int64_t rows, int64_t cols, int64_t batch) {
+    return rows * cols * batch <= (int64_t)128 * 128 * 256;
+}
+
 // Side of a panel of the overlapped form: the INT8 GEMM loses nothing down to 4096 x 4096.
 constexpr int64_t kOverlapPanel = 4096;
 

@@ -2,6 +2,7 @@
 runtime that records the launches and does nothing else."""
 import json
 import os
+import re
 import subprocess
 import sys
 
@@ -163,10 +164,14 @@ ONE = [("d", 256, 256, 256, 14), ("d", 256, 256, 256, 15), ("d", 64, 64, 64, 20)
        ("d", 449, 449, 256, 16), ("d", 385, 385, 128, 17), ("s", 400, 400, 256, 8), ("s", 400, 400, 256, 10), ("s", 300, 300, 512, 6),
        ("s", 449, 300, 500, 8), ("d", 8000, 30, 64, 15), ("d", 1, 1, 1, 2)]
 
+# Products whose INT8 GEMM has 127 to 129 tiles of 256 x 256 or thereabouts, and 256 and 272 of 128 x 128
+TILES = [("s", 1024, 1024, 600, 8), ("d", 2048, 2048, 600, 2), ("d", 256, 256 * 43, 600, 3), ("d", 512, 512, 600, 16),
+         ("d", 512, 512, 600, 17), ("s", 1024, 1024, 600, 9), ("d", 2048, 4096, 600, 14), ("d", 2304, 4096, 600, 14)]
+
 
 @pytest.fixture(scope="module")
 def product_launches(tmp_path_factory):
-    return run_on_stand_in(tmp_path_factory.mktemp("products"), PRODUCTS, data=json.dumps(TWO + ONE + [("d", 100, 100, 513, 7)]))
+    return run_on_stand_in(tmp_path_factory.mktemp("products"), PRODUCTS, data=json.dumps(TWO + ONE + [("d", 100, 100, 513, 7)] + TILES))
 
 
 def test_one_launch_form_where_it_gains(product_launches):
@@ -181,3 +186,24 @@ def test_one_launch_form_where_it_gains(product_launches):
         assert len(fast) == (2 if one else 3), (case, fast)
     for names in product_launches["d 100 100 513 7"]:     # beyond the limits of the form
         assert "k_tiny_product" not in " ".join(names) and "k_epilogue" in names[-1]
+
+
+def test_tiles_of_the_gemm(product_launches):
+    """Tiles of 128 x 128 up to 128 tiles of 256 x 256, 8 wavefronts while each has a compute unit; accurate mode's one slice by the
+    same rule."""
+    def tile(names):
+        return [re.search(r"k_int8_gemm(?:_persistent)?I((?:Li\d+E){6})", n).group(1) for n in names if "k_int8_gemm" in n]
+
+    def blocks(n):
+        return (n + 255) // 256
+
+    def expected(large):
+        return ("Li2ELi4ELi2ELi1ELi64ELi6E" if 4 * large <= 256 else "Li2ELi2ELi2ELi2ELi64ELi4E") if large <= 128 else "Li2ELi4ELi4ELi2ELi64ELi4E"
+    seen = set()
+    for case in TILES:
+        fast, accurate, prepared = product_launches["%s %d %d %d %d" % case]
+        slice_ = blocks(case[1]) * blocks(case[2])
+        assert tile(fast) == tile(prepared) == [expected(slice_ * case[4])], case
+        assert tile(accurate) == [expected(slice_), expected(slice_ * case[4])], case
+        seen |= {slice_, slice_ * case[4]}
+    assert {64, 68, 128, 129, 144} <= seen
