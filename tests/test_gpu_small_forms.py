@@ -23,7 +23,11 @@ pytestmark = pytest.mark.gpu
     (64, 1000, 256, 15, np.float64),                 # wide, 32 x 32
     (1000, 64, 256, 15, np.float64),
     (300, 300, 256, 15, np.float64),                 # 100 tiles, which 8 does not divide
-    (100, 90, 3000, 18, np.float64),                 # four groups of moduli, operands for the INT8 GEMM
+    (100, 90, 200, 18, np.float64),                  # four groups of moduli in 256 workgroups, operands for the INT8 GEMM
+    (100, 90, 200, 15, np.float64),                  # three groups in 192
+    (100, 90, 257, 18, np.float64),                  # longer vectors, fewer per workgroup: more than 256, not spread
+    (260, 90, 200, 18, np.float64),                  # the same by their number
+    (100, 90, 3000, 18, np.float64),                 # larger workgroups
     (128, 128, 512, 6, np.float32),                  # two groups, the second of one modulus
     (128, 128, 512, 5, np.float32),                  # one
 ])
@@ -59,3 +63,32 @@ def test_one_launch_and_two_give_the_same_bits(oz, t, m, n, k, N):
     finally:
         left.free()
         right.free()
+
+
+@pytest.mark.parametrize("m,n,k,N,dtype", [
+    (100, 90, 200, 18, np.float64),                  # 64 workgroups x 4 groups of moduli, the most that are spread
+    (100, 90, 200, 15, np.float64),                  # x 3
+    (100, 90, 257, 18, np.float64),                  # beyond: 128 x 4
+    (260, 90, 200, 18, np.float64),                  # beyond: 96 x 4
+    (100, 90, 200, 20, np.float32),                  # one reduction round or two, as the type asks
+    (7, 250, 129, 16, np.float64),                   # the last group of one modulus
+])
+def test_spread_groups_of_moduli_convert_alike(oz, m, n, k, N, dtype):
+    """Conversions whose groups of moduli have workgroups of their own, and those just beyond, against the general kernels:
+    shifts, slices with their padding, and C are equal bit for bit."""
+    import torch
+    from paper_2508_03984_amd import binding as b
+    A, B = (torch.from_numpy(x).cuda() for x in S.gemm_inputs(m, n, k, 2.0, seed=77, dtype=dtype))
+    A[m // 2, :] = 0.0
+    got = {}
+    try:
+        for fused in (True, False):
+            oz.oz2_set_small_conversion(fused)
+            C = oz.matmul(A, B, N)
+            torch.cuda.synchronize()
+            got[fused] = [C.clone()] + [oz.stage_tensor(st).clone() for st in (b.OZ2_STAGE_SHIFT_A, b.OZ2_STAGE_SHIFT_B,
+                                                                               b.OZ2_STAGE_RES_A, b.OZ2_STAGE_RES_B)]
+    finally:
+        oz.oz2_set_small_conversion(True)
+    for x, y, name in zip(got[True], got[False], ("C", "tA", "tB", "residues of A", "residues of B")):
+        assert torch.equal(x, y), name
