@@ -238,7 +238,8 @@ hipError_t launch_kind(const FusedFactor<T> &A, const FusedFactor<T> &B, const S
     const Side<T> a = side_of(A, plan), b = side_of(B, plan);
     // The smallest launches leave compute units idle while each thread walks through all moduli: where there is one for
     // each, every group of moduli gets workgroups of its own, which read the operands again, from the caches (whole calls
-    // repeated in a graph, other operands in each, us: 256^3 N = 14 13.1 -> 12.0, 64^3 N = 15 12.5 -> 11.4, 200^3 N = 15 14.7 -> 13.6).
+    // repeated in a graph, other operands in each, us, all else as it is: 256^3 N = 14 12.9 -> 11.9, 64^3 N = 15 11.5 -> 10.7, 200^3
+    // N = 15 13.6 -> 12.9, 100 x 90 x 200 N = 18 13.4 -> 12.2, 128^3 FP32 N = 8 8.9 -> 8.7).
     const unsigned blocks = a.blocks + b.blocks, groups = (unsigned)((ma.n + kModGroup - 1) / kModGroup);
     if constexpr (KIND == 0) {
         if (fused_split_applies(plan, blocks, groups)) {

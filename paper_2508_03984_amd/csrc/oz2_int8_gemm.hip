@@ -421,10 +421,12 @@ __global__ __launch_bounds__(64 * WM * WN) void k_int8_gemm(const int8_t *__rest
 // tile (its first STAGES - 1 K tiles) is requested before the results of the last one are
 // reduced and stored, and no workgroup is dispatched per tile.  With a short k a tile is a few
 // microseconds of matrix-core work, so that the dispatch between tiles and the wait for the
-// first operands weigh as much as the contraction (16384 x 16384 x 512, N = 15: 3.84 -> 3.09 ms;
-// 2048^3, N = 14: 2.5 % faster).  For long contractions the two forms take the same time (the
+// first operands weigh as much as the contraction.  For long contractions the two forms take the same time (the
 // store phase, which nothing overlaps in either form, is what a tile costs beyond its K loop),
-// so the plain one-workgroup-per-tile kernel is kept there.
+// so the plain one-workgroup-per-tile kernel is kept there.  Prepared operands, us, one workgroup per tile | this form: 8192 x 8192 x 128
+// N = 15 649 | 584, x 512 930 | 886, x 1024 1287 | 1228, x 2048 1898 | 1848, x 4096 3180 | 3138, x 6144 4492 | 4477 (on another card 4507 | 4538);
+// 2048 x 2048 x 512 N = 15 67.6 | 64.0; 2048^3 N = 14 129 | 125, 4096^3 N = 14 773 | 755; 8192^3 N = 8 3197 | 3190 (3215 | 3234), 4096 x 4096 x 8192 FP32 N = 8
+// 798 | 814, 1536 x 1000 x 40000 N = 18 865 | 878.
 template <int WM, int WN, int TM, int TN, int BK, int STAGES, int OUT>
 __global__ __launch_bounds__(64 * WM * WN) void k_int8_gemm_persistent(const int8_t *__restrict__ A,
                                                    const int8_t *__restrict__ B,
@@ -555,7 +557,7 @@ hipError_t launch_out(const int8_t *A, const int8_t *B, void *C, int batch, int6
     if (gemm_small_tiles(pn.rows, pn.cols, batch))
         return launch_small<OUT>(A, B, C, batch, Mp, Np, Kp, k_begin, k_len, pn, mods, stream);
     // 8 wavefronts (2 per SIMD), each 128 x 64: measured against 4 wavefronts of 128 x 128 on
-    // the same device it is 2 % faster at 16 x 16384^3 -- a wavefront that is held up issuing
+    // the same device (with 32x32x32 MFMAs) it is 2 % faster at 16 x 16384^3 -- a wavefront that is held up issuing
     // a load leaves the matrix core to its SIMD partner.
     if (k_len <= kPersistentMaxK)                      // short contraction: see k_int8_gemm_persistent
         return launch_persistent<2, 4, 4, 2, 64, 4, OUT>(A, B, C, batch, Mp, Np, Kp, k_begin, k_len, pn, mods,

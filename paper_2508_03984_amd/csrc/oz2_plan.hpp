@@ -221,8 +221,9 @@ inline Panels launch_panels(int64_t rows, int64_t cols, int64_t Kp) {
     return Q;
 }
 
-// ... and along k: a launch of such a panel is kept to about kLaunchMs of matrix-core work (a
-// round of 256 tiles takes about 13.4 ns per element of k), in equal K ranges that are multiples
+// ... and along k: a launch of such a panel is kept to about kLaunchMs of matrix-core work (counting
+// 13.4 ns per element of k for a round of 256 tiles, what it took with 32x32x32 MFMAs; with 16x16x64 it is 11.5
+// and the target about 6 ms), in equal K ranges that are multiples
 // of 8192; the results of the ranges are folded modulo p_s in the GEMM's store phase like the
 // ranges of 2^17 that exactness requires (Section 4.3).  Returns the length of a K range: Kp
 // itself when one launch is short enough, never more than OZ2_MAX_K.  Measured: 8192 x 8192 x

@@ -32,7 +32,7 @@ OZ2_HOST_DEVICE inline int divide(int x, Divisor d) { return (int)((uint64_t)(ui
 // tiles that are multiples of 16 have the same blocks more simply, dealt so that the upper and the lower half
 // of a region belong to four XCDs each (0.4 to 0.6 % faster at 16384^3 and 8192 x 8192 x 512).
 // Against ids in row-major order, where e.g. 8 tile columns put 4 slices with 8 A tile rows each and one B tile
-// row on an XCD (36 panels for its 32 tiles instead of 12), whole calls repeated in a graph, us: 1024^3 N = 15 44.7 -> 42.3,
+// row on an XCD (36 panels for its 32 tiles instead of 12), whole calls repeated in a graph, with 32x32x32 MFMAs, us: 1024^3 N = 15 44.7 -> 42.3,
 // 1500 x 1111 x 3001 (A transposed) N = 16 160.5 -> 133.1, 2048^3 FP32 N = 7 97.1 -> 90.4, 1536 x 1000 x 40000 N = 18
 // 1665 -> 1643, 5000 x 5000 x 512 N = 15 417 -> 400.
 //

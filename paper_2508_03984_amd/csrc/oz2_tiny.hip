@@ -192,8 +192,8 @@ hipError_t launch_tiny_product(const int8_t *A, const int8_t *B, uint8_t *U, int
         return hipGetLastError();
     };
     // Tiles of 16 x 16 where these and the padding have a compute unit each: four times as many units fetch operands and
-    // accumulate (whole calls repeated in a graph, other operands in each, us, 32 x 32 | 16 x 16: 256^3 N = 14 13.0 | 12.1, 200^3
-    // N = 15 14.2 | 13.6, 128^3 N = 14 12.5 | 11.5, 256 x 256 x 512 FP32 N = 6 11.6 | 10.1).
+    // accumulate (repeated in a graph, other operands in each call, us, 32 x 32 | 16 x 16: 256^3 N = 14 12.8 | 11.9, prepared 8.0 | 7.1; 200^3
+    // N = 15 13.5 | 12.9, 8.2 | 7.3; 128^3 N = 14 11.6 | 10.7, 7.7 | 6.9; 256 x 256 x 512 FP32 N = 6 11.4 | 9.7, 6.8 | 5.1).
     if (tiny_small_tiles(m, n)) return go(std::integral_constant<int, 1>{}, tiny_grid(m, n, 16));
     return go(std::integral_constant<int, 2>{}, tiny_grid(m, n, 32));
 }
