@@ -271,20 +271,22 @@ inline bool tiny_small_tiles(int64_t m, int64_t n) {
 // 400 x 400 x 1024 10.6 | 11.4, 128 x 128 x 1024 N = 14 10.0 | 10.2.
 //
 // A call that converts its factors itself gains less, and nothing where C is about as wide as high and the moduli are many
-// (whole calls, graph | one after another from Python, us, two launches -> one; taken back to two: 300 x 300 x 128 N = 15 12.3 -> 13.6 | 12.6 -> 13.5, 320 x 320 x 256
-// N = 16 +1.0 | +0.7, 400 x 400 x 384 FP32 N = 8 13.3 -> 13.8 | 13.4 -> 13.9, 512 x 300 x 128 N = 16 +0.7 | +1.0, with tiles of 16 x 16 200^3 N = 16 +1.0 | +1.4;
-// taken: 256^3 N = 14 0 | -0.6, 128^3 N = 14 +0.3 | -0.7, 400 x 400 x 128 FP32 N = 8 10.7 -> 9.9 | 11.8 -> 10.3, 512 x 512 x 512 FP32 N = 6
-// 14.3 -> 13.2 | 14.2 -> 13.0, 512 x 512 x 256 N = 15 16.5 -> 16.0 | 16.4 -> 15.8, 1000 x 250 x 256 17.3 -> 15.3 | 17.6 -> 15.3, 8000 x 30 x 64 27.5 -> 20.5).
-// Of those taken, N = 14 and 15 with Kp = 256 and tiles of 16 x 16 are even in a graph and lose up to 0.9 one after another,
-// Kp = 384 with N = 8 to 10 and C wider than 448 loses up to 1.7.  Accurate mode shows the same signs.
+// (whole calls, in a graph | one after another from Python, us, two launches -> one; two are taken for 300 x 300 x 128 N = 15
+// 12.3 -> 13.6 | 12.6 -> 13.5, 320 x 320 x 256 N = 16 +1.0 | +0.7, 400 x 400 x 384 FP32 N = 8 13.3 -> 13.8 | 13.4 -> 13.9, 512 x 300 x 128
+// N = 16 +0.7 | +1.0, with tiles of 16 x 16 200^3 N = 16 +1.0 | +1.4; one for 256^3 N = 14 0 | -0.6, 128^3 N = 14 +0.3 | -0.7,
+// 400 x 400 x 128 FP32 N = 8 10.7 -> 9.9 | 11.8 -> 10.3, 512 x 512 x 512 FP32 N = 6 14.3 -> 13.2 | 14.2 -> 13.0, 512 x 512 x 256 N = 15
+// 16.5 -> 16.0 | 16.4 -> 15.8, 1000 x 250 x 256 17.3 -> 15.3 | 17.6 -> 15.3, 8000 x 30 x 64 27.5 -> 20.5 | 27.9 -> 20.3).
+// Of those taken, 512 x 512 x 128 N = 12 gains 0.3 in a graph and loses 0.3 one after another, 64 x 250 x 256 N = 16 gains 0.4 | 0;
+// N = 14 and 15 with Kp = 256 and tiles of 16 x 16 are even in a graph and lose up to 0.9 one after another, Kp = 384 with N = 8 to 10
+// and C wider than 448 loses up to 1.7.  Accurate mode shows the same signs.
 inline bool tiny_product_applies(int64_t m, int64_t n, int64_t Kp, int N, bool prepared) {
     if ((m + 31) / 32 * ((n + 31) / 32) > 256 || (N + 15) / 16 * Kp > 512 || Kp * N > 4096) return false;
-    const int64_t longer = std::max(m, n);
-    if (prepared || longer >= 4 * std::min(m, n)) return true;
-    if (tiny_small_tiles(m, n)) return N <= 15 || longer <= 64;
+    const int64_t longer = std::max(m, n), shorter = std::min(m, n);
+    if (prepared || longer >= 4 * shorter) return true;
+    if (tiny_small_tiles(m, n)) return N <= 15 || shorter <= 64;
     if (N <= 6 || (N <= 10 && Kp <= 256)) return true;
     if (N > 16) return longer > 384;       // the INT8 GEMM of the other form has a second round
-    return Kp > 128 && longer > 448;
+    return longer > 448 && (Kp > 128 || N <= 13);
 }
 
 // The accumulation gives each thread kEpilogueColumns consecutive columns of a row, in workgroups of kEpilogueThreads, and works

@@ -162,7 +162,8 @@ TWO = [("d", 300, 300, 128, 15), ("d", 400, 400, 256, 15), ("s", 400, 400, 384, 
        ("d", 65, 66, 100, 16), ("d", 384, 384, 128, 17), ("d", 512, 512, 128, 16), ("d", 512, 130, 128, 16), ("s", 300, 300, 257, 7)]
 ONE = [("d", 256, 256, 256, 14), ("d", 256, 256, 256, 15), ("d", 64, 64, 64, 20), ("d", 512, 128, 128, 16), ("d", 100, 401, 256, 16),
        ("d", 449, 449, 256, 16), ("d", 385, 385, 128, 17), ("s", 400, 400, 256, 8), ("s", 400, 400, 256, 10), ("s", 300, 300, 512, 6),
-       ("s", 449, 300, 500, 8), ("d", 8000, 30, 64, 15), ("d", 1, 1, 1, 2)]
+       ("s", 449, 300, 500, 8), ("d", 449, 512, 128, 13), ("d", 64, 250, 256, 16),
+       ("d", 8000, 30, 64, 15), ("d", 1, 1, 1, 2)]
 
 # Products whose INT8 GEMM has 127 to 129 tiles of 256 x 256 or thereabouts, and 256 and 272 of 128 x 128
 TILES = [("s", 1024, 1024, 600, 8), ("d", 2048, 2048, 600, 2), ("d", 256, 256 * 43, 600, 3), ("d", 512, 512, 600, 16),
