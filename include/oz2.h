@@ -96,8 +96,8 @@ oz2_status oz2_sgemm(int64_t m, int64_t n, int64_t k, float alpha,
  * result (bit for bit) and errors as oz2_dgemm, but the workspace is a fixed array of
  * OZ2_NOALLOC_WORKSPACE_BYTES in the library's device image (each GPU the library runs on holds
  * its copy until the process ends; the first call on a GPU looks its address up there), so the
- * call neither allocates nor frees anything, on the device or through any library.  A product whose workspace (oz2_workspace_bytes) exceeds that
- * size returns OZ2_WORKSPACE and does nothing: with 16 moduli the limit is reached at about
+ * call neither allocates nor frees anything, on the device or through any library.  A product whose workspace (oz2_workspace_bytes, without the
+ * planes of K ranges described there) exceeds that size returns OZ2_WORKSPACE and does nothing: with 16 moduli the limit is reached at about
  * m = n = k = 1100.  All calls on one GPU share that GPU's array: the caller orders them (one
  * stream, or events); calls that overlap on one GPU race.  Nothing is assumed about what an
  * earlier call left in the array.  Contexts, options and the diagnostics (oz2_stage_ptr, stage
@@ -251,7 +251,10 @@ oz2_status oz2_ctx_sgemm_prepared(oz2_context *ctx, const oz2_operand *left, con
  * per-column partial results behind them), the INT8 residue slices of A and B (Algorithm 1 lines 4-5)
  * and the reduced products U_s (line 7; or the INT32 products of line 6 after
  * oz2_set_int32_products(1)): oz2_workspace_bytes gives the size for a
- * problem (0 if the arguments are unsupported).  oz2_set_workspace hands the
+ * problem (0 if the arguments are unsupported).  For a small C and a long contraction that includes
+ * planes for the residues of up to 16 K ranges, which are then contracted at once so that more of the compute units have work;
+ * a workspace that has room for everything but these (a smaller caller-owned one, a limit, the library's own buffer
+ * from an earlier call) serves such a product with one range, at the same result, bit for bit.  oz2_set_workspace hands the
  * library a caller-owned device buffer (kept, not freed, must stay valid until
  * replaced; 256-byte aligned); with (NULL, 0) the library goes back to
  * allocating its own buffer with hipMalloc (on the device that is current at the

@@ -61,10 +61,11 @@ Ctx &default_context() {
 inline Ctx &resolve(oz2_context *c) { return c ? *c : default_context(); }
 
 // Makes at least `need_min` bytes of workspace available, `need_whole` if nothing limits it;
-// *have receives the bytes the call may use.  Growing the library's own buffer (or moving it to
+// *have receives the bytes the call may use.  `extra` bytes more are allocated with a new buffer, if they are to be had, but a
+// buffer that lacks only these is not replaced.  Growing the library's own buffer (or moving it to
 // another device) waits for the device, frees and allocates: the only synchronising step of a
 // product call, and only when the buffer is too small.
-oz2_status ensure_workspace(Ctx &g, size_t need_whole, size_t need_min, size_t *have) {
+oz2_status ensure_workspace(Ctx &g, size_t need_whole, size_t need_min, size_t extra, size_t *have) {
     if (g.ws && !g.ws_owned) {                                // caller-owned: take it as it is
         if (g.ws_bytes < need_min) return OZ2_WORKSPACE;
         *have = g.ws_bytes;
@@ -86,7 +87,9 @@ oz2_status ensure_workspace(Ctx &g, size_t need_whole, size_t need_min, size_t *
             if (e != hipSuccess) return OZ2_HIP_ERROR;
         }
         void *p = nullptr;
-        if (hipMalloc(&p, want) != hipSuccess) { (void)hipGetLastError(); return OZ2_WORKSPACE; }
+        const size_t more = g.ws_limit ? std::max(want, std::min(g.ws_limit, want + extra)) : want + extra;
+        if (more > want && hipMalloc(&p, more) == hipSuccess) want = more;
+        else if (hipMalloc(&p, want) != hipSuccess) { (void)hipGetLastError(); return OZ2_WORKSPACE; }
         g.ws = static_cast<char *>(p); g.ws_bytes = want; g.ws_owned = true; g.ws_device = dev;
     }
     *have = g.ws_limit ? std::min(g.ws_bytes, std::max(g.ws_limit, need_min)) : g.ws_bytes;
@@ -160,7 +163,7 @@ hipError_t launch_block_residues(const T *X, int64_t ld, bool k_contiguous, int6
 // whose reduced results are folded together modulo p_s), then its accumulation and unscaling.
 template <typename T>
 oz2_status run_products(Ctx &g, const Layout &L, const Panels &P, const int8_t *rA, const int8_t *rB,
-                        const int32_t *tA, const int32_t *tB, void *prod, const ModArgs &ma,
+                        const int32_t *tA, const int32_t *tB, void *prod, size_t prod_bytes, const ModArgs &ma,
                         double alpha, double beta, T *C, int64_t ldc, hipStream_t stream) {
     // The product buffer holds one panel of C at a time: [N][rows][cols] (all of C if P.count is 1).
     // The GEMM launches of a panel are cut further (launch_panels, launch_k_len), each writing its
@@ -180,22 +183,24 @@ oz2_status run_products(Ctx &g, const Layout &L, const Panels &P, const int8_t *
             const int64_t rows = std::min(P.pr, L.Mp - row0), cols = std::min(P.pc, L.Np - col0);
             const Panels Q = g.cut_launches ? launch_panels(rows, cols, L.Kp) : Panels{rows, cols, 1};
             const int64_t k_len = g.cut_launches && L.prod_u8 ? launch_k_len(L.Kp, L.N, Q) : std::min<int64_t>(L.Kp, OZ2_MAX_K);
+            const int ranges = P.count == 1 && Q.count == 1 && k_len == L.Kp && prod_bytes >= L.prod_whole + L.prod_ranges ? L.ranges : 1;
             for (int64_t r1 = 0; r1 < rows; r1 += Q.pr)
                 for (int64_t c1 = 0; c1 < cols; c1 += Q.pc) {
-                    const GemmPanel pn{row0 + r1, std::min(Q.pr, rows - r1), col0 + c1, std::min(Q.pc, cols - c1), cols,
-                                       rows * cols};
+                    const int64_t pr = std::min(Q.pr, rows - r1), pc = std::min(Q.pc, cols - c1);
+                    const GemmPanel pn{row0 + r1, pr, col0 + c1, pc, cols, rows * cols, std::min(pr, L.m - row0 - r1),
+                                       std::min(pc, L.n - col0 - c1)};
                     void *dst = static_cast<char *>(prod) + (size_t)(r1 * cols + c1) * entry;
                     for (int64_t k0 = 0; k0 < L.Kp; k0 += k_len) {
                         ++g.last_gemm_launches;
                         OZ2_TRY(launch_int8_gemm(rA, rB, dst, L.N, L.Mp, L.Np, L.Kp, k0, std::min<int64_t>(k_len, L.Kp - k0),
-                                                 L.prod_u8, k0 > 0, &ma, stream, &pn));
+                                                 L.prod_u8, k0 > 0, &ma, stream, &pn, ranges));
                     }
                 }
             if (++done == P.count)                            // stage times: the last accumulation only
                 if (oz2_status st = mark(g, 3, stream)) return st;
             OZ2_TRY(launch_epilogue<T>(prod, L.prod_u8, rows, cols, std::min(L.m - row0, rows),
                                        std::min(L.n - col0, cols), tA + row0, tB + col0, ma, alpha, beta,
-                                       C + row0 * ldc + col0, ldc, stream));
+                                       C + row0 * ldc + col0, ldc, stream, ranges));
         }
     return mark(g, 4, stream);
 }
@@ -265,7 +270,7 @@ oz2_status run_overlapped(Ctx &g, const Layout &L, const Panels &P, const T *A, 
         if (j == 0) OZ2_TRY(hipStreamWaitEvent(stream, ev[eA + i], 0));
         if (i == 0) OZ2_TRY(hipStreamWaitEvent(stream, ev[eB + j], 0));
         if (g.profiling) OZ2_TRY(hipEventRecord(g.time_ev[2 * p], stream));
-        const GemmPanel pn{row0, rows, col0, cols, cols, rows * cols};
+        const GemmPanel pn{row0, rows, col0, cols, cols, rows * cols, std::min(rows, L.m - row0), std::min(cols, L.n - col0)};
         for (int64_t k0 = 0; k0 < L.Kp; k0 += OZ2_MAX_K) {
             const int64_t len = std::min<int64_t>(OZ2_MAX_K, L.Kp - k0);
             ++g.last_gemm_launches;
@@ -312,7 +317,7 @@ oz2_status gemm_impl(Ctx &g, int opA, int opB, int64_t m, int64_t n, int64_t k, 
                                  : L.prod_whole;
     size_t have = 0;
     Panels P{};
-    if (oz2_status st = ensure_workspace(g, L.off_prod + prod_want, L.off_prod + L.prod_min, &have)) return st;
+    if (oz2_status st = ensure_workspace(g, L.off_prod + prod_want, L.off_prod + L.prod_min, L.prod_ranges, &have)) return st;
     if (!plan_panels(L, have - L.off_prod, &P)) return OZ2_WORKSPACE;
     const Panels Po = overlap_panels(L, P);                // a workspace limit may have made the panels smaller
     const bool overlapped = g.overlap && overlap_applies(L.Kp, Po.count);
@@ -342,13 +347,13 @@ oz2_status gemm_impl(Ctx &g, int opA, int opB, int64_t m, int64_t n, int64_t k, 
         const int ranges = (int)((L.Kp + OZ2_MAX_K - 1) / OZ2_MAX_K);
         OZ2_TRY(launch_accurate_prescale<T>(A, lda, a_kc, B, ldb, b_kc, m, n, k, ranges, scratch, rA, rB, L.Mp,
                                             L.Np, L.Kp, g.small_conversion, stream));
-        const GemmPanel all{0, L.Mp, 0, L.Np, L.Np, L.Mp * L.Np};      // nothing is stored: no panels needed
+        const GemmPanel all{0, L.Mp, 0, L.Np, L.Np, L.Mp * L.Np, m, n};  // nothing is stored: no panels needed
         for (int r = 0; r < ranges; ++r) {
             int *row_max = nullptr, *col_max = nullptr;
             accurate_maxima(scratch, m, n, r, &row_max, &col_max);
             const int64_t k0 = (int64_t)r * OZ2_MAX_K;
             OZ2_TRY(launch_int8_gemm_maxima(rA, rB, L.Mp, L.Np, L.Kp, k0, std::min<int64_t>(OZ2_MAX_K, L.Kp - k0),
-                                            all, m, n, row_max, col_max, stream));
+                                            all, row_max, col_max, stream));
         }
         OZ2_TRY(launch_accurate_finish(m, n, ranges, make_accu_shift_args(tab), scratch, tA, tB, stream));
     } else {
@@ -376,7 +381,7 @@ oz2_status gemm_impl(Ctx &g, int opA, int opB, int64_t m, int64_t n, int64_t k, 
         if (!fuse[1]) OZ2_TRY(launch_any_residues<T>(B, ldb, b_kc, n, k, tB, ma, rB, L.Np, L.Kp, stream));
     }
     if (oz2_status st = mark(g, 2, stream)) return st;
-    if (oz2_status st = run_products<T>(g, L, P, rA, rB, tA, tB, prod, ma, alpha, beta, C, ldc, stream)) return st;
+    if (oz2_status st = run_products<T>(g, L, P, rA, rB, tA, tB, prod, have - L.off_prod, ma, alpha, beta, C, ldc, stream)) return st;
     g.ev_recorded = g.profiling;
     return OZ2_OK;
 }
@@ -453,13 +458,13 @@ oz2_status prepared_impl(Ctx &g, const oz2_operand *l, const oz2_operand *r, dou
     const Layout L = make_layout(l->rows, r->rows, l->k, l->N, !g.int32_products, false);
     size_t have = 0;
     Panels P{};
-    if (oz2_status st = ensure_workspace(g, L.prod_whole, L.prod_min, &have)) return st;
+    if (oz2_status st = ensure_workspace(g, L.prod_whole, L.prod_min, L.prod_ranges, &have)) return st;
     if (!plan_panels(L, have, &P)) return OZ2_WORKSPACE;
     g.last_panels = P; g.have_panels = true; g.last_overlapped_panels = 0; g.last_gemm_launches = 0;
     g.have_last = g.have_last_prod = false; g.ev_recorded = false;
     for (int i = 0; i < 3; ++i)
         if (oz2_status st = mark(g, i, stream)) return st;
-    if (oz2_status st = run_products<T>(g, L, P, l->res, r->res, l->t, r->t, g.ws, ma, alpha, beta, C, ldc, stream))
+    if (oz2_status st = run_products<T>(g, L, P, l->res, r->res, l->t, r->t, g.ws, have, ma, alpha, beta, C, ldc, stream))
         return st;
     g.ev_recorded = g.profiling;
     return OZ2_OK;
@@ -542,7 +547,7 @@ size_t oz2_ctx_workspace_bytes(oz2_context *ctx, int64_t m, int64_t n, int64_t k
     Ctx &g = resolve(ctx);
     std::lock_guard<std::mutex> lock(g.mu);
     const Layout L = make_layout(m, n, k, num_moduli, !g.int32_products);
-    return L.off_prod + L.prod_whole;
+    return L.off_prod + L.prod_whole + L.prod_ranges;
 }
 
 size_t oz2_ctx_workspace_min_bytes(oz2_context *ctx, int64_t m, int64_t n, int64_t k, int num_moduli) {

@@ -12,6 +12,21 @@ __device__ __forceinline__ uint32_t pack_low_bytes(uint32_t w0, uint32_t w1, uin
     return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
 }
 
+// (a + b) mod p on each of the four bytes of a and b, all of them below p <= 256: the even and
+// the odd bytes as two pairs of 16-bit sums (at most 510), each reduced by one packed unsigned
+// minimum (s - p wraps to a large number when s < p).
+typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t add_mod_bytes(uint32_t a, uint32_t b, int p) {
+    const us2 pp = {(unsigned short)p, (unsigned short)p};
+    auto reduce = [&](uint32_t x) {
+        const us2 v = __builtin_bit_cast(us2, x);
+        return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(v, (us2)(v - pp)));
+    };
+    const uint32_t even = reduce((a & 0x00ff00ffu) + (b & 0x00ff00ffu));
+    const uint32_t odd = reduce(((a >> 8) & 0x00ff00ffu) + ((b >> 8) & 0x00ff00ffu));
+    return even | (odd << 8);
+}
+
 // byte_mod_word on the device, for four sums, whose residues come packed: 3.75 vector instructions per entry, none of them a
 // 32-bit multiplication (the mulhi form of mod_small has two).  All four v_dot4 first, because what reads the result of one has
 // to stay three instructions behind it.  Measured for whole calls, us, mulhi form -> this one with the dot product converted by a

@@ -78,21 +78,6 @@ __device__ inline int swizzle_mask(int row) {
 //                (k_int8_gemm only.)
 enum { kOutI32 = 0, kOutI32Fold = 1, kOutU8 = 2, kOutU8Fold = 3, kOutMax = 4 };
 
-// (a + b) mod p on each of the four bytes of a and b, all of them below p <= 256: the even and
-// the odd bytes as two pairs of 16-bit sums (at most 510), each reduced by one packed unsigned
-// minimum (s - p wraps to a large number when s < p).
-typedef unsigned short us2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t add_mod_bytes(uint32_t a, uint32_t b, int p) {
-    const us2 pp = {(unsigned short)p, (unsigned short)p};
-    auto reduce = [&](uint32_t x) {
-        const us2 v = __builtin_bit_cast(us2, x);
-        return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(v, (us2)(v - pp)));
-    };
-    const uint32_t even = reduce((a & 0x00ff00ffu) + (b & 0x00ff00ffu));
-    const uint32_t odd = reduce(((a >> 8) & 0x00ff00ffu) + ((b >> 8) & 0x00ff00ffu));
-    return even | (odd << 8);
-}
-
 struct GemmMods {                       // moduli of the slices and what their reductions need
     int32_t p[kMaxModuli];
     int32_t pinv_prime[kMaxModuli];     // mulhi reduction (int32 forms)
@@ -335,10 +320,10 @@ struct GemmCore {
     // row (l % 16) of the C block and the four consecutive columns 4 * (l / 16) + {0,1,2,3}.  The
     // reduction to bytes is that of oz2_bytemod.hpp; the int32 forms use the mulhi reduction of Section 4.3.
     template <int OUT>
-    __device__ __forceinline__ void store(const v4i (&acc)[FM][FN], void *C, int s, int64_t bm, int64_t bn,
+    __device__ __forceinline__ void store(const v4i (&acc)[FM][FN], void *C, int s, int plane, int64_t bm, int64_t bn,
                                           int64_t c_ld, int64_t c_plane, const GemmMods &mods) const {
         const int p = mods.p[s], pv = mods.pinv_prime[s];
-        const int64_t c_off = (int64_t)s * c_plane + bm * c_ld + bn;   // C: [slice][row][column]
+        const int64_t c_off = (int64_t)plane * c_plane + bm * c_ld + bn;   // C: [plane][row][column]
         if (OUT == kOutU8 || OUT == kOutU8Fold) {
             const ByteMod b = mods.byte_mod[s];
             // The four residues a lane holds of a block pack into one dword; the lanes l, l + 16, l + 32 and
@@ -396,23 +381,29 @@ template <int WM, int WN, int TM, int TN, int BK, int STAGES, int OUT>
 __global__ __launch_bounds__(64 * WM * WN) void k_int8_gemm(const int8_t *__restrict__ A,
                                                    const int8_t *__restrict__ B,
                                                    void *__restrict__ C, int64_t Mp,
-                                                   int64_t Np, int64_t KB, int kb0, int KT,
+                                                   int64_t Np, int64_t KB, int kb0,
                                                    int64_t c_ld, int64_t c_plane,
-                                                   TileMap tmap, GemmMods mods) {
+                                                   GemmGrid grid, GemmMods mods) {
     typedef GemmCore<WM, WN, TM, TN, BK, STAGES> Core;
+    if (OUT == kOutU8 && Core::BM < kPadMN && (int)blockIdx.x >= grid.map.total) {
+        const GemmItem it = padding_item(grid, (int)blockIdx.x - grid.map.total);
+        uint8_t *const u = static_cast<uint8_t *>(C) + it.plane * c_plane + (int64_t)it.tr * Core::BM * c_ld + it.tc * Core::BN;
+        for (int q = threadIdx.x; q < Core::BM * Core::BN / 16; q += Core::THREADS)
+            *reinterpret_cast<v4i *>(u + q / (Core::BN / 16) * c_ld + q % (Core::BN / 16) * 16) = v4i{0, 0, 0, 0};
+        return;
+    }
     const Core core(Mp, Np);
-    int s, tile_r, tile_c;
-    map_tile(tmap, (int)blockIdx.x, s, tile_r, tile_c);
-    const int8_t *src = core.tile_source(A, B, s, tile_r, tile_c, Mp, Np, KB, kb0);
-    core.issue_head(src, KT);
+    const GemmItem it = map_item(grid, (int)blockIdx.x);
+    const int8_t *src = core.tile_source(A, B, it.s, it.tr, it.tc, Mp, Np, KB, kb0 + it.kb);
+    core.issue_head(src, it.kt);
     v4i acc[Core::FM][Core::FN];
-    core.contract(src, KT, first_acc(OUT), acc);
-    const int64_t bm = (int64_t)tile_r * Core::BM, bn = (int64_t)tile_c * Core::BN;
+    core.contract(src, it.kt, first_acc(OUT), acc);
+    const int64_t bm = (int64_t)it.tr * Core::BM, bn = (int64_t)it.tc * Core::BN;
     if (OUT == kOutMax) {
         int *rmax = static_cast<int *>(C);
         core.store_maxima(acc, rmax, rmax + c_plane, bm, bn, (int)(c_ld & 0xffffffff), (int)(c_ld >> 32));
     } else {
-        core.template store<OUT>(acc, C, s, bm, bn, c_ld, c_plane, mods);
+        core.template store<OUT>(acc, C, it.s, it.plane, bm, bn, c_ld, c_plane, mods);
     }
 }
 
@@ -463,7 +454,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_int8_gemm_persistent(const int
         if (next < tmap.total) core.issue_head(src_next, KT);
         // contract<kStores> takes the stores for younger than all of the head's loads: none may move across.
         pin_memory_order();
-        core.template store<OUT>(acc, C, s, (int64_t)tile_r * Core::BM, (int64_t)tile_c * Core::BN, c_ld, c_plane,
+        core.template store<OUT>(acc, C, s, s, (int64_t)tile_r * Core::BM, (int64_t)tile_c * Core::BN, c_ld, c_plane,
                                  mods);
         pin_memory_order();
         if (next >= tmap.total) break;                    // uniform over the workgroup
@@ -485,129 +476,126 @@ int compute_units() {
     return cached;
 }
 
+// What the launches of one product (or one slice of it) have in common.
+struct GemmLaunch {
+    const int8_t *A, *B;
+    void *C;
+    int batch;
+    int64_t Mp, Np, Kp, k_begin, k_len;
+    GemmPanel pn;
+    int ranges;                                               // K ranges with planes of their own
+    GemmMods mods;
+    hipStream_t stream;
+};
+
+template <typename Kernel>
+hipError_t allow_lds(Kernel kernel, size_t bytes, int &attr_device) {
+    int dev = -1;
+    if (hipError_t e = hipGetDevice(&dev)) return e;
+    if (attr_device != dev) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        if (e != hipSuccess) return e;
+        attr_device = dev;
+    }
+    return hipSuccess;
+}
+
+// The tiles of a launch; false: more than an int can number (with a grid's stride to spare).
+inline bool tiles_of(const GemmLaunch &g, int tile, GemmGrid *grid) {
+    const int64_t total = (g.pn.rows / tile) * (g.pn.cols / tile) * g.batch * g.ranges;
+    if (total > 0x7fff0000) return false;
+    *grid = make_gemm_grid(g.pn.rows, g.pn.cols, g.pn.valid_rows, g.pn.valid_cols, tile, g.batch, g.ranges, (int)(g.k_len / kBlockK));
+    return true;
+}
+
 template <int WM, int WN, int TM, int TN, int BK, int STAGES, int OUT>
-hipError_t launch_persistent(const int8_t *A, const int8_t *B, void *C, int batch, int64_t Mp, int64_t Np,
-                             int64_t Kp, int64_t k_begin, int64_t k_len, const GemmPanel &pn,
-                             const GemmMods &mods, hipStream_t stream) {
+hipError_t launch_persistent(const GemmLaunch &g) {
     constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN;
     constexpr size_t lds_bytes = (size_t)STAGES * (BM + BN) * BK;
     static_assert(lds_bytes > 80 * 1024, "one workgroup per compute unit is assumed");
     static thread_local int attr_device = -1;                // the attribute is per device (set again per thread: harmless)
-    int dev = -1;
-    if (hipError_t e = hipGetDevice(&dev)) return e;
-    if (attr_device != dev) {
-        hipError_t e = hipFuncSetAttribute(
-            reinterpret_cast<const void *>(&k_int8_gemm_persistent<WM, WN, TM, TN, BK, STAGES, OUT>),
-            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-        if (e != hipSuccess) return e;
-        attr_device = dev;
-    }
-    const int64_t total = (pn.rows / BM) * (pn.cols / BN) * batch;
-    if (total > 0x7fff0000) return hipErrorInvalidValue;      // tile ids (plus one grid stride) fit an int
-    const TileMap tm = make_tile_map((int)(pn.rows / BM), (int)(pn.cols / BN), (int)total);
+    if (hipError_t e = allow_lds(&k_int8_gemm_persistent<WM, WN, TM, TN, BK, STAGES, OUT>, lds_bytes, attr_device)) return e;
+    GemmGrid grid;
+    if (!tiles_of(g, BM, &grid)) return hipErrorInvalidValue;
+    const TileMap &tm = grid.map;
     // The grid is a multiple of 8, so that tile id -> XCD stays id mod 8 as in the tile map.
-    const int64_t units = compute_units() / 8 * 8;
+    const int units = compute_units() / 8 * 8;
     if (units < 8) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_int8_gemm_persistent<WM, WN, TM, TN, BK, STAGES, OUT>),
-                       dim3((unsigned)std::min(total, units)), dim3(64 * WM * WN), lds_bytes, stream,
-                       A + pn.row0 * BK, B + pn.col0 * BK, C, Mp, Np, Kp / BK, (int)(k_begin / BK),
-                       (int)(k_len / BK), pn.c_ld, pn.c_plane, tm, mods);
+    hipLaunchKernelGGL((k_int8_gemm_persistent<WM, WN, TM, TN, BK, STAGES, OUT>), dim3((unsigned)std::min(tm.total, units)),
+                       dim3(64 * WM * WN), lds_bytes, g.stream, g.A + g.pn.row0 * BK, g.B + g.pn.col0 * BK, g.C, g.Mp, g.Np, g.Kp / BK,
+                       (int)(g.k_begin / BK), (int)(g.k_len / BK), g.pn.c_ld, g.pn.c_plane, tm, g.mods);
     return hipGetLastError();
 }
 
 template <int WM, int WN, int TM, int TN, int BK, int STAGES, int OUT>
-hipError_t launch(const int8_t *A, const int8_t *B, void *C, int batch, int64_t Mp, int64_t Np,
-                  int64_t Kp, int64_t k_begin, int64_t k_len, const GemmPanel &pn,
-                  const GemmMods &mods, hipStream_t stream) {
+hipError_t launch(const GemmLaunch &g) {
     constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN;
     constexpr size_t lds_bytes = (size_t)STAGES * (BM + BN) * BK;
     static thread_local int attr_device = -1;                // the attribute is per device (set again per thread: harmless)
-    int dev = -1;
-    if (hipError_t e = hipGetDevice(&dev)) return e;
-    if (attr_device != dev) {
-        hipError_t e = hipFuncSetAttribute(
-            reinterpret_cast<const void *>(&k_int8_gemm<WM, WN, TM, TN, BK, STAGES, OUT>),
-            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-        if (e != hipSuccess) return e;
-        attr_device = dev;
-    }
-    const int64_t total = (pn.rows / BM) * (pn.cols / BN) * batch;
-    if (total > 0x7fff0000) return hipErrorInvalidValue;      // tile ids fit an int
-    const TileMap tm = make_tile_map((int)(pn.rows / BM), (int)(pn.cols / BN), (int)total);
-    hipLaunchKernelGGL((k_int8_gemm<WM, WN, TM, TN, BK, STAGES, OUT>), dim3((unsigned)total),
-                       dim3(64 * WM * WN), lds_bytes, stream, A + pn.row0 * BK, B + pn.col0 * BK, C, Mp,
-                       Np, Kp / BK, (int)(k_begin / BK), (int)(k_len / BK), pn.c_ld, pn.c_plane, tm, mods);
+    if (hipError_t e = allow_lds(&k_int8_gemm<WM, WN, TM, TN, BK, STAGES, OUT>, lds_bytes, attr_device)) return e;
+    GemmGrid grid;
+    if (!tiles_of(g, BM, &grid)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_int8_gemm<WM, WN, TM, TN, BK, STAGES, OUT>), dim3((unsigned)(grid.map.total + (OUT == kOutU8 ? grid.padding : 0))),
+                       dim3(64 * WM * WN), lds_bytes, g.stream, g.A + g.pn.row0 * BK, g.B + g.pn.col0 * BK, g.C, g.Mp, g.Np, g.Kp / BK,
+                       (int)(g.k_begin / BK), g.pn.c_ld, g.pn.c_plane, grid, g.mods);
     return hipGetLastError();
 }
 
-// Tiles of 128 x 128 (gemm_small_tiles, oz2_plan.hpp).
 template <int OUT>
-hipError_t launch_small(const int8_t *A, const int8_t *B, void *C, int batch, int64_t Mp, int64_t Np,
-                        int64_t Kp, int64_t k_begin, int64_t k_len, const GemmPanel &pn,
-                        const GemmMods &mods, hipStream_t stream) {
-    if (gemm_one_tile_per_unit(pn.rows, pn.cols, batch))
-        return launch<2, 4, 2, 1, 64, 6, OUT>(A, B, C, batch, Mp, Np, Kp, k_begin, k_len, pn, mods, stream);
-    return launch<2, 2, 2, 2, 64, 4, OUT>(A, B, C, batch, Mp, Np, Kp, k_begin, k_len, pn, mods, stream);
-}
-
-template <int OUT>
-hipError_t launch_out(const int8_t *A, const int8_t *B, void *C, int batch, int64_t Mp, int64_t Np,
-                      int64_t Kp, int64_t k_begin, int64_t k_len, const GemmPanel &pn,
-                      const GemmMods &mods, hipStream_t stream) {
-    if (gemm_small_tiles(pn.rows, pn.cols, batch))
-        return launch_small<OUT>(A, B, C, batch, Mp, Np, Kp, k_begin, k_len, pn, mods, stream);
+hipError_t launch_out(const GemmLaunch &g) {
+    const GemmTile tile = gemm_plan(g.pn.valid_rows, g.pn.valid_cols, g.batch, g.k_len / kBlockK, g.ranges > 1).tile;
+    if (tile == GemmTile::kOnePerUnit) return launch<2, 4, 2, 1, 64, 6, OUT>(g);
+    if (tile == GemmTile::kTwoPerUnit) return launch<2, 2, 2, 2, 64, 4, OUT>(g);
     // 8 wavefronts (2 per SIMD), each 128 x 64: measured against 4 wavefronts of 128 x 128 on
     // the same device (with 32x32x32 MFMAs) it is 2 % faster at 16 x 16384^3 -- a wavefront that is held up issuing
     // a load leaves the matrix core to its SIMD partner.
-    if (k_len <= kPersistentMaxK)                      // short contraction: see k_int8_gemm_persistent
-        return launch_persistent<2, 4, 4, 2, 64, 4, OUT>(A, B, C, batch, Mp, Np, Kp, k_begin, k_len, pn, mods,
-                                                         stream);
-    return launch<2, 4, 4, 2, 64, 4, OUT>(A, B, C, batch, Mp, Np, Kp, k_begin, k_len, pn, mods, stream);
+    if constexpr (OUT != kOutMax)
+        if (g.k_len <= kPersistentMaxK && g.ranges == 1)   // short contraction: see k_int8_gemm_persistent
+            return launch_persistent<2, 4, 4, 2, 64, 4, OUT>(g);
+    return launch<2, 4, 4, 2, 64, 4, OUT>(g);
+}
+
+// Whole tiles that exist, and at least a row and a column in the last of them.
+bool panel_fits(const GemmPanel &pn, int64_t Mp, int64_t Np) {
+    return pn.row0 >= 0 && pn.col0 >= 0 && pn.rows >= kPadMN && pn.cols >= kPadMN && pn.row0 % kPadMN == 0 && pn.col0 % kPadMN == 0 &&
+           pn.rows % kPadMN == 0 && pn.cols % kPadMN == 0 && pn.row0 + pn.rows <= Mp && pn.col0 + pn.cols <= Np &&
+           pn.valid_rows > pn.rows - kPadMN && pn.valid_rows <= pn.rows && pn.valid_cols > pn.cols - kPadMN && pn.valid_cols <= pn.cols;
 }
 
 }  // namespace
 
 hipError_t launch_int8_gemm_maxima(const int8_t *A, const int8_t *B, int64_t Mp, int64_t Np, int64_t Kp,
-                                   int64_t k_begin, int64_t k_len, const GemmPanel &pn, int64_t valid_rows,
-                                   int64_t valid_cols, int *row_max, int *col_max, hipStream_t stream) {
-    if (pn.row0 < 0 || pn.col0 < 0 || pn.rows < kPadMN || pn.cols < kPadMN || pn.row0 % kPadMN ||
-        pn.col0 % kPadMN || pn.rows % kPadMN || pn.cols % kPadMN || pn.row0 + pn.rows > Mp ||
-        pn.col0 + pn.cols > Np || valid_rows < 0 || valid_cols < 0 || valid_rows > pn.rows ||
-        valid_cols > pn.cols || k_begin < 0 || k_len < kPadK || k_len > kMaxExactK || k_begin % kPadK ||
+                                   int64_t k_begin, int64_t k_len, const GemmPanel &pn, int *row_max, int *col_max,
+                                   hipStream_t stream) {
+    if (!panel_fits(pn, Mp, Np) || k_begin < 0 || k_len < kPadK || k_len > kMaxExactK || k_begin % kPadK ||
         k_len % kPadK || k_begin + k_len > Kp || !row_max || !col_max)
         return hipErrorInvalidValue;
     // the kernel's view of these arguments: see kOutMax
-    GemmPanel q = pn;
-    q.c_ld = valid_rows | (valid_cols << 32);
-    q.c_plane = col_max - row_max;
-    const GemmMods none{};
-    if (gemm_small_tiles(pn.rows, pn.cols, 1))
-        return launch_small<kOutMax>(A, B, row_max, 1, Mp, Np, Kp, k_begin, k_len, q, none, stream);
-    return launch<2, 4, 4, 2, 64, 4, kOutMax>(A, B, row_max, 1, Mp, Np, Kp, k_begin, k_len, q, none, stream);
+    GemmLaunch g{A, B, row_max, 1, Mp, Np, Kp, k_begin, k_len, pn, 1, GemmMods{}, stream};
+    g.pn.c_ld = pn.valid_rows | (pn.valid_cols << 32);
+    g.pn.c_plane = col_max - row_max;
+    return launch_out<kOutMax>(g);
 }
 
 hipError_t launch_int8_gemm(const int8_t *A, const int8_t *B, void *C, int batch, int64_t Mp,
                             int64_t Np, int64_t Kp, int64_t k_begin, int64_t k_len, bool as_u8,
-                            bool fold, const ModArgs *ma, hipStream_t stream, const GemmPanel *panel) {
-    const GemmPanel whole{0, Mp, 0, Np, Np, Mp * Np};
-    const GemmPanel &pn = panel ? *panel : whole;
-    if (pn.row0 < 0 || pn.col0 < 0 || pn.rows < kPadMN || pn.cols < kPadMN || pn.row0 % kPadMN ||
-        pn.col0 % kPadMN || pn.rows % kPadMN || pn.cols % kPadMN || pn.row0 + pn.rows > Mp ||
-        pn.col0 + pn.cols > Np || pn.c_ld < pn.cols || pn.c_ld % 16 || pn.c_plane % 16)
+                            bool fold, const ModArgs *ma, hipStream_t stream, const GemmPanel *panel, int ranges) {
+    const GemmPanel pn = panel ? *panel : GemmPanel{0, Mp, 0, Np, Np, Mp * Np, Mp, Np};
+    if (!panel_fits(pn, Mp, Np) || pn.c_ld < pn.cols || pn.c_ld % 16 || pn.c_plane % 16)
         return hipErrorInvalidValue;                       // whole tiles, 16-byte stores
-    GemmMods mods{};
+    if (ranges < 1 || (ranges > 1 && (!as_u8 || fold || k_len / kBlockK < 2 * ranges))) return hipErrorInvalidValue;
+    GemmLaunch g{A, B, C, batch, Mp, Np, Kp, k_begin, k_len, pn, ranges, GemmMods{}, stream};
     if (ma)
         for (int i = 0; i < ma->n; ++i) {
-            mods.p[i] = ma->p[i]; mods.pinv_prime[i] = (int32_t)ma->pinv_prime[i];
-            mods.byte_mod[i] = make_byte_mod(ma->p[i]);
+            g.mods.p[i] = ma->p[i]; g.mods.pinv_prime[i] = (int32_t)ma->pinv_prime[i];
+            g.mods.byte_mod[i] = make_byte_mod(ma->p[i]);
         }
     else if (as_u8 || fold)
         return hipErrorInvalidValue;                       // the reduced forms need the moduli
-    if (as_u8)
-        return fold ? launch_out<kOutU8Fold>(A, B, C, batch, Mp, Np, Kp, k_begin, k_len, pn, mods, stream)
-                    : launch_out<kOutU8>(A, B, C, batch, Mp, Np, Kp, k_begin, k_len, pn, mods, stream);
-    return fold ? launch_out<kOutI32Fold>(A, B, C, batch, Mp, Np, Kp, k_begin, k_len, pn, mods, stream)
-                : launch_out<kOutI32>(A, B, C, batch, Mp, Np, Kp, k_begin, k_len, pn, mods, stream);
+    if (as_u8) return fold ? launch_out<kOutU8Fold>(g) : launch_out<kOutU8>(g);
+    // (the int32 forms compute the products of the padding, too)
+    g.pn.valid_rows = pn.rows; g.pn.valid_cols = pn.cols;
+    return fold ? launch_out<kOutI32Fold>(g) : launch_out<kOutI32>(g);
 }
 
 }  // namespace oz2

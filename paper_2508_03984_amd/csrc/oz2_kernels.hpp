@@ -177,13 +177,18 @@ hipError_t launch_col_maxbits(const T *X, int64_t ld, int64_t rows, int64_t cols
 struct GemmPanel {
     int64_t row0, rows, col0, cols;
     int64_t c_ld, c_plane;              // in elements; multiples of 16
+    // entries of C among them (the last tile of 256 has at least one); what lies beyond is padding, whose results are 0
+    int64_t valid_rows, valid_cols;
 };
 
 // panel == nullptr: the whole product, C = [batch][Mp][Np].
+// ranges > 1 (uint8, not folded): the contraction in so many K ranges, each with planes of its own: C = [ranges][batch] planes
+// c_plane apart, of which launch_epilogue makes U.  At least two K tiles of 64 per range.  What C holds as padding in the planes of
+// the second and later ranges is undefined.
 hipError_t launch_int8_gemm(const int8_t *A, const int8_t *B, void *C, int batch, int64_t Mp,
                             int64_t Np, int64_t Kp, int64_t k_begin, int64_t k_len, bool as_u8,
                             bool fold, const ModArgs *ma, hipStream_t stream,
-                            const GemmPanel *panel = nullptr);
+                            const GemmPanel *panel = nullptr, int ranges = 1);
 
 // Accurate mode (Section 4.2): the contraction of slice 0 of A and B over the K range
 // [k_begin, k_begin + k_len) (k_len <= 2^17) for one panel (as above), of which only the maxima
@@ -192,17 +197,17 @@ hipError_t launch_int8_gemm(const int8_t *A, const int8_t *B, void *C, int batch
 // non-negative numbers).  Both arrays are indexed from the panel's first row / column and are
 // updated with integer atomic maxima.
 hipError_t launch_int8_gemm_maxima(const int8_t *A, const int8_t *B, int64_t Mp, int64_t Np, int64_t Kp,
-                                   int64_t k_begin, int64_t k_len, const GemmPanel &panel,
-                                   int64_t valid_rows, int64_t valid_cols, int *row_max, int *col_max,
+                                   int64_t k_begin, int64_t k_len, const GemmPanel &panel, int *row_max, int *col_max,
                                    hipStream_t stream);
 
 // Algorithm 1 lines 7-12 and the alpha/beta update, fused:
 // C[i][j] = alpha * ldexp(C''(i,j), -(tA[i]+tB[j])) + beta * C[i][j]   (OutT = double or float)
 // prod: [n_mod][Mp][Np], int32 sums (prod_is_u8 = false; reduced here) or uint8 residues U_s.
+// ranges > 1 (uint8): prod is [ranges][n_mod][Mp][Np], residues of K ranges; U_s, their sum modulo p_s, replaces the first of them.
 template <typename OutT>
-hipError_t launch_epilogue(const void *prod, bool prod_is_u8, int64_t Mp, int64_t Np, int64_t m, int64_t n,
+hipError_t launch_epilogue(void *prod, bool prod_is_u8, int64_t Mp, int64_t Np, int64_t m, int64_t n,
                            const int32_t *tA, const int32_t *tB, const ModArgs &ma, double alpha,
-                           double beta, OutT *C, int64_t ldc, hipStream_t stream);
+                           double beta, OutT *C, int64_t ldc, hipStream_t stream, int ranges = 1);
 
 // launch_int8_gemm (uint8 form) and launch_epilogue in one launch, for products that
 // tiny_product_applies (oz2_plan.hpp) accepts: U with its padding, and C.

@@ -129,10 +129,14 @@ struct Layout {
     bool with_operands;                    // the call converts its factors itself
     size_t off_bt, off_ta, off_tb, off_ra, off_rb, off_prod;
     size_t prod_whole, prod_min;           // product part: all of C at once / one 256 x 256 panel
+    int ranges;                            // K ranges of a whole product (gemm_plan) ...
+    size_t prod_ranges;                    // ... and what they take beyond prod_whole, if it is to be had
 };
 
 // Bytes of product workspace per entry of C: N planes of uint8, or of int32 (diagnostic form).
 inline size_t bytes_per_entry(int N, bool prod_u8) { return (size_t)N * (prod_u8 ? 1 : 4); }
+
+inline int whole_product_ranges(int64_t m, int64_t n, int64_t Mp, int64_t Np, int64_t Kp, int N);
 
 inline Layout make_layout(int64_t m, int64_t n, int64_t k, int N, bool prod_u8, bool with_operands = true) {
     Layout L{};
@@ -149,6 +153,8 @@ inline Layout make_layout(int64_t m, int64_t n, int64_t k, int N, bool prod_u8, 
     L.off_prod = o;
     L.prod_whole = align256((size_t)L.Mp * L.Np * bytes_per_entry(N, prod_u8));
     L.prod_min = align256((size_t)kPadMN * kPadMN * bytes_per_entry(N, prod_u8));
+    L.ranges = prod_u8 ? whole_product_ranges(m, n, L.Mp, L.Np, L.Kp, N) : 1;
+    L.prod_ranges = (size_t)(L.ranges - 1) * L.prod_whole;
     return L;
 }
 
@@ -247,6 +253,9 @@ inline int64_t launch_k_len(int64_t Kp, int N, const Panels &Q) {
     return std::min<int64_t>(len, OZ2_MAX_K);
 }
 
+// K ranges with planes of their own, at most: 16 keep a workgroup on at least 12 K tiles where they help.
+constexpr int kMaxRanges = 16;
+
 // The smallest products run their GEMMs and the accumulation as one launch (oz2_tiny.hip): tiles of 16 x 16 where these and
 // the padding have a compute unit each, else of 32 x 32.
 struct TinyGrid {
@@ -299,21 +308,66 @@ inline int64_t epilogue_rows(int64_t groups, int64_t max_threads = kEpilogueMaxT
     return groups > 0x3fffffff ? 0 : max_threads / groups;
 }
 
-// The INT8 GEMM takes tiles of 128 x 128 where there would be at most 128 tiles of 256 x 256: those leave half of the compute units
-// without one, and up to there every unit has work with two of the small ones.  Prepared operands, other ones in
+// Which tiles the INT8 GEMM takes: 256 x 256, or 128 x 128 with 8 wavefronts and 6 stages of LDS (one workgroup per compute unit) or with 4
+// and 4 (two share a unit).
+//
+// The small ones where at most 512 of them hold entries of C: large ones would leave half of the compute units without one, and up to
+// there every unit has work with two of the small ones.  Prepared operands, other ones in
 // each call, us, 128 x 128 | 256 x 256: 96 large tiles (1024^3 FP32 N = 6) 19.4 | 21.9; 112 19.8 | 22.7; 120 (2048 x 256 x 1024 N = 15) 20.5 | 22.8; 128
 // (1024^3 FP32 N = 8) 21.4 | 23.9, (512 x 1024 x 8192 N = 16) 87.4 | 92.2, (2048^3 N = 2) 33.2 | 37.2; 135 (768 x 768 x 1024 N = 15) 26.8 | 24.0; 140
 // 29.3 | 25.3; 168 (1024 x 768 x 1024 N = 14) 27.2 | 23.5; 224 (1024^3 N = 14) 33.5 | 28.1; 448 (2048^3 FP32 N = 7) 78.6 | 66.3.  Accurate mode's one slice, whole
 // calls: 128 (2048 x 4096 x 2048 FP32 N = 6) 174 | 179, 144 (2304 x 4096 x 2048) 207 | 203.
-inline bool gemm_small_tiles(int64_t rows, int64_t cols, int64_t batch) {
-    return rows * cols * batch <= (int64_t)256 * 256 * 128;
-}
-// Of those, at most one per compute unit run with 8 wavefronts and 6 stages of LDS, more with 4 and 4, so that two share a unit.  us as
+//
+// Of those, at most one per compute unit run with 8 wavefronts and 6 stages.  us as
 // above, 4 and 4 | 8 and 6: 256 x 256 x 1024 N = 15 10.7 | 10.2, x 4096 30.7 | 26.0, 500 x 300 x 777 FP32 N = 8 9.9 | 9.6, 512 x 512 x 2048 N = 15 20.8 | 19.6, 512^3
 // N = 14 10.8 | 10.7, N = 16 (256 tiles) 11.6 | 11.5, N = 17 (272) 12.6 | 14.9, 768 x 768 x 512 N = 8 (288) 13.1 | 15.4; accurate mode, whole calls, 512^3
 // N = 15 35.9 | 34.7, 1024^3 63.1 | 61.4.
-inline bool gemm_one_tile_per_unit(int64_t rows, int64_t cols, int64_t batch) {
-    return rows * cols * batch <= (int64_t)128 * 128 * 256;
+enum class GemmTile { kLarge, kOnePerUnit, kTwoPerUnit };
+inline int64_t blocks_of_128(int64_t rows, int64_t cols) { return (rows + 127) / 128 * ((cols + 127) / 128); }
+
+// The contraction of a few tiles runs in K ranges at once, whose results meet in the accumulation: a range more is a workgroup more
+// per tile, and costs a plane more per modulus to write and read.  The estimates, in us, are fits of
+// prepared products (N = 16, k = 2048 to 40000, up to 16 ranges; 32 shapes, of which the choice made is within 3 % of the best on average):
+// a workgroup of 256 x 256 takes 0.57 per K tile of 64 while at most half of the units have one and 0.75, at the board's power limit,
+// when all have; one of 128 x 128 0.27 to 0.33, two that share a unit 0.55.  One range | chosen, us: 256 x 256 x 40000 175 | 67 (4 ranges, 128 x 128), x 4096 17.3 | 13.6;
+// 512 x 512 x 40000 199 | 144 (4), 512 x 768 x 8192 77 | 60 (2), 768 x 768 x 40000 367 | 309 (5), 1280 x 1024 x 40000 786 | 643 (4; 320 tiles); nothing to be gained
+// for 256 tiles, nor for 432 (1536 x 1000 x 40000 N = 18: 853 | 846, power).
+struct GemmPlan {
+    GemmTile tile;
+    int ranges;
+};
+inline double large_tiles_us(double tiles, double kt) {      // rounds of 256, of which the last may be partial
+    const double rounds = (double)(int64_t)(tiles / 256), last = tiles / 256 - rounds;
+    return rounds * (0.75 * kt + 4) + (last > 0 ? (0.57 + 0.36 * std::max(0.0, last - 0.5)) * kt + 4 : 0);
+}
+inline double small_tiles_us(double tiles, double kt) {      // at most 256, then two per unit in rounds of 512
+    if (tiles <= 256) return (0.27 + 0.08 * std::max(0.0, tiles / 256 - 0.25)) * kt;
+    return (double)(int64_t)((tiles + 511) / 512) * (0.55 * kt + 2);
+}
+// rows x cols entries of C; `slices` of them, whose contraction has kt K tiles; may_range: the results of K ranges can be kept.
+inline GemmPlan gemm_plan(int64_t rows, int64_t cols, int64_t slices, int64_t kt, bool may_range) {
+    const int64_t blocks = blocks_of_128(rows, cols) * slices;
+    const double large = (double)((rows + 255) / 256 * ((cols + 255) / 256) * slices);
+    GemmPlan best{blocks <= 256 ? GemmTile::kOnePerUnit : blocks <= 512 ? GemmTile::kTwoPerUnit : GemmTile::kLarge, 1};
+    if (!may_range || large > 448) return best;
+    // a range less has to be clearly worse
+    double best_us = 0.95 * (5 + (best.tile == GemmTile::kLarge ? large_tiles_us(large, (double)kt) : small_tiles_us((double)blocks, (double)kt)));
+    for (int s = 2; s <= kMaxRanges && kt / s >= 12; ++s) {
+        const double k = (double)kt / s, extra = 9 + s * (double)(rows * cols * slices) / 3e6;
+        const double some = large * s;
+        // (all units at once finish and store: a little more)
+        const double l = extra + large_tiles_us(some, k) + (some / 256 - (double)(int64_t)(some / 256 - 1e-9) > 0.9 ? 5 : 0);
+        if (large >= 24 && l < best_us) { best_us = l; best = GemmPlan{GemmTile::kLarge, s}; }
+        const double o = extra + small_tiles_us((double)(blocks * s), k);
+        if (blocks * s <= 256 && o < best_us) { best_us = o; best = GemmPlan{GemmTile::kOnePerUnit, s}; }
+    }
+    return best;
+}
+
+inline int whole_product_ranges(int64_t m, int64_t n, int64_t Mp, int64_t Np, int64_t Kp, int N) {
+    const Panels Q = launch_panels(Mp, Np, Kp);
+    if (Kp > OZ2_MAX_K || Q.count != 1 || launch_k_len(Kp, N, Q) != Kp) return 1;
+    return gemm_plan(m, n, N, Kp / kBlockK, true).ranges;
 }
 
 // Side of a panel of the overlapped form: the INT8 GEMM loses nothing down to 4096 x 4096.

@@ -291,6 +291,54 @@ __global__ __launch_bounds__(kEpilogueThreads) void k_epilogue(const uint8_t *__
     tail.store(C1, C2, ma, alpha, beta);
 }
 
+// The form for residues of K ranges (launch_int8_gemm), ranges x n planes: U_s is the sum of the ranges' residues modulo p_s, which
+// replaces those of the first.  A workgroup owns 256 columns of a row: a thread adds up 16 bytes of a modulus, all ranges requested at
+// once, and U_s goes to memory and through LDS to the threads that accumulate, one entry each.
+constexpr int kRangeColumns = 256;
+template <typename OutT>
+__global__ __launch_bounds__(256) void k_epilogue_ranges(uint8_t *U, int64_t plane, int ranges, int64_t Np, int64_t n,
+                                                         const int32_t *__restrict__ tA, const int32_t *__restrict__ tB, ModArgs ma,
+                                                         double alpha, double beta, OutT *C, int64_t ldc) {
+    constexpr int kFlight = 8;
+    __shared__ uint4 sum_lds[kMaxModuli][kRangeColumns / 16];
+    const int tid = threadIdx.x;
+    const int64_t i = blockIdx.y, j0 = (int64_t)blockIdx.x * kRangeColumns, j = j0 + tid;
+    uint8_t *const row = U + i * Np + j0;
+    const int64_t step = ma.n * plane;
+    const int shift = tA[i] + (j < n ? tB[j] : 0);
+    for (int q = tid; q < ma.n * (kRangeColumns / 16); q += 256) {
+        const int s = q / (kRangeColumns / 16), c = q % (kRangeColumns / 16);
+        if (j0 + 16 * c >= n) continue;                       // padding: zero in the first range, not written in the others
+        uint8_t *const u = row + s * plane + 16 * c;
+        uint4 x = *reinterpret_cast<const uint4 *>(u);
+        const int p = ma.p[s];
+        for (int z0 = 1; z0 < ranges; z0 += kFlight) {
+            uint4 y[kFlight];
+#pragma unroll
+            for (int z = 0; z < kFlight; ++z)                 // (beyond the last range: it again, not used)
+                y[z] = *reinterpret_cast<const uint4 *>(u + (z0 + z < ranges ? z0 + z : ranges - 1) * step);
+#pragma unroll
+            for (int z = 0; z < kFlight; ++z)
+                if (z0 + z < ranges)
+                    x = make_uint4(add_mod_bytes(x.x, y[z].x, p), add_mod_bytes(x.y, y[z].y, p), add_mod_bytes(x.z, y[z].z, p),
+                                   add_mod_bytes(x.w, y[z].w, p));
+        }
+        *reinterpret_cast<uint4 *>(u) = x;
+        sum_lds[s][c] = x;
+    }
+    __syncthreads();
+    if (j >= n) return;
+    const uint8_t *const mine = reinterpret_cast<const uint8_t *>(&sum_lds[0][0]) + tid;
+    double C1 = 0.0, C2 = 0.0;
+    for (int s = 0; s < ma.n; ++s) {                          // ascending, as everywhere
+        const double v = (double)(int)mine[s * kRangeColumns];
+        C1 = fma(ma.s1[s], v, C1);
+        C2 = fma(ma.s2[s], v, C2);
+    }
+    OutT *dst = C + i * ldc + j;
+    *dst = crt_entry<OutT>(C1, C2, shift, ma, alpha, beta, dst);
+}
+
 // The form for int32 sums (possibly folded partial sums), which are reduced here.  Bound: HBM.  Moduli in groups of 8, then 4, 2
 // and 1, a group's loads first.  Planes beyond the memory-side cache are read better by fewer wavefronts: LDS that nobody uses keeps
 // them to 4 per SIMD there.  us, loops of 4 moduli and single ones at the end | groups | groups, 4 wavefronts: 8192^2 N = 16 980 |
@@ -413,16 +461,25 @@ hipError_t launch_magnitudes(const T *X, int64_t ld, int64_t rows, int64_t len, 
 }
 
 template <typename OutT>
-hipError_t launch_epilogue(const void *prod, bool prod_is_u8, int64_t Mp, int64_t Np, int64_t m,
+hipError_t launch_epilogue(void *prod, bool prod_is_u8, int64_t Mp, int64_t Np, int64_t m,
                            int64_t n, const int32_t *tA, const int32_t *tB, const ModArgs &ma,
-                           double alpha, double beta, OutT *C, int64_t ldc, hipStream_t stream) {
+                           double alpha, double beta, OutT *C, int64_t ldc, hipStream_t stream, int ranges) {
     const int64_t groups = epilogue_groups(n), plane = Mp * Np, rows = epilogue_rows(groups);
     if (rows < 1) return hipErrorInvalidValue;
     for (int64_t r = 0; r < m; r += rows) {
         const int64_t count = std::min(rows, m - r);
         const unsigned blocks = (unsigned)((count * groups + kEpilogueThreads - 1) / kEpilogueThreads);
         hipError_t e;
-        if (prod_is_u8) {
+        if (ranges > 1) {
+            const int64_t most = 65535;                       // rows of a grid
+            e = hipSuccess;
+            for (int64_t q = 0; q < count && e == hipSuccess; q += most) {
+                hipLaunchKernelGGL((k_epilogue_ranges<OutT>), dim3((unsigned)((n + kRangeColumns - 1) / kRangeColumns), (unsigned)std::min(most, count - q)),
+                                   dim3(256), 0, stream, static_cast<uint8_t *>(prod) + (r + q) * Np, plane, ranges, Np, n, tA + r + q, tB, ma,
+                                   alpha, beta, C + (r + q) * ldc, ldc);
+                e = hipGetLastError();
+            }
+        } else if (prod_is_u8) {
             e = launch_epilogue_u8<OutT, OZ2_MIN_MODULI>(static_cast<const uint8_t *>(prod) + r * Np, plane, Np, count, n, tA + r, tB, ma,
                                                          alpha, beta, C + r * ldc, ldc, (int)groups, blocks, stream);
         } else {
@@ -454,10 +511,10 @@ hipError_t launch_scale_c(OutT *C, int64_t ldc, int64_t m, int64_t n, double bet
     template hipError_t launch_residues<T>(const T *, int64_t, int64_t, int64_t, const int32_t *, \
                                            const ModArgs &, int8_t *, int64_t, int64_t,           \
                                            hipStream_t, int64_t);                                 \
-    template hipError_t launch_epilogue<T>(const void *, bool, int64_t, int64_t, int64_t,        \
+    template hipError_t launch_epilogue<T>(void *, bool, int64_t, int64_t, int64_t,              \
                                            int64_t, const int32_t *, const int32_t *,             \
                                            const ModArgs &, double, double, T *, int64_t,         \
-                                           hipStream_t);                                          \
+                                           hipStream_t, int);                                          \
     template hipError_t launch_scale_c<T>(T *, int64_t, int64_t, int64_t, double, hipStream_t);
 OZ2_INSTANTIATE(double)
 OZ2_INSTANTIATE(float)

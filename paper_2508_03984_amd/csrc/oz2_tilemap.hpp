@@ -100,4 +100,54 @@ OZ2_HOST_DEVICE inline void map_tile(const TileMap &tm, int id, int &s, int &tr,
     tc = col0 + w - row * cols;
 }
 
+// The work of a launch with one workgroup per tile: the tiles of all slices, each slice once per K range (a `slice` of the map is
+// (range, slice), the slices of a range together).  Tiles of 128 x 128 that hold nothing but padding are not among them: they are
+// cleared by workgroups of their own, which come last.
+struct GemmGrid {
+    TileMap map;
+    int batch;                 // slices
+    Divisor by_batch;
+    int k_each, k_more;        // K tiles of a range: k_each, one more in the first k_more ranges
+    int padding;               // tiles to clear
+    int pad_right, pad_below;  // of a slice: at the right of the rows of tiles; below them
+};
+
+struct GemmItem {
+    int plane, s;              // where the results go (range * batch + slice); the slice
+    int tr, tc;                // tile row and column
+    int kb, kt;                // first K tile of the range and how many
+};
+
+// rows x cols entries of C, of which valid_rows x valid_cols exist, in tiles of `tile`; rows and cols are multiples of 256 that exceed the
+// valid ones by less than 256.  ranges: K ranges of kt_all K tiles in all.
+inline GemmGrid make_gemm_grid(int64_t rows, int64_t cols, int64_t valid_rows, int64_t valid_cols, int tile, int batch, int ranges,
+                               int kt_all) {
+    GemmGrid g{};
+    const int tiles_m = (int)((valid_rows + tile - 1) / tile), tiles_n = (int)((valid_cols + tile - 1) / tile);
+    g.pad_right = cols / tile > tiles_n ? tiles_m : 0;
+    g.pad_below = rows / tile > tiles_m ? (int)(cols / tile) : 0;
+    g.padding = (g.pad_right + g.pad_below) * batch;
+    g.map = make_tile_map(tiles_m, tiles_n, tiles_m * tiles_n * batch * ranges);
+    g.batch = batch;
+    g.by_batch = make_divisor(batch);
+    g.k_each = kt_all / ranges; g.k_more = kt_all % ranges;
+    return g;
+}
+
+OZ2_HOST_DEVICE inline GemmItem map_item(const GemmGrid &g, int id) {
+    GemmItem it;
+    map_tile(g.map, id, it.plane, it.tr, it.tc);
+    const int range = divide(it.plane, g.by_batch);
+    it.s = it.plane - range * g.batch;
+    it.kt = g.k_each + (range < g.k_more ? 1 : 0);
+    it.kb = range * g.k_each + (range < g.k_more ? range : g.k_more);
+    return it;
+}
+
+// Number j of the tiles to clear.
+OZ2_HOST_DEVICE inline GemmItem padding_item(const GemmGrid &g, int j) {
+    const int each = g.pad_right + g.pad_below, s = j / each, i = j - s * each;
+    return i < g.pad_right ? GemmItem{s, s, i, g.map.tiles_n, 0, 0} : GemmItem{s, s, g.map.tiles_m, i - g.pad_right, 0, 0};
+}
+
 }  // namespace oz2
