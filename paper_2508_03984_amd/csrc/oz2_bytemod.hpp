@@ -27,13 +27,14 @@ struct ByteMod {
     int32_t neg_p;
 };
 
-inline ByteMod make_byte_mod(int p) {
+// first: what the sums start at (u = x + first modulo 2^32, which has to be x + first itself, for p = 256 modulo 256).
+inline ByteMod make_byte_mod(int p, uint32_t first = 0x80000000u) {
     ByteMod b{};
     uint32_t power = 1 % p;
     for (int j = 0; j < 4; ++j) { b.coef |= power << (8 * j); power = power * 256u % (uint32_t)p; }
     const int h = (p - 1) / 2;
-    // x = u - 2^31, so t = -2^31 - h (mod p)
-    const int t = p == 256 ? 0 : (int)((((int64_t)p << 32) - ((int64_t)1 << 31) - h) % p);
+    // x = u - first, so t = -first - h (mod p)
+    const int t = p == 256 ? 0 : (int)((((int64_t)p << 32) - (int64_t)first - h) % p);
     b.base = (uint32_t)t;
     // -p j = h (mod 256): the inverse of an odd p modulo 256 by Newton's iteration (3, 6, 12 bits)
     uint32_t inverse = (uint32_t)p;

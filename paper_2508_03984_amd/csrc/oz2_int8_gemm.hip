@@ -36,6 +36,7 @@
 #include "oz2_epilogue.hpp"
 #include "oz2_kernels.hpp"
 #include "oz2_tilemap.hpp"
+#include "oz2_wide_gemm.hpp"
 
 namespace oz2 {
 namespace {
@@ -546,9 +547,19 @@ hipError_t launch_out(const GemmLaunch &g) {
     const GemmTile tile = gemm_plan(g.pn.valid_rows, g.pn.valid_cols, g.batch, g.k_len / kBlockK, g.ranges > 1).tile;
     if (tile == GemmTile::kOnePerUnit) return launch<2, 4, 2, 1, 64, 6, OUT>(g);
     if (tile == GemmTile::kTwoPerUnit) return launch<2, 2, 2, 2, 64, 4, OUT>(g);
-    // 8 wavefronts (2 per SIMD), each 128 x 64: measured against 4 wavefronts of 128 x 128 on
-    // the same device (with 32x32x32 MFMAs) it is 2 % faster at 16 x 16384^3 -- a wavefront that is held up issuing
-    // a load leaves the matrix core to its SIMD partner.
+    if constexpr (OUT == kOutU8 || OUT == kOutU8Fold) {
+        GemmGrid grid;
+        if (!tiles_of(g, 256, &grid)) return hipErrorInvalidValue;
+        if (wide_gemm_applies(grid.map.total, g.k_len, g.ranges)) {
+            const int units = compute_units() / 8 * 8;
+            if (units < 8) return hipErrorInvalidValue;
+            WideMods mods{};
+            for (int i = 0; i < g.batch; ++i) { mods.p[i] = g.mods.p[i]; mods.byte_mod[i] = make_byte_mod(g.mods.p[i], kWideFirst); }
+            return launch_wide_gemm(g.A + g.pn.row0 * kBlockK, g.B + g.pn.col0 * kBlockK, static_cast<uint8_t *>(g.C), g.Mp, g.Np, g.Kp / kBlockK,
+                                    (int)(g.k_begin / kBlockK), g.pn.c_ld, g.pn.c_plane, grid, mods, OUT == kOutU8Fold, units, g.stream);
+        }
+    }
+    // 8 wavefronts (2 per SIMD), each 128 x 64
     if constexpr (OUT != kOutMax)
         if (g.k_len <= kPersistentMaxK && g.ranges == 1)   // short contraction: see k_int8_gemm_persistent
             return launch_persistent<2, 4, 4, 2, 64, 4, OUT>(g);

@@ -107,7 +107,7 @@ struct GemmGrid {
     TileMap map;
     int batch;                 // slices
     Divisor by_batch;
-    int k_each, k_more;        // K tiles of a range: k_each, one more in the first k_more ranges
+    int k_each, k_more;        // K tiles of a range: k_each, two more in the first k_more ranges
     int padding;               // tiles to clear
     int pad_right, pad_below;  // of a slice: at the right of the rows of tiles; below them
 };
@@ -119,7 +119,7 @@ struct GemmItem {
 };
 
 // rows x cols entries of C, of which valid_rows x valid_cols exist, in tiles of `tile`; rows and cols are multiples of 256 that exceed the
-// valid ones by less than 256.  ranges: K ranges of kt_all K tiles in all.
+// valid ones by less than 256.  ranges: K ranges of kt_all K tiles in all, an even number in each.
 inline GemmGrid make_gemm_grid(int64_t rows, int64_t cols, int64_t valid_rows, int64_t valid_cols, int tile, int batch, int ranges,
                                int kt_all) {
     GemmGrid g{};
@@ -130,7 +130,7 @@ inline GemmGrid make_gemm_grid(int64_t rows, int64_t cols, int64_t valid_rows, i
     g.map = make_tile_map(tiles_m, tiles_n, tiles_m * tiles_n * batch * ranges);
     g.batch = batch;
     g.by_batch = make_divisor(batch);
-    g.k_each = kt_all / ranges; g.k_more = kt_all % ranges;
+    g.k_each = kt_all / 2 / ranges * 2; g.k_more = kt_all / 2 % ranges;
     return g;
 }
 
@@ -139,8 +139,8 @@ OZ2_HOST_DEVICE inline GemmItem map_item(const GemmGrid &g, int id) {
     map_tile(g.map, id, it.plane, it.tr, it.tc);
     const int range = divide(it.plane, g.by_batch);
     it.s = it.plane - range * g.batch;
-    it.kt = g.k_each + (range < g.k_more ? 1 : 0);
-    it.kb = range * g.k_each + (range < g.k_more ? range : g.k_more);
+    it.kt = g.k_each + (range < g.k_more ? 2 : 0);
+    it.kb = range * g.k_each + 2 * (range < g.k_more ? range : g.k_more);
     return it;
 }
 

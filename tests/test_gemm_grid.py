@@ -37,8 +37,8 @@ static void check(int hm, int hn, int tile, int batch, int ranges, int kt) {
             const GemmItem it = map_item(g, id);
             const int range = it.plane / batch;
             int first = 0;
-            for (int r = 0; r < range; ++r) first += kt / ranges + (r < kt % ranges ? 1 : 0);
-            if (it.kt < 1 || it.kb != first || it.kt != kt / ranges + (range < kt % ranges ? 1 : 0)) ++bad;
+            for (int r = 0; r < range; ++r) first += 2 * (kt / 2 / ranges + (r < kt / 2 % ranges ? 1 : 0));
+            if (it.kt < 2 || it.kb != first || it.kt != 2 * (kt / 2 / ranges + (range < kt / 2 % ranges ? 1 : 0))) ++bad;
             if (range == ranges - 1 && it.kb + it.kt != kt) ++bad;
             cover(it, false);
         }
@@ -62,8 +62,8 @@ int main(int argc, char **argv) {
         for (int n = 1; n < 36; ++n)
             for (int b : {1, 6, 15})
                 for (int ranges : {1, 2, 7}) {
-                    check(m, n, 256, b, ranges, 14 + m % 5);
-                    check(m, n, 128, b, ranges, 14 + n % 7);
+                    check(m, n, 256, b, ranges, 14 + m % 5 * 2);
+                    check(m, n, 128, b, ranges, 14 + n % 7 * 2);
                 }
     std::printf("bad=%ld\n", bad);
     return bad != 0;

@@ -1,0 +1,68 @@
+"""The INT8 GEMM by 4 wavefronts: numbers of K tiles around what its stream of K tiles needs, one to several tiles per workgroup, K ranges of
+different lengths, and the largest sums; exact, against the int32 sums of the other kernels."""
+import pytest
+import torch
+
+import paper_2508_03984_amd as oz
+from paper_2508_03984_amd import binding as b
+
+pytestmark = pytest.mark.gpu
+
+
+def residues_and_product(A, B, N):
+    """U_s of the default form, the same from the int32 sums, and both products."""
+    out = []
+    try:
+        for int32 in (False, True):
+            oz.oz2_set_int32_products(int32)
+            C = oz.matmul(A, B, N)
+            torch.cuda.synchronize()
+            if int32:
+                p = torch.tensor(oz.oz2_constants(N)["p"][:N].tolist(), dtype=torch.int32, device="cuda").view(N, 1, 1)
+                U = torch.remainder(oz.stage_tensor(b.OZ2_STAGE_PROD), p).to(torch.uint8)
+            else:
+                U = oz.stage_tensor(b.OZ2_STAGE_U).clone()
+            out += [U, C]
+    finally:
+        oz.oz2_set_int32_products(False)
+    return out
+
+
+# tiles: 272 (a second one for 16 workgroups), 320, 768 (three each), 1000 (ragged, four)
+@pytest.mark.parametrize("m,n,N", [(1000, 1050, 17), (1024, 1279, 16), (2048, 2048, 12), (2550, 2500, 10)])
+@pytest.mark.parametrize("k", [321, 512, 640, 768, 1100])
+def test_every_number_of_k_tiles(m, n, N, k):
+    gen = torch.Generator(device="cuda").manual_seed(k)
+    A = torch.rand((m, k), dtype=torch.float64, device="cuda", generator=gen) - 0.5
+    B = torch.rand((k, n), dtype=torch.float64, device="cuda", generator=gen) - 0.5
+    for _ in range(3):                                         # with operands in the caches, too
+        U, C, U32, C32 = residues_and_product(A, B, N)
+        assert torch.equal(U, U32) and torch.equal(C, C32)
+
+
+@pytest.mark.parametrize("m,n,k,N", [(1024, 1024, 8192, 15),     # one tile per workgroup, a long contraction
+                                     (700, 600, 30000, 16),      # K ranges of different lengths, several per workgroup
+                                     (600, 700, 65536, 7)])
+def test_long_contractions(m, n, k, N):
+    gen = torch.Generator(device="cuda").manual_seed(k)
+    A = torch.rand((m, k), dtype=torch.float32, device="cuda", generator=gen) - 0.5
+    B = torch.rand((k, n), dtype=torch.float32, device="cuda", generator=gen) - 0.5
+    U, C, U32, C32 = residues_and_product(A, B, N)
+    assert torch.equal(U, U32) and torch.equal(C, C32)
+
+
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_the_largest_sums(sign):
+    """All residues modulo 256 are -128: sums of 2^30, and -(2^30) is impossible, so the other sign has mixed ones."""
+    m, n, k, N = 1024, 1024, 65536, 16
+    A = torch.ones((m, k), dtype=torch.float64, device="cuda")
+    oz.matmul(A[:256], A[:256].t(), N)
+    torch.cuda.synchronize()
+    f = int(oz.stage_tensor(b.OZ2_STAGE_SHIFT_A)[0])            # the scaled integers are below 2^(f + 1)
+    A *= 1.0 + 2.0 ** (7 - f)                                   # 2^f + 128
+    B = sign * A[:n].t()
+    U, C, U32, C32 = residues_and_product(A, B, N)
+    oz.matmul(A, B, N)
+    torch.cuda.synchronize()
+    assert bool((oz.stage_tensor(b.OZ2_STAGE_RES_A)[0] == -128).all())
+    assert torch.equal(U, U32) and torch.equal(C, C32)
