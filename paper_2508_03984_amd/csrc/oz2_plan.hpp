@@ -325,17 +325,19 @@ inline int64_t epilogue_rows(int64_t groups, int64_t max_threads = kEpilogueMaxT
 enum class GemmTile { kLarge, kOnePerUnit, kTwoPerUnit };
 inline int64_t blocks_of_128(int64_t rows, int64_t cols) { return (rows + 127) / 128 * ((cols + 127) / 128); }
 
-// Large tiles in the uint8 forms go to the kernel of oz2_wide_gemm.hip if there are more of them than compute units, or the contraction
-// is long; its way to the first operands and its reduction, which has no other wavefront on its SIMD, weigh more where each unit has a
-// single short tile.  Prepared products, us, oz2_int8_gemm.hip | oz2_wide_gemm.hip: 16384 x 8192 x 16384 N = 8 12205 | 11625, 8192^3 FP32 N = 8
+// Large tiles in the uint8 forms go to the kernel of oz2_wide_gemm.hip if there are more of them than compute units (many more where the
+// contraction is short, and with it the gain: 0 to 3 %), or the contraction is long; its way to the first operands and its
+// reduction, which has no other wavefront on its SIMD, weigh more where each unit has a single short tile.  Prepared products, us, oz2_int8_gemm.hip | oz2_wide_gemm.hip: 16384 x 8192 x 16384 N = 8 12205 | 11625, 8192^3 FP32 N = 8
 // 3166 | 3020, 1536 x 1000 x 40000 N = 18 858 | 817, 4096^3 N = 14 755 | 732, 2048^3 N = 15 128.3 | 124.6, 8192 x 8192 x 1024 1181 | 1165, x 512 872 | 859;
 // 4096 x 4096 x 384 222 | 219, 1500 x 1500 x 512 N = 16 45.0 | 44.4; at most one tile per unit: 1024 x 1024 x 16384 188 | 181, x 4096 59.7 | 59.4, 768 x 768 x 4096
 // 50.9 | 51.7, 900 x 900 x 384 N = 16 23.3 | 23.9.  Beyond kWideMaxK its sums would not fit (see there).
 constexpr int kWideMinKTiles = 6;
-constexpr int64_t kWideMaxK = 65536, kWideLongK = 8192;
+constexpr int64_t kWideMaxK = 65536, kWideLongK = 8192, kWideShortK = 768, kWideShortTiles = 2048;
 // tiles: of all slices and K ranges; k_len elements of k in `ranges` ranges
 inline bool wide_gemm_applies(int64_t tiles, int64_t k_len, int ranges) {
-    return k_len <= kWideMaxK && k_len / (2 * kBlockK) / ranges * 2 >= kWideMinKTiles && (tiles > 256 || k_len / ranges >= kWideLongK);
+    if (k_len > kWideMaxK || k_len / (2 * kBlockK) / ranges * 2 < kWideMinKTiles) return false;
+    const int64_t k = k_len / ranges;
+    return k >= kWideLongK || tiles > (k >= kWideShortK ? 256 : kWideShortTiles);
 }
 
 // The contraction of a few tiles runs in K ranges at once, whose results meet in the accumulation: a range more is a workgroup more

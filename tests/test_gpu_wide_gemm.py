@@ -28,10 +28,11 @@ def residues_and_product(A, B, N):
     return out
 
 
-# tiles: 272 (a second one for 16 workgroups), 320, 768 (three each), 1000 (ragged, four)
-@pytest.mark.parametrize("m,n,N", [(1000, 1050, 17), (1024, 1279, 16), (2048, 2048, 12), (2550, 2500, 10)])
-@pytest.mark.parametrize("k", [321, 512, 640, 768, 1100])
-def test_every_number_of_k_tiles(m, n, N, k):
+# tiles: 340 (a second one for 84 workgroups), 320, 768 (three each), 1000 (ragged, four), and for short contractions 2112 and 2304
+@pytest.mark.parametrize("m,n,N,k", [(1000, 1050, 17, k) for k in (768, 890, 1100)] + [(1024, 1279, 16, k) for k in (700, 1024)] +
+                         [(2048, 2048, 12, 1100), (2550, 2500, 10, 768), (2550, 2500, 10, 2000)] +
+                         [(3000, 2700, 16, k) for k in (321, 512)] + [(3072, 3072, 16, k) for k in (384, 640)])
+def test_numbers_of_k_tiles(m, n, N, k):
     gen = torch.Generator(device="cuda").manual_seed(k)
     A = torch.rand((m, k), dtype=torch.float64, device="cuda", generator=gen) - 0.5
     B = torch.rand((k, n), dtype=torch.float64, device="cuda", generator=gen) - 0.5
