@@ -273,23 +273,19 @@ inline bool tiny_small_tiles(int64_t m, int64_t n) {
 }
 
 // Which products: at most one 32 x 32 tile of C per compute unit, at most 512 elements of k in a row for a wavefront (each of
-// the 16 takes every 16th modulus), and few enough operands for a compute unit to load (32 Kp N or 64 Kp N bytes).  Prepared operands
-// gain there nearly throughout (us, other operands in each call, two launches | one: 256^3 N = 14 8.1 | 7.3, 256 x 256 x 512 FP32 N = 8 8.3 | 5.6,
-// 400 x 400 x 256 N = 15 9.4 | 8.7, 400 x 400 x 384 FP32 N = 8 8.3 | 7.8, 512 x 512 x 256 N = 15 9.9 | 8.9; with Kp = 128, N = 15 and tiles of
-// 16 x 16 6.7 | 6.9).  Beyond the limits it is uneven: 200 x 200 x 1024 FP32 N = 8 9.5 | 7.3, but 500 x 300 x 777 9.6 | 11.2,
-// 400 x 400 x 1024 10.6 | 11.4, 128 x 128 x 1024 N = 14 10.0 | 10.2.
+// the 16 takes every 16th modulus), and few enough operands for a compute unit to load: 64 Kp N bytes with tiles of 32 x 32, 32 Kp N with
+// 16 x 16.  Prepared operands gain nearly throughout (us, other operands in each call, graph, two launches | one: 400 x 400 x 256 N = 15 10.5 | 9.9,
+// 512 x 512 x 512 FP32 N = 7 9.9 | 9.0, 512 x 512 x 256 N = 15 11.0 | 10.3, 500 x 500 x 128 N = 20 12.0 | 9.3, 150 x 150 x 512 N = 13 9.5 | 8.1; 300 x 300 x 512 FP32 N = 8
+// 8.7 | 9.2).  Beyond the limits: 231 x 384 x 512 N = 14 (32 x 32) 10.0 | 12.6, 277 x 277 x 300 N = 16 0.86, 105 x 172 x 512 N = 16 (16 x 16) 0.97.
 //
-// A call that converts its factors itself gains less, and nothing where C is about as wide as high and the moduli are many
-// (whole calls, in a graph | one after another from Python, us, two launches -> one; two are taken for 300 x 300 x 128 N = 15
-// 12.3 -> 13.6 | 12.6 -> 13.5, 320 x 320 x 256 N = 16 +1.0 | +0.7, 400 x 400 x 384 FP32 N = 8 13.3 -> 13.8 | 13.4 -> 13.9, 512 x 300 x 128
-// N = 16 +0.7 | +1.0, with tiles of 16 x 16 200^3 N = 16 +1.0 | +1.4; one for 256^3 N = 14 0 | -0.6, 128^3 N = 14 +0.3 | -0.7,
-// 400 x 400 x 128 FP32 N = 8 10.7 -> 9.9 | 11.8 -> 10.3, 512 x 512 x 512 FP32 N = 6 14.3 -> 13.2 | 14.2 -> 13.0, 512 x 512 x 256 N = 15
-// 16.5 -> 16.0 | 16.4 -> 15.8, 1000 x 250 x 256 17.3 -> 15.3 | 17.6 -> 15.3, 8000 x 30 x 64 27.5 -> 20.5 | 27.9 -> 20.3).
-// Of those taken, 512 x 512 x 128 N = 12 gains 0.3 in a graph and loses 0.3 one after another, 64 x 250 x 256 N = 16 gains 0.4 | 0;
-// N = 14 and 15 with Kp = 256 and tiles of 16 x 16 are even in a graph and lose up to 0.9 one after another, Kp = 384 with N = 8 to 10
-// and C wider than 448 loses up to 1.7.  Accurate mode shows the same signs.
+// A call that converts its factors itself gains less (whole calls, in a graph, us, two launches -> one: 209 x 209 x 512 N = 14 16.1 -> 15.8, 68 x 87 x 300
+// N = 14 13.8 -> 12.3, 188 x 140 x 256 N = 15 13.1 -> 11.3, 142 x 142 x 64 N = 14 12.0 -> 9.5, 512 x 512 x 512 FP32 N = 7 15.3 -> 14.8, 1000 x 250 x 256 N = 15
+// 18.1 -> 16.3), and may lose where C is about as wide as high and the moduli are many: 512 x 512 x 256 N = 16 17.4 -> 18.2,
+// 319 x 319 x 256 N = 17 15.7 -> 17.0, 300 x 300 x 512 FP32 N = 8 14.1 -> 15.7, 400 x 400 x 256 N = 15 16.3 -> 17.2.  The lines below are from before
+// the kernel's loads became fewer; on the safe side of them 200 x 200 x 256 N = 16 or 312 x 528 x 128 N = 18 would gain 5 to 15 % by now.
 inline bool tiny_product_applies(int64_t m, int64_t n, int64_t Kp, int N, bool prepared) {
-    if ((m + 31) / 32 * ((n + 31) / 32) > 256 || (N + 15) / 16 * Kp > 512 || Kp * N > 4096) return false;
+    if ((m + 31) / 32 * ((n + 31) / 32) > 256 || (N + 15) / 16 * Kp > 512) return false;
+    if (Kp * N > (tiny_small_tiles(m, n) ? 7168 : 4096)) return false;
     const int64_t longer = std::max(m, n), shorter = std::min(m, n);
     if (prepared || longer >= 4 * shorter) return true;
     if (tiny_small_tiles(m, n)) return N <= 15 || shorter <= 64;
