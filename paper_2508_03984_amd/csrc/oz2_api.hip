@@ -357,8 +357,8 @@ oz2_status gemm_impl(Ctx &g, int opA, int opB, int64_t m, int64_t n, int64_t k, 
         }
         OZ2_TRY(launch_accurate_finish(m, n, ranges, make_accu_shift_args(tab), scratch, tA, tB, stream));
     } else {
-        if (!fuse[0]) OZ2_TRY(launch_fast_shifts<T>(A, lda, a_kc, m, k, sa, scratch, tA, stream));
-        if (!fuse[1]) OZ2_TRY(launch_fast_shifts<T>(B, ldb, b_kc, n, k, sa, scratch, tB, stream));
+        if (!fuse[0]) OZ2_TRY(launch_fast_shifts<T>(A, lda, a_kc, m, k, sa, rA, tA, stream));
+        if (!fuse[1]) OZ2_TRY(launch_fast_shifts<T>(B, ldb, b_kc, n, k, sa, rB, tB, stream));
     }
     if (oz2_status st = mark(g, 1, stream)) return st;
     if (overlapped) {
@@ -394,7 +394,7 @@ struct oz2_operand {
     bool is_double;
     int N;
     int64_t rows, k, rows_pad, Kp;
-    char *mem;                             // one device allocation: [t | residues | scratch]
+    char *mem;                             // one device allocation: [t | residues]
     size_t bytes;
     int32_t *t;
     int8_t *res;
@@ -423,8 +423,7 @@ oz2_status prepare_impl(int side, int op, int64_t rows, int64_t k, const T *X, i
     o->side = side; o->is_double = is_double; o->N = N; o->rows = rows; o->k = k;
     o->rows_pad = round_up(rows, kPadMN); o->Kp = round_up(k, kPadK);
     const size_t off_res = align256((size_t)rows * 4);
-    const size_t off_scratch = off_res + align256((size_t)N * o->rows_pad * o->Kp);
-    o->bytes = off_scratch + align256(column_scratch_bytes(rows));
+    o->bytes = off_res + align256((size_t)N * o->rows_pad * o->Kp);
     void *p = nullptr;
     if (hipMalloc(&p, o->bytes) != hipSuccess) { (void)hipGetLastError(); delete o; return OZ2_WORKSPACE; }
     o->mem = static_cast<char *>(p);
@@ -435,7 +434,7 @@ oz2_status prepare_impl(int side, int op, int64_t rows, int64_t k, const T *X, i
         const FusedFactor<T> f{X, ld, k_contiguous, rows, k, o->t, o->res, o->rows_pad, o->Kp, nullptr, nullptr, 0, 0};
         e = launch_fused_conversion<T>(f, FusedFactor<T>{}, make_shift_args(tab), make_mod_args(tab, false), stream);
     } else {
-        e = launch_fast_shifts<T>(X, ld, k_contiguous, rows, k, make_shift_args(tab), o->mem + off_scratch, o->t, stream);
+        e = launch_fast_shifts<T>(X, ld, k_contiguous, rows, k, make_shift_args(tab), o->res, o->t, stream);
         if (e == hipSuccess)
             e = launch_any_residues<T>(X, ld, k_contiguous, rows, k, o->t, make_mod_args(tab, false), o->res,
                                        o->rows_pad, o->Kp, stream);

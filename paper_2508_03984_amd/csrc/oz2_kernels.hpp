@@ -80,7 +80,8 @@ hipError_t launch_residues(const T *X, int64_t ld, int64_t rows, int64_t len, co
 // The same two stages for the COLUMNS of X (rows x cols, leading dimension ld), reading X in
 // place: one shift per column, and residue slices of X transposed, K-blocked:
 // out[s][h / 64][c][h % 64] for c < cols_pad, h < rows_pad (zero beyond cols / rows).
-// scratch: column_scratch_bytes(cols) bytes of device memory, overwritten.
+// scratch: the memory of that factor's residue slices (at least 2 bytes per element of the padded factor), overwritten
+// before the slices are.
 template <typename T>
 hipError_t launch_shifts_cols(const T *X, int64_t ld, int64_t rows, int64_t cols,
                               const ShiftArgs &sa, void *scratch, int32_t *t, hipStream_t stream);

@@ -21,8 +21,6 @@ constexpr int kMaxKRanges = OZ2_MAX_K_BLOCKED / OZ2_MAX_K;
 inline int64_t round_up(int64_t x, int64_t to) { return (x + to - 1) / to * to; }
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// Scratch of the column kernels: per column a 64-bit maximum and a 64-bit sum of squares.
-inline size_t column_scratch_bytes(int64_t cols) { return (size_t)cols * 16; }
 // Scratch of accurate mode: per row of A and column of B the bits of max |.| (8 bytes), the
 // pre-shift (4) and one maximum of Cbar per K range (4 each).
 inline size_t accurate_scratch_bytes(int64_t m, int64_t n) { return (size_t)(m + n) * (12 + 4 * kMaxKRanges); }
@@ -144,7 +142,7 @@ inline Layout make_layout(int64_t m, int64_t n, int64_t k, int N, bool prod_u8, 
     L.Mp = round_up(m, kPadMN); L.Np = round_up(n, kPadMN); L.Kp = round_up(k, kPadK);
     size_t o = 0;
     if (with_operands) {
-        L.off_bt = o;   o += align256(std::max(column_scratch_bytes(std::max(m, n)), accurate_scratch_bytes(m, n)));
+        L.off_bt = o;   o += align256(accurate_scratch_bytes(m, n));
         L.off_ta = o;   o += align256((size_t)m * 4);
         L.off_tb = o;   o += align256((size_t)n * 4);
         L.off_ra = o;   o += align256((size_t)N * L.Mp * L.Kp);

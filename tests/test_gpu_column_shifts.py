@@ -1,0 +1,80 @@
+"""The shifts of columns from one read: tiles of a column whose maxima lie any number of binades below the column's, columns whose
+sum of squares is close to a threshold of the shift, against the oracle."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2508_03984_amd as oz
+from oracle import constants as K
+from paper_2508_03984_amd import binding as b
+
+pytestmark = pytest.mark.gpu
+
+TILE = 128                                               # rows of a column per workgroup
+
+
+def column_shifts(B, N):
+    k, n = B.shape
+    is_double = B.dtype == np.float64
+    dt = torch.float64 if is_double else torch.float32
+    A = torch.ones((2, k), dtype=dt, device="cuda")
+    wide = torch.full((k, n + 3), 7.0, dtype=dt, device="cuda")         # what lies beyond a row is not read as part of it
+    wide[:, :n] = torch.from_numpy(B).cuda()
+    C = torch.empty((2, n), dtype=dt, device="cuda")
+    (oz.oz2_dgemm if is_double else oz.oz2_sgemm)(2, n, k, 1.0, A, k, wide, n + 3, 0.0, C, n, N)
+    torch.cuda.synchronize()
+    return oz.stage_tensor(b.OZ2_STAGE_SHIFT_B).cpu().numpy()
+
+
+@pytest.mark.parametrize("dtype,N", [(np.float64, 15), (np.float32, 8)])
+@pytest.mark.parametrize("k,n", [(4097, 1), (4352, 63), (4353, 64), (5000, 65), (9001, 130), (16385, 70), (40001, 70), (65537, 9),
+                                 (270000, 5)])
+def test_tiles_of_any_scale(oracle, k, n, dtype, N):
+    rng = np.random.default_rng(k + n)
+    B = (rng.random((k, n)) - 0.5) * np.exp(0.5 * rng.standard_normal((k, n)))
+    tiles = -(-k // TILE)
+    scale = np.ldexp(1.0, -rng.integers(0, 9, (tiles, n)) * rng.integers(0, 5, n))     # some columns of one scale
+    scale[rng.random((tiles, n)) < 0.1] = 0.0            # tiles of zeros
+    B *= np.repeat(scale, TILE, axis=0)[:k]
+    B[:, n // 2] *= 2.0 ** (-1060 if dtype == np.float64 else -140)                    # subnormal numbers
+    if n > 2:
+        B[:, 1] = 0.0
+        B[:, 0] = 0.0
+        B[k - 1, 0] = -3.0                               # one number, in the last row
+    B = B.astype(dtype)
+    want, _, _ = oracle.shifts(B.astype(np.float64), 1, K.constants(N).Pfast)
+    assert np.array_equal(column_shifts(B, N), want)
+
+
+@pytest.mark.parametrize("dtype,N", [(np.float64, 16), (np.float32, 8)])
+@pytest.mark.parametrize("below", [2, 3, 5, 8])
+def test_sums_at_a_threshold(oracle, below, dtype, N):
+    """The first tile alone has the maximum; the others lie `below` binades lower, so that from 3 on only an interval of
+    theirs is stored.  The first tile's sum puts the whole one up to 32 steps below or above a threshold."""
+    k, n = 4500, 64
+    Pfast = K.constants(N).Pfast
+    rng = np.random.default_rng(below)
+    B = np.zeros((k, n))
+    B[TILE:] = np.ldexp(0.5 + 0.5 * rng.random((k - TILE, n)), 1 - below).astype(dtype)
+    B[np.arange(k) % 8 != 0] = 0.0
+    rest = np.square(np.ceil(B * 2.0 ** 15)).sum(axis=0)
+    # the shift falls by one where 0.51 log2(T 2^-30) crosses Pfast - j; here between 2^36.5 and 2^38.5
+    j = math.floor(Pfast - 0.51 * 6.5)
+    theta = math.floor(2.0 ** (30 + (Pfast - j) / 0.51))
+    step = max(1, int(0.1 * math.sqrt(TILE * rest.max()) / 2))
+    for c in range(n):
+        left = theta - int(rest[c]) + (c - n // 2) * step
+        assert left > 2 ** 32
+        i = 0
+        while left > 0:                                  # a sum of squares of q <= 65535
+            q = min(65535, math.isqrt(left))
+            B[i, c] = math.ldexp(q, -15)
+            left -= q * q
+            i += 1
+        assert i <= TILE
+    B = B.astype(dtype)
+    want, e, _ = oracle.shifts(B.astype(np.float64), 1, Pfast)
+    assert (e == 0).all() and len(set(want)) == 2        # both sides of the threshold
+    assert np.array_equal(column_shifts(B, N), want)
