@@ -265,7 +265,7 @@ __global__ __launch_bounds__(kResColThreads) void k_residues_cols(const T *__res
                                                        const int32_t *__restrict__ t, ModArgs ma,
                                                        int8_t *__restrict__ out, int64_t cols_pad,
                                                        int64_t rows_pad, int64_t cols_stride) {
-    residues_cols_block<T, ROUNDS, KIND, kResColThreads>(blockIdx.x, blockIdx.y, X, ld, rows, cols, t, ma, out, cols_pad,
+    residues_cols_block<T, ROUNDS, KIND, kResColThreads, true>(blockIdx.x, blockIdx.y, X, ld, rows, cols, t, ma, out, cols_pad,
                                          rows_pad, cols_stride);
 }
 

@@ -227,7 +227,8 @@ __device__ __forceinline__ void residues_block(int64_t block, const T *__restric
 
 // KIND as in the row kernel: 0 = residues for all moduli, 1 = the 7-bit magnitudes (slice 0).
 // THREADS: 512 (one piece of 8 elements per thread) or 256 (two).
-template <typename T, int ROUNDS, int KIND, int THREADS>
+// READ_ONCE: no other workgroup reads the same elements.
+template <typename T, int ROUNDS, int KIND, int THREADS, bool READ_ONCE>
 __device__ __forceinline__ void residues_cols_block(int64_t block_x, int64_t block_y,
                                                     const T *__restrict__ X, int64_t ld, int64_t rows,
                                                     int64_t cols, const int32_t *__restrict__ t,
@@ -245,21 +246,39 @@ __device__ __forceinline__ void residues_cols_block(int64_t block_x, int64_t blo
     // round when two are needed.
     constexpr int kGroup = kModGroup;
     constexpr int kWaves = THREADS / kWave, kHalves = 8 / kWaves;     // pieces wave, wave + kWaves
-    __shared__ uint2 stage[kGroup][8][65];
+    // Two of them in turn, so that one barrier per group is enough.
+    __shared__ uint2 stages[2][kGroup][8][65];
+    int turn = 0;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t c = block_x * kColStrip + lane;                     // column of X = row of the output
     const int64_t kb = block_y;                                       // K block
     const int sh = c < cols ? t[c] : 0;
 
+    // All loads first, from places that exist (a number beyond the end is not used), and past the L2 where nobody else reads
+    // them: the slices that are written meanwhile need the room.  us, masked loads in order of use and two barriers per group | this:
+    // 8192 x 8192 FP32 N = 8 188 | 142, 40000 x 1000 FP64 N = 18 209 | 192, 16384 x 16384 N = 16 1217 | 1198, 5000 x 2000 N = 15 50 | 45 (without
+    // the second stage 203 at 40000 x 1000, with ordinary loads 161 at 8192 x 8192; several K blocks per workgroup, the next one's
+    // loads ahead, 203 and 163; stores past the L2 238 and 205).
+    T raw[kHalves][8];
+    const T *x = X + (c < cols ? c : cols - 1);
+#pragma unroll
+    for (int half = 0; half < kHalves; ++half) {
+        const int64_t h0 = kb * kBlockK + (wave + kWaves * half) * 8;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const T *at = x + (h0 + i < rows ? h0 + i : rows - 1) * ld;
+            raw[half][i] = READ_ONCE ? __builtin_nontemporal_load(at) : *at;
+        }
+    }
     double v[kHalves][8];
 #pragma unroll
     for (int half = 0; half < kHalves; ++half) {
         const int64_t h0 = kb * kBlockK + (wave + kWaves * half) * 8;
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-            v[half][i] = !(c < cols && h0 + i < rows) ? 0.0
-                         : KIND == 0 ? trunc(ldexp((double)X[(h0 + i) * ld + c], sh))
-                                     : ceil(ldexp(fabs((double)X[(h0 + i) * ld + c]), sh));
+        for (int i = 0; i < 8; ++i) {
+            const double y = c < cols && h0 + i < rows ? (double)raw[half][i] : 0.0;
+            v[half][i] = KIND == 0 ? trunc(ldexp(y, sh)) : ceil(ldexp(fabs(y), sh));
+        }
     }
 
     // Write-out: per modulus the 64 columns x 64 bytes of this tile are contiguous in
@@ -273,6 +292,8 @@ __device__ __forceinline__ void residues_cols_block(int64_t block_x, int64_t blo
     const int n_slices = group_hi < (n_all + kGroup - 1) / kGroup ? group_hi * kGroup : n_all;
     for (int s0 = group_lo * kGroup; s0 < n_slices; s0 += kGroup) {
         const int ns = n_slices - s0 < kGroup ? n_slices - s0 : kGroup;
+        uint2 (*const stage)[8][65] = stages[turn];
+        turn ^= 1;
         if (KIND == 1) {
 #pragma unroll
             for (int half = 0; half < kHalves; ++half) {
@@ -302,7 +323,6 @@ __device__ __forceinline__ void residues_cols_block(int64_t block_x, int64_t blo
             const uint2 hi = stage[g][2 * quarter + 1][col];
             *reinterpret_cast<uint4 *>(dst + (int64_t)(s0 + g) * plane) = make_uint4(lo.x, lo.y, hi.x, hi.y);
         }
-        __syncthreads();
     }
 }
 

@@ -44,7 +44,7 @@ __global__ __launch_bounds__(256) void k_small_residues(SmallSide<T> a, SmallSid
                                      s.vecs_pad, g_lo, g_hi);
     } else {
         const int64_t strips = s.vecs_pad / kColStrip;
-        residues_cols_block<T, ROUNDS, 0, 256>(blk % strips, blk / strips, s.X, s.ld, s.len, s.vecs, s.t, ma, s.out,
+        residues_cols_block<T, ROUNDS, 0, 256, false>(blk % strips, blk / strips, s.X, s.ld, s.len, s.vecs, s.t, ma, s.out,
                                           s.vecs_pad, s.len_pad, s.vecs_pad, g_lo, g_hi);
     }
 }
