@@ -227,7 +227,7 @@ __device__ __forceinline__ void residues_block(int64_t block, const T *__restric
 
 // KIND as in the row kernel: 0 = residues for all moduli, 1 = the 7-bit magnitudes (slice 0).
 // THREADS: 512 (one piece of 8 elements per thread) or 256 (two).
-// READ_ONCE: no other workgroup reads the same elements.
+// READ_ONCE: no other workgroup reads the same elements (the launches of large factors).
 template <typename T, int ROUNDS, int KIND, int THREADS, bool READ_ONCE>
 __device__ __forceinline__ void residues_cols_block(int64_t block_x, int64_t block_y,
                                                     const T *__restrict__ X, int64_t ld, int64_t rows,
@@ -246,8 +246,10 @@ __device__ __forceinline__ void residues_cols_block(int64_t block_x, int64_t blo
     // round when two are needed.
     constexpr int kGroup = kModGroup;
     constexpr int kWaves = THREADS / kWave, kHalves = 8 / kWaves;     // pieces wave, wave + kWaves
-    // Two of them in turn, so that one barrier per group is enough.
-    __shared__ uint2 stages[2][kGroup][8][65];
+    // Two of them in turn, so that one barrier per group is enough, in the large launches (in accurate mode's launch for small residues
+    // one: 2048^3 N = 15 196.6 us a call, two 199.7).
+    constexpr int kStages = READ_ONCE ? 2 : 1;
+    __shared__ uint2 stages[kStages][kGroup][8][65];
     int turn = 0;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t c = block_x * kColStrip + lane;                     // column of X = row of the output
@@ -293,7 +295,7 @@ __device__ __forceinline__ void residues_cols_block(int64_t block_x, int64_t blo
     for (int s0 = group_lo * kGroup; s0 < n_slices; s0 += kGroup) {
         const int ns = n_slices - s0 < kGroup ? n_slices - s0 : kGroup;
         uint2 (*const stage)[8][65] = stages[turn];
-        turn ^= 1;
+        turn ^= kStages - 1;
         if (KIND == 1) {
 #pragma unroll
             for (int half = 0; half < kHalves; ++half) {
@@ -323,6 +325,7 @@ __device__ __forceinline__ void residues_cols_block(int64_t block_x, int64_t blo
             const uint2 hi = stage[g][2 * quarter + 1][col];
             *reinterpret_cast<uint4 *>(dst + (int64_t)(s0 + g) * plane) = make_uint4(lo.x, lo.y, hi.x, hi.y);
         }
+        if (kStages == 1) __syncthreads();
     }
 }
 

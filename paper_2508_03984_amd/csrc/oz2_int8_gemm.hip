@@ -11,7 +11,8 @@
 // Tiling: workgroup = WM x WN wavefronts, block tile (32 TM WM) x (32 TN WN) x 64, each
 // wavefront owns (32 TM) x (32 TN), in 2 TM x 2 TN accumulators of v_mfma_i32_16x16x64_i8.  The
 // large configuration is 2 x 4 wavefronts of 128 x 64 (a 256 x 256 block, 128 accumulator
-// registers per lane, two wavefronts per SIMD).
+// registers per lane, two wavefronts per SIMD).  Where there are many such blocks or the contraction is long, the uint8 forms go
+// to 4 wavefronts of 128 x 128 instead (oz2_wide_gemm.hip; wide_gemm_applies has the line).
 //
 // Bound: board power for large products of random residues (the clock falls to 1.6 GHz), so the instruction that
 // spends less energy per operation is the faster one: from registers 16x16x64 sustains 4.1 POP/s on
