@@ -36,7 +36,7 @@ INT8_PEAK_TOPS = 5000.0          # MI355X dense INT8 MFMA, published
 HBM_PEAK_GBS = 8000.0
 
 def measured_gemm_traffic(dtype: str, size: int, num_moduli: int):
-    """L2<->memory bytes per launch of k_int8_gemm for this workload, as measured with rocprofv3
+    """L2<->memory bytes per launch of the INT8 GEMM for this workload, as measured with rocprofv3
     (FETCH_SIZE / WRITE_SIZE runs of this script, scaled by what the counters read for
     `--stage copy`).  The figure is not measured by this run: it is read from the committed
     summary under profiles/ that holds it, from a line of the form
@@ -832,7 +832,7 @@ def main() -> int:
                                f"seed 0/1, {'accurate' if args.accurate else 'fast'} mode, N={N} moduli, "
                                f"alpha=1 beta=0",
                    "num_moduli": N, "m": m, "n": n, "k": k, "phi": args.phi},
-        "roofline": {"bound": "mfma", "kernel": "k_int8_gemm (batched over moduli)",
+        "roofline": {"bound": "mfma", "kernel": "INT8 GEMM: k_wide_gemm, or k_int8_gemm for fewer or smaller tiles (batched over moduli)",
                      "achieved": gemm_tops, "peak": INT8_PEAK_TOPS, "unit": "TFLOP/s",
                      "frac": gemm_tops / INT8_PEAK_TOPS,
                      # per launch of THIS run (the profiled run's bytes per call over this run's launches)
