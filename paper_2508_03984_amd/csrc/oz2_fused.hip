@@ -2,7 +2,7 @@
 // A workgroup owns whole vectors (V rows, or a strip of V columns, of a factor) and keeps them in
 // registers between the three things that are done to them: the maximum of |x|, the exact sum of
 // squares behind the shift (fast mode of Section 4.2), and the reduction modulo all N moduli.  The
-// general kernels (oz2_prepost.hip, oz2_columns.hip) do these in two to six launches and two or three
+// general kernels (oz2_prepost.hip, oz2_columns.hip) do these in two or three launches and two or three
 // reads; their results are the same bit for bit.  fused_plan (oz2_plan.hpp) says which vectors fit.
 //
 // Layout: after the load, thread `tid` holds in piece c the 8 consecutive elements of number
