@@ -88,8 +88,11 @@ oz2_status ensure_workspace(Ctx &g, size_t need_whole, size_t need_min, size_t e
         }
         void *p = nullptr;
         const size_t more = g.ws_limit ? std::max(want, std::min(g.ws_limit, want + extra)) : want + extra;
-        if (more > want && hipMalloc(&p, more) == hipSuccess) want = more;
-        else if (hipMalloc(&p, want) != hipSuccess) { (void)hipGetLastError(); return OZ2_WORKSPACE; }
+        if (more > want) {
+            if (hipMalloc(&p, more) == hipSuccess) want = more;
+            else (void)hipGetLastError();                     // no later success clears it, and the check after a launch would find it
+        }
+        if (!p && hipMalloc(&p, want) != hipSuccess) { (void)hipGetLastError(); return OZ2_WORKSPACE; }
         g.ws = static_cast<char *>(p); g.ws_bytes = want; g.ws_owned = true; g.ws_device = dev;
     }
     *have = g.ws_limit ? std::min(g.ws_bytes, std::max(g.ws_limit, need_min)) : g.ws_bytes;
