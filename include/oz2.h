@@ -253,15 +253,17 @@ oz2_status oz2_ctx_sgemm_prepared(oz2_context *ctx, const oz2_operand *left, con
  * oz2_set_int32_products(1)): oz2_workspace_bytes gives the size for a
  * problem (0 if the arguments are unsupported).  For a small C and a long contraction that includes
  * planes for the residues of up to 16 K ranges, which are then contracted at once so that more of the compute units have work;
- * a workspace that has room for everything but these (a smaller caller-owned one, a limit, the library's own buffer
- * from an earlier call) serves such a product with one range, at the same result, bit for bit.  oz2_set_workspace hands the
+ * a workspace that has room for everything but these (a smaller caller-owned one, a limit) serves such a product with
+ * one range, at the same result, bit for bit.  oz2_set_workspace hands the
  * library a caller-owned device buffer (kept, not freed, must stay valid until
  * replaced; 256-byte aligned); with (NULL, 0) the library goes back to
  * allocating its own buffer with hipMalloc (on the device that is current at the
  * call; a call made with another device current allocates anew there), growing it on
  * demand and keeping it until oz2_release.  The library's own buffer is sized for
- * oz2_workspace_bytes, except for calls that take the overlapped form described under
- * oz2_set_overlap (an option): those work through C in panels of at most 4096 x 4096
+ * oz2_workspace_bytes without the planes of K ranges; these lie in a reserve behind it that every new buffer gets, enough for any product that
+ * fits the rest (15 times the rest, at most 256 MiB; without it if that is refused, less of it under a limit), so that a buffer never
+ * grows for them and no product depends on the calls before it.  Calls that take the overlapped form described under
+ * oz2_set_overlap (an option) work through C in panels of at most 4096 x 4096
  * anyway, so their buffer holds the products of one such panel beside the residues (at
  * m = n = k = 16384 and 16 moduli 8.9 GB instead of 12.9 GB).
  *

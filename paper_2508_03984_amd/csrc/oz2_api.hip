@@ -23,6 +23,7 @@ struct oz2_context {
     std::mutex mu;                         // guards the host-side fields below, not the device buffers
     char *ws = nullptr;
     size_t ws_bytes = 0;
+    size_t ws_planes = 0;                  // of them (library's own buffer): reserve for the planes of K ranges
     bool ws_owned = false;
     int ws_device = -1;                    // device of the library's own buffer
     size_t ws_limit = 0;                   // for the library's own buffer; 0 = none
@@ -61,14 +62,18 @@ Ctx &default_context() {
 inline Ctx &resolve(oz2_context *c) { return c ? *c : default_context(); }
 
 // Makes at least `need_min` bytes of workspace available, `need_whole` if nothing limits it;
-// *have receives the bytes the call may use.  `extra` bytes more are allocated with a new buffer, if they are to be had, but a
-// buffer that lacks only these is not replaced.  Growing the library's own buffer (or moving it to
+// *have receives the bytes the call may use, *with_planes the same with what there is behind them for the planes of K ranges (a
+// caller's buffer: all of it).  Growing the library's own buffer (or moving it to
 // another device) waits for the device, frees and allocates: the only synchronising step of a
 // product call, and only when the buffer is too small.
-oz2_status ensure_workspace(Ctx &g, size_t need_whole, size_t need_min, size_t extra, size_t *have) {
+//
+// The planes of K ranges never make it grow: a call that has run once in a buffer finds the same buffer again, which a graph
+// that was captured between may hold.  Instead every new buffer has planes_reserve more, if that is to be had, so that whatever product
+// fits the rest has its planes, in whatever order calls come (256 x 256 x 40000 after the same C with a short k: 67 us, without planes 175).
+oz2_status ensure_workspace(Ctx &g, size_t need_whole, size_t need_min, size_t *have, size_t *with_planes) {
     if (g.ws && !g.ws_owned) {                                // caller-owned: take it as it is
         if (g.ws_bytes < need_min) return OZ2_WORKSPACE;
-        *have = g.ws_bytes;
+        *have = *with_planes = g.ws_bytes;
         return OZ2_OK;
     }
     size_t want = need_whole;
@@ -76,26 +81,32 @@ oz2_status ensure_workspace(Ctx &g, size_t need_whole, size_t need_min, size_t e
     if (want < need_min) return OZ2_WORKSPACE;
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) return OZ2_HIP_ERROR;
-    if (!g.ws || g.ws_bytes < want || g.ws_device != dev) {   // the buffer lives on the current device
+    if (!g.ws || g.ws_bytes - g.ws_planes < want || g.ws_device != dev) {   // the buffer lives on the current device
         if (g.ws) {                                           // wait on the device that may still use it
             const bool elsewhere = g.ws_device != dev;
             if (elsewhere && hipSetDevice(g.ws_device) != hipSuccess) return OZ2_HIP_ERROR;
             const hipError_t e = hipDeviceSynchronize();
             (void)hipFree(g.ws);
-            g.ws = nullptr; g.ws_bytes = 0;
+            g.ws = nullptr; g.ws_bytes = g.ws_planes = 0;
             if (elsewhere && hipSetDevice(dev) != hipSuccess) return OZ2_HIP_ERROR;
             if (e != hipSuccess) return OZ2_HIP_ERROR;
         }
         void *p = nullptr;
-        const size_t more = g.ws_limit ? std::max(want, std::min(g.ws_limit, want + extra)) : want + extra;
-        if (more > want) {
-            if (hipMalloc(&p, more) == hipSuccess) want = more;
-            else (void)hipGetLastError();                     // no later success clears it, and the check after a launch would find it
+        size_t planes = planes_reserve(want);
+        if (g.ws_limit) planes = std::min(planes, g.ws_limit - want);
+        if (planes > 0 && hipMalloc(&p, want + planes) != hipSuccess) {
+            (void)hipGetLastError();                          // no later success clears it, and the check after a launch would find it
+            p = nullptr;
         }
-        if (!p && hipMalloc(&p, want) != hipSuccess) { (void)hipGetLastError(); return OZ2_WORKSPACE; }
-        g.ws = static_cast<char *>(p); g.ws_bytes = want; g.ws_owned = true; g.ws_device = dev;
+        if (!p) {
+            planes = 0;
+            if (hipMalloc(&p, want) != hipSuccess) { (void)hipGetLastError(); return OZ2_WORKSPACE; }
+        }
+        g.ws = static_cast<char *>(p); g.ws_bytes = want + planes; g.ws_planes = planes; g.ws_owned = true; g.ws_device = dev;
     }
-    *have = g.ws_limit ? std::min(g.ws_bytes, std::max(g.ws_limit, need_min)) : g.ws_bytes;
+    const size_t limit = g.ws_limit ? std::max(g.ws_limit, need_min) : g.ws_bytes;
+    *have = std::min(g.ws_bytes - g.ws_planes, limit);
+    *with_planes = std::min(g.ws_bytes, limit);
     return OZ2_OK;
 }
 
@@ -166,7 +177,7 @@ hipError_t launch_block_residues(const T *X, int64_t ld, bool k_contiguous, int6
 // whose reduced results are folded together modulo p_s), then its accumulation and unscaling.
 template <typename T>
 oz2_status run_products(Ctx &g, const Layout &L, const Panels &P, const int8_t *rA, const int8_t *rB,
-                        const int32_t *tA, const int32_t *tB, void *prod, size_t prod_bytes, const ModArgs &ma,
+                        const int32_t *tA, const int32_t *tB, void *prod, size_t with_planes, const ModArgs &ma,
                         double alpha, double beta, T *C, int64_t ldc, hipStream_t stream) {
     // The product buffer holds one panel of C at a time: [N][rows][cols] (all of C if P.count is 1).
     // The GEMM launches of a panel are cut further (launch_panels, launch_k_len), each writing its
@@ -186,7 +197,7 @@ oz2_status run_products(Ctx &g, const Layout &L, const Panels &P, const int8_t *
             const int64_t rows = std::min(P.pr, L.Mp - row0), cols = std::min(P.pc, L.Np - col0);
             const Panels Q = g.cut_launches ? launch_panels(rows, cols, L.Kp) : Panels{rows, cols, 1};
             const int64_t k_len = g.cut_launches && L.prod_u8 ? launch_k_len(L.Kp, L.N, Q) : std::min<int64_t>(L.Kp, OZ2_MAX_K);
-            const int ranges = P.count == 1 && Q.count == 1 && k_len == L.Kp && prod_bytes >= L.prod_whole + L.prod_ranges ? L.ranges : 1;
+            const int ranges = P.count == 1 && Q.count == 1 && k_len == L.Kp && with_planes >= L.prod_whole + L.prod_ranges ? L.ranges : 1;
             for (int64_t r1 = 0; r1 < rows; r1 += Q.pr)
                 for (int64_t c1 = 0; c1 < cols; c1 += Q.pc) {
                     const int64_t pr = std::min(Q.pr, rows - r1), pc = std::min(Q.pc, cols - c1);
@@ -318,9 +329,9 @@ oz2_status gemm_impl(Ctx &g, int opA, int opB, int64_t m, int64_t n, int64_t k, 
     const size_t prod_want = g.overlap && overlap_applies(L.Kp, panels_4096)
                                  ? align256((size_t)side_r * side_c * bytes_per_entry(N, L.prod_u8))
                                  : L.prod_whole;
-    size_t have = 0;
+    size_t have = 0, with_planes = 0;
     Panels P{};
-    if (oz2_status st = ensure_workspace(g, L.off_prod + prod_want, L.off_prod + L.prod_min, L.prod_ranges, &have)) return st;
+    if (oz2_status st = ensure_workspace(g, L.off_prod + prod_want, L.off_prod + L.prod_min, &have, &with_planes)) return st;
     if (!plan_panels(L, have - L.off_prod, &P)) return OZ2_WORKSPACE;
     const Panels Po = overlap_panels(L, P);                // a workspace limit may have made the panels smaller
     const bool overlapped = g.overlap && overlap_applies(L.Kp, Po.count);
@@ -384,7 +395,7 @@ oz2_status gemm_impl(Ctx &g, int opA, int opB, int64_t m, int64_t n, int64_t k, 
         if (!fuse[1]) OZ2_TRY(launch_any_residues<T>(B, ldb, b_kc, n, k, tB, ma, rB, L.Np, L.Kp, stream));
     }
     if (oz2_status st = mark(g, 2, stream)) return st;
-    if (oz2_status st = run_products<T>(g, L, P, rA, rB, tA, tB, prod, have - L.off_prod, ma, alpha, beta, C, ldc, stream)) return st;
+    if (oz2_status st = run_products<T>(g, L, P, rA, rB, tA, tB, prod, with_planes - L.off_prod, ma, alpha, beta, C, ldc, stream)) return st;
     g.ev_recorded = g.profiling;
     return OZ2_OK;
 }
@@ -458,15 +469,15 @@ oz2_status prepared_impl(Ctx &g, const oz2_operand *l, const oz2_operand *r, dou
     if (oz2_status st = bind_device_resources(g)) return st;
     const ModArgs ma = make_mod_args(table(l->N, is_double), false);
     const Layout L = make_layout(l->rows, r->rows, l->k, l->N, !g.int32_products, false);
-    size_t have = 0;
+    size_t have = 0, with_planes = 0;
     Panels P{};
-    if (oz2_status st = ensure_workspace(g, L.prod_whole, L.prod_min, L.prod_ranges, &have)) return st;
+    if (oz2_status st = ensure_workspace(g, L.prod_whole, L.prod_min, &have, &with_planes)) return st;
     if (!plan_panels(L, have, &P)) return OZ2_WORKSPACE;
     g.last_panels = P; g.have_panels = true; g.last_overlapped_panels = 0; g.last_gemm_launches = 0;
     g.have_last = g.have_last_prod = false; g.ev_recorded = false;
     for (int i = 0; i < 3; ++i)
         if (oz2_status st = mark(g, i, stream)) return st;
-    if (oz2_status st = run_products<T>(g, L, P, l->res, r->res, l->t, r->t, g.ws, have, ma, alpha, beta, C, ldc, stream))
+    if (oz2_status st = run_products<T>(g, L, P, l->res, r->res, l->t, r->t, g.ws, with_planes, ma, alpha, beta, C, ldc, stream))
         return st;
     g.ev_recorded = g.profiling;
     return OZ2_OK;
@@ -477,7 +488,7 @@ void release_workspace(Ctx &g) {                           // g.mu is held
         (void)hipDeviceSynchronize();
         (void)hipFree(g.ws);
     }
-    g.ws = nullptr; g.ws_bytes = 0; g.ws_owned = false; g.have_last = g.have_last_prod = false;
+    g.ws = nullptr; g.ws_bytes = g.ws_planes = 0; g.ws_owned = false; g.have_last = g.have_last_prod = false;
     drop_device_resources(g);
     g.res_device = -1;
 }
@@ -570,6 +581,7 @@ oz2_status oz2_ctx_set_workspace(oz2_context *ctx, void *dev_ptr, size_t bytes) 
     }
     g.ws = static_cast<char *>(dev_ptr);
     g.ws_bytes = dev_ptr ? bytes : 0;
+    g.ws_planes = 0;
     g.ws_owned = false;
     g.have_last = g.have_last_prod = false;
     return OZ2_OK;

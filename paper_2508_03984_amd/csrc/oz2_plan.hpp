@@ -379,6 +379,11 @@ inline int whole_product_ranges(int64_t m, int64_t n, int64_t Mp, int64_t Np, in
     return gemm_plan(m, n, N, Kp / kBlockK, true).ranges;
 }
 
+// What the library's own workspace of `bytes` bytes has beside them for the planes of K ranges: as much as the planes of any product whose
+// workspace fits `bytes` can take (15 times its first planes, with C of few tiles; 247.5 MiB, at 1 x 5377 x 108416 N = 12).
+constexpr size_t kMaxPlanes = (size_t)256 << 20;
+inline size_t planes_reserve(size_t bytes) { return std::min((size_t)(kMaxRanges - 1) * bytes, kMaxPlanes); }
+
 // Side of a panel of the overlapped form: the INT8 GEMM loses nothing down to 4096 x 4096.
 constexpr int64_t kOverlapPanel = 4096;
 
