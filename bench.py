@@ -34,6 +34,27 @@ if ROOT not in sys.path:
 
 INT8_PEAK_TOPS = 5000.0          # MI355X dense INT8 MFMA, published
 HBM_PEAK_GBS = 8000.0
+MEMORY_SIDE_CACHE = 256 << 20
+STAGES = ("shifts", "residues", "int8_gemm", "epilogue")
+
+
+def bytes_of_stages(m, n, k, N, E, PB=1, accurate=False):
+    """What the four stages of a call on untransposed operands of E bytes per element read and write, each pass counted once:
+    A's rows and B's columns are converted by different kernels.  PB: bytes per entry of the products."""
+    Mp, Np, Kp = -(-m // 256) * 256, -(-n // 256) * 256, -(-k // 128) * 128
+    # factors whose vectors fit a workgroup: one read for shifts and residues (in accurate mode for maxima and magnitudes)
+    a_fused, b_fused = Kp <= 16384, Kp <= 4096
+    slices = N * (Mp + Np) * Kp
+    if accurate:             # maxima, then 7-bit magnitudes, which the product C-bar reads
+        shifts = E * ((1 if a_fused else 2) * m * k + (1 if b_fused else 2) * k * n) + 2 * (Mp + Np) * Kp
+    else:                    # rows beyond 49152 elements are read twice; columns once, with sums of squares per 128 rows
+        a = 0 if a_fused else (1 if k <= 49152 else 2) * m * k
+        b = 0 if b_fused else k * n
+        # 3 words of 8 bytes per column and 128 rows, of which 2 are read back
+        shifts = E * (a + b) + (0 if b_fused else 40 * n * -(-k // 128))
+    return dict(zip(STAGES, (shifts + 4 * (m + n), E * (m * k + k * n) + slices, slices + PB * N * Mp * Np,
+                             PB * N * m * n + E * m * n)))
+
 
 def measured_gemm_traffic(dtype: str, size: int, num_moduli: int):
     """L2<->memory bytes per launch of the INT8 GEMM for this workload, as measured with rocprofv3
@@ -709,15 +730,11 @@ def main() -> int:
     gemm_tops = gemm_ops / (stage_ms[2] * 1e-3) / 1e12            # stage_ms[2]: all GEMM launches of a step
     E = 4 if args.sgemm else 8
     PB = 4 if args.int32_products else 1                        # bytes per product entry
-    # factors whose vectors fit a workgroup get their shifts from the launch of the residues (fast mode)
-    a_fused, b_fused = not args.accurate and Kp <= 16384, not args.accurate and Kp <= 4096
-    stage_bytes = [
-        E * ((0 if a_fused else m * k) + (0 if b_fused else 2 * k * n)) + 4 * (m + n),   # shifts: A once, B twice (max, then sum)
-        E * (m * k + k * n) + N * (Mp * Kp + Np * Kp),          # residues
-        N * (Mp * Kp + Np * Kp) + PB * N * Mp * Np,             # GEMM compulsory traffic
-        PB * N * m * n + E * m * n,                             # epilogue
-    ]
+    stage_bytes = list(bytes_of_stages(m, n, k, N, E, PB, args.accurate).values())
     stage_gbs = [b / (t * 1e-3) / 1e9 if t > 0 else 0.0 for b, t in zip(stage_bytes, stage_ms)]
+    beyond = [s for s, r, b in zip(STAGES, stage_gbs, stage_bytes) if r > HBM_PEAK_GBS and b > MEMORY_SIDE_CACHE]
+    if beyond:                                       # more than the memory can give: the byte counts are not what the kernels do
+        log(f"stages beyond the HBM peak: {beyond}")
 
     # what a plain device copy moves on this device (read + write), as the practical ceiling of
     # the bandwidth-bound stages: dC <- dA, 2 GiB each way at the default size
