@@ -54,7 +54,7 @@ def test_long_contractions(m, n, k, N):
 
 @pytest.mark.parametrize("sign", [1.0, -1.0])
 def test_the_largest_sums(sign):
-    """All residues modulo 256 are -128: sums of 2^30, and -(2^30) is impossible, so the other sign has mixed ones."""
+    """All residues modulo 256 are -128, whatever the sign (-128 = 128 there): sums of 2^30, the largest that any slice can have."""
     m, n, k, N = 1024, 1024, 65536, 16
     A = torch.ones((m, k), dtype=torch.float64, device="cuda")
     oz.matmul(A[:256], A[:256].t(), N)
@@ -66,4 +66,29 @@ def test_the_largest_sums(sign):
     oz.matmul(A, B, N)
     torch.cuda.synchronize()
     assert bool((oz.stage_tensor(b.OZ2_STAGE_RES_A)[0] == -128).all())
+    assert torch.equal(U, U32) and torch.equal(C, C32)
+
+
+@pytest.mark.parametrize("sign", [1, -1])
+@pytest.mark.parametrize("p", [255, 253])
+def test_the_largest_sums_of_an_odd_modulus(sign, p):
+    """All residues of A are (p - 1) / 2 modulo p and those of B the same or the opposite: for p = 255 sums of +-127^2 65536, next to
+    which a sum that left its side of zero would have another residue."""
+    m, n, k, N = 1024, 1024, 65536, 14
+    s = oz.oz2_constants(N)["p"].tolist().index(p)
+    A = torch.ones((m, k), dtype=torch.float64, device="cuda")
+    oz.matmul(A[:256], A[:256].t(), N)
+    torch.cuda.synchronize()
+    f = int(oz.stage_tensor(b.OZ2_STAGE_SHIFT_A)[0])            # the scaled integers are below 2^(f + 1)
+    assert 8 < f <= 52
+    half = (p - 1) // 2
+    A *= 1.0 + (half - 2 ** f) % p * 2.0 ** -f                  # 2^f + r = half (mod p)
+    B = sign * A[:n].t()
+    U, C, U32, C32 = residues_and_product(A, B, N)
+    assert bool((oz.stage_tensor(b.OZ2_STAGE_PROD)[s] == sign * half * half * k).all())
+    oz.matmul(A, B, N)
+    torch.cuda.synchronize()
+    assert bool((oz.stage_tensor(b.OZ2_STAGE_RES_A)[s] == half).all())
+    assert bool((oz.stage_tensor(b.OZ2_STAGE_RES_B)[s] == sign * half).all())
+    assert bool((U[s] == sign * half * half * k % p).all())
     assert torch.equal(U, U32) and torch.equal(C, C32)
