@@ -227,8 +227,8 @@ __device__ __forceinline__ void residues_block(int64_t block, const T *__restric
 
 // KIND as in the row kernel: 0 = residues for all moduli, 1 = the 7-bit magnitudes (slice 0).
 // THREADS: 512 (one piece of 8 elements per thread) or 256 (two).
-// READ_ONCE: no other workgroup reads the same elements (the launches of large factors).
-template <typename T, int ROUNDS, int KIND, int THREADS, bool READ_ONCE>
+// LARGE: the launches of large factors (k_residues_cols); otherwise those of accurate mode's small ones (oz2_small.hip).
+template <typename T, int ROUNDS, int KIND, int THREADS, bool LARGE>
 __device__ __forceinline__ void residues_cols_block(int64_t block_x, int64_t block_y,
                                                     const T *__restrict__ X, int64_t ld, int64_t rows,
                                                     int64_t cols, const int32_t *__restrict__ t,
@@ -248,7 +248,7 @@ __device__ __forceinline__ void residues_cols_block(int64_t block_x, int64_t blo
     constexpr int kWaves = THREADS / kWave, kHalves = 8 / kWaves;     // pieces wave, wave + kWaves
     // Two of them in turn, so that one barrier per group is enough, in the large launches (in accurate mode's launch for small residues
     // one: 2048^3 N = 15 196.6 us a call, two 199.7).
-    constexpr int kStages = READ_ONCE ? 2 : 1;
+    constexpr int kStages = LARGE ? 2 : 1;
     __shared__ uint2 stages[kStages][kGroup][8][65];
     int turn = 0;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -256,21 +256,19 @@ __device__ __forceinline__ void residues_cols_block(int64_t block_x, int64_t blo
     const int64_t kb = block_y;                                       // K block
     const int sh = c < cols ? t[c] : 0;
 
-    // All loads first, from places that exist (a number beyond the end is not used), and past the L2 where nobody else reads
-    // them: the slices that are written meanwhile need the room.  us, masked loads in order of use and two barriers per group | this:
-    // 8192 x 8192 FP32 N = 8 188 | 142, 40000 x 1000 FP64 N = 18 209 | 192, 16384 x 16384 N = 16 1217 | 1198, 5000 x 2000 N = 15 50 | 45 (without
-    // the second stage 203 at 40000 x 1000, with ordinary loads 161 at 8192 x 8192; several K blocks per workgroup, the next one's
-    // loads ahead, 203 and 163; stores past the L2 238 and 205).
+    // All loads first, from places that exist (a number beyond the end is not used).  Ordinary ones: past the L2 the
+    // kernel is 5 to 8 % faster where rows are whole 128-byte lines, but 10 to 30 % slower where they are not (strips share lines
+    // then), and what follows finds less of the operand in the memory-side cache.  The kernel | a whole call with 64 rows of A, us, masked loads in
+    // order of use and two barriers per group; this; past the L2: 8192 x 8192 FP32 N = 8 165 | 404; 129 | 342; 121 | 346,
+    // 1000 columns of 40000 FP64 N = 15 181 | 563; 165 | 444; 161 | 454, 1057 of 5182 26 | 96; 25 | 71; 34 | 80, 33 of 50000 FP32 25 | 202; 20 | 85; 31 | 96,
+    // 4096 of 5000 FP32 45 | 130; 41 | 108; 39 | 104, 12001 of 12000 FP64 610 | 1497; 602 | 1287; 642 | 1341.
     T raw[kHalves][8];
     const T *x = X + (c < cols ? c : cols - 1);
 #pragma unroll
     for (int half = 0; half < kHalves; ++half) {
         const int64_t h0 = kb * kBlockK + (wave + kWaves * half) * 8;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const T *at = x + (h0 + i < rows ? h0 + i : rows - 1) * ld;
-            raw[half][i] = READ_ONCE ? __builtin_nontemporal_load(at) : *at;
-        }
+        for (int i = 0; i < 8; ++i) raw[half][i] = x[(h0 + i < rows ? h0 + i : rows - 1) * ld];
     }
     double v[kHalves][8];
 #pragma unroll
@@ -325,7 +323,7 @@ __device__ __forceinline__ void residues_cols_block(int64_t block_x, int64_t blo
             const uint2 hi = stage[g][2 * quarter + 1][col];
             *reinterpret_cast<uint4 *>(dst + (int64_t)(s0 + g) * plane) = make_uint4(lo.x, lo.y, hi.x, hi.y);
         }
-        if (kStages == 1) __syncthreads();
+        if (!LARGE) __syncthreads();
     }
 }
 
