@@ -33,16 +33,19 @@ constexpr unsigned kSplitModuliBelow = OZ2_SPLIT_MODULI_BELOW;   // residue laun
 // gridDim.y > 1: workgroup row y produces the moduli of group y only (groups of kModGroup), so
 // that the smallest problems, whose few workgroups would each walk through all N moduli one after
 // the other, fill more of the chip; the operand is then read once per group, from the caches.
-template <typename T, int ROUNDS>
-__global__ __launch_bounds__(256) void k_small_residues(SmallSide<T> a, SmallSide<T> b, ModArgs ma) {
+// COLUMNS: one of the factors has strided vectors.  Two factors of rows have a kernel of their own, without the registers and
+// the LDS of the column form (1552 x 1520 x 1061, N = 15, us: 15.7 with them, 14.3 without).  7 workgroups per compute unit, as many as LDS
+// has room for, are 72 registers in FP64 instead of 86 (2048^3 N = 15 37.8 -> 35.8 us; 256^3 N = 14 5.2 -> 5.5).
+template <typename T, int ROUNDS, bool COLUMNS>
+__global__ __launch_bounds__(256, 7) void k_small_residues(SmallSide<T> a, SmallSide<T> b, ModArgs ma) {
     const bool first = blockIdx.x < a.blocks;
     const SmallSide<T> s = first ? a : b;
     const int64_t blk = first ? blockIdx.x : blockIdx.x - a.blocks;
     const int g_lo = gridDim.y > 1 ? (int)blockIdx.y : 0, g_hi = gridDim.y > 1 ? (int)blockIdx.y + 1 : 1 << 30;
-    if (s.k_contiguous) {
+    if (!COLUMNS || s.k_contiguous) {
         residues_block<T, ROUNDS, 0>(blk, s.X, s.ld, s.vecs, s.len, s.t, ma, s.out, s.vecs_pad, s.len_pad,
                                      s.vecs_pad, g_lo, g_hi);
-    } else {
+    } else if constexpr (COLUMNS) {
         const int64_t strips = s.vecs_pad / kColStrip;
         residues_cols_block<T, ROUNDS, 0, 256, false>(blk % strips, blk / strips, s.X, s.ld, s.len, s.vecs, s.t, ma, s.out,
                                           s.vecs_pad, s.len_pad, s.vecs_pad, g_lo, g_hi);
@@ -75,10 +78,9 @@ hipError_t launch_small_residues(const T *A, int64_t lda, bool a_k_contiguous, c
     // few workgroups: one row of workgroups per group of moduli (see k_small_residues)
     const unsigned groups = (unsigned)((ma.n + kModGroup - 1) / kModGroup);
     const unsigned rows = (a.blocks + b.blocks) < kSplitModuliBelow ? groups : 1u;
-    if (ma.rounds == 1)
-        hipLaunchKernelGGL((k_small_residues<T, 1>), dim3(a.blocks + b.blocks, rows), dim3(256), 0, stream, a, b, ma);
-    else
-        hipLaunchKernelGGL((k_small_residues<T, 2>), dim3(a.blocks + b.blocks, rows), dim3(256), 0, stream, a, b, ma);
+    const auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(a.blocks + b.blocks, rows), dim3(256), 0, stream, a, b, ma); };
+    if (a.k_contiguous && b.k_contiguous) ma.rounds == 1 ? go(k_small_residues<T, 1, false>) : go(k_small_residues<T, 2, false>);
+    else ma.rounds == 1 ? go(k_small_residues<T, 1, true>) : go(k_small_residues<T, 2, true>);
     return hipGetLastError();
 }
 
