@@ -201,8 +201,9 @@ oz2_status run_products(Ctx &g, const Layout &L, const Panels &P, const int8_t *
             for (int64_t r1 = 0; r1 < rows; r1 += Q.pr)
                 for (int64_t c1 = 0; c1 < cols; c1 += Q.pc) {
                     const int64_t pr = std::min(Q.pr, rows - r1), pc = std::min(Q.pc, cols - c1);
-                    const GemmPanel pn{row0 + r1, pr, col0 + c1, pc, cols, rows * cols, std::min(pr, L.m - row0 - r1),
-                                       std::min(pc, L.n - col0 - c1)};
+                    const int64_t vr = std::min(pr, L.m - row0 - r1), vc = std::min(pc, L.n - col0 - c1);
+                    const bool padding = k_len < L.Kp && padding_computed(pr, pc, vr, vc, L.N);
+                    const GemmPanel pn{row0 + r1, pr, col0 + c1, pc, cols, rows * cols, padding ? pr : vr, padding ? pc : vc};
                     void *dst = static_cast<char *>(prod) + (size_t)(r1 * cols + c1) * entry;
                     for (int64_t k0 = 0; k0 < L.Kp; k0 += k_len) {
                         ++g.last_gemm_launches;

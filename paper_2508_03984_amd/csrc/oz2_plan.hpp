@@ -373,6 +373,15 @@ inline GemmPlan gemm_plan(int64_t rows, int64_t cols, int64_t slices, int64_t kt
     return best;
 }
 
+// A contraction of several launches (k beyond 2^17), which has no K ranges at once: blocks of padding are computed like the others
+// where all of them have a compute unit each and at most half hold entries of C.  Their workgroups read the same rows of A or columns of B as
+// those beside them, and with so few in the launch that help is worth more than the idle units (prepared, us, padding
+// cleared | computed: 64 x 100 x 10^6 N = 6 4227 | 4020, 128 x 128 x 400000 N = 16 1721 | 1693, 16 x 16 x 10^6 N = 15 4292 | 4201, 200 x 100 x 150000 N = 14
+// 649 | 637; with three quarters of the blocks in use 300 x 200 x 200000 N = 15 864 | 883).
+inline bool padding_computed(int64_t rows, int64_t cols, int64_t valid_rows, int64_t valid_cols, int64_t slices) {
+    return blocks_of_128(rows, cols) * slices <= 256 && 2 * blocks_of_128(valid_rows, valid_cols) <= blocks_of_128(rows, cols);
+}
+
 inline int whole_product_ranges(int64_t m, int64_t n, int64_t Mp, int64_t Np, int64_t Kp, int N) {
     const Panels Q = launch_panels(Mp, Np, Kp);
     if (Kp > OZ2_MAX_K || Q.count != 1 || launch_k_len(Kp, N, Q) != Kp) return 1;
