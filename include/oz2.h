@@ -247,9 +247,9 @@ oz2_status oz2_ctx_sgemm_prepared(oz2_context *ctx, const oz2_operand *left, con
                                   float alpha, float beta, float *C, int64_t ldc, hipStream_t stream);
 
 /*
- * Workspace.  A call needs device scratch for the shift vectors (and the
- * per-column partial results behind them), the INT8 residue slices of A and B (Algorithm 1 lines 4-5)
- * and the reduced products U_s (line 7; or the INT32 products of line 6 after
+ * Workspace.  A call needs device scratch for the shift vectors (and accurate mode's
+ * maxima and pre-shifts before them), the INT8 residue slices of A and B (Algorithm 1 lines 4-5; the sums of squares
+ * of long columns lie where their slices go afterwards) and the reduced products U_s (line 7; or the INT32 products of line 6 after
  * oz2_set_int32_products(1)): oz2_workspace_bytes gives the size for a
  * problem (0 if the arguments are unsupported).  For a small C and a long contraction that includes
  * planes for the residues of up to 16 K ranges, which are then contracted at once so that more of the compute units have work;
@@ -269,7 +269,7 @@ oz2_status oz2_ctx_sgemm_prepared(oz2_context *ctx, const oz2_operand *left, con
  *
  * Bounded workspace ("block matrix multiplication" over the rows and columns of C): the
  * products U_s are the largest part (num_moduli * m * n bytes).  When the workspace may
- * not hold them all -- a caller-owned buffer smaller than oz2_workspace_bytes, or a limit
+ * not hold them all -- a caller-owned buffer smaller than oz2_workspace_bytes without the planes of further K ranges, or a limit
  * set with oz2_set_workspace_limit for the library's own buffer (0 = no limit) -- the call
  * computes C panel by panel: the shifts and residues of the whole of A and B once, then
  * for each (row panel, column panel) the INT8 GEMMs and the accumulation of that panel

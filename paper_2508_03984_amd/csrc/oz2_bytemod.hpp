@@ -2,8 +2,8 @@
 // the store phase of the INT8 GEMM.  The constants per modulus and the arithmetic, in one place for
 // the device and for a host build (no HIP needed), so that the CPU can check every value.
 //
-// The sums start at -2^31 instead of 0, so that what they hold is u = x + 2^31 as an
-// unsigned number.  Then, with h = (p - 1) / 2:
+// The sums start at -2^31 (oz2_int8_gemm.hip, oz2_tiny.hip) or at -2^30 (oz2_wide_gemm.hip) instead of 0, so that what they hold is, as an
+// unsigned number, u = x + first with first = 2^31 or 3 2^30.  Then, with h = (p - 1) / 2:
 //   f = t + sum_j byte_j(u) (256^j mod p), one v_dot4_u32_u8.  t in [0, p) is chosen so that
 //       f = x - h (mod p); f <= 255 (1 + 3 * 255) + 255 < 2^18;
 //   q = round(f / p) by one FMA.  The bits of f are those of the subnormal binary32 number 2^-149 f, so no
@@ -47,7 +47,7 @@ inline ByteMod make_byte_mod(int p, uint32_t first = 0x80000000u) {
     return b;
 }
 
-// What the device computes from the biased sum u: a word whose low byte is mod(u - 2^31, p).
+// What the device computes from the biased sum u: a word whose low byte is mod(u - first, p).
 inline uint32_t byte_mod_word(uint32_t u, const ByteMod &b) {
     uint32_t f = b.base;
     for (int j = 0; j < 4; ++j) f += ((u >> (8 * j)) & 0xffu) * ((b.coef >> (8 * j)) & 0xffu);

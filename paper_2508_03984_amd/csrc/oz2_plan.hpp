@@ -279,8 +279,10 @@ inline bool tiny_small_tiles(int64_t m, int64_t n) {
 // A call that converts its factors itself gains less (whole calls, in a graph, us, two launches -> one: 209 x 209 x 512 N = 14 16.1 -> 15.8, 68 x 87 x 300
 // N = 14 13.8 -> 12.3, 188 x 140 x 256 N = 15 13.1 -> 11.3, 142 x 142 x 64 N = 14 12.0 -> 9.5, 512 x 512 x 512 FP32 N = 7 15.3 -> 14.8, 1000 x 250 x 256 N = 15
 // 18.1 -> 16.3), and may lose where C is about as wide as high and the moduli are many: 512 x 512 x 256 N = 16 17.4 -> 18.2,
-// 319 x 319 x 256 N = 17 15.7 -> 17.0, 300 x 300 x 512 FP32 N = 8 14.1 -> 15.7, 400 x 400 x 256 N = 15 16.3 -> 17.2.  The lines below are from before
-// the kernel's loads became fewer; on the safe side of them 200 x 200 x 256 N = 16 or 312 x 528 x 128 N = 18 would gain 5 to 15 % by now.
+// 319 x 319 x 256 N = 17 15.7 -> 17.0, 300 x 300 x 512 FP32 N = 8 14.1 -> 15.7, 400 x 400 x 256 N = 15 16.3 -> 17.2.  The lines below were drawn
+// for a kernel that also requested chunks of k that do not exist and have not been drawn again.  On the side of two launches, calls one after
+// another, two -> one: 200 x 200 x 256 N = 16 17.2 -> 15.3, 150 x 130 x 200 N = 17 16.7 -> 14.5, 300 x 300 x 128 N = 15 17.2 -> 15.7, 448 x 448 x 256 N = 16 18.4 -> 18.3,
+// 312 x 528 x 128 N = 18 15.7 -> 16.2, 500 x 300 x 390 FP32 N = 8 14.5 -> 14.9.
 inline bool tiny_product_applies(int64_t m, int64_t n, int64_t Kp, int N, bool prepared) {
     if ((m + 31) / 32 * ((n + 31) / 32) > 256 || (N + 15) / 16 * Kp > 512) return false;
     if (Kp * N > (tiny_small_tiles(m, n) ? 7168 : 4096)) return false;
@@ -320,11 +322,13 @@ enum class GemmTile { kLarge, kOnePerUnit, kTwoPerUnit };
 inline int64_t blocks_of_128(int64_t rows, int64_t cols) { return (rows + 127) / 128 * ((cols + 127) / 128); }
 
 // Large tiles in the uint8 forms go to the kernel of oz2_wide_gemm.hip if there are more of them than compute units (many more where the
-// contraction is short, and with it the gain: 0 to 3 %), or the contraction is long; its way to the first operands and its
+// contraction is short), or the contraction is long; its way to the first operands and its
 // reduction, which has no other wavefront on its SIMD, weigh more where each unit has a single short tile.  Prepared products, us, oz2_int8_gemm.hip | oz2_wide_gemm.hip: 16384 x 8192 x 16384 N = 8 12205 | 11625, 8192^3 FP32 N = 8
 // 3166 | 3020, 1536 x 1000 x 40000 N = 18 858 | 817, 4096^3 N = 14 755 | 732, 2048^3 N = 15 128.3 | 124.6, 8192 x 8192 x 1024 1181 | 1165, x 512 872 | 859;
 // 4096 x 4096 x 384 222 | 219, 1500 x 1500 x 512 N = 16 45.0 | 44.4; at most one tile per unit: 1024 x 1024 x 16384 188 | 181, x 4096 59.7 | 59.4, 768 x 768 x 4096
-// 50.9 | 51.7, 900 x 900 x 384 N = 16 23.3 | 23.9.  Beyond kWideMaxK its sums would not fit (see there).
+// 50.9 | 51.7, 900 x 900 x 384 N = 16 23.3 | 23.9; short contractions with few tiles per unit: 1131 x 1290 x 469 N = 16 (480 tiles) 30.2 | 31.3, 2079 x 2123 x 747 FP32
+// N = 8 (648) 46.0 | 47.6, 2391 x 1846 x 623 N = 14 (1120) 72.3 | 72.5, 2375 x 4052 x 442 FP32 N = 9 (1440) 80.8 | 80.6, 1779 x 3983 x 513 N = 15 (1680) 103.2 | 102.5 (36 shapes of 257 to
+// 2048 tiles with k = 385 to 767: 0.6 % slower on average).  Beyond kWideMaxK its sums would not fit (see there).
 constexpr int kWideMinKTiles = 6;
 constexpr int64_t kWideMaxK = 65536, kWideLongK = 8192, kWideShortK = 768, kWideShortTiles = 2048;
 // tiles: of all slices and K ranges; k_len elements of k in `ranges` ranges

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
     (1, 1, 1, 2, np.float64),                        # one entry, one chunk of k, two moduli
     (31, 33, 128, 16, np.float64),                   # tile edges; a modulus per wavefront
     (33, 64, 129, 16, np.float64),                   # two chunks
-    (100, 100, 200, 17, np.float32),                 # Kp N just beyond 4096: two launches
+    (100, 100, 200, 17, np.float32),                 # 17 moduli, neither factor narrow: two launches
     (100, 100, 120, 17, np.float32),                 # a second modulus for one wavefront
     (512, 500, 250, 8, np.float32),                  # 256 tiles, the most of the one-launch form
     (513, 500, 250, 8, np.float32),                  # one row more: two launches
