@@ -67,11 +67,14 @@ constexpr int kSumRows = kSumThreads / kWave * kSumPer, kSumLevels = 3;
 constexpr int kExpBias = 2048, kExpShift = 48;
 constexpr uint64_t kSumMask = ((uint64_t)1 << kExpShift) - 1;
 static_assert(kSumRows <= 1 << (39 - 32), "S_d and the exponent share a word");
-// The words of all tiles lie where the residue slices of the same factor go afterwards: N >= 2 bytes per element.
-static_assert(kSumLevels * sizeof(uint64_t) * ((kPadK + kSumRows - 1) / kSumRows) <= OZ2_MIN_MODULI * kPadK, "words beyond the slices");
+// The words of all tiles, and behind them two per column for sums from a second read (see k_col_shift), lie where the residue slices of the
+// same factor go afterwards: N >= 2 bytes per element.
+static_assert((kSumLevels * ((kPadK + kSumRows - 1) / kSumRows) + 2) * sizeof(uint64_t) <= OZ2_MIN_MODULI * kPadK, "words beyond the slices");
+static_assert(kSumThreads / kWave > kSumLevels, "a wavefront clears what k_col_shift adds to");
 
+// (3 workgroups per compute unit: 168 registers in FP64; two more cost a third of them and 5 to 10 %.)
 template <typename T>
-__global__ __launch_bounds__(kSumThreads) void k_col_sums(const T *__restrict__ X, int64_t ld, int64_t rows,
+__global__ __launch_bounds__(kSumThreads, 3) void k_col_sums(const T *__restrict__ X, int64_t ld, int64_t rows,
                                                           int64_t cols, uint64_t *__restrict__ words) {
     constexpr int kWaves = kSumThreads / kWave;
     __shared__ uint64_t part[kSumLevels][kWaves][kColStrip];
@@ -122,6 +125,10 @@ __global__ __launch_bounds__(kSumThreads) void k_col_sums(const T *__restrict__ 
 #pragma unroll
     for (int d = 0; d < kSumLevels; ++d) part[d][wave][lane] = sum[d];
     __syncthreads();
+    if (wave == kSumLevels && c < cols && blockIdx.y == 0) {
+        uint64_t *const second = words + (int64_t)gridDim.y * kSumLevels * cols;
+        second[c] = second[cols + c] = 0;
+    }
     if (wave < kSumLevels && c < cols) {                              // wavefront d writes S_d
         uint64_t t = 0;
 #pragma unroll
@@ -138,11 +145,15 @@ __global__ __launch_bounds__(kSumThreads) void k_col_sums(const T *__restrict__ 
 // q / 2^d' <= q' < q / 2^d' + 1, and with Cauchy's sum q <= sqrt(n S)
 //   S / 4^d' - n <= sum q'^2 <= S / 4^d' + 2 sqrt(n S) / 2^d' + n
 // (the n below is for numbers that the scaling takes to zero).  If both ends of T's interval give the same
-// shift, that is the shift; otherwise the workgroup reads the column again.  The thresholds are a
-// factor of 4 apart, T is at least 2^30 and the interval is narrow, so this is rare.
+// shift, that is the shift; otherwise the tiles with an interval are read again.  The thresholds are a
+// factor of 4 apart, T is at least 2^30 and the interval is narrow (2^-6 to 2^-10 of T), so this is rare.  A compute unit reads 0.5 to 0.6 rows of
+// a column per ns, so for long ones, whose columns are often few, gridDim.y workgroups come to the same conclusion about them and
+// share the rows; the last one to add its sum computes the shift.  us, one workgroup | shares, before either from two reads of everything, uniform
+// numbers with one row 1000 times the others: 10^6 x 100 2231 | 282, 300000 x 300 623 | 247 (with k_col_sums 752 | 374; two reads 420).
 //
 // THREADS / COLS threads go through the words of a column, the first kHeld tiles of each from registers.
 constexpr int kHeld = 8;
+constexpr int kShareTiles = 64;      // tiles of a share of the rows that are read again, at least
 
 // v combined over the lanes of a wavefront with the same lane % COLS
 template <int COLS, typename V, typename F>
@@ -154,12 +165,12 @@ __device__ __forceinline__ V over_column(V v, F f) {
 
 template <typename T, int THREADS, int COLS>
 __global__ __launch_bounds__(THREADS) void k_col_shift(const T *__restrict__ X, int64_t ld, int64_t rows, int64_t cols,
-                                                       const uint64_t *__restrict__ words, ShiftArgs sa,
-                                                       int32_t *__restrict__ t) {
+                                                       const uint64_t *__restrict__ words, unsigned long long *__restrict__ second,
+                                                       ShiftArgs sa, int32_t *__restrict__ t) {
     constexpr int kWaves = THREADS / kWave, kGroups = THREADS / COLS;
     __shared__ uint64_t part[kWaves][COLS];
     __shared__ double low[kWaves][COLS], high[kWaves][COLS];
-    __shared__ uint64_t again;
+    __shared__ uint64_t again, known[COLS];
     __shared__ int exponent[COLS];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = threadIdx.x % COLS, group = threadIdx.x / COLS;
     const int64_t c0 = (int64_t)blockIdx.x * COLS, c = c0 + col;
@@ -226,25 +237,45 @@ __global__ __launch_bounds__(THREADS) void k_col_shift(const T *__restrict__ X, 
         bool open = false;
         if (lane < COLS && c < cols) {
             exponent[col] = e;
+            known[col] = sum;
             // 2^-40 and 1 cover the rounding of lo and hi
             const double a = (double)sum + lo * (1.0 - 0x1p-40) - 1.0, b = (double)sum + hi * (1.0 + 0x1p-40) + 1.0;
             const bool exact = hi == 0.0;
             const int f = shift_exponent(exact ? sum : a > 0.0 ? (uint64_t)a : 0, sa);
             open = !exact && f != shift_exponent((uint64_t)b, sa);
-            t[c] = top ? f - e : 0;                                   // 0: an all-zero column
+            if (!open && blockIdx.y == 0) t[c] = top ? f - e : 0;     // 0: an all-zero column
         }
         const uint64_t mask = __ballot(open);
         if (lane == 0) again = mask;
     }
     __syncthreads();
+    const int share = (tiles + (int)gridDim.y - 1) / (int)gridDim.y, first = (int)blockIdx.y * share;
+    const int64_t end = (int64_t)(first + share) * kSumRows < rows ? (int64_t)(first + share) * kSumRows : rows;
     for (uint64_t m = again; m; m &= m - 1) {                         // the same in every thread
         const int j = __ffsll((unsigned long long)m) - 1;
         const int e = exponent[j];
         sum = 0;
-#pragma unroll 8
-        for (int64_t r = threadIdx.x; r < rows; r += THREADS) {
-            const uint64_t q = (uint64_t)ceil(ldexp(fabs((double)X[r * ld + c0 + j]), 15 - e));
-            sum += q * q;
+        // A wavefront's 64 rows lie in one tile.
+        constexpr int kFlight = 8;
+        for (int64_t r0 = (int64_t)first * kSumRows + wave * kWave; r0 < end; r0 += kFlight * THREADS) {
+            T x[kFlight];
+            uint64_t u0[kFlight];
+#pragma unroll
+            for (int i = 0; i < kFlight; ++i) {
+                const int64_t r = r0 + i * THREADS;
+                u0[i] = words[(r < end ? r : r0) / kSumRows * kSumLevels * cols + c0 + j];
+            }
+#pragma unroll
+            for (int i = 0; i < kFlight; ++i) {
+                const int64_t r = r0 + i * THREADS + lane;
+                x[i] = T(0);
+                if (u0[i] && e + kExpBias - (int)(u0[i] >> kExpShift) >= kSumLevels && r < end) x[i] = X[r * ld + c0 + j];
+            }
+#pragma unroll
+            for (int i = 0; i < kFlight; ++i) {
+                const uint64_t q = (uint64_t)ceil(ldexp(fabs((double)x[i]), 15 - e));
+                sum += q * q;
+            }
         }
         sum = wave_sum(sum);
         __syncthreads();                                              // part is reused
@@ -252,7 +283,15 @@ __global__ __launch_bounds__(THREADS) void k_col_shift(const T *__restrict__ X, 
         __syncthreads();
         if (threadIdx.x == 0) {
             for (int i = 1; i < kWaves; ++i) sum += part[i][0];
-            t[c0 + j] = shift_exponent(sum, sa) - e;
+            bool last = true;
+            if (gridDim.y > 1) {
+                atomicAdd(&second[c0 + j], (unsigned long long)sum);
+                __threadfence();
+                last = atomicAdd(&second[cols + c0 + j], 1ull) == gridDim.y - 1;
+                __threadfence();
+                if (last) sum = atomicAdd(&second[c0 + j], 0ull);
+            }
+            if (last) t[c0 + j] = shift_exponent(known[j] + sum, sa) - e;
         }
     }
 }
@@ -278,16 +317,20 @@ hipError_t launch_shifts_cols(const T *X, int64_t ld, int64_t rows, int64_t cols
     const unsigned strips = (unsigned)((cols + kColStrip - 1) / kColStrip);
     hipLaunchKernelGGL((k_col_sums<T>), dim3(strips, (unsigned)((rows + kSumRows - 1) / kSumRows)), dim3(kSumThreads), 0,
                        stream, X, ld, rows, cols, words);
-    const auto shift = [&](auto kernel, int threads, int per) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)((cols + per - 1) / per)), dim3(threads), 0, stream, X, ld, rows, cols, words,
-                           sa, t);
+    const int64_t tiles = (rows + kSumRows - 1) / kSumRows;
+    unsigned long long *second = reinterpret_cast<unsigned long long *>(words + tiles * kSumLevels * cols);
+    const auto shift = [&](auto kernel, int threads, int per, int most) {
+        const int64_t groups = (cols + per - 1) / per;
+        const int64_t shares = std::max<int64_t>(1, std::min(most / groups, tiles / kShareTiles));
+        hipLaunchKernelGGL(kernel, dim3((unsigned)groups, (unsigned)shares), dim3(threads), 0, stream, X, ld, rows, cols, words, second, sa, t);
     };
     // The fewest threads per column (16, 64 or 256) whose registers hold all its words; of long columns, which are often few,
     // fewer per workgroup.  us for 16 | 64 | 256: 16384 x 16384 10.5 | 28 | 69, 40000 x 1000 16 | 7.6 | 8.3, 10^6 x 100 383 | 110 | 44.
-    const int64_t tiles = (rows + kSumRows - 1) / kSumRows;
-    if (tiles <= 16 * kHeld) shift(k_col_shift<T, 256, 16>, 256, 16);
-    else if (tiles <= 64 * kHeld) shift(k_col_shift<T, 256, 4>, 256, 4);
-    else shift(k_col_shift<T, 1024, 4>, 1024, 4);
+    // Shares only of the longest, and no more workgroups for them than compute units: each reads the words, too (300000 x 300, nothing to
+    // read again, us, 1 share | 3 | 6: 17 | 20 | 36; 40000 x 1000 1 | 4: 7.6 | 11).
+    if (tiles <= 16 * kHeld) shift(k_col_shift<T, 256, 16>, 256, 16, 1);
+    else if (tiles <= 64 * kHeld) shift(k_col_shift<T, 256, 4>, 256, 4, 1);
+    else shift(k_col_shift<T, 1024, 4>, 1024, 4, 256);
     return hipGetLastError();
 }
 

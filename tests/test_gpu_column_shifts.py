@@ -78,3 +78,40 @@ def test_sums_at_a_threshold(oracle, below, dtype, N):
     want, e, _ = oracle.shifts(B.astype(np.float64), 1, Pfast)
     assert (e == 0).all() and len(set(want)) == 2        # both sides of the threshold
     assert np.array_equal(column_shifts(B, N), want)
+
+
+@pytest.mark.parametrize("dtype,N", [(np.float64, 16), (np.float32, 8)])
+@pytest.mark.parametrize("k,n,below,live", [(17000, 9, 4, 1), (40000, 70, 5, 3), (65536, 3, 8, 2), (65537, 5, 6, 1), (130000, 70, 7, 5),
+                                            (300001, 3, 8, 1)])
+def test_long_columns_at_a_threshold(oracle, k, n, below, live, dtype, N):
+    """As above for columns whose second read is shared by several workgroups (and by one, for 16 columns each): every `live`-th tile lies
+    `below` binades under the first, the others one or two, which are known exactly and not read again."""
+    Pfast = K.constants(N).Pfast
+    rng = np.random.default_rng(k)
+    tile = np.arange(k) // TILE
+    down = np.where(tile % live == 0, below, 1 + tile % 2)
+    sparse = np.arange(k) % 97 == 5
+    B = np.ldexp(0.5 + 0.5 * rng.random((k, n)), 1 - down[:, None]).astype(dtype).astype(np.float64)
+    B[~sparse] = 0.0
+    B[(tile % live != 0) & (np.arange(k) % (97 * 64) != 5)] = 0.0
+    B[:TILE] = 0.0
+    rest = np.square(np.ceil(B * 2.0 ** 15)).sum(axis=0)
+    far = np.square(np.ceil(B[tile % live == 0] * 2.0 ** 15)).sum(axis=0)
+    j = math.floor(Pfast - 0.51 * 6.5)
+    theta = math.floor(2.0 ** (30 + (Pfast - j) / 0.51))
+    step = max(1, int(0.1 * math.sqrt(TILE * far.max()) / n))
+    for c in range(n):
+        left = theta - int(rest[c]) + (c - n // 2) * step
+        assert left > 2 ** 32
+        i = 0
+        while left > 0:
+            q = min(65535, math.isqrt(left))
+            B[i, c] = math.ldexp(q, -15)
+            left -= q * q
+            i += 1
+        assert i <= TILE
+    B = B.astype(dtype)
+    want, e, _ = oracle.shifts(B.astype(np.float64), 1, Pfast)
+    assert (e == 0).all() and len(set(want)) == 2
+    for _ in range(3):
+        assert np.array_equal(column_shifts(B, N), want)
