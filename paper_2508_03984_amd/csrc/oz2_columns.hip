@@ -67,10 +67,21 @@ constexpr int kSumRows = kSumThreads / kWave * kSumPer, kSumLevels = 3;
 constexpr int kExpBias = 2048, kExpShift = 48;
 constexpr uint64_t kSumMask = ((uint64_t)1 << kExpShift) - 1;
 static_assert(kSumRows <= 1 << (39 - 32), "S_d and the exponent share a word");
-// The words of all tiles, and behind them two per column for sums from a second read (see k_col_shift), lie where the residue slices of the
-// same factor go afterwards: N >= 2 bytes per element.
-static_assert((kSumLevels * ((kPadK + kSumRows - 1) / kSumRows) + 2) * sizeof(uint64_t) <= OZ2_MIN_MODULI * kPadK, "words beyond the slices");
+// The words of all tiles, and behind them what k_col_shift leaves to k_col_again (five words per column, or fewer), lie where the residue slices
+// of the same factor go afterwards: N >= 2 bytes per element.
+static_assert((kSumLevels * ((kPadK + kSumRows - 1) / kSumRows) + 5) * sizeof(uint64_t) <= OZ2_MIN_MODULI * kPadK, "words beyond the slices");
 static_assert(kSumThreads / kWave > kSumLevels, "a wavefront clears what k_col_shift adds to");
+
+// Columns to read again, in strips of kAgainCols: the sum of a column's known tiles; of a strip, which columns and how many workgroups are
+// done with it; the strips that have any, and how many these are.
+constexpr int kAgainCols = 16;
+struct Again {
+    unsigned long long *sum, *mask, *done, *list, *count;
+    __host__ __device__ Again(uint64_t *words, int64_t tiles, int64_t cols) {
+        sum = reinterpret_cast<unsigned long long *>(words + tiles * kSumLevels * cols);
+        mask = sum + cols; done = mask + cols; list = done + cols; count = list + cols;
+    }
+};
 
 // (3 workgroups per compute unit: 168 registers in FP64; two more cost a third of them and 5 to 10 %.)
 template <typename T>
@@ -125,9 +136,10 @@ __global__ __launch_bounds__(kSumThreads, 3) void k_col_sums(const T *__restrict
 #pragma unroll
     for (int d = 0; d < kSumLevels; ++d) part[d][wave][lane] = sum[d];
     __syncthreads();
-    if (wave == kSumLevels && c < cols && blockIdx.y == 0) {
-        uint64_t *const second = words + (int64_t)gridDim.y * kSumLevels * cols;
-        second[c] = second[cols + c] = 0;
+    if (wave == kSumLevels && c < cols && c % kAgainCols == 0 && blockIdx.y == 0) {
+        const Again a(words, gridDim.y, cols);
+        a.mask[c / kAgainCols] = a.done[c / kAgainCols] = 0;
+        if (c == 0) *a.count = 0;
     }
     if (wave < kSumLevels && c < cols) {                              // wavefront d writes S_d
         uint64_t t = 0;
@@ -147,13 +159,10 @@ __global__ __launch_bounds__(kSumThreads, 3) void k_col_sums(const T *__restrict
 // (the n below is for numbers that the scaling takes to zero).  If both ends of T's interval give the same
 // shift, that is the shift; otherwise the tiles with an interval are read again.  The thresholds are a
 // factor of 4 apart, T is at least 2^30 and the interval is narrow (2^-6 to 2^-10 of T), so this is rare.  A compute unit reads 0.5 to 0.6 rows of
-// a column per ns, so for long ones, whose columns are often few, gridDim.y workgroups come to the same conclusion about them and
-// share the rows; the last one to add its sum computes the shift.  us, one workgroup | shares, before either from two reads of everything, uniform
-// numbers with one row 1000 times the others: 10^6 x 100 2231 | 282, 300000 x 300 623 | 247 (with k_col_sums 752 | 374; two reads 420).
+// a column per ns, so those of long columns (LATER) go to a launch of their own, k_col_again.
 //
 // THREADS / COLS threads go through the words of a column, the first kHeld tiles of each from registers.
 constexpr int kHeld = 8;
-constexpr int kShareTiles = 64;      // tiles of a share of the rows that are read again, at least
 
 // v combined over the lanes of a wavefront with the same lane % COLS
 template <int COLS, typename V, typename F>
@@ -163,9 +172,9 @@ __device__ __forceinline__ V over_column(V v, F f) {
     return v;
 }
 
-template <typename T, int THREADS, int COLS>
+template <typename T, int THREADS, int COLS, bool LATER>
 __global__ __launch_bounds__(THREADS) void k_col_shift(const T *__restrict__ X, int64_t ld, int64_t rows, int64_t cols,
-                                                       const uint64_t *__restrict__ words, unsigned long long *__restrict__ second,
+                                                       const uint64_t *__restrict__ words, Again later,
                                                        ShiftArgs sa, int32_t *__restrict__ t) {
     constexpr int kWaves = THREADS / kWave, kGroups = THREADS / COLS;
     __shared__ uint64_t part[kWaves][COLS];
@@ -243,33 +252,37 @@ __global__ __launch_bounds__(THREADS) void k_col_shift(const T *__restrict__ X, 
             const bool exact = hi == 0.0;
             const int f = shift_exponent(exact ? sum : a > 0.0 ? (uint64_t)a : 0, sa);
             open = !exact && f != shift_exponent((uint64_t)b, sa);
-            if (!open && blockIdx.y == 0) t[c] = top ? f - e : 0;     // 0: an all-zero column
+            t[c] = open ? e : top ? f - e : 0;                        // 0: an all-zero column; e: for k_col_again
+            if (LATER && open) {
+                later.sum[c] = sum;
+                const int64_t strip = c / kAgainCols;
+                if (atomicOr(&later.mask[strip], 1ull << (c % kAgainCols)) == 0) later.list[atomicAdd(later.count, 1ull)] = strip;
+            }
         }
         const uint64_t mask = __ballot(open);
         if (lane == 0) again = mask;
     }
+    if (LATER) return;
     __syncthreads();
-    const int share = (tiles + (int)gridDim.y - 1) / (int)gridDim.y, first = (int)blockIdx.y * share;
-    const int64_t end = (int64_t)(first + share) * kSumRows < rows ? (int64_t)(first + share) * kSumRows : rows;
     for (uint64_t m = again; m; m &= m - 1) {                         // the same in every thread
         const int j = __ffsll((unsigned long long)m) - 1;
         const int e = exponent[j];
         sum = 0;
         // A wavefront's 64 rows lie in one tile.
         constexpr int kFlight = 8;
-        for (int64_t r0 = (int64_t)first * kSumRows + wave * kWave; r0 < end; r0 += kFlight * THREADS) {
+        for (int64_t r0 = wave * kWave; r0 < rows; r0 += kFlight * THREADS) {
             T x[kFlight];
             uint64_t u0[kFlight];
 #pragma unroll
             for (int i = 0; i < kFlight; ++i) {
                 const int64_t r = r0 + i * THREADS;
-                u0[i] = words[(r < end ? r : r0) / kSumRows * kSumLevels * cols + c0 + j];
+                u0[i] = words[(r < rows ? r : r0) / kSumRows * kSumLevels * cols + c0 + j];
             }
 #pragma unroll
             for (int i = 0; i < kFlight; ++i) {
                 const int64_t r = r0 + i * THREADS + lane;
                 x[i] = T(0);
-                if (u0[i] && e + kExpBias - (int)(u0[i] >> kExpShift) >= kSumLevels && r < end) x[i] = X[r * ld + c0 + j];
+                if (u0[i] && e + kExpBias - (int)(u0[i] >> kExpShift) >= kSumLevels && r < rows) x[i] = X[r * ld + c0 + j];
             }
 #pragma unroll
             for (int i = 0; i < kFlight; ++i) {
@@ -283,15 +296,70 @@ __global__ __launch_bounds__(THREADS) void k_col_shift(const T *__restrict__ X, 
         __syncthreads();
         if (threadIdx.x == 0) {
             for (int i = 1; i < kWaves; ++i) sum += part[i][0];
-            bool last = true;
-            if (gridDim.y > 1) {
-                atomicAdd(&second[c0 + j], (unsigned long long)sum);
-                __threadfence();
-                last = atomicAdd(&second[cols + c0 + j], 1ull) == gridDim.y - 1;
-                __threadfence();
-                if (last) sum = atomicAdd(&second[c0 + j], 0ull);
+            t[c0 + j] = shift_exponent(known[j] + sum, sa) - e;
+        }
+    }
+}
+
+// The second read of long columns: workgroups in teams, a strip of columns for each team at a time, of which a wavefront reads
+// 32 rows of a tile that has to be read, 4 rows at a time (t holds the exponents).  The last member of a team to add its sums computes the shifts.
+// Bound: memory latency.  Whole calls with 64 rows of A, us, everything read twice (no words) | read again in k_col_shift, by at most 256 workgroups
+// for all columns | this: 200000 x 400 FP32 with one row 1000 times the others 1425 | 1540 | 1340, 300000 x 300 FP32 exp(2 normal) 2099 | 2144 | 1946, 70000 x 2000
+// FP64 exp(4 normal) 1772 | 1517 | 1390, 70000 x 8192 5725 | 5131 | 5020; nothing to read again: 66000 x 64 552 | 289 | 291, 300000 x 300 2763 | 2558 | 2556.
+// Up to 65536 rows a column costs at most 0.13 ms in k_col_shift, and two launches of sums and words are what the calls of a few columns consist of.
+constexpr int kAgainThreads = 1024, kAgainGrid = 256;
+
+template <typename T>
+__global__ __launch_bounds__(kAgainThreads) void k_col_again(const T *__restrict__ X, int64_t ld, int64_t rows, int64_t cols,
+                                                             const uint64_t *__restrict__ words, Again a, ShiftArgs sa, int32_t *t) {
+    constexpr int kWaves = kAgainThreads / kWave, kRows = kWave / kAgainCols, kFlight = 8, kUnit = kRows * kFlight;
+    static_assert(kSumRows % kUnit == 0, "a unit's rows lie in one tile");
+    __shared__ uint64_t part[kWaves][kAgainCols];
+    __shared__ bool last;
+    const int strips = (int)*a.count;
+    if (strips == 0) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane % kAgainCols, row = lane / kAgainCols;
+    const int teams = strips < (int)gridDim.x ? strips : (int)gridDim.x, members = (int)gridDim.x / teams;
+    const int team = (int)blockIdx.x / members, member = (int)blockIdx.x % members;
+    if (team >= teams) return;
+    const int64_t units = (rows + kUnit - 1) / kUnit;
+    for (int i = team; i < strips; i += teams) {                      // the same in every thread of a workgroup
+        const int64_t strip = (int64_t)a.list[i], c = strip * kAgainCols + col;
+        const bool open = a.mask[strip] >> col & 1;
+        const int e = open ? t[c] : 0;
+        const auto word = [&](int64_t u) { return open && u < units ? words[u * kUnit / kSumRows * kSumLevels * cols + c] : 0; };
+        uint64_t sum = 0, u0 = word(member * kWaves + wave);
+        for (int64_t u = member * kWaves + wave; u < units; u += members * kWaves) {
+            const uint64_t next = word(u + members * kWaves);
+            if (u0 && e + kExpBias - (int)(u0 >> kExpShift) >= kSumLevels) {
+                T x[kFlight];
+#pragma unroll
+                for (int j = 0; j < kFlight; ++j) {
+                    const int64_t r = u * kUnit + j * kRows + row;
+                    x[j] = r < rows ? X[r * ld + c] : T(0);
+                }
+#pragma unroll
+                for (int j = 0; j < kFlight; ++j) {
+                    const uint64_t q = (uint64_t)ceil(ldexp(fabs((double)x[j]), 15 - e));
+                    sum += q * q;
+                }
             }
-            if (last) t[c0 + j] = shift_exponent(known[j] + sum, sa) - e;
+            u0 = next;
+        }
+        sum = over_column<kAgainCols>(sum, [](uint64_t x, uint64_t y) { return x + y; });
+        if (lane < kAgainCols) part[wave][col] = sum;
+        __syncthreads();
+        if (threadIdx.x < kAgainCols && open) {
+            for (int w = 1; w < kWaves; ++w) sum += part[w][col];
+            atomicAdd(&a.sum[c], (unsigned long long)sum);
+            __threadfence();
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) last = atomicAdd(&a.done[strip], 1ull) == (unsigned long long)members - 1;
+        __syncthreads();
+        if (last && threadIdx.x < kAgainCols && open) {
+            __threadfence();
+            t[c] = shift_exponent(atomicAdd(&a.sum[c], 0ull), sa) - e;
         }
     }
 }
@@ -318,19 +386,18 @@ hipError_t launch_shifts_cols(const T *X, int64_t ld, int64_t rows, int64_t cols
     hipLaunchKernelGGL((k_col_sums<T>), dim3(strips, (unsigned)((rows + kSumRows - 1) / kSumRows)), dim3(kSumThreads), 0,
                        stream, X, ld, rows, cols, words);
     const int64_t tiles = (rows + kSumRows - 1) / kSumRows;
-    unsigned long long *second = reinterpret_cast<unsigned long long *>(words + tiles * kSumLevels * cols);
-    const auto shift = [&](auto kernel, int threads, int per, int most) {
-        const int64_t groups = (cols + per - 1) / per;
-        const int64_t shares = std::max<int64_t>(1, std::min(most / groups, tiles / kShareTiles));
-        hipLaunchKernelGGL(kernel, dim3((unsigned)groups, (unsigned)shares), dim3(threads), 0, stream, X, ld, rows, cols, words, second, sa, t);
+    const Again later(words, tiles, cols);
+    const auto shift = [&](auto kernel, int threads, int per) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((cols + per - 1) / per)), dim3(threads), 0, stream, X, ld, rows, cols, words, later, sa, t);
     };
     // The fewest threads per column (16, 64 or 256) whose registers hold all its words; of long columns, which are often few,
     // fewer per workgroup.  us for 16 | 64 | 256: 16384 x 16384 10.5 | 28 | 69, 40000 x 1000 16 | 7.6 | 8.3, 10^6 x 100 383 | 110 | 44.
-    // Shares only of the longest, and no more workgroups for them than compute units: each reads the words, too (300000 x 300, nothing to
-    // read again, us, 1 share | 3 | 6: 17 | 20 | 36; 40000 x 1000 1 | 4: 7.6 | 11).
-    if (tiles <= 16 * kHeld) shift(k_col_shift<T, 256, 16>, 256, 16, 1);
-    else if (tiles <= 64 * kHeld) shift(k_col_shift<T, 256, 4>, 256, 4, 1);
-    else shift(k_col_shift<T, 1024, 4>, 1024, 4, 256);
+    if (tiles <= 16 * kHeld) shift(k_col_shift<T, 256, 16, false>, 256, 16);
+    else if (tiles <= 64 * kHeld) shift(k_col_shift<T, 256, 4, false>, 256, 4);
+    else {
+        shift(k_col_shift<T, 1024, 4, true>, 1024, 4);
+        hipLaunchKernelGGL((k_col_again<T>), dim3(kAgainGrid), dim3(kAgainThreads), 0, stream, X, ld, rows, cols, words, later, sa, t);
+    }
     return hipGetLastError();
 }
 

@@ -80,12 +80,9 @@ def test_sums_at_a_threshold(oracle, below, dtype, N):
     assert np.array_equal(column_shifts(B, N), want)
 
 
-@pytest.mark.parametrize("dtype,N", [(np.float64, 16), (np.float32, 8)])
-@pytest.mark.parametrize("k,n,below,live", [(17000, 9, 4, 1), (40000, 70, 5, 3), (65536, 3, 8, 2), (65537, 5, 6, 1), (130000, 70, 7, 5),
-                                            (300001, 3, 8, 1)])
-def test_long_columns_at_a_threshold(oracle, k, n, below, live, dtype, N):
-    """As above for columns whose second read is shared by several workgroups (and by one, for 16 columns each): every `live`-th tile lies
-    `below` binades under the first, the others one or two, which are known exactly and not read again."""
+def at_a_threshold(k, n, below, live, dtype, N):
+    """Columns with sums up to n / 2 steps below or above a threshold: every `live`-th tile lies `below` binades under the first, the others
+    one or two, which are known exactly and not read again."""
     Pfast = K.constants(N).Pfast
     rng = np.random.default_rng(k)
     tile = np.arange(k) // TILE
@@ -110,8 +107,36 @@ def test_long_columns_at_a_threshold(oracle, k, n, below, live, dtype, N):
             left -= q * q
             i += 1
         assert i <= TILE
-    B = B.astype(dtype)
-    want, e, _ = oracle.shifts(B.astype(np.float64), 1, Pfast)
+    return B.astype(dtype)
+
+
+@pytest.mark.parametrize("dtype,N", [(np.float64, 16), (np.float32, 8)])
+@pytest.mark.parametrize("k,n,below,live", [(17000, 9, 4, 1), (40000, 70, 5, 3), (65536, 3, 8, 2), (65537, 5, 6, 1), (130000, 70, 7, 5),
+                                            (300001, 3, 8, 1)])
+def test_long_columns_at_a_threshold(oracle, k, n, below, live, dtype, N):
+    """The second read by the workgroup that finds it necessary, for 16 columns and for 4, and from 65537 rows on by a launch of its own."""
+    B = at_a_threshold(k, n, below, live, dtype, N)
+    want, e, _ = oracle.shifts(B.astype(np.float64), 1, K.constants(N).Pfast)
     assert (e == 0).all() and len(set(want)) == 2
     for _ in range(3):
         assert np.array_equal(column_shifts(B, N), want)
+
+
+@pytest.mark.parametrize("n,every", [(4200, 1), (4200, 16), (330, 1), (1000, 200)])
+def test_strips_of_a_second_read(oracle, n, every):
+    """More strips of 16 columns to read again than workgroups of that launch, fewer, and a few among others: one column near a threshold,
+    scaled by powers of two and with either sign, in every `every`-th place, and columns of ones."""
+    k, N = 65600, 8
+    column = at_a_threshold(k, 1, 6, 1, np.float32, N)
+    ones = np.ones((k, 1), np.float32)
+    shift, one = (oracle.shifts(x.astype(np.float64), 1, K.constants(N).Pfast)[0][0] for x in (column, ones))
+    place = torch.arange(n, device="cuda")
+    B = torch.where(place % every == 0, torch.from_numpy(column).cuda(), torch.from_numpy(ones).cuda())
+    B *= torch.ldexp(torch.where(place % 2 == 0, 1.0, -1.0).cuda(), place % 7 - 3)
+    want = torch.where(place % every == 0, int(shift), int(one)) - (place % 7 - 3)
+    A = torch.ones((2, k), dtype=torch.float32, device="cuda")
+    C = torch.empty((2, n), dtype=torch.float32, device="cuda")
+    for _ in range(3):
+        oz.oz2_sgemm(2, n, k, 1.0, A, k, B, n, 0.0, C, n, N)
+        torch.cuda.synchronize()
+        assert torch.equal(oz.stage_tensor(b.OZ2_STAGE_SHIFT_B).long(), want)
