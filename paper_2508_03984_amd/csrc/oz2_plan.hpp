@@ -363,14 +363,19 @@ inline GemmPlan gemm_plan(int64_t rows, int64_t cols, int64_t slices, int64_t kt
     const double large = (double)((rows + 255) / 256 * ((cols + 255) / 256) * slices);
     GemmPlan best{blocks <= 256 ? GemmTile::kOnePerUnit : blocks <= 512 ? GemmTile::kTwoPerUnit : GemmTile::kLarge, 1};
     if (!may_range || large > 448) return best;
-    // a range less has to be clearly worse
+    // A range less has to be clearly worse, the more so for ranges of large tiles where the estimate makes one range of small ones up to 40 % too
+    // slow.  Those have a unit each and a contraction below 8192 (us, one range | as estimated, the estimate of the ratio: 191 x 390 x 7676 N = 12 26.2 | 22.8
+    // (0.66), 481 x 212 x 6626 N = 14 24.0 | 23.8 (0.75), 181 x 404 x 6807 N = 18 25.1 | 26.5 (0.76), 586 x 191 x 7076 N = 14 26.3 | 27.2 (0.82), 244 x 386 x 4623 N = 18 21.2 | 23.9
+    // (0.93)), or two share one and it is below 4480 (133 x 1163 x 4378 N = 18 32.2 | 30.2 (0.82), 1133 x 246 x 2834 N = 15 23.9 | 24.1 (0.87), 1637 x 618 x 4286 N = 5 35.4 | 36.4
+    // (0.89), 418 x 1753 x 2274 N = 5 20.8 | 22.0 (0.93); 1303 x 477 x 4573 N = 8 33.7 | 32.5 (0.86), 967 x 1484 x 7032 N = 5 54.0 | 52.4 (0.93)).
     double best_us = 0.95 * (5 + (best.tile == GemmTile::kLarge ? large_tiles_us(large, (double)kt) : small_tiles_us((double)blocks, (double)kt)));
+    const double large_us = best_us * (best.tile == GemmTile::kOnePerUnit && kt < 128 ? 0.8 : best.tile == GemmTile::kTwoPerUnit && kt < 70 ? 0.9 : 1.0);
     for (int s = 2; s <= kMaxRanges && kt / s >= 12; ++s) {
         const double k = (double)kt / s, extra = 9 + s * (double)(rows * cols * slices) / 3e6;
         const double some = large * s;
         // (all units at once finish and store: a little more)
         const double l = extra + large_tiles_us(some, k) + (some / 256 - (double)(int64_t)(some / 256 - 1e-9) > 0.9 ? 5 : 0);
-        if (large >= 24 && l < best_us) { best_us = l; best = GemmPlan{GemmTile::kLarge, s}; }
+        if (large >= 24 && l < std::min(best_us, large_us)) { best_us = l; best = GemmPlan{GemmTile::kLarge, s}; }
         const double o = extra + small_tiles_us((double)(blocks * s), k);
         if (blocks * s <= 256 && o < best_us) { best_us = o; best = GemmPlan{GemmTile::kOnePerUnit, s}; }
     }

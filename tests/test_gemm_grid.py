@@ -119,3 +119,29 @@ def test_plans_of_k_ranges(tmp_path):
     subprocess.check_call(["g++", "-O1", "-std=c++17", "-fsanitize=undefined", "-I", CSRC, str(src), "-o", str(exe)])
     out = subprocess.run([str(exe)], capture_output=True, text=True)
     assert out.returncode == 0 and out.stdout.strip() == "bad=0 1", out.stdout + out.stderr[-500:]
+
+
+LINES = r"""
+#include <cstdio>
+#include "oz2_plan.hpp"
+using namespace oz2;
+int main() {
+    long m, n, k; int N;
+    while (std::scanf("%ld %ld %ld %d", &m, &n, &k, &N) == 4) std::printf("%d\n", make_layout(m, n, k, N, true).ranges);
+}
+"""
+
+
+def test_large_tiles_of_middle_contractions(tmp_path):
+    """Ranges of large tiles only where they are faster than one of small tiles, which have a unit each or two share one."""
+    cases = {(244, 386, 4623, 18): 1, (990, 189, 6626, 10): 1, (181, 404, 6807, 18): 1, (459, 696, 5323, 6): 1, (191, 390, 7676, 12): 9,   # a unit each
+             (1012, 494, 3398, 12): 1, (1637, 618, 4286, 5): 1, (133, 1163, 4378, 18): 2,                             # two share one, k < 4480
+             (967, 1484, 7032, 5): 2, (1337, 194, 5656, 16): 2, (787, 578, 6979, 9): 2,                               # ... and beyond
+             (574, 264, 9904, 10): 3, (716, 202, 12328, 18): 4, (849, 1104, 6219, 16): 2,                             # 8192 and beyond; large tiles anyway
+             (31, 42, 2611, 11): 3, (18, 1701, 2725, 9): 2}                                                           # ranges of small tiles
+    src = tmp_path / "lines.cpp"
+    src.write_text(LINES)
+    exe = tmp_path / "lines"
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-I", CSRC, str(src), "-o", str(exe)])
+    out = subprocess.run([str(exe)], input="\n".join("%d %d %d %d" % c for c in cases), capture_output=True, text=True)
+    assert dict(zip(cases, map(int, out.stdout.split()))) == cases
