@@ -92,7 +92,8 @@ __global__ __launch_bounds__(64 * kWaves) void k_tiny_product(const int8_t *__re
     if (total > 0) {
         // (Chunks beyond the last one are not requested: the last one again in their place, to spare the branches, is what the loads
         // of a compute unit at k = 256 consisted of by half and at 128 by three quarters.  Graph of calls, other operands in each, us: 256^3
-        // N = 14 12.9 -> 11.1, prepared 8.7 -> 7.0, 128^3 12.0 -> 9.5, 300 x 300 x 128 N = 15 prepared 9.7 -> 8.0.)
+        // N = 14 12.9 -> 11.1, prepared 8.7 -> 7.0, 128^3 12.0 -> 9.5, 300 x 300 x 128 N = 15 prepared 9.7 -> 8.0.  Calls one after another from Python, whose pace
+        // the host's work for two launches sets, are level: 256^3 11.8 -> 11.9.)
 #pragma unroll
         for (int b = 0; b < kFlight; ++b)
             if (b < total) load(b, b);
