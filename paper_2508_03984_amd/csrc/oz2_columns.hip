@@ -2,7 +2,7 @@
 // (Algorithm 1 line 1: nu in F^n) and its residue slices are wanted K-contiguous
 // (transposed).  These kernels read B in place, coalesced along its rows, so no transposed
 // copy of B is ever written:
-//   k_col_sums, k_col_shift  -- the fast-mode shift of Section 4.2 per column;
+//   k_col_sums, k_col_shift, k_col_again  -- the fast-mode shift of Section 4.2 per column;
 //   k_col_max  -- the maximum of each column (accurate mode): partial maxima per (column strip, row
 //       chunk) combined with 64-bit integer atomics, which is exact and order-independent;
 //   k_residues_cols -- Algorithm 1 lines 3 and 5 for B: a 64 x 64 tile of B is read row-wise,
